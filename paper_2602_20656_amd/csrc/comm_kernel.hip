@@ -5,10 +5,12 @@
 //   NT  threads    -> workgroup size (NT/64 wavefronts),
 //   C   chunk size -> the unit of work a channel takes at a time: chunk g of the byte
 //                     range is moved by workgroup g mod NC.
-// Inside a chunk every lane moves 16-byte vectors; consecutive lanes touch consecutive
-// vectors, so one wavefront instruction covers 1 KiB of contiguous HBM.  A lane issues the
-// loads of U vectors of every source before it uses any of them.  Every byte is touched
-// once, so stores always carry the non-temporal hint (measured on MI355X: +3..7 % and no
+// A wavefront's work is a sequence of units of 1 KiB (64 lanes x 16 bytes): unit n of a chunk belongs to
+// wavefront n mod (NT/64), and the sequence runs on from chunk to chunk.  The walk over it lives in scalar
+// registers, and the loads of the next batch of units are issued before the current batch is added and stored
+// (see "the pipelined mover" below), so that a channel is bound by what a compute unit's memory pipeline
+// moves (100 - 116 GB/s, loads and stores together, from 8 wavefronts up) and not by one memory latency per batch.
+// Every byte is touched once, so stores always carry the non-temporal hint (measured on MI355X: +3..7 % and no
 // write-allocate traffic in the L2 that a co-running GEMM depends on).  Loads carry it only
 // when the launch has at least kStreamLoadsFromNC channels: with that many channels the
 // kernel is bandwidth-bound and streams from HBM (+6..13 %), while with few channels it is
@@ -24,15 +26,45 @@
 
 namespace {
 
+// How a buffer (a shard of a gather-copy, any buffer of a reduce-copy) is cut: chunks of C bytes, of which the last may be
+// short, in units of 1 KiB that a wavefront moves with one instruction.
+struct Shape {
+    int64_t shard_bytes;       // bytes per source
+    int64_t chunk_bytes;       // C
+    uint32_t nshards;          // of a gather-copy; 1 for a reduce-copy
+    uint32_t chunks;           // per shard
+    uint32_t step_shards, step_chunks;   // NC chunks further: that many shards and chunks
+    uint32_t full_units, full_rest;   // of a whole chunk: units, and bytes of whole 16-byte vectors in the last of them
+    uint32_t last_units, last_rest;   // of a shard's last chunk (0 units: it holds no whole vector)
+};
 struct CommArgs {
     const char* src[LAGOM_MAX_SRCS];
     char* dst[LAGOM_MAX_DSTS];
     int32_t nsrc, ndst;
-    int64_t shard_bytes;       // bytes per source
-    int64_t chunk_bytes;       // C
-    int64_t chunks_per_shard;
-    int64_t total_chunks;      // reduce: chunks_per_shard; gather: nsrc * chunks_per_shard
+    Shape shape;
 };
+
+Shape make_shape(int64_t shard_bytes, int64_t chunk_bytes, int nshards, int nc) {
+    Shape s{};
+    if (chunk_bytes > shard_bytes) chunk_bytes = (shard_bytes + 15) & ~(int64_t)15;
+    // chunk numbers are 32-bit on the device: more than 2^30 of them (64 GiB in 16-byte chunks at the least, and then the
+    // result is the same) are taken as larger chunks
+    while ((shard_bytes + chunk_bytes - 1) / chunk_bytes * nshards > (int64_t)1 << 30) chunk_bytes *= 2;
+    s.shard_bytes = shard_bytes;
+    s.chunk_bytes = chunk_bytes;
+    s.nshards = (uint32_t)nshards;
+    s.chunks = (uint32_t)((shard_bytes + chunk_bytes - 1) / chunk_bytes);
+    s.step_shards = (uint32_t)nc / s.chunks;
+    s.step_chunks = (uint32_t)nc % s.chunks;
+    auto cut = [](int64_t bytes, uint32_t* units, uint32_t* rest) {
+        const int64_t whole = bytes & ~(int64_t)15;
+        *units = (uint32_t)((whole + 1023) >> 10);
+        *rest = (uint32_t)(whole - ((int64_t)*units - 1) * 1024);
+    };
+    cut(chunk_bytes < shard_bytes ? chunk_bytes : shard_bytes, &s.full_units, &s.full_rest);
+    cut(shard_bytes - (int64_t)(s.chunks - 1) * chunk_bytes, &s.last_units, &s.last_rest);
+    return s;
+}
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -50,13 +82,13 @@ __device__ __forceinline__ void st16(char* p, u32x4 v) { __builtin_nontemporal_s
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// fp32 -> bf16 bits, round to nearest, ties to even; NaN keeps a quiet payload.
-__device__ __forceinline__ uint32_t bf16_round(float f) {
-    const uint32_t u = __float_as_uint(f);
-    const uint32_t upper = u >> 16, lower = u & 0xffffu;
-    const uint32_t up = (lower > 0x8000u || (lower == 0x8000u && (upper & 1u))) ? 1u : 0u;
-    const uint32_t r = upper + up;
-    return ((u & 0x7fffffffu) > 0x7f800000u) ? (upper | 0x0040u) : r;
+// Two fp32 -> a packed pair of bf16, round to nearest, ties to even; NaN keeps a quiet payload.  v_cvt_pk_bf16_f32
+// gives the bits of the integer formula (upper + round-up, NaN: upper | 0x40) on all 2^32 inputs (checked); it
+// replaces 14 integer instructions per pair, which with two sources were half of a channel's VALU time.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_round2(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
 template <int DT>
@@ -86,7 +118,7 @@ struct Acc<LAGOM_BF16> {
     __device__ __forceinline__ u32x4 result() const {
         u32x4 r;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = bf16_round(a[2 * i]) | (bf16_round(a[2 * i + 1]) << 16);
+        for (int i = 0; i < 4; ++i) r[i] = bf16_round2(a[2 * i], a[2 * i + 1]);
         return r;
     }
 };
@@ -101,52 +133,21 @@ __device__ __forceinline__ void reduce_tail_element(const SRC& src, const DST& d
     } else {
         float acc = bf16_lo(*reinterpret_cast<const uint16_t*>(src(0) + byte_off));
         for (int s = 1; s < nsrc; ++s) acc = acc + bf16_lo(*reinterpret_cast<const uint16_t*>(src(s) + byte_off));
-        const uint16_t r = (uint16_t)bf16_round(acc);
+        const uint16_t r = (uint16_t)bf16_round2(acc, acc);
         for (int d = 0; d < ndst; ++d) *reinterpret_cast<uint16_t*>(dst(d) + byte_off) = r;
     }
 }
 
-// One chunk [base, base + len) of a reduce-copy, moved by the nt threads of a workgroup.
-// S > 0: number of sources known at compile time (all loads of a batch issued before the
-// first add).  S == 0: any number of sources, loaded source by source.
-// U: 16-byte vectors a lane has in flight per source.  src(s) / dst(d) give the buffers.
-template <int DT, int S, int U, bool STREAM, class SRC, class DST>
-__device__ __forceinline__ void reduce_chunk(const SRC& src, const DST& dst, int nsrc, int ndst, int64_t base, int64_t len, int tid, int nt) {
+// What is left of a chunk behind whole LDS batches, moved vector by vector with the nt threads of a workgroup.
+template <int DT, class SRC, class DST>
+__device__ __forceinline__ void reduce_rest(const SRC& src, const DST& dst, int nsrc, int ndst, int64_t base, int64_t len, int tid, int nt) {
     const int esize = DT == LAGOM_F32 ? 4 : 2;
     const int64_t nvec = len >> 4;
-    int64_t v = tid;
-    if constexpr (S > 0) {
-        // full batches: U vectors per source per lane, strided by the workgroup size
-        for (; v + (int64_t)(U - 1) * nt < nvec; v += (int64_t)U * nt) {
-            u32x4 r[S][U];
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int u = 0; u < U; ++u) r[s][u] = ld16<STREAM>(src(s) + base + ((v + (int64_t)u * nt) << 4));
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                Acc<DT> acc;
-                acc.init(r[0][u]);
-#pragma unroll
-                for (int s = 1; s < S; ++s) acc.add(r[s][u]);
-                const u32x4 o = acc.result();
-                for (int d = 0; d < ndst; ++d) st16(dst(d) + base + ((v + (int64_t)u * nt) << 4), o);
-            }
-        }
-    }
-    // remaining vectors (and every vector when S == 0)
-    for (; v < nvec; v += nt) {
+    for (int64_t v = tid; v < nvec; v += nt) {
         const int64_t off = base + (v << 4);
         Acc<DT> acc;
-        acc.init(ld16<STREAM>(src(0) + off));
-        const int ns = S > 0 ? S : nsrc;
-        int s = 1;
-        for (; s + 3 < ns; s += 4) {          // four loads in flight, added in source order
-            const u32x4 x0 = ld16<STREAM>(src(s) + off), x1 = ld16<STREAM>(src(s + 1) + off);
-            const u32x4 x2 = ld16<STREAM>(src(s + 2) + off), x3 = ld16<STREAM>(src(s + 3) + off);
-            acc.add(x0); acc.add(x1); acc.add(x2); acc.add(x3);
-        }
-        for (; s < ns; ++s) acc.add(ld16<STREAM>(src(s) + off));
+        acc.init(ld16<false>(src(0) + off));
+        for (int s = 1; s < nsrc; ++s) acc.add(ld16<false>(src(s) + off));
         const u32x4 o = acc.result();
         for (int d = 0; d < ndst; ++d) st16(dst(d) + off, o);
     }
@@ -154,22 +155,11 @@ __device__ __forceinline__ void reduce_chunk(const SRC& src, const DST& dst, int
     const int tail_elems = (int)(len & 15) / esize;
     if (tid < tail_elems) reduce_tail_element<DT>(src, dst, nsrc, ndst, base + (nvec << 4) + (int64_t)tid * esize);
 }
-
-// One chunk of a plain copy of one source to ndst destinations (bytes are moved, never interpreted).
-template <int U, bool STREAM, class DST>
-__device__ __forceinline__ void copy_chunk(const char* src, const DST& dst, int ndst, int64_t dst_off, int64_t len, int tid, int nt) {
+template <class DST>
+__device__ __forceinline__ void copy_rest(const char* src, const DST& dst, int ndst, int64_t dst_off, int64_t len, int tid, int nt) {
     const int64_t nvec = len >> 4;
-    int64_t v = tid;
-    for (; v + (int64_t)(U - 1) * nt < nvec; v += (int64_t)U * nt) {
-        u32x4 x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = ld16<STREAM>(src + ((v + (int64_t)u * nt) << 4));
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            for (int d = 0; d < ndst; ++d) st16(dst(d) + dst_off + ((v + (int64_t)u * nt) << 4), x[u]);
-    }
-    for (; v < nvec; v += nt) {
-        const u32x4 x = ld16<STREAM>(src + (v << 4));
+    for (int64_t v = tid; v < nvec; v += nt) {
+        const u32x4 x = ld16<false>(src + (v << 4));
         for (int d = 0; d < ndst; ++d) st16(dst(d) + dst_off + (v << 4), x);
     }
     const int tail = (int)(len & 15);          // only at the very end of a buffer: bytes, copied one by one
@@ -179,29 +169,264 @@ __device__ __forceinline__ void copy_chunk(const char* src, const DST& dst, int 
     }
 }
 
-template <int DT, int S, int U, bool STREAM, int MAXNT>
-__global__ void __launch_bounds__(MAXNT) reduce_copy_kernel(const CommArgs p) {
+// ------------------------------------------------------------------ the pipelined mover
+// A wavefront's walk over its share: chunks blockIdx, blockIdx + NC, ... of every shard in turn, and in each chunk the
+// 1 KiB units wave, wave + nw, ...  All of it is wave-uniform: 32-bit arithmetic on scalar registers (gfx9 has no 64-bit
+// scalar compare), and a step is straight-line code -- with loops in it the compiler's control flow holds paths on which
+// a batch seems never to be waited for, and it drains the memory pipeline on each.  Which lane moves an element
+// depends on the sizes, NC, NT and C only, not on how many units are in flight: the steps of one launch rely on that.
+template <bool GATHER>
+struct Walk {
+    Shape s;
+    uint32_t wave, nw;
+    uint32_t c, r;                              // current chunk of the shard, shard (0 in a reduce-copy)
+    uint32_t n, units, rest;                    // unit, units of the chunk, bytes of whole vectors in its last unit
+    bool more;                                  // the walk stands on something to move
+    __device__ __forceinline__ void open() {
+        const bool end = c + 1 == s.chunks;
+        units = end ? s.last_units : s.full_units;
+        rest = end ? s.last_rest : s.full_rest;
+        n = wave;
+    }
+    __device__ __forceinline__ void first() {
+        c = blockIdx.x; r = 0;
+        if (GATHER) { r = c / s.chunks; c -= r * s.chunks; }
+        open();
+        more = GATHER ? r < s.nshards && s.full_units > 0 : c < s.chunks && n < units;
+    }
+    __device__ __forceinline__ void next(uint32_t batch) {
+        n += batch * nw;
+        if (n >= units) {
+            if (GATHER) {
+                // a shard's short last chunk may hold no unit for this wavefront; the walk still stops there (and moves nothing)
+                c += s.step_chunks; r += s.step_shards;
+                if (c >= s.chunks) { c -= s.chunks; ++r; }
+            } else {
+                c += gridDim.x;                 // at most 2^30 + 65535
+            }
+            open();
+            more = more && (GATHER ? r < s.nshards : c < s.chunks && n < units);   // only the last chunk can have fewer units
+        }
+    }
+    // Where there is nothing to move the walk points at the start of a shard, for loads that nobody uses.
+    __device__ __forceinline__ uint32_t shard() const { return more ? r : 0; }
+    __device__ __forceinline__ bool empty() const { return !more || (GATHER && n >= units); }
+    __device__ __forceinline__ int64_t offset() const {         // byte in the shard
+        return empty() ? 0 : (int64_t)c * s.chunk_bytes + ((int64_t)n << 10);
+    }
+    // offset from offset() of the chunk's last vector (from 2^20 units on: larger than any offset in a batch)
+    __device__ __forceinline__ uint32_t limit() const {
+        const uint32_t left = units - 1 - n;
+        return empty() ? 0u : (left < (1u << 20) ? left << 10 : 1u << 30) + rest - 16;
+    }
+};
+
+template <bool GATHER>
+__device__ __forceinline__ Walk<GATHER> make_walk(const Shape& s) {
+    Walk<GATHER> w{};
+    w.s = s;
+    w.wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w.nw = blockDim.x >> 6;
+    return w;
+}
+
+// Where the walk reads and writes.
+template <class SRC, class DST>
+struct ReduceIo {                               // src(s) and dst(d) at the same offset
+    const SRC& src; const DST& dst; int ndst;
+    __device__ __forceinline__ const char* from(const Walk<false>& w, int s) const { return src(s) + w.offset(); }
+    __device__ __forceinline__ int64_t to(const Walk<false>& w) const { return w.offset(); }
+};
+template <class SRC, class DST>
+struct GatherIo {                               // shard r goes to r * shard_bytes
+    const SRC& src; const DST& dst; int ndst;
+    __device__ __forceinline__ const char* from(const Walk<true>& w, int) const { return src(w.shard()) + w.offset(); }
+    __device__ __forceinline__ int64_t to(const Walk<true>& w) const { return w.shard() * w.s.shard_bytes + w.offset(); }
+};
+
+// A batch: U units of one chunk, S sources each.
+template <int S, int U>
+struct Batch {
+    u32x4 v[U][S];
+    int64_t off;               // of the first unit in a destination
+    int32_t limit;             // lanes whose offset from there is larger store nothing
+};
+
+// Copies (S = 1) and reductions: while one batch is added and stored, the loads of the next one are in flight.  Loads and
+// stores share one in-order counter, so issuing the next loads in front of the stores also keeps the stores'
+// acknowledgements off the path.  U: units per batch.
+template <int DT, int S, int U, bool STREAM, bool COPY, class WALK, class IO>
+__device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane) {
+    w.first();
+    if (!w.more) return;
+    uint32_t at[U];                             // a lane's offsets in a batch
+#pragma unroll
+    for (int u = 0; u < U; ++u) at[u] = lane * 16 + ((u * w.nw) << 10);
+    auto fetch = [&](Batch<S, U>& b) {          // past the chunk's end its last vector is read again (and not stored)
+        b.off = io.to(w);
+        const uint32_t last = w.limit();
+        b.limit = w.empty() ? -1 : (int32_t)last;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t o = at[u] < last ? at[u] : last;
+#pragma unroll
+            for (int s = 0; s < S; ++s) b.v[u][s] = ld16<STREAM>(io.from(w, s) + o);
+        }
+    };
+    auto finish = [&](const Batch<S, U>& b, int u) {
+        if (COPY) return b.v[u][0];             // bytes are moved, never interpreted
+        Acc<DT> acc;
+        acc.init(b.v[u][0]);
+#pragma unroll
+        for (int s = 1; s < S; ++s) acc.add(b.v[u][s]);
+        return acc.result();
+    };
+    auto put = [&](Batch<S, U>& b) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            b.v[u][0] = finish(b, u);
+            // Used here, in front of the branch: where the compiler sees a path on which a load is never waited for, it
+            // drains the memory pipeline before the register is loaded again.
+            asm volatile("" ::"v"(b.v[u][0]));
+        }
+        if (b.limit >= (int32_t)((((U - 1) * w.nw) << 10) + 1008)) {      // whole units
+            for (int d = 0; d < io.ndst; ++d)
+#pragma unroll
+                for (int u = 0; u < U; ++u) st16(io.dst(d) + b.off + at[u], b.v[u][0]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if ((int32_t)at[u] <= b.limit)
+                    for (int d = 0; d < io.ndst; ++d) st16(io.dst(d) + b.off + at[u], b.v[u][0]);
+        }
+    };
+    Batch<S, U> b0, b1;
+    fetch(b0);
+    w.next(U);
+    while (w.more) {
+        fetch(b1);
+        put(b0);
+        w.next(U);
+        fetch(b0);          // behind the end: empty
+        put(b1);
+        w.next(U);
+    }
+    put(b0);
+}
+
+// Many sources: a unit's sources are loaded in two halves, and while one half is added the other (of this unit, then of
+// the next one) is in flight.  Half the registers of two whole units.
+template <int DT, int S, bool STREAM, class IO>
+__device__ __forceinline__ void move_halves(Walk<false> w, const IO& io, uint32_t lane) {
+    constexpr int SA = (S + 1) / 2, SB = S - SA;
+    w.first();
+    if (!w.more) return;
+    const uint32_t lo = lane * 16;
+    u32x4 a[SA], b[SB];
+    auto clamped = [&]() { const uint32_t l = w.limit(); return lo < l ? lo : l; };
+    uint32_t o = clamped();
+#pragma unroll
+    for (int s = 0; s < SA; ++s) a[s] = ld16<STREAM>(io.from(w, s) + o);
+    while (w.more) {
+#pragma unroll
+        for (int s = 0; s < SB; ++s) b[s] = ld16<STREAM>(io.from(w, SA + s) + o);
+        const int64_t off = io.to(w);
+        const bool mine = lo <= w.limit();
+        Acc<DT> acc;
+        acc.init(a[0]);
+#pragma unroll
+        for (int s = 1; s < SA; ++s) acc.add(a[s]);
+        auto finish = [&]() {
+#pragma unroll
+            for (int s = 0; s < SB; ++s) acc.add(b[s]);
+            const u32x4 r = acc.result();
+            if (mine) {
+                st16(io.dst(0) + off + lo, r);
+                for (int d = 1; d < io.ndst; ++d) st16(io.dst(d) + off + lo, r);
+            }
+        };
+        w.next(1);
+        o = clamped();
+#pragma unroll
+        for (int s = 0; s < SA; ++s) a[s] = ld16<STREAM>(io.from(w, s) + o);     // behind the end: unused
+        finish();
+    }
+}
+
+// Any number of sources, four loads in flight: the steps of more than two sources of a fused launch.
+template <int DT, bool STREAM, class IO>
+__device__ __forceinline__ void move_any(Walk<false> w, const IO& io, int nsrc, uint32_t lane) {
+    const uint32_t lo = lane * 16;
+    for (w.first(); w.more; w.next(1)) {
+        if (lo > w.limit()) continue;
+        Acc<DT> acc;
+        acc.init(ld16<STREAM>(io.from(w, 0) + lo));
+        int s = 1;
+        for (; s + 3 < nsrc; s += 4) {            // added in source order
+            const u32x4 x0 = ld16<STREAM>(io.from(w, s) + lo), x1 = ld16<STREAM>(io.from(w, s + 1) + lo);
+            const u32x4 x2 = ld16<STREAM>(io.from(w, s + 2) + lo), x3 = ld16<STREAM>(io.from(w, s + 3) + lo);
+            acc.add(x0); acc.add(x1); acc.add(x2); acc.add(x3);
+        }
+        for (; s < nsrc; ++s) acc.add(ld16<STREAM>(io.from(w, s) + lo));
+        const u32x4 r = acc.result();
+        for (int d = 0; d < io.ndst; ++d) st16(io.dst(d) + w.offset() + lo, r);
+    }
+}
+
+// How much a lane keeps in flight.  A channel of up to kDeepNT threads (one wavefront per SIMD) may use the 120 registers
+// that a GEMM workgroup leaves on its SIMDs for that one wavefront; with more threads the wavefronts of a SIMD share
+// them, and their number keeps the memory pipeline busy instead.  One memory latency per batch, the previous form
+// -> this one, us (data in the last-level cache): 64 MiB gather-copy at (8, 256, 2 MiB) 138.5 -> 86.3; 12 MiB two-source fp32
+// reduce at (4, 256, 128 KiB) 55.1 -> 33.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 18.9 (there
+// one source at a time in flight before); a ring share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 65.3; 72 MiB
+// eight-source reduce at (256, 512, 32 KiB) 13.6 -> 12.9.
+constexpr int kDeepNT = 256;
+constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
+constexpr bool in_halves(int S, bool deep) { return deep ? S > 8 : S > 4; }
+
+template <int DT, int S, bool STREAM, bool DEEP, class IO>
+__device__ __forceinline__ void move_reduce(const Walk<false>& w, const IO& io, uint32_t lane) {
+    if constexpr (in_halves(S, DEEP)) move_halves<DT, S, STREAM>(w, io, lane);
+    else move_batches<DT, S, units_in_batch(S, DEEP), STREAM, false>(w, io, lane);
+}
+
+// The channel of a buffer's last chunk moves what is left behind the last whole vector.
+__device__ __forceinline__ bool owns_last(uint32_t chunks) { return (chunks - 1) % gridDim.x == blockIdx.x; }
+template <int DT, class SRC, class DST>
+__device__ __forceinline__ void reduce_tail(const SRC& src, const DST& dst, int nsrc, int ndst, int64_t bytes, uint32_t chunks) {
+    const int esize = DT == LAGOM_F32 ? 4 : 2;
+    const int left = (int)(bytes & 15) / esize, tid = threadIdx.x;
+    if (tid < left && owns_last(chunks)) reduce_tail_element<DT>(src, dst, nsrc, ndst, (bytes & ~(int64_t)15) + tid * esize);
+}
+template <class DST>
+__device__ __forceinline__ void copy_tail(const char* src, const DST& dst, int ndst, int64_t bytes, uint32_t chunks) {
+    const int left = (int)(bytes & 15), tid = threadIdx.x;
+    if (tid < left && owns_last(chunks)) {
+        const int64_t at = (bytes & ~(int64_t)15) + tid;
+        const char b = src[at];
+        for (int d = 0; d < ndst; ++d) dst(d)[at] = b;
+    }
+}
+
+template <int DT, int S, bool STREAM, bool DEEP>
+__global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) reduce_copy_kernel(const CommArgs p) {
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
-    for (int64_t g = blockIdx.x; g < p.total_chunks; g += gridDim.x) {
-        const int64_t base = g * p.chunk_bytes;
-        const int64_t left = p.shard_bytes - base;
-        reduce_chunk<DT, S, U, STREAM>(src, dst, p.nsrc, p.ndst, base, left < p.chunk_bytes ? left : p.chunk_bytes, threadIdx.x, blockDim.x);
-    }
+    const ReduceIo<decltype(src), decltype(dst)> io{src, dst, p.ndst};
+    move_reduce<DT, S, STREAM, DEEP>(make_walk<false>(p.shape), io, threadIdx.x & 63);
+    reduce_tail<DT>(src, dst, S, p.ndst, p.shape.shard_bytes, p.shape.chunks);
 }
 
 // Gather-copy with 16-byte vectors; needs shard_bytes % 16 == 0 (or a single shard) so that
 // every shard starts 16-byte aligned in the destination.
-template <int U, bool STREAM, int MAXNT>
-__global__ void __launch_bounds__(MAXNT) gather_copy_kernel(const CommArgs p) {
+template <bool STREAM, bool DEEP>
+__global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) gather_copy_kernel(const CommArgs p) {
+    const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
-    for (int64_t g = blockIdx.x; g < p.total_chunks; g += gridDim.x) {
-        const int64_t r = g / p.chunks_per_shard;
-        const int64_t base = (g - r * p.chunks_per_shard) * p.chunk_bytes;
-        const int64_t left = p.shard_bytes - base;
-        copy_chunk<U, STREAM>(p.src[r] + base, dst, p.ndst, r * p.shard_bytes + base, left < p.chunk_bytes ? left : p.chunk_bytes,
-                              threadIdx.x, blockDim.x);
-    }
+    const GatherIo<decltype(src), decltype(dst)> io{src, dst, p.ndst};
+    move_batches<LAGOM_F32, 1, units_in_batch(1, DEEP), STREAM, true>(make_walk<true>(p.shape), io,
+                                                                      threadIdx.x & 63);
+    if (p.nsrc == 1) copy_tail(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
 }
 
 // Gather-copy for shards whose byte length is not a multiple of 16: destinations of shards
@@ -209,53 +434,50 @@ __global__ void __launch_bounds__(MAXNT) gather_copy_kernel(const CommArgs p) {
 template <typename E>
 __global__ void __launch_bounds__(1024) gather_copy_elements_kernel(const CommArgs p) {
     const int nt = blockDim.x;
-    for (int64_t g = blockIdx.x; g < p.total_chunks; g += gridDim.x) {
-        const int64_t r = g / p.chunks_per_shard;
-        const int64_t base = (g - r * p.chunks_per_shard) * p.chunk_bytes;
-        const int64_t left = p.shard_bytes - base;
-        const int64_t len = left < p.chunk_bytes ? left : p.chunk_bytes;
+    for (int64_t g = blockIdx.x; g < (int64_t)p.shape.chunks * p.nsrc; g += gridDim.x) {
+        const int64_t r = g / p.shape.chunks;
+        const int64_t base = (g - r * p.shape.chunks) * p.shape.chunk_bytes;
+        const int64_t left = p.shape.shard_bytes - base;
+        const int64_t len = left < p.shape.chunk_bytes ? left : p.shape.chunk_bytes;
         const int64_t n = len / (int64_t)sizeof(E);
         const E* src = reinterpret_cast<const E*>(p.src[r] + base);
         for (int64_t i = threadIdx.x; i < n; i += nt) {
             const E x = src[i];
-            for (int d = 0; d < p.ndst; ++d) reinterpret_cast<E*>(p.dst[d] + r * p.shard_bytes + base)[i] = x;
+            for (int d = 0; d < p.ndst; ++d) reinterpret_cast<E*>(p.dst[d] + r * p.shape.shard_bytes + base)[i] = x;
         }
     }
 }
 
-// MAXNT is the launch bound the kernel is compiled for: 512 threads leave 256 registers per lane,
-// 1024 only 128.  Measured on the eight-source bf16 reduce: the same code compiled for 1024 threads
-// loses up to 40 % at 512 threads because the loads of a batch no longer stay in flight together.
-template <int DT, bool STREAM, int MAXNT>
+template <int DT, bool STREAM, bool DEEP, int S>
+void launch_reduce_s(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
+    if constexpr (S > LAGOM_MAX_SRCS) return;
+    else if (a.nsrc == S) hipLaunchKernelGGL((reduce_copy_kernel<DT, S, STREAM, DEEP && !(in_halves(S, true))>), grid, block, 0, st, a);
+    else launch_reduce_s<DT, STREAM, DEEP, S + 1>(a, grid, block, st);
+}
+template <int DT>
 void launch_reduce(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    switch (a.nsrc) {
-        case 1: hipLaunchKernelGGL((reduce_copy_kernel<DT, 1, 4, STREAM, MAXNT>), grid, block, 0, st, a); break;
-        case 2: hipLaunchKernelGGL((reduce_copy_kernel<DT, 2, 4, STREAM, MAXNT>), grid, block, 0, st, a); break;
-        case 3: hipLaunchKernelGGL((reduce_copy_kernel<DT, 3, 4, STREAM, MAXNT>), grid, block, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((reduce_copy_kernel<DT, 4, 4, STREAM, MAXNT>), grid, block, 0, st, a); break;
-        case 8: hipLaunchKernelGGL((reduce_copy_kernel<DT, 8, 2, STREAM, MAXNT>), grid, block, 0, st, a); break;
-        default: hipLaunchKernelGGL((reduce_copy_kernel<DT, 0, 1, STREAM, MAXNT>), grid, block, 0, st, a); break;
-    }
+    const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
+    if (stream) deep ? launch_reduce_s<DT, true, true, 1>(a, grid, block, st) : launch_reduce_s<DT, true, false, 1>(a, grid, block, st);
+    else deep ? launch_reduce_s<DT, false, true, 1>(a, grid, block, st) : launch_reduce_s<DT, false, false, 1>(a, grid, block, st);
 }
 
-template <int DT, bool STREAM>
-void launch_reduce_nt(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    if (block.x <= 512) launch_reduce<DT, STREAM, 512>(a, grid, block, st);
-    else launch_reduce<DT, STREAM, 1024>(a, grid, block, st);
-}
-
-template <bool STREAM>
 void launch_gather(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    if (block.x <= 512) hipLaunchKernelGGL((gather_copy_kernel<4, STREAM, 512>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((gather_copy_kernel<4, STREAM, 1024>), grid, block, 0, st, a);
+    const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
+    if (stream) {
+        if (deep) hipLaunchKernelGGL((gather_copy_kernel<true, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((gather_copy_kernel<true, false>), grid, block, 0, st, a);
+    } else {
+        if (deep) hipLaunchKernelGGL((gather_copy_kernel<false, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((gather_copy_kernel<false, false>), grid, block, 0, st, a);
+    }
 }
 
 // Several local steps of one collective in one launch: the channels are persistent and every channel walks the steps in
 // order, taking chunks k, k+NC, ... of each (how a ring collective runs inside a collective library: one kernel whose
 // channels loop over the ring steps).  Every buffer of every step holds the same number of bytes, so a given byte offset
 // is always moved by the same lane of the same channel: a location that one step writes and a later step reads or
-// overwrites through the same pointer is ordered by that lane's program order.  There is no synchronisation between
-// channels.
+// overwrites through the same pointer is ordered by that lane's program order (a step's loads are issued behind the
+// previous step's last store).  There is no synchronisation between channels.
 constexpr int kMaxSteps = LAGOM_MAX_STEPS;
 constexpr int kMaxStepPtrs = LAGOM_MAX_STEP_PTRS;
 struct StepsArgs {
@@ -263,46 +485,39 @@ struct StepsArgs {
     uint16_t first[kMaxSteps];
     uint8_t nsrc[kMaxSteps], ndst[kMaxSteps], op[kMaxSteps];
     int32_t nsteps;
-    int64_t bytes;                    // per buffer
-    int64_t chunk_bytes, total_chunks;
+    Shape shape;                      // one shard: a buffer
 };
 
-template <int DT, int S, int U, bool STREAM>
-__device__ __forceinline__ void reduce_step(const StepsArgs& p, int first, int nsrc, int ndst) {
-    const auto src = [&p, first](int s) { return p.ptr[first + s]; };
-    const auto dst = [&p, first, nsrc](int d) { return const_cast<char*>(p.ptr[first + nsrc + d]); };
-    for (int64_t g = blockIdx.x; g < p.total_chunks; g += gridDim.x) {
-        const int64_t base = g * p.chunk_bytes;
-        const int64_t left = p.bytes - base;
-        reduce_chunk<DT, S, U, STREAM>(src, dst, nsrc, ndst, base, left < p.chunk_bytes ? left : p.chunk_bytes, threadIdx.x, blockDim.x);
-    }
-}
-
-template <int DT, bool STREAM, int MAXNT>
-__global__ void __launch_bounds__(MAXNT) comm_steps_kernel(const StepsArgs p) {
+template <int DT, bool STREAM, bool DEEP>
+__global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const StepsArgs p) {
+    const Walk<false> w = make_walk<false>(p.shape);
+    const uint32_t lane = threadIdx.x & 63;
     for (int st = 0; st < p.nsteps; ++st) {
         const int first = p.first[st], nsrc = p.nsrc[st], ndst = p.ndst[st];
+        const auto src = [&p, first](int s) { return p.ptr[first + s]; };
+        const auto dst = [&p, first, nsrc](int d) { return const_cast<char*>(p.ptr[first + nsrc + d]); };
+        const ReduceIo<decltype(src), decltype(dst)> io{src, dst, ndst};
         if (p.op[st] == LAGOM_GATHER_COPY) {        // one source: a plain copy to every destination
-            const auto dst = [&p, first](int d) { return const_cast<char*>(p.ptr[first + 1 + d]); };
-            for (int64_t g = blockIdx.x; g < p.total_chunks; g += gridDim.x) {
-                const int64_t base = g * p.chunk_bytes;
-                const int64_t left = p.bytes - base;
-                copy_chunk<4, STREAM>(p.ptr[first] + base, dst, ndst, base, left < p.chunk_bytes ? left : p.chunk_bytes, threadIdx.x, blockDim.x);
-            }
-        } else if (nsrc == 1) {
-            reduce_step<DT, 1, 4, STREAM>(p, first, nsrc, ndst);
-        } else if (nsrc == 2) {
-            reduce_step<DT, 2, 4, STREAM>(p, first, nsrc, ndst);
-        } else {
-            reduce_step<DT, 0, 1, STREAM>(p, first, nsrc, ndst);
+            move_batches<DT, 1, units_in_batch(1, DEEP), STREAM, true>(w, io, lane);
+            copy_tail(p.ptr[first], dst, ndst, p.shape.shard_bytes, p.shape.chunks);
+            continue;
         }
+        if (nsrc == 2) move_batches<DT, 2, units_in_batch(2, DEEP), STREAM, false>(w, io, lane);
+        else move_any<DT, STREAM>(w, io, nsrc, lane);
+        reduce_tail<DT>(src, dst, nsrc, ndst, p.shape.shard_bytes, p.shape.chunks);
     }
 }
 
-template <int DT, bool STREAM>
+template <int DT>
 void launch_steps(const StepsArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    if (block.x <= 512) hipLaunchKernelGGL((comm_steps_kernel<DT, STREAM, 512>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((comm_steps_kernel<DT, STREAM, 1024>), grid, block, 0, st, a);
+    const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
+    if (stream) {
+        if (deep) hipLaunchKernelGGL((comm_steps_kernel<DT, true, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((comm_steps_kernel<DT, true, false>), grid, block, 0, st, a);
+    } else {
+        if (deep) hipLaunchKernelGGL((comm_steps_kernel<DT, false, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((comm_steps_kernel<DT, false, false>), grid, block, 0, st, a);
+    }
 }
 
 // ------------------------------------------------------------------ staged through LDS
@@ -390,22 +605,22 @@ __global__ void __launch_bounds__(MAXNT) comm_lds_kernel(const CommArgs p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     u32x4* ring = lds_ring + wave * (LDS_BYTES_PER_WAVE / 16);
     const auto dst = [&p](int d) { return p.dst[d]; };
-    for (int64_t g = blockIdx.x; g < p.total_chunks; g += gridDim.x) {
-        const int64_t r = GATHER ? g / p.chunks_per_shard : 0;
-        const int64_t base = (g - r * p.chunks_per_shard) * p.chunk_bytes;
-        const int64_t left = p.shard_bytes - base;
-        const int64_t len = left < p.chunk_bytes ? left : p.chunk_bytes;
+    for (int64_t g = blockIdx.x; g < (int64_t)p.shape.chunks * (GATHER ? p.nsrc : 1); g += gridDim.x) {
+        const int64_t r = GATHER ? g / p.shape.chunks : 0;
+        const int64_t base = (g - r * p.shape.chunks) * p.shape.chunk_bytes;
+        const int64_t left = p.shape.shard_bytes - base;
+        const int64_t len = left < p.shape.chunk_bytes ? left : p.shape.chunk_bytes;
         const int64_t bulk = len / (LDS_U * 1024) * (LDS_U * 1024);
-        const int64_t dst_base = r * p.shard_bytes + base;
+        const int64_t dst_base = r * p.shape.shard_bytes + base;
         if (GATHER) {
             const char* one = p.src[r];
             const auto src = [one](int) { return one; };
             lds_chunk<DT, true>(ring, src, dst, 1, p.ndst, base, dst_base, len, lane, wave, nw);
-            copy_chunk<1, false>(one + base + bulk, dst, p.ndst, dst_base + bulk, len - bulk, tid, blockDim.x);
+            copy_rest(one + base + bulk, dst, p.ndst, dst_base + bulk, len - bulk, tid, blockDim.x);
         } else {
             const auto src = [&p](int s) { return p.src[s]; };
             lds_chunk<DT, false>(ring, src, dst, p.nsrc, p.ndst, base, dst_base, len, lane, wave, nw);
-            reduce_chunk<DT, 0, 1, false>(src, dst, p.nsrc, p.ndst, base + bulk, len - bulk, tid, blockDim.x);
+            reduce_rest<DT>(src, dst, p.nsrc, p.ndst, base + bulk, len - bulk, tid, blockDim.x);
         }
     }
 }
@@ -476,24 +691,14 @@ extern "C" int lagom_comm_kernel(lagom_op op, lagom_dtype dt, const void* const*
     for (int s = 0; s < nsrc; ++s) a.src[s] = static_cast<const char*>(srcs[s]);
     for (int d = 0; d < ndst; ++d) a.dst[d] = static_cast<char*>(dsts[d]);
     a.nsrc = nsrc; a.ndst = ndst;
-    a.shard_bytes = count * lagom::elem_size(dt);
-    a.chunk_bytes = cfg->chunk_bytes;
-    a.chunks_per_shard = (a.shard_bytes + a.chunk_bytes - 1) / a.chunk_bytes;
-    a.total_chunks = op == LAGOM_REDUCE_COPY ? a.chunks_per_shard : a.chunks_per_shard * nsrc;
+    a.shape = make_shape(count * lagom::elem_size(dt), cfg->chunk_bytes, op == LAGOM_REDUCE_COPY ? 1 : nsrc, cfg->nc);
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const dim3 grid((unsigned)cfg->nc), block((unsigned)cfg->nt);
-    const bool stream = cfg->nc >= kStreamLoadsFromNC;
-    if (op == LAGOM_REDUCE_COPY) {
-        if (dt == LAGOM_F32) stream ? launch_reduce_nt<LAGOM_F32, true>(a, grid, block, st) : launch_reduce_nt<LAGOM_F32, false>(a, grid, block, st);
-        else stream ? launch_reduce_nt<LAGOM_BF16, true>(a, grid, block, st) : launch_reduce_nt<LAGOM_BF16, false>(a, grid, block, st);
-    } else if (nsrc == 1 || (a.shard_bytes & 15) == 0) {
-        stream ? launch_gather<true>(a, grid, block, st) : launch_gather<false>(a, grid, block, st);
-    } else if (dt == LAGOM_F32) {
-        hipLaunchKernelGGL((gather_copy_elements_kernel<uint32_t>), grid, block, 0, st, a);
-    } else {
-        hipLaunchKernelGGL((gather_copy_elements_kernel<uint16_t>), grid, block, 0, st, a);
-    }
+    if (op == LAGOM_REDUCE_COPY) dt == LAGOM_F32 ? launch_reduce<LAGOM_F32>(a, grid, block, st) : launch_reduce<LAGOM_BF16>(a, grid, block, st);
+    else if (nsrc == 1 || (a.shape.shard_bytes & 15) == 0) launch_gather(a, grid, block, st);
+    else if (dt == LAGOM_F32) hipLaunchKernelGGL((gather_copy_elements_kernel<uint32_t>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((gather_copy_elements_kernel<uint16_t>), grid, block, 0, st, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "comm kernel launch: %s", hipGetErrorString(e));
     return LAGOM_OK;
@@ -548,14 +753,10 @@ extern "C" int lagom_comm_steps(lagom_dtype dt, const lagom_comm_step* steps, in
         for (int d = 0; d < steps[i].ndst; ++d) a.ptr[n++] = static_cast<const char*>(steps[i].dsts[d]);
     }
     a.nsteps = nsteps;
-    a.bytes = count * lagom::elem_size(dt);
-    a.chunk_bytes = cfg->chunk_bytes;
-    a.total_chunks = (a.bytes + a.chunk_bytes - 1) / a.chunk_bytes;
+    a.shape = make_shape(count * lagom::elem_size(dt), cfg->chunk_bytes, 1, cfg->nc);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const dim3 grid((unsigned)cfg->nc), block((unsigned)cfg->nt);
-    const bool stream = cfg->nc >= kStreamLoadsFromNC;
-    if (dt == LAGOM_F32) stream ? launch_steps<LAGOM_F32, true>(a, grid, block, st) : launch_steps<LAGOM_F32, false>(a, grid, block, st);
-    else stream ? launch_steps<LAGOM_BF16, true>(a, grid, block, st) : launch_steps<LAGOM_BF16, false>(a, grid, block, st);
+    dt == LAGOM_F32 ? launch_steps<LAGOM_F32>(a, grid, block, st) : launch_steps<LAGOM_BF16>(a, grid, block, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "comm steps launch: %s", hipGetErrorString(e));
     return LAGOM_OK;
@@ -573,10 +774,7 @@ extern "C" int lagom_comm_kernel_lds(lagom_op op, lagom_dtype dt, const void* co
     for (int s = 0; s < nsrc; ++s) a.src[s] = static_cast<const char*>(srcs[s]);
     for (int d = 0; d < ndst; ++d) a.dst[d] = static_cast<char*>(dsts[d]);
     a.nsrc = nsrc; a.ndst = ndst;
-    a.shard_bytes = shard_bytes;
-    a.chunk_bytes = cfg->chunk_bytes;
-    a.chunks_per_shard = (a.shard_bytes + a.chunk_bytes - 1) / a.chunk_bytes;
-    a.total_chunks = op == LAGOM_REDUCE_COPY ? a.chunks_per_shard : a.chunks_per_shard * nsrc;
+    a.shape = make_shape(shard_bytes, cfg->chunk_bytes, op == LAGOM_REDUCE_COPY ? 1 : nsrc, cfg->nc);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const dim3 grid((unsigned)cfg->nc), block((unsigned)cfg->nt);
     const bool small = block.x <= 512;

@@ -386,3 +386,42 @@ def test_full_size_launches_in_the_light_channel_and_roofline_shapes():
     for run, cfgs in ((_run, [(128, 128, 64 << 10), (256, 128, 32 << 10), (512, 512, 16 << 10)]), (_run_lds, [(512, 512, 16 << 10)])):
         for cfg in cfgs:
             assert same_bits(run(lg.LAGOM_GATHER_COPY, "bf16", shards, 1, cfg, 8 * 2097152)[0], whole), (run.__name__, cfg)
+
+
+# ------------------------------------------------------------- edges of the pipelined mover
+def _edge_counts(nt, units, chunk, esz):
+    """Element counts at which a wavefront's walk begins, ends or is empty: around one 1 KiB unit, one round of the
+    workgroup, one and two batches of `units` rounds, whole chunks, and a short last chunk with a unit for some wavefronts only."""
+    round_ = (nt // 64) * 1024
+    sizes = {16, 1008, 1024, 1040, round_ - 16, round_, round_ + 1024, units * round_, units * round_ + 16, 2 * units * round_ - 16,
+             2 * units * round_ + 1040, 3 * chunk, 3 * chunk + 16, 3 * chunk + round_ - 1040, 5 * chunk - 16}
+    return sorted({max(16, s) // esz for s in sizes})
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("nt", [64, 256, 320, 1024])           # one wavefront; the deepest; the first shallow; the most wavefronts
+@pytest.mark.parametrize("nsrc", [1, 2, 4, 7, 8, 9, 16])       # 8, 4, 2 units in flight, one unit, in halves
+def test_reduce_copy_at_the_edges_of_its_batches(dtype, nt, nsrc):
+    esz = 4 if dtype == "f32" else 2
+    for chunk, nc in [(16384, 2), (48 * 1024 + 16, 3)]:
+        for count in _edge_counts(nt, 8 if nsrc == 1 else 4, chunk, esz):
+            srcs = _sources(dtype, nsrc, count + 1, 1000)        # one element that fills no vector
+            want = oc.reduce_copy(srcs, dtype)[0]
+            for ndst in (1, 3):
+                for got in _run(lg.LAGOM_REDUCE_COPY, dtype, srcs, ndst, (nc, nt, chunk), count + 1):
+                    assert same_bits(got, want), (count, nc, chunk, ndst)
+
+
+@pytest.mark.parametrize("nt", [64, 256, 320, 1024])
+@pytest.mark.parametrize("P", [1, 2, 5])
+def test_gather_copy_at_the_edges_of_its_batches(nt, P):
+    """nc below, at and above the chunks of a shard, so that a channel's next chunk lies in the same, the next or a later shard."""
+    for chunk in (16384, 48 * 1024 + 16):
+        for count in _edge_counts(nt, 8, chunk, 2):
+            count = count // 8 * 8
+            shards = _sources("bf16", P, count, 1100)
+            want = np.concatenate(shards)
+            chunks = -(-count * 2 // chunk)
+            for nc in {1, 2, chunks, 3 * chunks + 1, 64}:
+                got = _run(lg.LAGOM_GATHER_COPY, "bf16", shards, 1, (nc, nt, chunk), P * count)[0]
+                assert same_bits(got, want), (count, nc, chunk)
