@@ -76,6 +76,13 @@ __device__ __forceinline__ u32x4 ld16(const char* p) {
     if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
     return *reinterpret_cast<const u32x4*>(p);
 }
+// from an element-aligned address (global loads need no more)
+typedef u32x4 u32x4_element_aligned __attribute__((aligned(2)));
+template <bool STREAM>
+__device__ __forceinline__ u32x4 ld16_ragged(const char* p) {
+    if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_element_aligned*>(p));
+    return *reinterpret_cast<const u32x4_element_aligned*>(p);
+}
 __device__ __forceinline__ void st16(char* p, u32x4 v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p)); }
 
 // bf16 is the upper half of an fp32 pattern.
@@ -170,34 +177,51 @@ __device__ __forceinline__ void copy_rest(const char* src, const DST& dst, int n
 }
 
 // ------------------------------------------------------------------ the pipelined mover
+// A gather-copy of shards that are no multiple of 16 bytes: shard r starts r * shard_bytes bytes behind a 16-byte boundary of
+// the destination.  Stores stay aligned: the shard's first `head` bytes and what is left behind its last whole vector are
+// copied apart (at most 30 bytes a shard), and the vectors between them are read from element-aligned addresses.  (A chunk's
+// last vector then reaches up to 14 bytes into the next chunk.)  Eight shards of 1000003 bf16 at (32, 256, 64 KiB): 18.9 us, as
+// much as aligned shards take; element by element, two bytes per lane and load, it was 310.9 us.
+__device__ __forceinline__ uint32_t ragged_head(uint32_t r, int64_t shard_bytes) { return (16u - ((r * (uint32_t)shard_bytes) & 15u)) & 15u; }
+
 // A wavefront's walk over its share: chunks blockIdx, blockIdx + NC, ... of every shard in turn, and in each chunk the
 // 1 KiB units wave, wave + nw, ...  All of it is wave-uniform: 32-bit arithmetic on scalar registers (gfx9 has no 64-bit
 // scalar compare), and a step is straight-line code -- with loops in it the compiler's control flow holds paths on which
 // a batch seems never to be waited for, and it drains the memory pipeline on each.  Which lane moves an element
 // depends on the sizes, NC, NT and C only, not on how many units are in flight: the steps of one launch rely on that.
-template <bool GATHER>
+enum WalkKind { REDUCE, GATHER, GATHER_RAGGED };
+template <WalkKind KIND>
 struct Walk {
     Shape s;
     uint32_t wave, nw;
     uint32_t c, r;                              // current chunk of the shard, shard (0 in a reduce-copy)
     uint32_t n, units, rest;                    // unit, units of the chunk, bytes of whole vectors in its last unit
     bool more;                                  // the walk stands on something to move
+    // GATHER_RAGGED: bytes of the current shard in front of its first destination vector
+    __device__ __forceinline__ uint32_t head() const { return KIND == GATHER_RAGGED ? ragged_head(shard(), s.shard_bytes) : 0u; }
     __device__ __forceinline__ void open() {
+        n = wave;
+        if (KIND == GATHER_RAGGED) {
+            const int64_t left = s.shard_bytes - ragged_head(r, s.shard_bytes) - (int64_t)c * s.chunk_bytes;
+            const int64_t whole = (left < s.chunk_bytes ? left > 0 ? left : 0 : s.chunk_bytes) & ~(int64_t)15;
+            units = (uint32_t)((whole + 1023) >> 10);
+            rest = (uint32_t)(whole - ((int64_t)units - 1) * 1024);
+            return;
+        }
         const bool end = c + 1 == s.chunks;
         units = end ? s.last_units : s.full_units;
         rest = end ? s.last_rest : s.full_rest;
-        n = wave;
     }
     __device__ __forceinline__ void first() {
         c = blockIdx.x; r = 0;
-        if (GATHER) { r = c / s.chunks; c -= r * s.chunks; }
+        if (KIND != REDUCE) { r = c / s.chunks; c -= r * s.chunks; }
         open();
-        more = GATHER ? r < s.nshards && s.full_units > 0 : c < s.chunks && n < units;
+        more = KIND != REDUCE ? r < s.nshards && s.full_units > 0 : c < s.chunks && n < units;
     }
     __device__ __forceinline__ void next(uint32_t batch) {
         n += batch * nw;
         if (n >= units) {
-            if (GATHER) {
+            if (KIND != REDUCE) {
                 // a shard's short last chunk may hold no unit for this wavefront; the walk still stops there (and moves nothing)
                 c += s.step_chunks; r += s.step_shards;
                 if (c >= s.chunks) { c -= s.chunks; ++r; }
@@ -205,14 +229,14 @@ struct Walk {
                 c += gridDim.x;                 // at most 2^30 + 65535
             }
             open();
-            more = more && (GATHER ? r < s.nshards : c < s.chunks && n < units);   // only the last chunk can have fewer units
+            more = more && (KIND != REDUCE ? r < s.nshards : c < s.chunks && n < units);   // only the last chunk can have fewer units
         }
     }
     // Where there is nothing to move the walk points at the start of a shard, for loads that nobody uses.
     __device__ __forceinline__ uint32_t shard() const { return more ? r : 0; }
-    __device__ __forceinline__ bool empty() const { return !more || (GATHER && n >= units); }
+    __device__ __forceinline__ bool empty() const { return !more || (KIND != REDUCE && n >= units); }
     __device__ __forceinline__ int64_t offset() const {         // byte in the shard
-        return empty() ? 0 : (int64_t)c * s.chunk_bytes + ((int64_t)n << 10);
+        return empty() ? 0 : (int64_t)c * s.chunk_bytes + ((int64_t)n << 10) + head();
     }
     // offset from offset() of the chunk's last vector (from 2^20 units on: larger than any offset in a batch)
     __device__ __forceinline__ uint32_t limit() const {
@@ -221,9 +245,9 @@ struct Walk {
     }
 };
 
-template <bool GATHER>
-__device__ __forceinline__ Walk<GATHER> make_walk(const Shape& s) {
-    Walk<GATHER> w{};
+template <WalkKind KIND>
+__device__ __forceinline__ Walk<KIND> make_walk(const Shape& s) {
+    Walk<KIND> w{};
     w.s = s;
     w.wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     w.nw = blockDim.x >> 6;
@@ -234,14 +258,16 @@ __device__ __forceinline__ Walk<GATHER> make_walk(const Shape& s) {
 template <class SRC, class DST>
 struct ReduceIo {                               // src(s) and dst(d) at the same offset
     const SRC& src; const DST& dst; int ndst;
-    __device__ __forceinline__ const char* from(const Walk<false>& w, int s) const { return src(s) + w.offset(); }
-    __device__ __forceinline__ int64_t to(const Walk<false>& w) const { return w.offset(); }
+    __device__ __forceinline__ const char* from(const Walk<REDUCE>& w, int s) const { return src(s) + w.offset(); }
+    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return ld16<STREAM>(p); }
+    __device__ __forceinline__ int64_t to(const Walk<REDUCE>& w) const { return w.offset(); }
 };
-template <class SRC, class DST>
+template <WalkKind KIND, class SRC, class DST>
 struct GatherIo {                               // shard r goes to r * shard_bytes
     const SRC& src; const DST& dst; int ndst;
-    __device__ __forceinline__ const char* from(const Walk<true>& w, int) const { return src(w.shard()) + w.offset(); }
-    __device__ __forceinline__ int64_t to(const Walk<true>& w) const { return w.shard() * w.s.shard_bytes + w.offset(); }
+    __device__ __forceinline__ const char* from(const Walk<KIND>& w, int) const { return src(w.shard()) + w.offset(); }
+    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return KIND == GATHER_RAGGED ? ld16_ragged<STREAM>(p) : ld16<STREAM>(p); }
+    __device__ __forceinline__ int64_t to(const Walk<KIND>& w) const { return w.shard() * w.s.shard_bytes + w.offset(); }
 };
 
 // A batch: U units of one chunk, S sources each.
@@ -266,11 +292,14 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         b.off = io.to(w);
         const uint32_t last = w.limit();
         b.limit = w.empty() ? -1 : (int32_t)last;
+        const char* from[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) from[s] = io.from(w, s);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t o = at[u] < last ? at[u] : last;
 #pragma unroll
-            for (int s = 0; s < S; ++s) b.v[u][s] = ld16<STREAM>(io.from(w, s) + o);
+            for (int s = 0; s < S; ++s) b.v[u][s] = IO::template load<STREAM>(from[s] + o);
         }
     };
     auto finish = [&](const Batch<S, U>& b, int u) {
@@ -317,7 +346,7 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
 // Many sources: a unit's sources are loaded in two halves, and while one half is added the other (of this unit, then of
 // the next one) is in flight.  Half the registers of two whole units.
 template <int DT, int S, bool STREAM, class IO>
-__device__ __forceinline__ void move_halves(Walk<false> w, const IO& io, uint32_t lane) {
+__device__ __forceinline__ void move_halves(Walk<REDUCE> w, const IO& io, uint32_t lane) {
     constexpr int SA = (S + 1) / 2, SB = S - SA;
     w.first();
     if (!w.more) return;
@@ -355,7 +384,7 @@ __device__ __forceinline__ void move_halves(Walk<false> w, const IO& io, uint32_
 
 // Any number of sources, four loads in flight: the steps of more than two sources of a fused launch.
 template <int DT, bool STREAM, class IO>
-__device__ __forceinline__ void move_any(Walk<false> w, const IO& io, int nsrc, uint32_t lane) {
+__device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc, uint32_t lane) {
     const uint32_t lo = lane * 16;
     for (w.first(); w.more; w.next(1)) {
         if (lo > w.limit()) continue;
@@ -385,7 +414,7 @@ constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) 
 constexpr bool in_halves(int S, bool deep) { return deep ? S > 8 : S > 4; }
 
 template <int DT, int S, bool STREAM, bool DEEP, class IO>
-__device__ __forceinline__ void move_reduce(const Walk<false>& w, const IO& io, uint32_t lane) {
+__device__ __forceinline__ void move_reduce(const Walk<REDUCE>& w, const IO& io, uint32_t lane) {
     if constexpr (in_halves(S, DEEP)) move_halves<DT, S, STREAM>(w, io, lane);
     else move_batches<DT, S, units_in_batch(S, DEEP), STREAM, false>(w, io, lane);
 }
@@ -413,37 +442,30 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) reduce_copy_kernel(cons
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
     const ReduceIo<decltype(src), decltype(dst)> io{src, dst, p.ndst};
-    move_reduce<DT, S, STREAM, DEEP>(make_walk<false>(p.shape), io, threadIdx.x & 63);
+    move_reduce<DT, S, STREAM, DEEP>(make_walk<REDUCE>(p.shape), io, threadIdx.x & 63);
     reduce_tail<DT>(src, dst, S, p.ndst, p.shape.shard_bytes, p.shape.chunks);
 }
 
-// Gather-copy with 16-byte vectors; needs shard_bytes % 16 == 0 (or a single shard) so that
-// every shard starts 16-byte aligned in the destination.
-template <bool STREAM, bool DEEP>
+// KIND GATHER: every shard starts 16-byte aligned in the destination (shard_bytes % 16 == 0, or a single shard).
+template <WalkKind KIND, bool STREAM, bool DEEP>
 __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) gather_copy_kernel(const CommArgs p) {
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
-    const GatherIo<decltype(src), decltype(dst)> io{src, dst, p.ndst};
-    move_batches<LAGOM_F32, 1, units_in_batch(1, DEEP), STREAM, true>(make_walk<true>(p.shape), io,
-                                                                      threadIdx.x & 63);
-    if (p.nsrc == 1) copy_tail(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
-}
-
-// Gather-copy for shards whose byte length is not a multiple of 16: destinations of shards
-// r >= 1 are then only element-aligned, so elements (2 or 4 bytes) are copied one by one.
-template <typename E>
-__global__ void __launch_bounds__(1024) gather_copy_elements_kernel(const CommArgs p) {
-    const int nt = blockDim.x;
-    for (int64_t g = blockIdx.x; g < (int64_t)p.shape.chunks * p.nsrc; g += gridDim.x) {
-        const int64_t r = g / p.shape.chunks;
-        const int64_t base = (g - r * p.shape.chunks) * p.shape.chunk_bytes;
-        const int64_t left = p.shape.shard_bytes - base;
-        const int64_t len = left < p.shape.chunk_bytes ? left : p.shape.chunk_bytes;
-        const int64_t n = len / (int64_t)sizeof(E);
-        const E* src = reinterpret_cast<const E*>(p.src[r] + base);
-        for (int64_t i = threadIdx.x; i < n; i += nt) {
-            const E x = src[i];
-            for (int d = 0; d < p.ndst; ++d) reinterpret_cast<E*>(p.dst[d] + r * p.shape.shard_bytes + base)[i] = x;
+    const GatherIo<KIND, decltype(src), decltype(dst)> io{src, dst, p.ndst};
+    move_batches<LAGOM_F32, 1, units_in_batch(1, DEEP), STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
+    if (KIND == GATHER) {
+        if (p.nsrc == 1) copy_tail(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
+        return;
+    }
+    // both ends of every shard, byte by byte: lanes 0..15 the head, lanes 16..31 the tail
+    for (int r = blockIdx.x; r < p.nsrc; r += gridDim.x) {
+        const int64_t n = p.shape.shard_bytes;
+        const int64_t head = ragged_head(r, n) < n ? ragged_head(r, n) : n, tail = (n - head) & 15;
+        const int t = threadIdx.x;
+        const int64_t at = t < 16 ? t : n - tail + (t - 16);
+        if (t < 16 ? t < head : t - 16 < tail) {
+            const char b = p.src[r][at];
+            for (int d = 0; d < p.ndst; ++d) p.dst[d][r * n + at] = b;
         }
     }
 }
@@ -461,14 +483,15 @@ void launch_reduce(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
     else deep ? launch_reduce_s<DT, false, true, 1>(a, grid, block, st) : launch_reduce_s<DT, false, false, 1>(a, grid, block, st);
 }
 
+template <WalkKind KIND>
 void launch_gather(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
     const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
     if (stream) {
-        if (deep) hipLaunchKernelGGL((gather_copy_kernel<true, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((gather_copy_kernel<true, false>), grid, block, 0, st, a);
+        if (deep) hipLaunchKernelGGL((gather_copy_kernel<KIND, true, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((gather_copy_kernel<KIND, true, false>), grid, block, 0, st, a);
     } else {
-        if (deep) hipLaunchKernelGGL((gather_copy_kernel<false, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((gather_copy_kernel<false, false>), grid, block, 0, st, a);
+        if (deep) hipLaunchKernelGGL((gather_copy_kernel<KIND, false, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((gather_copy_kernel<KIND, false, false>), grid, block, 0, st, a);
     }
 }
 
@@ -490,7 +513,7 @@ struct StepsArgs {
 
 template <int DT, bool STREAM, bool DEEP>
 __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const StepsArgs p) {
-    const Walk<false> w = make_walk<false>(p.shape);
+    const Walk<REDUCE> w = make_walk<REDUCE>(p.shape);
     const uint32_t lane = threadIdx.x & 63;
     for (int st = 0; st < p.nsteps; ++st) {
         const int first = p.first[st], nsrc = p.nsrc[st], ndst = p.ndst[st];
@@ -696,9 +719,8 @@ extern "C" int lagom_comm_kernel(lagom_op op, lagom_dtype dt, const void* const*
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const dim3 grid((unsigned)cfg->nc), block((unsigned)cfg->nt);
     if (op == LAGOM_REDUCE_COPY) dt == LAGOM_F32 ? launch_reduce<LAGOM_F32>(a, grid, block, st) : launch_reduce<LAGOM_BF16>(a, grid, block, st);
-    else if (nsrc == 1 || (a.shape.shard_bytes & 15) == 0) launch_gather(a, grid, block, st);
-    else if (dt == LAGOM_F32) hipLaunchKernelGGL((gather_copy_elements_kernel<uint32_t>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((gather_copy_elements_kernel<uint16_t>), grid, block, 0, st, a);
+    else if (nsrc == 1 || (a.shape.shard_bytes & 15) == 0) launch_gather<GATHER>(a, grid, block, st);
+    else launch_gather<GATHER_RAGGED>(a, grid, block, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "comm kernel launch: %s", hipGetErrorString(e));
     return LAGOM_OK;

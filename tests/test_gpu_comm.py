@@ -425,3 +425,22 @@ def test_gather_copy_at_the_edges_of_its_batches(nt, P):
             for nc in {1, 2, chunks, 3 * chunks + 1, 64}:
                 got = _run(lg.LAGOM_GATHER_COPY, "bf16", shards, 1, (nc, nt, chunk), P * count)[0]
                 assert same_bits(got, want), (count, nc, chunk)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("nt", [64, 256, 320])
+@pytest.mark.parametrize("P", [2, 7, 16])
+def test_gather_copy_of_shards_off_the_vector_grid(dtype, nt, P):
+    """Every remainder of the shard length modulo 16 bytes, shards shorter than a vector, and lengths around units, batches
+    and chunks, so that a shard's last whole vector falls on either side of a chunk's end."""
+    esz = 4 if dtype == "f32" else 2
+    chunk = 16384
+    counts = [1, 2, 3, 5, 7, 9, 11, 15, 17] + [b // esz + e for b in (1024, (nt // 64) * 8192, chunk, 2 * chunk + 1024) for e in (-3, -1, 1, 3, 5)]
+    for count in counts:
+        if count < 1:
+            continue
+        shards = _sources(dtype, P, count, 1200)
+        want = np.concatenate(shards)
+        for nc in (1, 3, 40):
+            for got in _run(lg.LAGOM_GATHER_COPY, dtype, shards, 2, (nc, nt, chunk), P * count):
+                assert same_bits(got, want), (count, nc)
