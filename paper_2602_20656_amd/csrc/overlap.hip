@@ -3,10 +3,11 @@
 // Eq. 1) -- and time it with HIP events.  This is Alg. 2's ProfileTime and the experiment
 // behind Fig. 3.
 //
-// Both streams are released together: each starts with a short, bounded delay kernel that holds it
-// while the host enqueues every launch of both streams.  The kernel on the communication stream picks
-// the tick of the constant-rate wall clock at which the hold ends and publishes it through a word of
-// pinned host memory; the kernel on the computation stream reads it and holds until the same tick.
+// Both streams are released together: each starts with a short, bounded gate kernel that holds it
+// while the host enqueues every launch of both streams.  The host says when it has finished through a word
+// of pinned host memory; the gate on the communication stream then picks the tick of the constant-rate
+// wall clock at which the hold ends and publishes it beside that word; the gate on the computation stream
+// reads it and holds until the same tick.
 // (An event wait across streams instead of the second kernel released the computation stream 6 - 7 us
 // after the communication stream, which showed in Z of every computation-bound group.)  The kernels
 // therefore run back to back, unaffected by host launch latency, and start at a common instant.
@@ -38,19 +39,31 @@ __global__ void gate_delay_kernel(long long ticks, int max_iter) {
     }
 }
 
-// The start gate of a co-run.  The leader publishes the tick at which both streams go on, then the
-// sequence number of this repetition (release); the follower waits for its sequence number (acquire),
-// reads the tick and holds until then.  Every loop is bounded by `max_iter` whatever memory or the
-// clock say; a follower that never sees its number just ends late.
-struct GateWord { unsigned long long deadline; unsigned long long seq; };
+// The start gate of a repetition.  The host stores the sequence number of the repetition into `go` when it has enqueued
+// the last launch; the leader (every repetition has one) waits for it, for at most `max_ticks`, picks the tick `lead_ticks`
+// later, publishes it and then the sequence number (release), and holds until that tick; the follower (co-runs only) waits
+// for the sequence number (acquire), reads the tick and holds until then.  Every loop is bounded by `max_iter` whatever
+// memory, the host or the clock say; a follower that never sees its number just ends late.
+// What bounds a gate is the host's enqueueing: 20 - 40 us for a ring share beside one product.  A hold of fixed length has to
+// cover the worst host instead; 60 us + 12 us per launch and event kept both streams waiting 337 us of a 556 us repetition.
+struct alignas(64) GateWord { unsigned long long deadline, seq, go; };
+constexpr double kGateLeadUs = 12.0;
+constexpr int kGateWords = 64;       // repetition n uses word n mod 64: co-runs of several threads do not meet in one
 
-__global__ void gate_leader_kernel(GateWord* g, unsigned long long seq, long long ticks, int max_iter) {
+__global__ void gate_leader_kernel(GateWord* g, unsigned long long seq, long long max_ticks, long long lead_ticks, int max_iter) {
     if (threadIdx.x == 0) {
         const long long t0 = wall_clock64();
-        __hip_atomic_store(&g->deadline, (unsigned long long)(t0 + ticks), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        int i = 0;
+        for (; i < max_iter; ++i) {
+            if (__hip_atomic_load(&g->go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == seq) break;
+            if (wall_clock64() - t0 >= max_ticks) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+        const long long t1 = wall_clock64();
+        __hip_atomic_store(&g->deadline, (unsigned long long)(t1 + lead_ticks), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&g->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        for (int i = 0; i < max_iter; ++i) {
-            if (wall_clock64() - t0 >= ticks) break;
+        for (; i < max_iter; ++i) {
+            if (wall_clock64() - t1 >= lead_ticks) break;
             __builtin_amdgcn_s_sleep(8);
         }
     }
@@ -71,9 +84,9 @@ __global__ void gate_follower_kernel(GateWord* g, unsigned long long seq, int ma
     }
 }
 
-// One gate word of pinned host memory per device, allocated at the first co-run on that device and
-// kept until the process ends (16 bytes; pinned host memory, not device memory).
-int gate_word(int dev, GateWord** out) {
+// The gate words of a device: pinned host memory (one page, not device memory), allocated at the first repetition on
+// that device and kept until the process ends.
+int gate_words(int dev, GateWord** out) {
     static std::mutex mu;
     static std::vector<GateWord*> words;
     std::lock_guard<std::mutex> lock(mu);
@@ -81,9 +94,9 @@ int gate_word(int dev, GateWord** out) {
     if ((size_t)dev >= words.size()) words.resize((size_t)dev + 1, nullptr);
     if (!words[dev]) {
         void* p = nullptr;
-        HIP_TRY(hipHostMalloc(&p, sizeof(GateWord), hipHostMallocDefault));
+        HIP_TRY(hipHostMalloc(&p, kGateWords * sizeof(GateWord), hipHostMallocDefault));
         GateWord* w = static_cast<GateWord*>(p);
-        w->deadline = 0; w->seq = 0;
+        for (int i = 0; i < kGateWords; ++i) w[i] = GateWord{0, 0, 0};
         words[dev] = w;
     }
     *out = words[dev];
@@ -277,7 +290,8 @@ int require_overlap(hipStream_t sa, hipStream_t sb) {
 // Two bounded delay kernels, a long one on stream a and, behind a common event, a short one on
 // stream b: on separate hardware queues the short one ends before the long one does, on a shared
 // queue it cannot start until the long one has ended.  The long kernel has to outlast the host's
-// submission of the short one; a verdict of "shared" is therefore confirmed with a ten times longer one.
+// submission of the short one (10 - 20 us), or a pair that overlaps looks shared; a verdict of "shared" is therefore
+// confirmed twice, with kernels of up to fifty times that.  "Overlaps" needs no confirmation: the short one cannot end early.
 extern "C" int lagom_streams_overlap(void* stream_a, void* stream_b, int* overlap) {
     if (!overlap) return lagom::fail(LAGOM_EINVAL, "null output");
     hipStream_t sa = static_cast<hipStream_t>(stream_a), sb = static_cast<hipStream_t>(stream_b);
@@ -288,7 +302,7 @@ extern "C" int lagom_streams_overlap(void* stream_a, void* stream_b, int* overla
     if (hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || clock_khz <= 0) clock_khz = 100000;
     Events E;
     if (int rc = E.make(3)) return rc;
-    for (const double long_us : {300.0, 3000.0}) {
+    for (const double long_us : {60.0, 300.0, 3000.0}) {
         HIP_TRY(hipEventRecord(E.ev[0], sa));
         HIP_TRY(hipStreamWaitEvent(sb, E.ev[0], 0));
         hipLaunchKernelGGL(gate_delay_kernel, dim3(1), dim3(64), 0, sa, (long long)(long_us * clock_khz / 1000.0), 1 << 14);
@@ -335,15 +349,17 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
     int dev = 0, clock_khz = 100000;
     HIP_TRY(hipGetDevice(&dev));
     if (hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || clock_khz <= 0) clock_khz = 100000;
-    // long enough for the host to enqueue everything: ~12 us per queued item plus a floor
+    // The longest hold, should the host not get to opening the gate: ~12 us per queued item plus a floor
     const int items = (run_comm ? nlaunch + 2 * ngroups : 0) + 3 * ncomp_run + 4;
     const double delay_us = 60.0 + 12.0 * items;
     const long long ticks = (long long)(delay_us * clock_khz / 1000.0);
     // a pass of the gates' loops takes 0.3 - 0.4 us: several times the passes the delay needs, and no more
     const int max_iter = (int)std::min(8.0 * delay_us + 4096.0, 4.0e6);
-    GateWord* word = nullptr;
-    if (run_comm && run_comp)
-        if (int rc = gate_word(dev, &word)) return rc;
+    // the leader's tick has to reach the follower through host memory: with 6 us in hand the streams are released 1.7 us apart,
+    // with 12 us 0.1 - 0.2 us
+    const long long lead_ticks = run_comm && run_comp ? (long long)(kGateLeadUs * clock_khz / 1000.0) : 0;
+    GateWord* words = nullptr;
+    if (int rc = gate_words(dev, &words)) return rc;
 
     std::vector<std::vector<double>> xs(ncfg), ys(ncomp);
     std::vector<double> Xs, Ys, Zs, startsA, startsB;
@@ -352,18 +368,18 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
     std::vector<double> Ysums;
     // one repetition: gate, both streams enqueued, both drained
     auto repetition = [&]() -> int {
-        if (word) {
-            const unsigned long long seq = next_gate_seq();
-            hipLaunchKernelGGL(gate_leader_kernel, dim3(1), dim3(64), 0, sa, word, seq, ticks, max_iter);
-            HIP_TRY(hipGetLastError());
+        const unsigned long long seq = next_gate_seq();
+        GateWord* word = words + seq % kGateWords;
+        hipLaunchKernelGGL(gate_leader_kernel, dim3(1), dim3(64), 0, gate_stream, word, seq, ticks, lead_ticks, max_iter);
+        HIP_TRY(hipGetLastError());
+        if (run_comm && run_comp) {
             hipLaunchKernelGGL(gate_follower_kernel, dim3(1), dim3(64), 0, sb, word, seq, max_iter);
             HIP_TRY(hipGetLastError());
-        } else {
-            hipLaunchKernelGGL(gate_delay_kernel, dim3(1), dim3(64), 0, gate_stream, ticks, max_iter);
-            HIP_TRY(hipGetLastError());
         }
-        if (int rc = enqueue_group(plan, launches, run_comm ? nlaunch : 0, cfgs, comps, ncomp_run, deps, sa, sb,
-                                   ga_start, ga_end, gb_start, gb_end)) return rc;
+        const int rc = enqueue_group(plan, launches, run_comm ? nlaunch : 0, cfgs, comps, ncomp_run, deps, sa, sb,
+                                     ga_start, ga_end, gb_start, gb_end);
+        __atomic_store_n(&word->go, seq, __ATOMIC_RELEASE);       // also behind a failure: what is queued is to drain
+        if (rc) return rc;
         if (run_comm) HIP_TRY(hipStreamSynchronize(sa));
         if (run_comp) HIP_TRY(hipStreamSynchronize(sb));
         return LAGOM_OK;

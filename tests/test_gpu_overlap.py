@@ -1,4 +1,6 @@
 """GPU checks of the overlap runner, the contention profiler and the measured tuner."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -51,6 +53,18 @@ def test_both_streams_are_released_at_the_same_instant(tiny):
         assert t.Z_us == pytest.approx(later_end, abs=3.0)          # medians of different repetitions: not an identity
     r = lg.lagom_overlap_run(tiny["launches"], [(4, 256, 128 << 10)], tiny["comps"], tiny["s1"], tiny["s2"], 1, 5, lg.LAGOM_ALONE_COMM)
     assert r.comp_start_us == 0.0 and r.comm_start_us >= 0.0
+
+
+@pytest.mark.parametrize("mode", [lg.LAGOM_CORUN, lg.LAGOM_ALONE_COMM, lg.LAGOM_ALONE_COMP])
+def test_gates_open_over_more_repetitions_than_there_are_gate_words(tiny, mode):
+    """65 repetitions use every gate word and the first one again.  A gate that missed its word would hold its stream to the
+    bound of its loop, tens of milliseconds where a repetition takes a tenth of one."""
+    run = lambda n: lg.lagom_overlap_run(tiny["launches"], [(64, 256, 64 << 10)], tiny["comps"], tiny["s1"], tiny["s2"], 0, n, mode)
+    run(1)
+    t0 = time.perf_counter()
+    t = run(65)
+    assert time.perf_counter() - t0 < 65 * 2e-3
+    assert abs(t.comm_start_us - t.comp_start_us) <= 4.0
 
 
 def test_streams_that_share_a_hardware_queue_are_detected_and_refused(tiny):
