@@ -79,10 +79,7 @@ __device__ __forceinline__ int swz(int row, int cg) { return row * 8 + (cg ^ (ro
 // Workgroup id -> (tile_m, tile_n).  Hardware deals consecutive ids round-robin to the 8 XCDs;
 // id = x + 8*q is given the q-th tile of the x-th eighth of the tile list, and the list itself
 // runs down columns of 8 tile-rows so that neighbours share B panels and reuse A panels.
-__device__ __forceinline__ void tile_of(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
-    const int total = tiles_m * tiles_n;
-    int lin = id;
-    if ((total & 7) == 0) lin = (id & 7) * (total >> 3) + (id >> 3);
+__device__ __forceinline__ void tile_in_list(int lin, int tiles_m, int tiles_n, int* tm, int* tn) {
     constexpr int GROUP = 8;
     const int per_group = GROUP * tiles_n;
     const int grp = lin / per_group;
@@ -91,6 +88,12 @@ __device__ __forceinline__ void tile_of(int id, int tiles_m, int tiles_n, int* t
     const int in = lin - grp * per_group;
     *tm = first_m + in % rows;
     *tn = in / rows;
+}
+__device__ __forceinline__ void tile_of(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
+    const int total = tiles_m * tiles_n;
+    int lin = id;
+    if ((total & 7) == 0) lin = (id & 7) * (total >> 3) + (id >> 3);
+    tile_in_list(lin, tiles_m, tiles_n, tm, tn);
 }
 
 template <bool B_NK, bool OUT_BF16>
@@ -247,7 +250,7 @@ typedef __attribute__((address_space(3))) char* lds_bytes;
 // and transposed by the LDS reads.
 // K_TAIL: K is not a multiple of 64; the last K % 64 columns are multiplied in a step of their own after the loop.
 template <bool B_KN, bool OUT_BF16, bool K_TAIL>
-__device__ __forceinline__ void fast_gemm_body(const GemmArgs& p) {
+__device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn) {
     extern __shared__ u32x4 smem[];   // LDS_SLOTS operand tiles of 2048 16-byte slots
     // Wavefronts of a communication kernel may share this wavefront's SIMD (this kernel leaves them
     // registers): let the instruction arbiter prefer the GEMM.
@@ -256,8 +259,6 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    int tm, tn;
-    tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int64_t M = p.M, N = p.N, K = p.K;
     const char* smem_bytes = reinterpret_cast<const char*>(smem);
@@ -575,14 +576,14 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p) {
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { fast_gemm_body<false, OUT_BF16, false>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { fast_gemm_body<true, OUT_BF16, false>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
 // K >= 64 and not a multiple of 64 (kernels of their own: the extra step costs registers the others leave free)
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { fast_gemm_body<false, OUT_BF16, true>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { fast_gemm_body<true, OUT_BF16, true>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<true, OUT_BF16, true>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- small-tile kernels
 // 128 x 128 x 64 and 256 x 128 x 64 tiles for products with too few 256 x 256 tiles to fill the chip.
@@ -609,7 +610,7 @@ __device__ __forceinline__ int kn_swz128(int k) { return (((k >> 3) & 1) << 3) |
 
 // K_TAIL: K is not a multiple of 64; the last K % 64 columns get a step of their own (see the large kernel).
 template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL>
-__device__ __forceinline__ void small_gemm_body(const GemmArgs& p) {
+__device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int tn) {
     typedef SmallTile<NI> T;
     constexpr int S_STAGES = T::STAGES, S_AHEAD = T::AHEAD, S_STAGE_BYTES = T::STAGE_BYTES, S_OPERAND_BYTES = T::A_BYTES;
     constexpr int LA = T::LA, LB = T::LB, PER_TILE = LA + LB;
@@ -619,8 +620,6 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p) {
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    int tm, tn;
-    tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn);
     const int64_t m0 = (int64_t)tm * T::BM_, n0 = (int64_t)tn * SBN;
     const int64_t M = p.M, N = p.N, K = p.K;
     const char* smem_bytes = reinterpret_cast<const char*>(smem);
@@ -893,26 +892,71 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p) {
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_kernel(const GemmArgs p) { small_gemm_body<4, false, OUT_BF16, false>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_kernel(const GemmArgs p) { small_gemm_body<4, true, OUT_BF16, false>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, true, OUT_BF16, false>(p, tm, tn); }
 // 256 x 128 tiles
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_kernel(const GemmArgs p) { small_gemm_body<8, false, OUT_BF16, false>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_kernel(const GemmArgs p) { small_gemm_body<8, true, OUT_BF16, false>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, true, OUT_BF16, false>(p, tm, tn); }
 // K >= 64 and not a multiple of 64
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_tail_kernel(const GemmArgs p) { small_gemm_body<4, false, OUT_BF16, true>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_tail_kernel(const GemmArgs p) { small_gemm_body<4, true, OUT_BF16, true>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, true, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_tail_kernel(const GemmArgs p) { small_gemm_body<8, false, OUT_BF16, true>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_tail_kernel(const GemmArgs p) { small_gemm_body<8, true, OUT_BF16, true>(p); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, true, OUT_BF16, true>(p, tm, tn); }
 
-template <void (*KERNEL)(const GemmArgs)>
-int launch_fast(const GemmArgs& a, dim3 grid, hipStream_t st) {
+// ------------------------------------------------------------------------- large tiles, the last round in small ones
+// A product of more than 256 large tiles runs in rounds of 256 (one per compute unit), and the last round costs as much
+// as a full one however few tiles are in it: 4100 x 4200 has 289, of which 33 kept 256 compute units waiting.  Here the
+// whole rounds are large tiles and what is left over is cut into its 128 x 128 quadrants, which spread over the chip and
+// start as the large tiles of the last whole round end.  The large tiles are the first `nlarge` of a list that has the
+// tiles inside C first and those its edges cut through last, so quadrants that lie outside C altogether (they return at
+// once) are saved too.  Every element is summed in the same order whichever tile holds it.
+struct MixedArgs {
+    GemmArgs g;                 // tiles_m, tiles_n: 256 x 256
+    int32_t full_m, full_n;     // tiles inside C altogether
+    int32_t nlarge;             // a multiple of 256
+    int32_t per_xcd;            // left-over tiles an XCD takes the quadrants of
+};
+
+template <bool B_KN, bool OUT_BF16, bool K_TAIL>
+__device__ __forceinline__ void mixed_gemm_body(const MixedArgs& p) {
+    const int id = blockIdx.x, x = id & 7;
+    const bool large = id < p.nlarge;
+    // XCD x: the x-th eighth of the large tiles, then the quadrants of the x-th eighth of the rest, four in a row of one tile
+    const int j = (id - p.nlarge) >> 3;
+    const int lin = large ? x * (p.nlarge >> 3) + (id >> 3) : p.nlarge + x * p.per_xcd + (j >> 2);
+    const int inside = p.full_m * p.full_n, right = p.full_m * (p.g.tiles_n - p.full_n);
+    int tm, tn;
+    if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, &tm, &tn);
+    else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
+    else { tm = p.full_m; tn = lin - inside - right; }
+    if (large) {
+        fast_gemm_body<B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
+        return;
+    }
+    if (lin >= p.g.tiles_m * p.g.tiles_n) return;
+    tm = 2 * tm + (j & 1);
+    tn = 2 * tn + ((j >> 1) & 1);
+    if ((int64_t)tm * SBM >= p.g.M || (int64_t)tn * SBN >= p.g.N) return;
+    small_gemm_body<4, B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
+}
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_mixed_kernel(const MixedArgs p) { mixed_gemm_body<false, OUT_BF16, false>(p); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_mixed_kernel(const MixedArgs p) { mixed_gemm_body<true, OUT_BF16, false>(p); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_mixed_tail_kernel(const MixedArgs p) { mixed_gemm_body<false, OUT_BF16, true>(p); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_mixed_tail_kernel(const MixedArgs p) { mixed_gemm_body<true, OUT_BF16, true>(p); }
+
+template <auto KERNEL, class ARGS>
+int launch_fast(const ARGS& a, dim3 grid, hipStream_t st) {
     // set once per kernel (and per device: a process may drive several); a failure is not remembered
     static std::atomic<uint64_t> done_on_device{0};
     int dev = 0;
@@ -938,6 +982,30 @@ Tiling choose_tiling(int64_t M, int64_t N, int64_t K) {
     if (((M + SBM - 1) / SBM) * cols <= 256) return TILE_128x128;
     if (((M + MBM - 1) / MBM) * cols <= 256) return TILE_256x128;
     return TILE_256x256;
+}
+
+constexpr int kRound = 256;         // workgroups in a round: one per compute unit
+// A chip full of 128 x 128 tiles takes 0.39 of the time of one full of 256 x 256 tiles, so up to two rounds of quadrants
+// are cheaper than one more round of large tiles.  us, large tiles only -> cut: 4096 x N x 4096 with N = 4352 (16 left
+// over) 154.9 -> 113.2, 4608 (32) 157.1 -> 116.5, 5120 (64) 158.4 -> 123.0, 6144 (128, two rounds of quadrants) 164.0 ->
+// 154.4; 4100 x 4200 x 2048 (33 left over, 65 quadrants) 86.1 -> 64.8; 8192 x 8448 x 8192 (fifth round, 32) 808 -> 733.
+constexpr int kMaxQuadrants = 2 * kRound;
+
+// Whether the last round of a product in large tiles is worth cutting into quadrants, and how.
+bool choose_mixed(const GemmArgs& g, MixedArgs* out) {
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
+    const int rest = (int)(tiles % kRound);
+    if (tiles <= kRound || rest == 0) return false;
+    MixedArgs a{g, (int32_t)(g.M / BM), (int32_t)(g.N / BN), (int32_t)(tiles - rest), (rest + 7) / 8};
+    // quadrants that hold something: 4 of a tile inside C, fewer of one that an edge cuts through
+    const int64_t inside = (int64_t)a.full_m * a.full_n, right = (int64_t)a.full_m * (g.tiles_n - a.full_n);
+    const int halves_m = g.M % BM == 0 || g.M % BM > SBM ? 2 : 1, halves_n = g.N % BN == 0 || g.N % BN > SBN ? 2 : 1;
+    int quadrants = 0;
+    for (int64_t lin = a.nlarge; lin < tiles; ++lin)
+        quadrants += lin < inside ? 4 : lin < inside + right ? 2 * halves_n : halves_m * (lin - inside - right < a.full_n ? 2 : halves_n);
+    if (quadrants > kMaxQuadrants) return false;
+    *out = a;
+    return true;
 }
 
 }  // namespace
@@ -1019,7 +1087,17 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     const dim3 grid((unsigned)tiles), block(THREADS);
     const bool bf = out_dt == LAGOM_BF16;
     const bool fast = K >= BK && K <= FAST_MAX_K && (b_is_nk || N <= FAST_MAX_N_KN);
-    if (fast) {
+    MixedArgs mixed;
+    if (fast && choose_mixed(a, &mixed)) {
+        const dim3 both((unsigned)(mixed.nlarge + 32 * mixed.per_xcd));
+        const bool tail = K % BK != 0;
+        int rc;
+#define LAGOM_PICK(NAME) (bf ? launch_fast<NAME<true>>(mixed, both, st) : launch_fast<NAME<false>>(mixed, both, st))
+        if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk_mixed_tail_kernel) : LAGOM_PICK(gemm_bf16_nk_mixed_kernel);
+        else rc = tail ? LAGOM_PICK(gemm_bf16_kn_mixed_tail_kernel) : LAGOM_PICK(gemm_bf16_kn_mixed_kernel);
+#undef LAGOM_PICK
+        if (rc) return rc;
+    } else if (fast) {
         int rc;
         if (K % BK == 0) {
             if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_nk_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_nk_kernel<false>>(a, grid, st);

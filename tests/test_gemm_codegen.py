@@ -145,3 +145,30 @@ def test_small_tile_step_has_one_side_instruction_per_mfma(assembly, name):
         elif not l.startswith(("s_waitcnt", "s_barrier")):
             run += 1
     assert worst <= 4, worst   # an address add or two with a read; an offset add with an M0 write
+
+
+MIXED = tuple("gemm_bf16_%s_mixed%s_kernelILb%dE" % (k, t, o) for k in ("nk", "kn") for t in ("", "_tail") for o in (1, 0))   # both bodies in one kernel
+
+
+@pytest.mark.parametrize("name", MIXED)
+def test_both_bodies_of_a_mixed_kernel_keep_their_accumulators(assembly, name):
+    sym, _ = _body(assembly, name)
+    start = assembly.index("\n" + sym + ":")
+    lines = [l.split(";")[0].strip() for l in assembly[start:assembly.index(".Lfunc_end", start)].splitlines()[2:]]   # past the early ends
+    lines = [l for l in lines if l]
+    meta = _metadata(assembly, sym)
+    assert meta["vgpr_spill_count"] == "0" and meta["sgpr_spill_count"] == "0", meta
+    assert meta["agpr_count"] == "256" and meta["private_segment_fixed_size"] == "0", meta
+    waits = [i for i in range(len(lines) - 2) if all(l.startswith("s_nop 7") for l in lines[i:i + 3])]
+    assert len(waits) == 2
+    start = 0
+    for nop in waits:
+        mfma = [i for i in range(start, nop) if lines[i].startswith("v_mfma_f32_16x16x32_bf16")]
+        assert len(mfma) >= 3 * 64 // 2
+        for falls_in, block in _blocks(lines[mfma[0]:nop]):
+            has_mfma = any(l.startswith("v_mfma") for l in block)
+            for l in block:
+                if not l.startswith("v_mfma_f32_16x16x32_bf16") and AGPR.search(l):
+                    assert not has_mfma and not falls_in and l.startswith(("v_accvgpr_mov_b32", "v_accvgpr_write_b32")), l
+        start = nop + 3
+    assert not any(l.startswith("v_mfma") for l in lines[start:])

@@ -200,3 +200,19 @@ def test_gemm_more_tiles_than_compute_units_integer_inputs_are_exact(M, N, K, b_
         want = oc.bf16_to_f32(oc.f32_to_bf16(want))
     bad = np.argwhere(got != want)
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]} (tile {bad[0][0] // 256}, {bad[0][1] // 256})"
+
+
+@pytest.mark.parametrize("M,N", [(3970, 4456),     # 16 x 18 tiles, 255 inside: an edge tile among the large ones
+                                 (4096, 6144),     # two rounds of quadrants, none empty
+                                 (4096, 6400),     # more than two rounds: large tiles only
+                                 (4224, 4232),     # edge tiles with one half in C exactly, and with 8 columns of the second
+                                 (130, 66000)])    # one row of tiles, none inside
+@pytest.mark.parametrize("K", [64, 200])
+@pytest.mark.parametrize("b_is_nk", [True, False])
+def test_gemm_last_round_in_quadrants_integer_inputs_are_exact(M, N, K, b_is_nk):
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+    got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
+    bad = np.argwhere(got != (a @ (b.T if b_is_nk else b)))
+    assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
