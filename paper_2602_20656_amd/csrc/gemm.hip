@@ -37,9 +37,11 @@
 //     in memory, 64 rows (k) of 256 columns, and ds_read_b64_tr_b16 transposes while reading: two
 //     reads give a lane the 8 consecutive k of one column.  48 instead of 32 LDS reads per K-step,
 //     still one per MFMA.
-//   * K not a multiple of 64 (kernels of their own): after the loop's whole steps the last K % 64
-//     columns are fetched with guarded loads, zero filled from K on, stored to LDS in the loop's
-//     layout and multiplied by the same reads and MFMAs.
+//   * K not a multiple of 64 (kernels of their own): the last step takes the last 64 columns, of which
+//     the loop has multiplied some already, and clears those in its operand fragments (in both, so
+//     that no stray NaN meets a zero).  Its loads are in flight like any other step's; the rest of K
+//     fetched behind the loop with guarded loads cost a memory latency per tile: 4096 x 4096 x 184
+//     14.7 -> 13.4 us, x 72 12.7 -> 12.0, 4096 x 4352 x 2056 76.4 -> 74.0, 128 x 128 x 520 6.9 -> 6.7.
 // General kernel (any K multiple of 8, either B layout, v_mfma_f32_32x32x16_bf16): tiles are
 // fetched into registers with bounds checks and zero fill, then stored to LDS ([K,N]: 8 x 8
 // blocks transposed in registers first); single buffered.  Slower; used for K < 64 and beyond
@@ -244,11 +246,29 @@ __device__ __forceinline__ int kn_swz(int k) { return (((k >> 3) & 3) << 3) | ((
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+// Clears an operand fragment in the lanes that do not keep theirs.
+template <class FRAG>
+__device__ __forceinline__ void keep_frag(FRAG& f, bool keep) {
+    typedef uint32_t words __attribute__((ext_vector_type(sizeof(FRAG) / 4)));
+    words w = __builtin_bit_cast(words, f);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(FRAG) / 4); ++i) w[i] = keep ? w[i] : 0u;
+    f = __builtin_bit_cast(FRAG, w);
+    asm volatile("" : "+v"(f));
+}
+// An MFMA may read a register that a vector instruction wrote only some wait states later, and the compiler does not see
+// the MFMAs in the asm statements.
+__device__ __forceinline__ void wait_before_mfma() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 3" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 typedef __attribute__((address_space(3))) char* lds_bytes;
 
 // B_KN = false: B stored [N,K]; true: B stored [K,N], its tiles kept in LDS as 64 rows (k) of 256 columns
 // and transposed by the LDS reads.
-// K_TAIL: K is not a multiple of 64; the last K % 64 columns are multiplied in a step of their own after the loop.
+// K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64, behind the start of the one before it.
 template <bool B_KN, bool OUT_BF16, bool K_TAIL>
 __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn) {
     extern __shared__ u32x4 smem[];   // LDS_SLOTS operand tiles of 2048 16-byte slots
@@ -309,7 +329,12 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     // (no immediate offset: the hardware would add it to the LDS address as well)
     auto load_m0 = [&](const char* sbase, uint32_t voff) { asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory"); };
 
-    const int64_t ksteps = K / BK;
+    const int64_t ksteps = K_TAIL ? (K + BK - 1) / BK : K / BK;
+    const int again = K_TAIL ? (int)(ksteps * BK - K) : 0;      // columns of the last tile that the one before it holds as well
+    const int64_t again_a = 2 * again, again_b = B_KN ? 2 * again * N : 2 * again;   // in bytes
+    // (a K_TAIL product has at least two steps)
+    const char* const base_a1 = base_a + BK * 2 - (K_TAIL && ksteps == 2 ? again_a : 0);
+    const char* const base_b1 = base_b + b_step - (K_TAIL && ksteps == 2 ? again_b : 0);
     // prologue: A0 -> slot 0, B0 -> slot 1, A1 -> slot 2, first half of B1 -> slot 3
 #pragma unroll
     for (int d = 0; d < 8; ++d) load_now(base_a, a_off[d], 0, d);
@@ -317,9 +342,9 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     for (int d = 0; d < 8; ++d) load_now(base_b, b_off[d], 1, d);
     if (ksteps > 1) {
 #pragma unroll
-        for (int d = 0; d < 8; ++d) load_now(base_a + BK * 2, a_off[d], 2, d);
+        for (int d = 0; d < 8; ++d) load_now(base_a1, a_off[d], 2, d);
 #pragma unroll
-        for (int d = 0; d < 4; ++d) load_now(base_b + b_step, b_off[d], 3, d);
+        for (int d = 0; d < 4; ++d) load_now(base_b1, b_off[d], 3, d);
         asm volatile("s_waitcnt vmcnt(12)" ::: "memory");   // loads complete in issue order: A0 and B0 are in
     } else {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -383,7 +408,7 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     // every role two slots along a ring of five, which is a pure rotation of these five values.
     uint32_t o_a = 0, o_b = SLOT_BYTES, o_a1 = 2 * SLOT_BYTES, o_b1 = 3 * SLOT_BYTES, o_a2 = 4 * SLOT_BYTES;
     const char* g_a = base_a + 2 * (BK * 2);   // &A[m0][(kt+2)*64]
-    const char* g_b = base_b + b_step;         // tile kt+1 of B; tile kt+2 is reached through b_off_next
+    const char* g_b = base_b1;                 // tile kt+1 of B; tile kt+2 is reached through b_off_next
     uint32_t b_off_next[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) b_off_next[d] = b_off[d] + (uint32_t)b_step;
@@ -405,6 +430,15 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
         const uint32_t l_b1 = lds0 + o_b1, l_a2 = lds0 + o_a2, l_a = lds0 + o_a;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
+            if (K_TAIL && !more1) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    keep_frag(fa[ks][r], ks * 4 + kq >= again / 8);
+                    if (!B_KN) keep_frag(fb[ks][r], ks * 4 + kq >= again / 8);
+                    else { keep_frag(fbh[ks][r][0], ks * 4 + kq >= again / 8); keep_frag(fbh[ks][r][1], ks * 4 + kq >= again / 8); }
+                }
+                wait_before_mfma();
+            }
 #pragma unroll
             for (int g = 0; g < 8; ++g) {
                 const int q = ks * 8 + g;
@@ -453,54 +487,17 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     };
     int kt = 0;
     const int nk = (int)ksteps;
-    for (; kt + 2 < nk; ++kt) step(std::true_type{}, std::true_type{});
+    for (; kt + (K_TAIL ? 3 : 2) < nk; ++kt) step(std::true_type{}, std::true_type{});
+    if (K_TAIL && kt + 2 < nk) {     // the step that begins to load the last tile
+        g_a -= again_a;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) b_off_next[d] -= (uint32_t)again_b;
+        step(std::true_type{}, std::true_type{});
+        g_b -= again_b;
+        ++kt;
+    }
     if (kt + 1 < nk) { step(std::true_type{}, std::false_type{}); ++kt; }
     if (kt < nk) step(std::false_type{}, std::false_type{});
-    if (K_TAIL) {
-        // The last K % 64 columns: fetched with ordinary guarded loads (zeros from K on, in both operands),
-        // put into the first two slots in the layout the loop uses, and multiplied by the same fragment
-        // reads and MFMAs.  Every wavefront is past the last step's barrier, behind which nothing reads
-        // LDS and no LDS-direct load is in flight.
-        const int64_t kbase = ksteps * BK;
-        u32x4 ta[8], tb[8];
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int id = tid + THREADS * i;
-            const int64_t gm = m0 + (id >> 3), gk = kbase + (id & 7) * 8;
-            ta[i] = (gm < M && gk < K) ? *reinterpret_cast<const u32x4*>(p.A + gm * K + gk) : zero;
-            if (B_KN) {
-                const int64_t bk = kbase + (id >> 5), gn = n0 + (id & 31) * 8;
-                tb[i] = (bk < K && gn < N) ? *reinterpret_cast<const u32x4*>(p.B + bk * N + gn) : zero;
-            } else {
-                const int64_t gn = n0 + (id >> 3);
-                tb[i] = (gn < N && gk < K) ? *reinterpret_cast<const u32x4*>(p.B + gn * K + gk) : zero;
-            }
-        }
-        u32x4* slot_a = smem;
-        u32x4* slot_b = smem + SLOT_BYTES / 16;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int id = tid + THREADS * i;
-            slot_a[swz64(id >> 3, id & 7)] = ta[i];
-            if (B_KN) slot_b[(id >> 5) * 32 + ((id & 31) ^ kn_swz(id >> 5))] = tb[i];
-            else slot_b[swz64(id >> 3, id & 7)] = tb[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            if (ks == 1 && K - kbase <= 32) break;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                read_frag(slot_a, slot_b, ks, r, 0, 0);
-                if (B_KN && r >= 8) read_frag(slot_a, slot_b, ks, r, 0, 1);
-            }
-#pragma unroll
-            for (int g = 0; g < 8; ++g)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) LAGOM_MFMA_16x16x32(acc[g][j], b_frag(0, j), fa[0][g]);
-        }
-    }
     // The compiler does not see an MFMA inside the asm statements and therefore adds none of the wait
     // states an accumulator read needs after one: give the last results their cycles here, and make
     // every later use of an accumulator depend on a statement that follows these cycles.
@@ -608,7 +605,7 @@ constexpr int SBM = SmallTile<4>::BM_, MBM = SmallTile<8>::BM_;
 // c ^ kn_swz128(k), which spreads the rows of a transposing read over the 8 32-byte windows of a row.
 __device__ __forceinline__ int kn_swz128(int k) { return (((k >> 3) & 1) << 3) | ((k & 3) << 1); }
 
-// K_TAIL: K is not a multiple of 64; the last K % 64 columns get a step of their own (see the large kernel).
+// K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64 (see the large kernel).
 template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL>
 __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int tn) {
     typedef SmallTile<NI> T;
@@ -654,7 +651,15 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         }
     }
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
-    auto load_tile = [&](int stage) {   // the tile g_a / g_b point at, then advance them one K-step
+    const int nk = (int)(K_TAIL ? (K + BK - 1) / BK : K / BK);
+    const int again = K_TAIL ? (int)((int64_t)nk * BK - K) : 0;      // columns of the last tile that the one before it holds as well
+    const int64_t again_a = 2 * again, again_b = B_KN ? 2 * again * N : 2 * again;   // in bytes
+    // g_a / g_b from the tile in front of `t` to tile t.  (The compiler must not know `t`: it would peel the loop's last
+    // iterations for this comparison, and copy accumulators between them.)
+    auto is_last = [&](int t) { asm volatile("" : "+s"(t)); return t == nk - 1; };
+    auto next_a = [&](int t) { g_a += BK * 2; if (K_TAIL) g_a -= is_last(t) ? again_a : 0; };
+    auto next_b = [&](int t) { g_b += b_step; if (K_TAIL) g_b -= is_last(t) ? again_b : 0; };
+    auto load_tile = [&](int stage) {   // the tile g_a / g_b point at (tile `stage`), then advance them one K-step
         const uint32_t base = lds0 + stage * S_STAGE_BYTES;
 #pragma unroll
         for (int d = 0; d < LA; ++d)
@@ -662,11 +667,10 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
         for (int d = 0; d < LB; ++d)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base + S_OPERAND_BYTES + d * 4096), "v"(b_off[d]), "s"(g_b) : "memory");
-        g_a += BK * 2;
-        g_b += b_step;
+        next_a(stage + 1);
+        next_b(stage + 1);
     };
 
-    const int nk = (int)(K / BK);
     for (int t = 0; t < S_AHEAD && t < nk; ++t) load_tile(t);
     // Tile t >= AHEAD is loaded in two halves: A behind the barrier of step t-STAGES, B in the first half of
     // step t-AHEAD (g_a / g_b point at the next tile to load of their operand).
@@ -676,7 +680,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
         for (int d = 0; d < LA; ++d)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + S_AHEAD * S_STAGE_BYTES + d * 4096), "v"(a_off[d]), "s"(g_a) : "memory");
-        g_a += BK * 2;
+        next_a(S_AHEAD + 1);
     }
 
     const int arow = wm * (16 * NI) + (lane & 15), brow = wn * 64 + (lane & 15), kq = lane >> 4;
@@ -749,6 +753,17 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (K_TAIL && !NEXT) {
+                const bool keep = ks * 4 + kq >= again / 8;
+#pragma unroll
+                for (int i = 0; i < NI; ++i) keep_frag(fa[ks][i], keep);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (!B_KN) keep_frag(fb[ks][j], keep);
+                    else { keep_frag(fbh[ks][j][0], keep); keep_frag(fbh[ks][j][1], keep); }
+                }
+                wait_before_mfma();
+            }
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -768,8 +783,8 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
-        if (LOAD_B) g_b += b_step;
-        if (LOAD_A) g_a += BK * 2;
+        if (LOAD_B) next_b(kt + S_AHEAD + 1);
+        if (LOAD_A) next_a(kt + S_STAGES + 1);
         o_cur = o_next;
         o_next = o_next + S_STAGE_BYTES == S_STAGES * S_STAGE_BYTES ? 0 : o_next + S_STAGE_BYTES;
         o_b4 = o_b4 + S_STAGE_BYTES == S_STAGES * S_STAGE_BYTES ? 0 : o_b4 + S_STAGE_BYTES;
@@ -785,53 +800,6 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         if (kt + 1 < nk) step(std::false_type{}, std::false_type{}, std::true_type{});
     }
     if (kt < nk) step(std::false_type{}, std::false_type{}, std::false_type{});
-    if (K_TAIL) {
-        // Every wavefront is past the barrier of the last step, behind which nothing reads LDS and no
-        // LDS-direct load is in flight: the first slot takes the zero-filled rest of K in the loop's layout.
-        const int64_t kbase = (int64_t)nk * BK;
-        u32x4 ta[LA], tb[LB];
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int id = tid + THREADS * i;
-            const int64_t gm = m0 + (id >> 3), gk = kbase + (id & 7) * 8;
-            ta[i] = (gm < M && gk < K) ? *reinterpret_cast<const u32x4*>(p.A + gm * K + gk) : zero;
-        }
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int id = tid + THREADS * i;
-            if (B_KN) {
-                const int64_t bk = kbase + (id >> 4), gn = n0 + (id & 15) * 8;
-                tb[i] = (bk < K && gn < N) ? *reinterpret_cast<const u32x4*>(p.B + bk * N + gn) : zero;
-            } else {
-                const int64_t gn = n0 + (id >> 3), gk = kbase + (id & 7) * 8;
-                tb[i] = (gn < N && gk < K) ? *reinterpret_cast<const u32x4*>(p.B + gn * K + gk) : zero;
-            }
-        }
-        u32x4* slot_b = smem + S_OPERAND_BYTES / 16;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int id = tid + THREADS * i;
-            smem[swz64(id >> 3, id & 7)] = ta[i];
-        }
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int id = tid + THREADS * i;
-            if (B_KN) slot_b[(id >> 4) * 16 + ((id & 15) ^ kn_swz128(id >> 4))] = tb[i];
-            else slot_b[swz64(id >> 3, id & 7)] = tb[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            if (ks == 1 && K - kbase <= 32) break;
-#pragma unroll
-            for (int u = 0; u < UNITS; ++u) read_unit(0, 0 + ks, u);
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) LAGOM_MFMA_16x16x32(acc[i][j], b_frag(ks, j), fa[ks][i]);
-        }
-    }
     // wait states behind the last inline-asm MFMA, as in the large kernel
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll

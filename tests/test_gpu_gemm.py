@@ -216,3 +216,19 @@ def test_gemm_last_round_in_quadrants_integer_inputs_are_exact(M, N, K, b_is_nk)
     got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
     bad = np.argwhere(got != (a @ (b.T if b_is_nk else b)))
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
+
+
+@pytest.mark.parametrize("M,N", [(130, 136), (2100, 2056), (2100, 3720)])     # 128 x 128, 256 x 128 and 256 x 256 tiles
+@pytest.mark.parametrize("K", [72, 120, 136, 200, 264, 328, 392, 456])       # two to eight steps, each peeled form of the loop
+@pytest.mark.parametrize("b_is_nk", [True, False])
+def test_gemm_columns_in_two_k_steps_count_once(M, N, K, b_is_nk):
+    """The last K-step begins at column K - 64, so it loads columns that the step before it has multiplied: those must
+    neither count twice (exact integers) nor carry an infinity of theirs into zero times infinity."""
+    rng = np.random.default_rng(M + K)
+    a = rng.integers(-3, 4, size=(M, K)).astype(np.float32)
+    b = rng.integers(-3, 4, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+    a[3, K // 64 * 64 - 1] = np.inf             # in the overlap: one row of C is infinite or NaN, and no other
+    with np.errstate(invalid="ignore"):
+        want = a @ (b.T if b_is_nk else b)
+    got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
+    assert np.array_equal(got, want, equal_nan=True)
