@@ -140,7 +140,9 @@ int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
  * D = bytes each workgroup reads and writes).  The tiling depends on the size only: the smallest
  * of 128 x 128, 256 x 128 and 256 x 256 of which at most 256 tiles cover C (256 x 256 whenever
  * K < 64 or K > 2^22).  What is left over behind whole rounds of 256 tiles of 256 x 256 may run as
- * 128 x 128 quadrants; mu counts it in whole tiles.  Host only. */
+ * 128 x 128 quadrants; mu counts it in whole tiles.  Products so small that tiles of at most
+ * 64 x 64 cover C in one round run on those, with K split over a workgroup's wavefronts; they are
+ * reported as 128 x 128.  Host only. */
 typedef struct {
     int64_t mu;
     int32_t tb;

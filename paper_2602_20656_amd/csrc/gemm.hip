@@ -5,7 +5,8 @@
 // walks K in steps of 64; each wavefront owns a 128 x 128 block, i.e. 256 fp32 accumulators per
 // lane (the whole AGPR file), so one workgroup is resident per compute unit.  Products that at
 // most 256 tiles of 128 x 128 or of 256 x 128 cover use those instead: 256 x 256 tiles would
-// leave compute units idle (see the small-tile kernels below).
+// leave compute units idle (see the small-tile kernels below); still smaller ones split K over a
+// workgroup's wavefronts (see "few tiles").
 // Workgroup ids are remapped so that the workgroups of one XCD (ids equal modulo 8) cover a
 // compact block of tiles and share A/B panels in that XCD's L2.
 //
@@ -923,9 +924,188 @@ __global__ void __launch_bounds__(THREADS) gemm_bf16_nk_mixed_tail_kernel(const 
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_kn_mixed_tail_kernel(const MixedArgs p) { mixed_gemm_body<true, OUT_BF16, true>(p); }
 
-template <auto KERNEL, class ARGS>
-int launch_fast(const ARGS& a, dim3 grid, hipStream_t st) {
-    // set once per kernel (and per device: a process may drive several); a failure is not remembered
+// ------------------------------------------------------------------------- few tiles: K split over a workgroup
+// Products whose 128 x 128 tiles occupy a small part of the chip.  Each of those tiles is bound by what one compute unit
+// loads, so the time is that of (rows + columns of a tile) x K and the idle compute units do not help; here tiles are
+// 64 x 64 or smaller, and the wavefronts of a workgroup take the 64-wide slices of K in turn (slice s belongs to
+// wavefront s mod WAVES), each summing the whole tile over its slices.  A wavefront has LDS of its own for SETS slices,
+// filled by LDS-direct loads in the other kernels' layout, and waits for them by itself: no barrier in the loop.  (Loaded
+// straight into fragments, neighbouring lanes read different rows, and the compute unit's cache serves 16 instead of 64
+// bytes a cycle.)  The partial tiles are added through LDS in the order of the wavefronts: the result depends on the
+// sizes only.
+template <int MI, int NJ, int WAVES_, int SETS_> struct SplitTile {
+    static constexpr int MI_ = MI, NJ_ = NJ, WAVES = WAVES_, SETS = SETS_;
+    static constexpr int TM = 16 * MI, TN = 16 * NJ;
+    static constexpr int LA = TM / 8, LB = TN / 8, PER_SET = LA + LB;       // load instructions of a slice, 1 KiB each
+    static constexpr int ITEMS = MI * NJ * 64;                              // 16-byte pieces of a partial tile
+    static constexpr int LDS_BYTES = WAVES * (SETS * PER_SET * 1024 > ITEMS * 16 ? SETS * PER_SET * 1024 : ITEMS * 16);
+    static_assert(LDS_BYTES <= FAST_LDS_BYTES, "the slices in flight fit the LDS");
+};
+
+// B stored [K,N]: a slice is 64 rows (k) of TN columns; 16-byte group c of row k sits at c ^ kn_swz_split(k), which sends
+// the rows that half a wavefront's transposing read touches to different 32-byte windows of LDS's 256 bytes.
+template <int NJ> __device__ __forceinline__ int kn_swz_split(int k) {
+    return NJ == 4 ? (((k >> 3) & 1) << 2) | (((k >> 1) & 1) << 1) : ((k >> 3) & 1) << 1;
+}
+
+template <class T, bool B_KN, bool K_TAIL>
+__global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const GemmArgs p, const int out_bf16) {
+    constexpr int MI = T::MI_, NJ = T::NJ_, WAVES = T::WAVES, SETS = T::SETS, LA = T::LA, LB = T::LB;
+    static_assert(!B_KN || NJ == 2 || NJ == 4, "the [K,N] swizzle is for rows of 64 or 128 bytes");
+    extern __shared__ u32x4 smem[];            // [wavefront][set][rows of A, B]; then [wavefront][ITEMS]
+    __builtin_amdgcn_s_setprio(3);
+    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, r = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // XCD x takes the x-th eighth of the tiles, neighbours along the shorter side of C first: they share the longer panels
+    const int tiles = p.tiles_m * p.tiles_n, lin = (blockIdx.x & 7) * ((tiles + 7) >> 3) + (blockIdx.x >> 3);
+    if (lin >= tiles) return;
+    const bool m_first = p.tiles_m <= p.tiles_n;
+    const int inner = m_first ? p.tiles_m : p.tiles_n;
+    const int tm = m_first ? lin % inner : lin / inner, tn = m_first ? lin / inner : lin % inner;
+    const int64_t m0 = (int64_t)tm * T::TM, n0 = (int64_t)tn * T::TN, M = p.M, N = p.N, K = p.K;
+
+    const int slices = (int)((K + BK - 1) / BK);
+    const int again = K_TAIL ? (int)((int64_t)slices * BK - K) : 0;    // the last slice begins at K - 64, as in the tiled kernels
+    // Load d of an operand: 8 rows of 128 bytes, lane -> row 8*d + lane/8, stored group lane%8 (see the large kernel).
+    // Rows past the edge re-read the last one.
+    uint32_t a_off[LA], b_off[LB];
+#pragma unroll
+    for (int d = 0; d < LA; ++d) {
+        const int row = 8 * d + (lane >> 3);
+        const int64_t last = M - 1 - m0;
+        a_off[d] = (uint32_t)(((row < last ? row : last) * K + 8 * ((lane & 7) ^ ((row >> 1) & 7))) * 2);
+    }
+#pragma unroll
+    for (int d = 0; d < LB; ++d) {
+        if (B_KN) {   // TN/8 groups a row: lane -> row (512/TN)*d + lane/(TN/8); groups past the last column re-read the last one
+            const int krow = (512 / T::TN) * d + lane / LB;
+            const int64_t grp = (lane % LB) ^ kn_swz_split<NJ>(krow), last = (N - n0) / 8 - 1;
+            b_off[d] = (uint32_t)((krow * N + (grp < last ? grp : last) * 8) * 2);
+        } else {
+            const int row = 8 * d + (lane >> 3);
+            const int64_t last = N - 1 - n0;
+            b_off[d] = (uint32_t)(((row < last ? row : last) * K + 8 * ((lane & 7) ^ ((row >> 1) & 7))) * 2);
+        }
+    }
+    const char* const base_a = reinterpret_cast<const char*>(p.A + m0 * K);
+    const char* const base_b = reinterpret_cast<const char*>(B_KN ? p.B + n0 : p.B + n0 * K);
+    constexpr int SET_BYTES = T::PER_SET * 1024, B_BYTES = LA * 1024;       // B's place in a set
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)smem + wave * (SETS * SET_BYTES);
+    const char* const mine = reinterpret_cast<const char*>(smem) + wave * (SETS * SET_BYTES);
+    auto load = [&](uint32_t lds, const char* sbase, uint32_t voff) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory");
+    };
+    auto fetch = [&](int set, int slice) {
+        // behind the last slice every lane reads the same 16 bytes, for nothing: the waits below count loads
+        const bool there = slice < slices;
+        const uint32_t mask = there ? ~0u : 0u;
+        const int64_t k0 = there ? (K_TAIL && slice == slices - 1 ? K - BK : (int64_t)slice * BK) : 0;
+        const char* const from_a = base_a + 2 * k0;
+        const char* const from_b = base_b + 2 * (B_KN ? k0 * N : k0);
+#pragma unroll
+        for (int d = 0; d < LA; ++d) load(lds0 + set * SET_BYTES + d * 1024, from_a, a_off[d] & mask);
+#pragma unroll
+        for (int d = 0; d < LB; ++d) load(lds0 + set * SET_BYTES + B_BYTES + d * 1024, from_b, b_off[d] & mask);
+    };
+    f32x4 acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 fa[2][MI], fb[2][NJ];
+    auto read = [&](int set) {
+        const u32x4* sa = reinterpret_cast<const u32x4*>(mine + set * SET_BYTES);
+        const u32x4* sb = reinterpret_cast<const u32x4*>(mine + set * SET_BYTES + B_BYTES);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) fa[h][i] = sa[swz64(16 * i + r, 4 * h + q)];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                if (!B_KN) {
+                    fb[h][j] = sb[swz64(16 * j + r, 4 * h + q)];
+                } else {      // two transposing reads, as in the large kernel
+                    typedef s16x4 __attribute__((address_space(3))) * tr_ptr;
+                    const int krow = 32 * h + 8 * q + (r >> 2), grp = 2 * j + ((r & 3) >> 1);
+                    s16x4 x[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        x[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)((lds_bytes)(const char*)sb + (krow + 4 * u) * (2 * T::TN) +
+                                                                               ((grp ^ kn_swz_split<NJ>(krow + 4 * u)) << 4) + 8 * (r & 1)));
+                    fb[h][j] = __builtin_bit_cast(u32x4, __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+        }
+    };
+    auto multiply = [&](int slice) {
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool keep = !K_TAIL || slice < slices - 1 || 4 * h + q >= again / 8;
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)      // B first: a lane's 4 results are C[row lane%16][4 consecutive columns]
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, keep ? fb[h][j] : zero),
+                                                                        __builtin_bit_cast(bf16x8, keep ? fa[h][i] : zero), acc[i][j], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < SETS; ++t) fetch(t, wave + t * WAVES);
+    for (int slice = wave; slice < slices;) {
+#pragma unroll
+        for (int t = 0; t < SETS; ++t) {
+            if (t > 0 && slice >= slices) break;
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((SETS - 1) * T::PER_SET) : "memory");     // loads complete in issue order
+            read(t);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the fragments are in registers: the set may be filled again
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(t, slice + SETS * WAVES);
+            multiply(slice);
+            slice += WAVES;
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();       // nothing is in flight into LDS, and nobody reads a slice any more
+
+    f32x4* const partial = reinterpret_cast<f32x4*>(smem);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) partial[wave * T::ITEMS + (i * NJ + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    for (int item = tid; item < T::ITEMS; item += 64 * WAVES) {
+        f32x4 x = partial[item];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) x = x + partial[w * T::ITEMS + item];
+        const int ij = item >> 6;
+        const int64_t row = m0 + 16 * (ij / NJ) + r, col = n0 + 16 * (ij % NJ) + 4 * q;
+        if (row >= M || col >= N) continue;
+        if (out_bf16) {
+            uint16_t* out = reinterpret_cast<uint16_t*>(p.C) + row * N + col;
+            uint2 v;
+            v.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[0], x[1]}, bf16x2));
+            v.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[2], x[3]}, bf16x2));
+            if ((N & 3) == 0) *reinterpret_cast<uint2*>(out) = v;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < N) out[e] = (uint16_t)((e < 2 ? v.x : v.y) >> (16 * (e & 1)));
+        } else {
+            float* out = reinterpret_cast<float*>(p.C) + row * N + col;
+            if ((N & 3) == 0) *reinterpret_cast<f32x4*>(out) = x;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < N) out[e] = x[e];
+        }
+    }
+}
+
+// Lets a kernel have a compute unit's whole LDS: set once per kernel (and per device: a process may drive several); a
+// failure is not remembered.
+template <auto KERNEL>
+int allow_lds() {
     static std::atomic<uint64_t> done_on_device{0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev > 63) dev = 63;
@@ -936,9 +1116,34 @@ int launch_fast(const ARGS& a, dim3 grid, hipStream_t st) {
         if (attr != hipSuccess) return lagom::fail(LAGOM_EHIP, "gemm: cannot raise the LDS limit: %s", hipGetErrorString(attr));
         done_on_device.fetch_or(bit, std::memory_order_release);
     }
+    return LAGOM_OK;
+}
+
+template <auto KERNEL, class ARGS>
+int launch_fast(const ARGS& a, dim3 grid, hipStream_t st) {
+    if (int rc = allow_lds<KERNEL>()) return rc;
     hipLaunchKernelGGL(KERNEL, grid, dim3(THREADS), FAST_LDS_BYTES, st, a);
     return LAGOM_OK;
 }
+
+template <class T, bool B_KN, bool K_TAIL>
+int launch_split_kernel(const GemmArgs& a, bool out_bf16, hipStream_t st) {
+    constexpr auto kernel = gemm_bf16_split_kernel<T, B_KN, K_TAIL>;
+    if (int rc = allow_lds<kernel>()) return rc;
+    const dim3 grid((unsigned)(((int64_t)a.tiles_m * a.tiles_n + 7) / 8 * 8));
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * T::WAVES), T::LDS_BYTES, st, a, out_bf16 ? 1 : 0);
+    return LAGOM_OK;
+}
+template <class T>
+int launch_split(GemmArgs a, bool b_is_nk, bool out_bf16, hipStream_t st) {
+    a.tiles_m = (int32_t)((a.M + T::TM - 1) / T::TM);
+    a.tiles_n = (int32_t)((a.N + T::TN - 1) / T::TN);
+    const bool tail = a.K % BK != 0;
+    if (b_is_nk) return tail ? launch_split_kernel<T, false, true>(a, out_bf16, st) : launch_split_kernel<T, false, false>(a, out_bf16, st);
+    return tail ? launch_split_kernel<T, true, true>(a, out_bf16, st) : launch_split_kernel<T, true, false>(a, out_bf16, st);
+}
+
+constexpr int kRound = 256;         // workgroups in a round: one per compute unit
 
 // The smallest tile that still covers C in one round of workgroups (256 compute units): 128 x 128, else
 // 256 x 128, else 256 x 256.  Fewer, larger tiles would leave compute units idle; smaller tiles in several
@@ -952,7 +1157,27 @@ Tiling choose_tiling(int64_t M, int64_t N, int64_t K) {
     return TILE_256x256;
 }
 
-constexpr int kRound = 256;         // workgroups in a round: one per compute unit
+// The smallest tile that covers C in one round is the fastest here too, whatever it loads in all: a compute unit loads
+// about 130 GB/s of (rows + columns of a tile) x K.  us, 128 x 128 tiles -> 64 x 64 | 64 x 32 | 32 x 32 | 16 x 32:
+//   33 x 1000 x 4096    23.6 -> 11.5 |  8.9 |  6.9 |  5.9 (96 workgroups)     256 x 256 x 8192   43.1 -> 18.7 | 17.7 | 13.0 | 10.9 (128)
+//   512 x 512 x 512      6.3 ->  5.6 |  4.7 |  4.1 (256) |  6.3               640 x 640 x 4096   24.5 -> 14.9 | 12.0 (200) | 18.0 | 28.0
+//   1024 x 1024 x 4096  25.1 -> 16.8 (256) | 26.8 | 43.8 | 77.1               40 x 8192 x 8192   42.9 -> 24.1 | 22.6 (256) | 27.4 | 31.0
+// With fewer slices than wavefronts the additions at the end cost what the split gains: 64 x 64 tiles 5.4 us against 5.3 us at
+// 1024 x 1024 x 256 and 5.8 against 5.9 at K = 384; 64 x 32 tiles 4.4 against 5.1 at 640 x 640 x 256, 4.3 against 4.3 at
+// K = 128 and 4.3 against 4.1 at K = 64; 32 x 32 tiles 4.1 against 4.1 at 512 x 512 x 64.
+typedef int (*SplitLaunch)(GemmArgs, bool, bool, hipStream_t);
+SplitLaunch choose_split(int64_t M, int64_t N, int64_t K) {
+    if (K < BK || K > FAST_MAX_K) return nullptr;
+    auto tiles = [&](int64_t tm, int64_t tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+    if (tiles(16, 32) <= kRound) return launch_split<SplitTile<1, 2, 8, 3>>;
+    if (tiles(32, 32) <= kRound) return launch_split<SplitTile<2, 2, 8, 2>>;
+    if (K < 2 * BK) return nullptr;
+    if (tiles(64, 32) <= kRound && tiles(64, 32) <= tiles(32, 64)) return launch_split<SplitTile<4, 2, 4, 3>>;
+    if (tiles(32, 64) <= kRound) return launch_split<SplitTile<2, 4, 4, 3>>;
+    if (tiles(64, 64) <= kRound && K > 4 * BK) return launch_split<SplitTile<4, 4, 4, 2>>;
+    return nullptr;
+}
+
 // A chip full of 128 x 128 tiles takes 0.39 of the time of one full of 256 x 256 tiles, so up to two rounds of quadrants
 // are cheaper than one more round of large tiles.  us, large tiles only -> cut: 4096 x N x 4096 with N = 4352 (16 left
 // over) 154.9 -> 113.2, 4608 (32) 157.1 -> 116.5, 5120 (64) 158.4 -> 123.0, 6144 (128, two rounds of quadrants) 164.0 ->
@@ -1024,6 +1249,13 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (int rc = lagom::check_gemm_args(A, B, C, M, N, K, out_dt)) return rc;
     if (!b_is_nk && (N % 8)) return lagom::fail(LAGOM_EINVAL, "B stored [K,N] needs N to be a multiple of 8");
     const Tiling tiling = choose_tiling(M, N, K);
+    if (const SplitLaunch split = choose_split(M, N, K)) {
+        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0};
+        if (int rc = split(a, b_is_nk != 0, out_dt == LAGOM_BF16, static_cast<hipStream_t>(hip_stream))) return rc;
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "gemm launch: %s", hipGetErrorString(e));
+        return LAGOM_OK;
+    }
     if (tiling != TILE_256x256) {
         const int bm = tiling == TILE_128x128 ? SBM : MBM;
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,

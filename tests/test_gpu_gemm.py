@@ -232,3 +232,31 @@ def test_gemm_columns_in_two_k_steps_count_once(M, N, K, b_is_nk):
         want = a @ (b.T if b_is_nk else b)
     got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
     assert np.array_equal(got, want, equal_nan=True)
+
+
+@pytest.mark.parametrize("M,N,Ks", [
+    (1, 8, (64, 4096)), (33, 1000, (72, 512, 1544)), (250, 500, (128,)),              # 16 x 32 tiles
+    (500, 501, (64, 120, 1032)), (40, 4000, (576,)),                                  # 32 x 32
+    (640, 640, (128, 264, 1544)), (65, 3000, (200,)), (700, 507, (320,)),             # 64 x 32
+    (90, 5400, (128, 840)), (65, 5443, (136,)),                                       # 32 x 64
+    (1000, 1000, (320, 328, 1544)), (1025, 963, (384,)),                              # 64 x 64
+    (1000, 1000, (64, 256)), (1200, 1288, (64, 72, 136, 320, 1032))])                 # 128 x 128, K not split
+@pytest.mark.parametrize("b_is_nk", [True, False])
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+def test_gemm_few_tiles_integer_inputs_are_exact(M, N, Ks, b_is_nk, out):
+    """K split over the wavefronts of a workgroup: fewer slices of K than wavefronts, one more than a multiple of them, a
+    last slice that overlaps the one before it (an infinity in the overlap reaches one row only), ragged tiles."""
+    if not b_is_nk:
+        N = (N + 7) // 8 * 8
+    for K in Ks:
+        rng = np.random.default_rng(M + N + K)
+        a = rng.integers(-3, 4, size=(M, K)).astype(np.float32)
+        b = rng.integers(-3, 4, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+        if K % 64:
+            a[M // 2, K // 64 * 64 - 1] = np.inf
+        with np.errstate(invalid="ignore"):
+            want = a @ (b.T if b_is_nk else b)
+        if out == "bf16":        # one rounding at the store, the oracle's
+            want = oc.bf16_to_f32(oc.f32_to_bf16(want.astype(np.float32)))
+        got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, out)
+        assert np.array_equal(got, want, equal_nan=True), (K, np.argwhere(got != want)[:3])
