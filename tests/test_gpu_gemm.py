@@ -260,3 +260,17 @@ def test_gemm_few_tiles_integer_inputs_are_exact(M, N, Ks, b_is_nk, out):
             want = oc.bf16_to_f32(oc.f32_to_bf16(want.astype(np.float32)))
         got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, out)
         assert np.array_equal(got, want, equal_nan=True), (K, np.argwhere(got != want)[:3])
+
+
+@pytest.mark.parametrize("M,N", [(1201, 1203), (1202, 1285), (2100, 2201), (2065, 2308), (2100, 3725), (4100, 4198)])   # 128 x 128, 256 x 128, 256 x 256 tiles, and with quadrants
+@pytest.mark.parametrize("K", [64, 136])
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+def test_gemm_rows_off_the_16_byte_grid(M, N, K, out):
+    """N no multiple of 8: rows of C start off the 16-byte grid and end inside a vector (1 to 7 elements of it)."""
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K)).astype(np.float32)
+    want = a @ b.T
+    if out == "bf16":
+        want = oc.bf16_to_f32(oc.f32_to_bf16(want))
+    assert np.array_equal(_gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), True, out), want)
