@@ -12,7 +12,7 @@
 // moves (100 - 116 GB/s, loads and stores together, from 8 wavefronts up) and not by one memory latency per batch.
 // Every byte is touched once, so stores always carry the non-temporal hint (measured on MI355X: +3..7 % and no
 // write-allocate traffic in the L2 that a co-running GEMM depends on).  Loads carry it only
-// when the launch has at least kStreamLoadsFromNC channels: with that many channels the
+// when at least kStreamLoadsFromNC channels have work: with that many channels the
 // kernel is bandwidth-bound and streams from HBM (+6..13 %), while with few channels it is
 // latency-bound and its sources are usually still in the last-level cache, where the hint
 // costs 15..30 %.
@@ -69,7 +69,15 @@ Shape make_shape(int64_t shard_bytes, int64_t chunk_bytes, int nshards, int nc) 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kStreamLoadsFromNC = 128;
+constexpr uint32_t kStreamLoadsFromNC = 128;
+// Channels that have a chunk to move count: a launch of many channels over a few chunks is as latency-bound as one of few
+// channels.  us, loads with the hint -> without: eight-source reduce of 248712 bf16 at (256, 128, 256 KiB), two busy channels,
+// 87.6 -> 67.1; gather of two such shards at (256, 256, 512 KiB) 14.0 -> 11.0; gather of nine shards of 1092728 bf16 at
+// (128, 256, 2 MiB), eighteen busy channels, 70.0 -> 46.2.
+bool stream_loads(uint32_t nc, const Shape& s) {
+    const uint64_t chunks = (uint64_t)s.chunks * s.nshards;
+    return (chunks < nc ? chunks : nc) >= kStreamLoadsFromNC;
+}
 
 template <bool STREAM>
 __device__ __forceinline__ u32x4 ld16(const char* p) {
@@ -478,14 +486,14 @@ void launch_reduce_s(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
 }
 template <int DT>
 void launch_reduce(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
+    const bool stream = stream_loads(grid.x, a.shape), deep = block.x <= kDeepNT;
     if (stream) deep ? launch_reduce_s<DT, true, true, 1>(a, grid, block, st) : launch_reduce_s<DT, true, false, 1>(a, grid, block, st);
     else deep ? launch_reduce_s<DT, false, true, 1>(a, grid, block, st) : launch_reduce_s<DT, false, false, 1>(a, grid, block, st);
 }
 
 template <WalkKind KIND>
 void launch_gather(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
+    const bool stream = stream_loads(grid.x, a.shape), deep = block.x <= kDeepNT;
     if (stream) {
         if (deep) hipLaunchKernelGGL((gather_copy_kernel<KIND, true, true>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((gather_copy_kernel<KIND, true, false>), grid, block, 0, st, a);
@@ -533,7 +541,7 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const
 
 template <int DT>
 void launch_steps(const StepsArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    const bool stream = grid.x >= kStreamLoadsFromNC, deep = block.x <= kDeepNT;
+    const bool stream = stream_loads(grid.x, a.shape), deep = block.x <= kDeepNT;
     if (stream) {
         if (deep) hipLaunchKernelGGL((comm_steps_kernel<DT, true, true>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((comm_steps_kernel<DT, true, false>), grid, block, 0, st, a);

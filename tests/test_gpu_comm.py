@@ -444,3 +444,16 @@ def test_gather_copy_of_shards_off_the_vector_grid(dtype, nt, P):
         for nc in (1, 3, 40):
             for got in _run(lg.LAGOM_GATHER_COPY, dtype, shards, 2, (nc, nt, chunk), P * count):
                 assert same_bits(got, want), (count, nc)
+
+
+@pytest.mark.parametrize("nt", [64, 512])
+@pytest.mark.parametrize("busy", [1, 127, 128, 150])
+def test_wide_launches_with_few_busy_channels(nt, busy):
+    """150 channels, of which one to all have a chunk: below and from the number on that streams its loads."""
+    cfg = (150, nt, 2048)
+    count = busy * 1024 - 8                                      # bf16: the last chunk is short
+    srcs = _sources("bf16", 3, count, 1300)
+    want = oc.reduce_copy(srcs, "bf16")[0]
+    assert same_bits(_run(lg.LAGOM_REDUCE_COPY, "bf16", srcs, 1, cfg, count)[0], want)
+    copy = _run(lg.LAGOM_GATHER_COPY, "bf16", srcs, 1, cfg, 3 * count)[0]
+    assert same_bits(copy, np.concatenate(srcs))
