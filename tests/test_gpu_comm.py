@@ -263,6 +263,25 @@ def test_steps_in_one_launch_equal_the_oracle_sequence(dtype):
             assert same_bits(got[k], want[k]), (dtype, count, cfg, k)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("nt", [64, 256, 320, 1024])
+def test_runs_of_dependent_steps_at_the_edges_of_their_batches(dtype, nt):
+    """Every step reads what the step before it wrote, in runs of one kind: wavefronts with no, one, two or more batches to a
+    step, short last chunks that hold nothing for some wavefronts, channels without a chunk."""
+    esz = 4 if dtype == "f32" else 2
+    steps = ([("reduce_copy", ["a", "b"], ["b"])] * 3 + [("reduce_copy", ["b", "c"], ["c", "d"]), ("reduce_copy", ["d", "c"], ["a"])] +
+             [("gather_copy", ["a"], ["e"]), ("gather_copy", ["e"], ["f", "b"]), ("gather_copy", ["b"], ["g"]), ("gather_copy", ["c"], ["e"])] +
+             [("reduce_copy", ["g", "e"], ["e"]), ("reduce_copy", ["e", "f"], ["f"])])
+    for chunk, nc in [(1024, 3), (16384, 2), (48 * 1024 + 16, 3)]:
+        for count in _edge_counts(nt, 4, chunk, esz) + _edge_counts(nt, 8, chunk, esz):
+            count += 1
+            bufs = dict(zip("abcdefg", _sources(dtype, 7, count, 1400)))
+            want = oc.comm_steps(bufs, steps, dtype)
+            got = _steps_case(dtype, count, (nc, nt, chunk), steps, bufs)
+            for k in bufs:
+                assert same_bits(got[k], want[k]), (count, nc, chunk, k)
+
+
 def test_ring_share_as_one_launch_equals_the_separate_launches_and_the_oracle():
     """The DP bucket's share of the ring (7 reduce steps, 7 store-and-forward steps over two wire buffers each way) as
     one lagom_comm_steps launch: the same bits as fourteen lagom_comm_kernel launches and as the oracle's sequence."""
