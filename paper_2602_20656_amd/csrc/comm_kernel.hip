@@ -269,6 +269,7 @@ __device__ __forceinline__ Walk<KIND> make_walk(const Shape& s) {
 // Where the walk reads and writes.
 template <class SRC, class DST>
 struct ReduceIo {                               // src(s) and dst(d) at the same offset
+    static constexpr bool SCALAR_OUT = false;
     const SRC& src; const DST& dst; int ndst;
     __device__ __forceinline__ const char* from(const Walk<REDUCE>& w, int s) const { return src(s) + w.offset(); }
     template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return ld16<STREAM>(p); }
@@ -278,6 +279,7 @@ struct ReduceIo {                               // src(s) and dst(d) at the same
 };
 template <WalkKind KIND, class SRC, class DST>
 struct GatherIo {                               // shard r goes to r * shard_bytes
+    static constexpr bool SCALAR_OUT = false;
     const SRC& src; const DST& dst; int ndst;
     __device__ __forceinline__ const char* from(const Walk<KIND>& w, int) const { return src(w.shard()) + w.offset(); }
     template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return KIND == GATHER_RAGGED ? ld16_ragged<STREAM>(p) : ld16<STREAM>(p); }
@@ -302,6 +304,9 @@ template <int DT, int S, int U, bool STREAM, bool COPY, class WALK, class IO>
 __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane) {
     w.first();
     if (!w.more) return;
+    // The compiler must not see that the walks of a fused launch have their lanes' offsets in common: it would compute those of
+    // every kind of step in front of the loop over the steps and hold them all, in registers that a product beside the kernel needs.
+    asm volatile("" : "+v"(lane));
     uint32_t at[U];                             // a lane's offsets in a batch
 #pragma unroll
     for (int u = 0; u < U; ++u) at[u] = lane * 16 + ((u * w.nw) << 10);
@@ -320,6 +325,8 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
             for (int s = 0; s < S; ++s) b.v[u][s] = IO::template load<STREAM>(from[s] + o);
         }
     };
+    // SCALAR_OUT: where the compiler sees that the offsets are the same in every batch, it holds them as 64-bit addresses, too.
+    auto offset = [](uint32_t& o) { if (IO::SCALAR_OUT) asm volatile("" : "+v"(o)); return o; };
     auto finish = [&](const Batch<S, U>& b, int u) {
         if (COPY) return b.v[u][0];             // bytes are moved, never interpreted
         Acc<DT> acc;
@@ -339,12 +346,12 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         if (b.limit >= (int32_t)((((U - 1) * w.nw) << 10) + 1008)) {      // whole units
             for (int d = 0; d < io.copies(b.r); ++d)
 #pragma unroll
-                for (int u = 0; u < U; ++u) st16(io.out(b.r, d) + b.off + at[u], b.v[u][0]);
+                for (int u = 0; u < U; ++u) st16(io.out(b.r, d) + b.off + offset(at[u]), b.v[u][0]);
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if ((int32_t)at[u] <= b.limit)
-                    for (int d = 0; d < io.copies(b.r); ++d) st16(io.out(b.r, d) + b.off + at[u], b.v[u][0]);
+                    for (int d = 0; d < io.copies(b.r); ++d) st16(io.out(b.r, d) + b.off + offset(at[u]), b.v[u][0]);
         }
     };
     Batch<S, U> b0, b1;
@@ -420,9 +427,9 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
     }
 }
 
-// How much a lane keeps in flight.  A channel of up to kDeepNT threads (one wavefront per SIMD) may use the 120 registers
-// that a GEMM workgroup leaves on its SIMDs for that one wavefront; with more threads the wavefronts of a SIMD share
-// them, and their number keeps the memory pipeline busy instead.  One memory latency per batch, the previous form
+// How much a lane keeps in flight.  A GEMM workgroup of large tiles leaves 120 registers of a SIMD ([N,K]) or 112 ([K,N]) to
+// the wavefronts beside it.  A channel of up to kDeepNT threads (one wavefront per SIMD) may use them all; with more threads
+// the wavefronts of a SIMD share them, and their number keeps the memory pipeline busy instead.  One memory latency per batch, the previous form
 // -> this one, us (data in the last-level cache): 64 MiB gather-copy at (8, 256, 2 MiB) 138.5 -> 86.3; 12 MiB two-source fp32
 // reduce at (4, 256, 128 KiB) 55.1 -> 33.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 18.9 (there
 // one source at a time in flight before); a ring share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 65.3; 72 MiB
@@ -539,7 +546,9 @@ struct StepsArgs {
 };
 static_assert(kMaxStepPtrs <= 256 && LAGOM_MAX_SRCS < 256 && LAGOM_MAX_DSTS < 256, "a step is packed in bytes");
 
+template <bool DEEP>
 struct StepsIo {                      // step r of the walk is step st + r of the launch
+    static constexpr bool SCALAR_OUT = !DEEP;
     const StepsArgs& p; uint32_t st;
     __device__ __forceinline__ const char* from(const Walk<STEPS>& w, int s) const { return p.src(st + w.shard(), s) + w.offset(); }
     template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* q) { return ld16<STREAM>(q); }
@@ -569,10 +578,10 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const
         int run = 1;
         if (p.kind(st) == StepsArgs::kind_of(LAGOM_GATHER_COPY, 1)) {        // a plain copy to every destination
             run = steps_in_walk(p, st, U1, w);
-            move_batches<DT, 1, U1, STREAM, true>(w, StepsIo{p, (uint32_t)st}, lane);
+            move_batches<DT, 1, U1, STREAM, true>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
         } else if (p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 2)) {
             run = steps_in_walk(p, st, U2, w);
-            move_batches<DT, 2, U2, STREAM, false>(w, StepsIo{p, (uint32_t)st}, lane);
+            move_batches<DT, 2, U2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
         } else {
             const auto src = [&p, st](int s) { return p.src(st, s); };
             const auto dst = [&p, st](int d) { return p.dst(st, d); };
