@@ -579,6 +579,9 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const
         if (p.kind(st) == StepsArgs::kind_of(LAGOM_GATHER_COPY, 1)) {        // a plain copy to every destination
             run = steps_in_walk(p, st, U1, w);
             move_batches<DT, 1, U1, STREAM, true>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+        } else if (DT == LAGOM_BF16 && p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 1)) {     // (of fp32: a copy)
+            run = steps_in_walk(p, st, U1, w);
+            move_batches<DT, 1, U1, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
         } else if (p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 2)) {
             run = steps_in_walk(p, st, U2, w);
             move_batches<DT, 2, U2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
@@ -835,7 +838,9 @@ extern "C" int lagom_comm_steps(lagom_dtype dt, const lagom_comm_step* steps, in
     StepsArgs a{};
     int n = 0;
     for (int i = 0; i < nsteps; ++i) {
-        a.step[i] = (uint32_t)n | (uint32_t)steps[i].nsrc << 8 | (uint32_t)steps[i].ndst << 16 | (uint32_t)steps[i].op << 24;
+        // one source of fp32 is added to nothing: a copy, bit for bit (bf16 may hold a NaN that the reduction makes quiet)
+        const int op = dt == LAGOM_F32 && steps[i].nsrc == 1 ? (int)LAGOM_GATHER_COPY : steps[i].op;
+        a.step[i] = (uint32_t)n | (uint32_t)steps[i].nsrc << 8 | (uint32_t)steps[i].ndst << 16 | (uint32_t)op << 24;
         for (int s = 0; s < steps[i].nsrc; ++s) a.ptr[n++] = static_cast<const char*>(steps[i].srcs[s]);
         for (int d = 0; d < steps[i].ndst; ++d) a.ptr[n++] = static_cast<const char*>(steps[i].dsts[d]);
     }

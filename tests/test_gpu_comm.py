@@ -271,7 +271,8 @@ def test_runs_of_dependent_steps_at_the_edges_of_their_batches(dtype, nt):
     esz = 4 if dtype == "f32" else 2
     steps = ([("reduce_copy", ["a", "b"], ["b"])] * 3 + [("reduce_copy", ["b", "c"], ["c", "d"]), ("reduce_copy", ["d", "c"], ["a"])] +
              [("gather_copy", ["a"], ["e"]), ("gather_copy", ["e"], ["f", "b"]), ("gather_copy", ["b"], ["g"]), ("gather_copy", ["c"], ["e"])] +
-             [("reduce_copy", ["g", "e"], ["e"]), ("reduce_copy", ["e", "f"], ["f"])])
+             [("reduce_copy", ["g", "e"], ["e"]), ("reduce_copy", ["e", "f"], ["f"])] +
+             [("reduce_copy", ["f"], ["b"]), ("reduce_copy", ["b"], ["a", "c"]), ("reduce_copy", ["c"], ["d"]), ("gather_copy", ["d"], ["g"])])
     for chunk, nc in [(1024, 3), (16384, 2), (48 * 1024 + 16, 3)]:
         for count in _edge_counts(nt, 4, chunk, esz) + _edge_counts(nt, 8, chunk, esz):
             count += 1
@@ -476,3 +477,30 @@ def test_wide_launches_with_few_busy_channels(nt, busy):
     assert same_bits(_run(lg.LAGOM_REDUCE_COPY, "bf16", srcs, 1, cfg, count)[0], want)
     copy = _run(lg.LAGOM_GATHER_COPY, "bf16", srcs, 1, cfg, 3 * count)[0]
     assert same_bits(copy, np.concatenate(srcs))
+
+
+def _fused_us(dtype, op, nsrc, count, cfg, nsteps=4):
+    """Microseconds of one launch of independent steps (median of events around ten launches)."""
+    td, code = (torch.float32, lg.LAGOM_F32) if dtype == "f32" else (torch.bfloat16, lg.LAGOM_BF16)
+    bufs = [[torch.zeros(count, dtype=td, device="cuda") for _ in range(nsrc + 1)] for _ in range(nsteps)]
+    steps = [(op, b[:nsrc], [b[nsrc]]) for b in bufs]
+    times = []
+    for _ in range(7):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(10):
+            lg.lagom_comm_steps(code, steps, count, cfg, torch.cuda.current_stream())
+        e1.record()
+        torch.cuda.synchronize()
+        times.append(e0.elapsed_time(e1) * 100.0)
+    return sorted(times)[3]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cfg", [(8, 256, 2 << 20), (16, 64, 32 << 10), (32, 256, 64 << 10)])
+def test_fused_reduces_of_one_source_keep_loads_in_flight(dtype, cfg):
+    """They move the bytes of a copy.  With one load in flight they take 3.9 to 10 times as long; a lone wavefront that widens and
+    rounds bf16 between its loads takes 1.5 times as long, all others 1.0 to 1.1."""
+    count = (12 << 20) // (4 if dtype == "f32" else 2)
+    copy, reduce = (_fused_us(dtype, op, 1, count, cfg) for op in (lg.LAGOM_GATHER_COPY, lg.LAGOM_REDUCE_COPY))
+    assert reduce < 2.0 * copy, (reduce, copy)
