@@ -22,6 +22,7 @@
 // fused operation can change the rounding.
 #include <hip/hip_runtime.h>
 #include <atomic>
+#include <type_traits>
 #include "common.h"
 
 namespace {
@@ -407,21 +408,32 @@ __device__ __forceinline__ void move_halves(Walk<REDUCE> w, const IO& io, uint32
     }
 }
 
-// Any number of sources, four loads in flight: the steps of more than two sources of a fused launch.
+// Any number of sources, up to four loads in flight: the steps of more than two sources of a fused launch.  The first group
+// takes what is over four, so that every later one is whole and no source is waited for by itself.
 template <int DT, bool STREAM, class IO>
 __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc, uint32_t lane) {
     const uint32_t lo = lane * 16;
     for (w.first(); w.more; w.next(1)) {
         if (lo > w.limit()) continue;
         Acc<DT> acc;
-        acc.init(ld16<STREAM>(io.from(w, 0) + lo));
-        int s = 1;
-        for (; s + 3 < nsrc; s += 4) {            // added in source order
+        auto first = [&](auto n) {                // added in source order
+            u32x4 x[decltype(n)::value];
+#pragma unroll
+            for (int s = 0; s < decltype(n)::value; ++s) x[s] = ld16<STREAM>(io.from(w, s) + lo);
+            acc.init(x[0]);
+#pragma unroll
+            for (int s = 1; s < decltype(n)::value; ++s) acc.add(x[s]);
+        };
+        const int over = nsrc & 3;
+        if (over == 1) first(std::integral_constant<int, 1>{});
+        else if (over == 2) first(std::integral_constant<int, 2>{});
+        else if (over == 3) first(std::integral_constant<int, 3>{});
+        else first(std::integral_constant<int, 4>{});
+        for (int s = over ? over : 4; s < nsrc; s += 4) {
             const u32x4 x0 = ld16<STREAM>(io.from(w, s) + lo), x1 = ld16<STREAM>(io.from(w, s + 1) + lo);
             const u32x4 x2 = ld16<STREAM>(io.from(w, s + 2) + lo), x3 = ld16<STREAM>(io.from(w, s + 3) + lo);
             acc.add(x0); acc.add(x1); acc.add(x2); acc.add(x3);
         }
-        for (; s < nsrc; ++s) acc.add(ld16<STREAM>(io.from(w, s) + lo));
         const u32x4 r = acc.result();
         for (int d = 0; d < io.ndst; ++d) st16(io.dst(d) + w.offset() + lo, r);
     }

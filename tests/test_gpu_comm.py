@@ -479,6 +479,21 @@ def test_wide_launches_with_few_busy_channels(nt, busy):
     assert same_bits(copy, np.concatenate(srcs))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("nt", [64, 320])
+def test_fused_reduces_of_many_sources(dtype, nt):
+    """Three to sixteen sources: a first group of one to four, then groups of four, added in source order."""
+    for count in (3, 40 * 1024 + 5):
+        for lo in (3, 7, 11, 14):
+            srcs = _sources(dtype, 16, count, 1500 + lo)
+            bufs = {**{"s%d" % i: x for i, x in enumerate(srcs)}, **{"d%d" % n: x for n, x in enumerate(_sources(dtype, 3, count, 1600))}}
+            steps = [("reduce_copy", ["s%d" % i for i in range(lo + n)], ["d%d" % n]) for n in range(min(3, 17 - lo))]
+            want = oc.comm_steps(bufs, steps, dtype)
+            got = _steps_case(dtype, count, (3, nt, 4096), steps, bufs)
+            for k in ("d0", "d1", "d2"):
+                assert same_bits(got[k], want[k]), (count, lo, k)
+
+
 def _fused_us(dtype, op, nsrc, count, cfg, nsteps=4):
     """Microseconds of one launch of independent steps (median of events around ten launches)."""
     td, code = (torch.float32, lg.LAGOM_F32) if dtype == "f32" else (torch.bfloat16, lg.LAGOM_BF16)
