@@ -464,13 +464,14 @@ __device__ __forceinline__ void reduce_tail(const SRC& src, const DST& dst, int 
     const int left = (int)(bytes & 15) / esize, tid = threadIdx.x;
     if (tid < left && owns_last(chunks)) reduce_tail_element<DT>(src, dst, nsrc, ndst, (bytes & ~(int64_t)15) + tid * esize);
 }
-template <class DST>
+// E: what a lane takes.  In a fused launch it is the element, as in a reduction's tail: a step then reads what the same lane wrote.
+template <class E, class DST>
 __device__ __forceinline__ void copy_tail(const char* src, const DST& dst, int ndst, int64_t bytes, uint32_t chunks) {
-    const int left = (int)(bytes & 15), tid = threadIdx.x;
+    const int left = (int)(bytes & 15) / (int)sizeof(E), tid = threadIdx.x;
     if (tid < left && owns_last(chunks)) {
-        const int64_t at = (bytes & ~(int64_t)15) + tid;
-        const char b = src[at];
-        for (int d = 0; d < ndst; ++d) dst(d)[at] = b;
+        const int64_t at = (bytes & ~(int64_t)15) + tid * (int)sizeof(E);
+        const E b = *reinterpret_cast<const E*>(src + at);
+        for (int d = 0; d < ndst; ++d) *reinterpret_cast<E*>(dst(d) + at) = b;
     }
 }
 
@@ -491,7 +492,7 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) gather_copy_kernel(cons
     const GatherIo<KIND, decltype(src), decltype(dst)> io{src, dst, p.ndst};
     move_batches<LAGOM_F32, 1, units_in_batch(1, DEEP), STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
     if (KIND == GATHER) {
-        if (p.nsrc == 1) copy_tail(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
+        if (p.nsrc == 1) copy_tail<uint8_t>(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
         return;
     }
     // both ends of every shard, byte by byte: lanes 0..15 the head, lanes 16..31 the tail
@@ -605,7 +606,7 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const
         for (const int end = st + run; st < end; ++st) {       // behind the last whole vector: bytes that no walk touches
             const auto src = [&p, st](int s) { return p.src(st, s); };
             const auto dst = [&p, st](int d) { return p.dst(st, d); };
-            if (p.step[st] >> 24 == LAGOM_GATHER_COPY) copy_tail(src(0), dst, p.ndst(st), p.shape.shard_bytes, p.shape.chunks);
+            if (p.step[st] >> 24 == LAGOM_GATHER_COPY) copy_tail<std::conditional_t<DT == LAGOM_F32, uint32_t, uint16_t>>(src(0), dst, p.ndst(st), p.shape.shard_bytes, p.shape.chunks);
             else reduce_tail<DT>(src, dst, p.nsrc(st), p.ndst(st), p.shape.shard_bytes, p.shape.chunks);
         }
     }
