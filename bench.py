@@ -163,13 +163,15 @@ def comm_bytes(launches):
     return [lg.lagom_comm_bytes(l.op, l.dtype, len(l.srcs), len(l.dsts), l.count) for l in launches]
 
 
-def gemm_kernel_name(geo, out_bf16=True):
-    """The kernel lagom_gemm dispatches for a geometry (names as they appear in a kernel trace)."""
-    if (geo.tile_m, geo.tile_n) == (128, 128):
-        return "gemm_bf16_nk128_kernel"
-    if (geo.tile_m, geo.tile_n) == (256, 128):
-        return "gemm_bf16_nk256x128_kernel"
-    return "gemm_bf16_nk_kernel"
+def gemm_kernel_name(geo, M, N, K):
+    """The kernel lagom_gemm dispatches for an [N,K] product (names as they appear in a kernel trace)."""
+    if geo.tile_m * geo.tile_n <= 64 * 64:
+        return "gemm_bf16_split_kernel"
+    if K < 64 or K > 1 << 22:
+        return "gemm_bf16_general_kernel"
+    tiles = -(-M // geo.tile_m) * -(-N // geo.tile_n)
+    kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "" if geo.mu == tiles else "_mixed")
+    return f"gemm_bf16_nk{kind}{'_tail' if K % 64 else ''}_kernel"
 
 
 def rotating_comm_roofline(st1, st2, op, dt_name, nsrc, count, cfgs, iters, final_iters=20):
@@ -536,7 +538,7 @@ def run_config(name, args, s_comm, s_comp, dependent=False):
     graph_tuned_us = lg.lagom_overlap_steps_graph(launches, tuned.cfgs, comps, s_comm, s_comp, args.steps)
 
     tflops = flops / gemm_us / 1e6
-    roofline = {"bound": "mfma", "kernel": gemm_kernel_name(geo), "shape": f"{M}x{N}x{K}", "achieved": tflops, "peak": BF16_PEAK_TFLOPS,
+    roofline = {"bound": "mfma", "kernel": gemm_kernel_name(geo, M, N, K), "shape": f"{M}x{N}x{K}", "achieved": tflops, "peak": BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": tflops / BF16_PEAK_TFLOPS, "traffic": None,
                 "traffic_from_profile": TRAFFIC_FROM_PROFILE.get(f"gemm {M}x{N}x{K}"),
                 "us_per_launch": gemm_us, "flop_per_launch": flops, "launches_timed": args.rounds * args.steps * len(comps)}

@@ -137,12 +137,18 @@ int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
 
 /* Workgroup geometry of lagom_gemm for a problem size, as the cost model needs it
  * (Eq. 5-6: mu = total workgroups, TB = workgroups resident per compute unit,
- * D = bytes each workgroup reads and writes).  The tiling depends on the size only: the smallest
- * of 128 x 128, 256 x 128 and 256 x 256 of which at most 256 tiles cover C (256 x 256 whenever
- * K < 64 or K > 2^22).  What is left over behind whole rounds of 256 tiles of 256 x 256 may run as
- * 128 x 128 quadrants; mu counts it in whole tiles.  Products so small that tiles of at most
- * 64 x 64 cover C in one round run on those, with K split over a workgroup's wavefronts; they are
- * reported as 128 x 128.  Host only. */
+ * D = bytes each workgroup reads and writes), by the rules lagom_gemm itself launches by.  They depend
+ * on the size only:
+ *   K < 64 or K > 2^22                 256 x 256 tiles
+ *   tiles of 16 x 32, 32 x 32, and from K = 128 on 64 x 32 or 32 x 64, and above K = 256 64 x 64:
+ *                                      the smallest of which at most 256 cover C, if any; K is split
+ *                                      over the workgroup's wavefronts
+ *   else                               the smallest of 128 x 128, 256 x 128 and 256 x 256 of which at
+ *                                      most 256 cover C, 256 x 256 if none does
+ * What is left over behind whole rounds of 256 tiles of 256 x 256 runs as 128 x 128 quadrants where
+ * they take at most two rounds ([K,N] with N > 2^23 apart): then mu counts the large tiles and the
+ * quadrants that hold something, D and d_bytes_past_l2 are means over them, and tile_m x tile_n is the
+ * large tile.  Host only. */
 typedef struct {
     int64_t mu;
     int32_t tb;

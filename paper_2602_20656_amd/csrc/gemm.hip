@@ -1177,17 +1177,21 @@ Tiling choose_tiling(int64_t M, int64_t N, int64_t K) {
 // With fewer slices than wavefronts the additions at the end cost what the split gains: 64 x 64 tiles 5.4 us against 5.3 us at
 // 1024 x 1024 x 256 and 5.8 against 5.9 at K = 384; 64 x 32 tiles 4.4 against 5.1 at 640 x 640 x 256, 4.3 against 4.3 at
 // K = 128 and 4.3 against 4.1 at K = 64; 32 x 32 tiles 4.1 against 4.1 at 512 x 512 x 64.
-typedef int (*SplitLaunch)(GemmArgs, bool, bool, hipStream_t);
-SplitLaunch choose_split(int64_t M, int64_t N, int64_t K) {
-    if (K < BK || K > FAST_MAX_K) return nullptr;
+struct Split {
+    int (*launch)(GemmArgs, bool, bool, hipStream_t);      // null: K is not split
+    int tm, tn, threads;
+};
+template <class T> Split split_with() { return {launch_split<T>, T::TM, T::TN, 64 * T::WAVES}; }
+Split choose_split(int64_t M, int64_t N, int64_t K) {
+    if (K < BK || K > FAST_MAX_K) return {};
     auto tiles = [&](int64_t tm, int64_t tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-    if (tiles(16, 32) <= kRound) return launch_split<SplitTile<1, 2, 8, 3>>;
-    if (tiles(32, 32) <= kRound) return launch_split<SplitTile<2, 2, 8, 2>>;
-    if (K < 2 * BK) return nullptr;
-    if (tiles(64, 32) <= kRound && tiles(64, 32) <= tiles(32, 64)) return launch_split<SplitTile<4, 2, 4, 3>>;
-    if (tiles(32, 64) <= kRound) return launch_split<SplitTile<2, 4, 4, 3>>;
-    if (tiles(64, 64) <= kRound && K > 4 * BK) return launch_split<SplitTile<4, 4, 4, 2>>;
-    return nullptr;
+    if (tiles(16, 32) <= kRound) return split_with<SplitTile<1, 2, 8, 3>>();
+    if (tiles(32, 32) <= kRound) return split_with<SplitTile<2, 2, 8, 2>>();
+    if (K < 2 * BK) return {};
+    if (tiles(64, 32) <= kRound && tiles(64, 32) <= tiles(32, 64)) return split_with<SplitTile<4, 2, 4, 3>>();
+    if (tiles(32, 64) <= kRound) return split_with<SplitTile<2, 4, 4, 3>>();
+    if (tiles(64, 64) <= kRound && K > 4 * BK) return split_with<SplitTile<4, 4, 4, 2>>();
+    return {};
 }
 
 // A chip full of 128 x 128 tiles takes 0.39 of the time of one full of 256 x 256 tiles, so up to two rounds of quadrants
@@ -1196,11 +1200,11 @@ SplitLaunch choose_split(int64_t M, int64_t N, int64_t K) {
 // 154.4; 4100 x 4200 x 2048 (33 left over, 65 quadrants) 86.1 -> 64.8; 8192 x 8448 x 8192 (fifth round, 32) 808 -> 733.
 constexpr int kMaxQuadrants = 2 * kRound;
 
-// Whether the last round of a product in large tiles is worth cutting into quadrants, and how.
-bool choose_mixed(const GemmArgs& g, MixedArgs* out) {
+// Whether the last round of a product in large tiles is worth cutting into quadrants (their number, else 0), and how.
+int choose_mixed(const GemmArgs& g, MixedArgs* out) {
     const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
     const int rest = (int)(tiles % kRound);
-    if (tiles <= kRound || rest == 0) return false;
+    if (tiles <= kRound || rest == 0) return 0;
     MixedArgs a{g, (int32_t)(g.M / BM), (int32_t)(g.N / BN), (int32_t)(tiles - rest), (rest + 7) / 8};
     // quadrants that hold something: 4 of a tile inside C, fewer of one that an edge cuts through
     const int64_t inside = (int64_t)a.full_m * a.full_n, right = (int64_t)a.full_m * (g.tiles_n - a.full_n);
@@ -1208,10 +1212,12 @@ bool choose_mixed(const GemmArgs& g, MixedArgs* out) {
     int quadrants = 0;
     for (int64_t lin = a.nlarge; lin < tiles; ++lin)
         quadrants += lin < inside ? 4 : lin < inside + right ? 2 * halves_n : halves_m * (lin - inside - right < a.full_n ? 2 : halves_n);
-    if (quadrants > kMaxQuadrants) return false;
+    if (quadrants > kMaxQuadrants) return 0;
     *out = a;
-    return true;
+    return quadrants;
 }
+
+constexpr int64_t kMaxDim = 1 << 24;
 
 }  // namespace
 
@@ -1219,7 +1225,7 @@ namespace lagom {
 int check_gemm_args(const void* A, const void* B, const void* C, int64_t M, int64_t N, int64_t K, int out_dt) {
     if (!A || !B || !C) return fail(LAGOM_EINVAL, "null matrix pointer");
     if (M < 1 || N < 1 || K < 1) return fail(LAGOM_EINVAL, "M, N, K must be positive");
-    if (M > (1 << 24) || N > (1 << 24) || K > (1 << 24)) return fail(LAGOM_EINVAL, "dimension above 2^24");
+    if (M > kMaxDim || N > kMaxDim || K > kMaxDim) return fail(LAGOM_EINVAL, "dimension above 2^24");
     if (K % 8) return fail(LAGOM_EINVAL, "K=%lld must be a multiple of 8", (long long)K);
     if (elem_size(out_dt) == 0) return fail(LAGOM_EINVAL, "unknown output dtype %d", out_dt);
     if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) return fail(LAGOM_EALIGN, "matrix pointer not 16-byte aligned");
@@ -1229,19 +1235,37 @@ int check_gemm_args(const void* A, const void* B, const void* C, int64_t M, int6
 
 extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype out_dt, lagom_gemm_geometry* out) {
     if (!out || M < 1 || N < 1 || K < 1 || lagom::elem_size(out_dt) == 0) return lagom::fail(LAGOM_EINVAL, "bad argument");
-    // the tiling lagom_gemm uses for this shape (it does not depend on B's layout)
+    // what lagom_gemm launches for this shape, by the same rules ([K,N] with N above FAST_MAX_N_KN apart, whose kernel has no quadrants)
+    const double out_bytes = lagom::elem_size(out_dt);
+    auto loads = [&](int64_t rows, int64_t cols) { return (double)(rows + cols) * (double)K * 2.0; };
+    out->tb = 1;   // one workgroup per compute unit: LDS, or the general kernel's 256 accumulators a lane
+    out->tile_k = BK;
+    if (const Split split = choose_split(M, N, K); split.launch) {
+        const int64_t tm = (M + split.tm - 1) / split.tm, tn = (N + split.tn - 1) / split.tn;
+        out->mu = tm * tn;
+        out->tile_m = split.tm; out->tile_n = split.tn; out->threads = split.threads;
+        out->d_bytes = loads(split.tm, split.tn) + (double)split.tm * split.tn * out_bytes;
+        // an XCD takes an eighth of the tiles, along the shorter side of C first
+        const int64_t n = (out->mu + 7) / 8, inner = tm <= tn ? tm : tn, in = inner < n ? inner : n, across = (n + in - 1) / in;
+        const int64_t rows = tm <= tn ? in : across, cols = tm <= tn ? across : in;
+        out->d_bytes_past_l2 = loads(rows * split.tm, cols * split.tn) / (double)n + (double)split.tm * split.tn * out_bytes;
+        return LAGOM_OK;
+    }
     const Tiling tiling = choose_tiling(M, N, K);
     const int64_t bm = tiling == TILE_128x128 ? SBM : BM, bn = tiling == TILE_256x256 ? BN : SBN;
     const int64_t tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn;
     out->mu = tm * tn;
-    out->tb = 1;   // either kernel takes all of a compute unit's LDS: one workgroup per compute unit
-    out->d_bytes = (double)(bm + bn) * (double)K * 2.0 + (double)bm * bn * lagom::elem_size(out_dt);
-    out->tile_m = (int32_t)bm; out->tile_n = (int32_t)bn; out->tile_k = BK; out->threads = THREADS;
+    out->d_bytes = loads(bm, bn) + (double)bm * bn * out_bytes;
+    out->tile_m = (int32_t)bm; out->tile_n = (int32_t)bn; out->threads = THREADS;
+    const bool may_cut = tiling == TILE_256x256 && K >= BK && K <= FAST_MAX_K && M <= kMaxDim && N <= kMaxDim;
+    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn};
+    MixedArgs mixed;
+    const int quadrants = may_cut ? choose_mixed(a, &mixed) : 0;
     // the block of tiles an XCD works on at a time under tile_of() (32 compute units per XCD): n tiles in
     // r tile-rows and c tile-columns need r A panels and c B panels between them
     const int64_t total = tm * tn;
     int64_t n, rows, cols;
-    if (total % 8 == 0) {
+    if (total % 8 == 0 || quadrants) {
         n = total / 8 < 32 ? total / 8 : 32;
         rows = tm < 8 ? tm : 8;
         if (rows > n) rows = n;
@@ -1251,8 +1275,14 @@ extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype 
         rows = 1;
         cols = n;
     }
-    out->d_bytes_past_l2 = ((double)rows * bm + (double)cols * bn) * (double)K * 2.0 / (double)n +
-                           (double)bm * bn * lagom::elem_size(out_dt);
+    out->d_bytes_past_l2 = loads(rows * bm, cols * bn) / (double)n + (double)bm * bn * out_bytes;
+    if (quadrants) {   // means over the large tiles and the quadrants that hold something; the four of a tile share its panels
+        const double quadrant_out = (double)SBM * SBN * out_bytes;
+        out->mu = mixed.nlarge + quadrants;
+        auto mean = [&](double large, double quadrant) { return (mixed.nlarge * large + quadrants * quadrant) / (double)out->mu; };
+        out->d_bytes = mean(out->d_bytes, loads(SBM, SBN) + quadrant_out);
+        out->d_bytes_past_l2 = mean(out->d_bytes_past_l2, loads(2 * SBM, 2 * SBN) / 4.0 + quadrant_out);
+    }
     return LAGOM_OK;
 }
 
@@ -1261,9 +1291,9 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (int rc = lagom::check_gemm_args(A, B, C, M, N, K, out_dt)) return rc;
     if (!b_is_nk && (N % 8)) return lagom::fail(LAGOM_EINVAL, "B stored [K,N] needs N to be a multiple of 8");
     const Tiling tiling = choose_tiling(M, N, K);
-    if (const SplitLaunch split = choose_split(M, N, K)) {
+    if (const Split split = choose_split(M, N, K); split.launch) {
         const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0};
-        if (int rc = split(a, b_is_nk != 0, out_dt == LAGOM_BF16, static_cast<hipStream_t>(hip_stream))) return rc;
+        if (int rc = split.launch(a, b_is_nk != 0, out_dt == LAGOM_BF16, static_cast<hipStream_t>(hip_stream))) return rc;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "gemm launch: %s", hipGetErrorString(e));
         return LAGOM_OK;

@@ -44,26 +44,63 @@ def test_host_only_helpers():
     assert g.mu == (8192 // g.tile_m) * (8192 // g.tile_n) and g.tb >= 1
     assert g.d_bytes == (g.tile_m + g.tile_n) * 8192 * 2 + g.tile_m * g.tile_n * 2
     assert (g.tile_m, g.tile_n, g.tile_k) == (256, 256, 64)
-    # at most 256 tiles of 128 x 128 (and K a multiple of 64): the small tiling
-    few = lg.lagom_gemm_describe(100, 300, 64)
-    assert (few.tile_m, few.tile_n, few.mu, few.tb) == (128, 128, 1 * 3, 1)
+    # at most 256 tiles of 128 x 128 (and more than that of 64 x 64): the small tiling
+    few = lg.lagom_gemm_describe(1200, 1288, 64)
+    assert (few.tile_m, few.tile_n, few.mu, few.tb, few.threads) == (128, 128, 10 * 11, 1, 256)
     assert few.d_bytes == (128 + 128) * 64 * 2 + 128 * 128 * 2
     assert lg.lagom_gemm_describe(2048, 2048, 4096).mu == 256
     mid = lg.lagom_gemm_describe(2048, 2176, 4096)             # 272 tiles of 128 x 128, 136 of 256 x 128
     assert (mid.tile_m, mid.tile_n, mid.mu) == (256, 128, 8 * 17)
     assert mid.d_bytes == (256 + 128) * 4096 * 2 + 256 * 128 * 2
     assert lg.lagom_gemm_describe(3072, 3072, 3072).tile_n == 256   # 288 tiles of 256 x 128: the large tiling
-    assert lg.lagom_gemm_describe(512, 512, 72).tile_m == 128       # K need not be a multiple of 64 for that
+    assert lg.lagom_gemm_describe(1200, 1288, 72).tile_m == 128     # K need not be a multiple of 64 for that
     assert lg.lagom_gemm_describe(512, 512, 56).tile_m == 256       # K < 64: the general kernel's tiling
     # bytes past an XCD's L2: the 32 tiles an XCD holds at a time form an 8 x 4 block -> A panels shared by 4, B by 8
     for M, N, K in [(4096, 4096, 4096), (8192, 4096, 4096), (8192, 8192, 8192)]:
         assert lg.lagom_gemm_describe(M, N, K).d_bytes_past_l2 == (8 * 256 + 4 * 256) * K * 2 / 32 + 256 * 256 * 2
-    small = lg.lagom_gemm_describe(512, 512, 512)          # 16 small tiles, two per XCD, in one tile-column: a B panel shared by 2
-    assert small.d_bytes_past_l2 == (2 * 128 + 1 * 128) * 512 * 2 / 2 + 128 * 128 * 2
-    lone = lg.lagom_gemm_describe(256, 256, 512)           # 4 tiles: nothing is shared
-    assert lone.d_bytes_past_l2 == lone.d_bytes
+    small = lg.lagom_gemm_describe(1152, 1280, 512)        # 90 small tiles: ids not remapped, an XCD holds 12 of them
+    assert small.d_bytes_past_l2 == (1 * 128 + 12 * 128) * 512 * 2 / 12 + 128 * 128 * 2
+    lone = lg.lagom_gemm_describe(64, 64, 512)             # 8 tiles of 16 x 32, one per XCD: nothing is shared
+    assert lone.mu == 8 and lone.d_bytes_past_l2 == lone.d_bytes
     # 16 x 14 tiles: 28 per XCD at a time, 8 tile-rows x 4 tile-columns (the last one half full)
     assert lg.lagom_gemm_describe(4096, 3584, 8192).d_bytes_past_l2 == (8 * 256 + 4 * 256) * 8192 * 2 / 28 + 256 * 256 * 2
+
+
+@pytest.mark.parametrize("M,N,K,tile,mu,threads,block", [
+    (33, 1000, 4096, (16, 32), 3 * 32, 512, (3, 4)),      # an XCD's twelve tiles: three tile-rows of four
+    (512, 512, 512, (32, 32), 16 * 16, 512, (16, 2)),
+    (512, 512, 64, (32, 32), 16 * 16, 512, (16, 2)),
+    (640, 640, 128, (64, 32), 10 * 20, 256, (10, 3)),
+    (90, 5400, 128, (32, 64), 3 * 85, 256, (3, 11)),
+    (5400, 90, 128, (64, 32), 85 * 3, 256, (11, 3)),      # the shorter side of C first
+    (1024, 1024, 320, (64, 64), 16 * 16, 256, (16, 2))])
+def test_geometry_of_a_product_with_k_split_over_wavefronts(M, N, K, tile, mu, threads, block):
+    g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
+    assert (g.tile_m, g.tile_n, g.mu, g.threads, g.tile_k, g.tb) == (*tile, mu, threads, 64, 1)
+    out = tile[0] * tile[1] * 4
+    assert g.d_bytes == sum(tile) * K * 2 + out
+    assert g.d_bytes_past_l2 == (block[0] * tile[0] + block[1] * tile[1]) * K * 2 / -(-mu // 8) + out
+
+
+def test_geometry_where_k_is_not_split():
+    """K too short for the tile, or one tile more than a round holds."""
+    for M, N, K in [(640, 640, 64), (1024, 1024, 256), (1025, 1024, 4096)]:
+        assert lg.lagom_gemm_describe(M, N, K).tile_m == 128
+
+
+@pytest.mark.parametrize("M,N,large,quadrants", [
+    (4096, 4352, 256, 4 * 16),
+    (4100, 4200, 256, 65),          # 33 tiles left over: 16 + 17 at two edges, half or a quarter of each in C
+    (4096, 6144, 256, 4 * 128),
+    (3970, 4456, 256, 14 * 2 + 17 * 4 + 2),       # 16 x 18 tiles, 255 inside; 14 of the right edge's, the lower edge's and the corner
+    (4096, 6400, 400, 0)])          # 144 tiles left over are more than two rounds of quadrants: whole tiles
+def test_geometry_of_a_product_with_its_last_round_in_quadrants(M, N, large, quadrants):
+    K = 2048
+    g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
+    whole, quarter = (256 + 256) * K * 2 + 256 * 256 * 4, (128 + 128) * K * 2 + 128 * 128 * 4
+    assert (g.tile_m, g.tile_n, g.threads, g.mu) == (256, 256, 256, large + quadrants)
+    assert g.d_bytes == pytest.approx((large * whole + quadrants * quarter) / g.mu, rel=1e-12)
+    assert g.d_bytes_past_l2 < g.d_bytes
 
 
 def test_argument_errors_are_reported_before_any_gpu_work():
