@@ -222,9 +222,9 @@ typedef struct {
  *   comm_stream, comp_stream : two distinct hipStream_t of default priority.
  *   Each of warmup + iters repetitions starts both streams together behind a gate and
  *   drains both before the next; every value reported is the median over `iters`.  In LAGOM_CORUN
- *   the gate is a bounded delay kernel on either stream; the two agree on the instant of release
- *   through 16 bytes of pinned host memory that the library allocates once per device and keeps
- *   (calls that overlap in time on one device share it and may delay each other's release).
+ *   the gate is a bounded kernel on either stream; the host opens it when everything is enqueued, and the
+ *   two agree on the instant of release, through pinned host memory that the library allocates once per
+ *   device and keeps (64 words of 64 bytes, one to a repetition in flight).
  *   Cross-stream dependencies (after_comp / after_comm_id) are enforced with events in
  *   LAGOM_CORUN; the two enqueue orders are merged on the host so that every awaited event
  *   has been recorded first, and a dependency cycle is LAGOM_EINVAL.  With dependencies X and
@@ -237,6 +237,11 @@ int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch,
                       const lagom_gemm_desc* comps, int ncomp,
                       void* comm_stream, void* comp_stream,
                       int warmup, int iters, int mode, lagom_timing* out);
+
+/* Repetitions of all lagom_overlap_run calls of the process so far whose gate was not opened by the host
+ * but by its time bound (the host took longer to enqueue the group), and whose second stream did not see
+ * the common instant: their kernels may have started before everything was enqueued, or apart. */
+int lagom_gate_misses(int64_t* by_bound, int64_t* unseen);
 
 /* Sustained rate of an overlap group (the executor path of a training loop): `steps` repetitions of
  * the group of lagom_overlap_run(LAGOM_CORUN) are enqueued back to back; between repetitions the two

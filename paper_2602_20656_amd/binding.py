@@ -31,7 +31,8 @@ LAGOM_MAX_STEPS, LAGOM_MAX_STEP_PTRS = 32, 96
 EXPORTS = ["lagom_strerror", "lagom_last_error", "lagom_comm_kernel", "lagom_gemm", "lagom_gemm_describe",
            "lagom_overlap_run", "lagom_contention_sweep", "lagom_comm_bytes", "lagom_cost_model", "lagom_tune",
            "lagom_model_profile", "lagom_overlap_profile", "lagom_streams_overlap", "lagom_overlap_steps", "lagom_overlap_steps_graph",
-           "lagom_model_fill", "lagom_model_calibrate", "lagom_ladder_chunks", "lagom_comm_steps", "lagom_comm_kernel_lds"]
+           "lagom_model_fill", "lagom_model_calibrate", "lagom_ladder_chunks", "lagom_comm_steps", "lagom_comm_kernel_lds",
+           "lagom_gate_misses"]
 
 
 class LagomError(RuntimeError):
@@ -182,6 +183,7 @@ def lib() -> C.CDLL:
         L.lagom_contention_sweep.argtypes = [C.POINTER(lagom_comm_desc), C.c_int, C.c_int, C.POINTER(lagom_gemm_desc), C.c_int,
                                              C.POINTER(lagom_cfg), C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_int,
                                              C.POINTER(lagom_sweep_point)]
+        L.lagom_gate_misses.argtypes = [C.POINTER(C.c_int64), C.POINTER(C.c_int64)]
         L.lagom_streams_overlap.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_int)]
         L.lagom_overlap_steps.argtypes = [C.POINTER(lagom_comm_desc), C.c_int, C.POINTER(lagom_cfg), C.c_int,
                                           C.POINTER(lagom_gemm_desc), C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.POINTER(C.c_double)]
@@ -374,6 +376,13 @@ def lagom_overlap_run(launches: Sequence[CommLaunch], cfgs: Sequence[CfgLike], c
                                    _stream(comm_stream), _stream(comp_stream), warmup, iters, mode, C.byref(t)))
     return Timing(t.X_us, t.Y_us, t.Z_us, list(x)[:ncfg], list(y)[:grp.ncomp], list(xm)[:ncfg], t.Ysum_us, t.Ysum_mad_us, t.Z_mad_us,
                   t.comm_start_us, t.comp_start_us)
+
+
+def lagom_gate_misses() -> Tuple[int, int]:
+    """Repetitions so far whose gate its time bound opened, and whose second stream missed the common instant."""
+    late, unseen = C.c_int64(), C.c_int64()
+    _check(lib().lagom_gate_misses(C.byref(late), C.byref(unseen)))
+    return late.value, unseen.value
 
 
 def lagom_overlap_steps(launches: Sequence[CommLaunch], cfgs: Sequence[CfgLike], comps: Sequence[GemmDesc],

@@ -43,10 +43,11 @@ __global__ void gate_delay_kernel(long long ticks, int max_iter) {
 // the last launch; the leader (every repetition has one) waits for it, for at most `max_ticks`, picks the tick `lead_ticks`
 // later, publishes it and then the sequence number (release), and holds until that tick; the follower (co-runs only) waits
 // for the sequence number (acquire), reads the tick and holds until then.  Every loop is bounded by `max_iter` whatever
-// memory, the host or the clock say; a follower that never sees its number just ends late.
+// memory, the host or the clock say; a follower that never sees its number just ends late.  Either writes down that it did
+// not end as it should (`late`: the leader opened by its bound; `unseen`), for lagom_gate_misses.
 // What bounds a gate is the host's enqueueing: 20 - 40 us for a ring share beside one product.  A hold of fixed length has to
 // cover the worst host instead; 60 us + 12 us per launch and event kept both streams waiting 337 us of a 556 us repetition.
-struct alignas(64) GateWord { unsigned long long deadline, seq, go; };
+struct alignas(64) GateWord { unsigned long long deadline, seq, go, late, unseen; };
 constexpr double kGateLeadUs = 12.0;
 constexpr int kGateWords = 64;       // repetition n uses word n mod 64: co-runs of several threads do not meet in one
 
@@ -54,11 +55,13 @@ __global__ void gate_leader_kernel(GateWord* g, unsigned long long seq, long lon
     if (threadIdx.x == 0) {
         const long long t0 = wall_clock64();
         int i = 0;
+        bool opened = false;
         for (; i < max_iter; ++i) {
-            if (__hip_atomic_load(&g->go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == seq) break;
-            if (wall_clock64() - t0 >= max_ticks) break;
+            opened = __hip_atomic_load(&g->go, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) == seq;
+            if (opened || wall_clock64() - t0 >= max_ticks) break;
             __builtin_amdgcn_s_sleep(8);
         }
+        if (!opened) __hip_atomic_store(&g->late, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         const long long t1 = wall_clock64();
         __hip_atomic_store(&g->deadline, (unsigned long long)(t1 + lead_ticks), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&g->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -81,6 +84,7 @@ __global__ void gate_follower_kernel(GateWord* g, unsigned long long seq, int ma
             if (known && wall_clock64() - deadline >= 0) break;
             __builtin_amdgcn_s_sleep(8);
         }
+        if (!known) __hip_atomic_store(&g->unseen, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -96,7 +100,7 @@ int gate_words(int dev, GateWord** out) {
         void* p = nullptr;
         HIP_TRY(hipHostMalloc(&p, kGateWords * sizeof(GateWord), hipHostMallocDefault));
         GateWord* w = static_cast<GateWord*>(p);
-        for (int i = 0; i < kGateWords; ++i) w[i] = GateWord{0, 0, 0};
+        for (int i = 0; i < kGateWords; ++i) w[i] = GateWord{};
         words[dev] = w;
     }
     *out = words[dev];
@@ -107,6 +111,16 @@ unsigned long long next_gate_seq() {
     static std::atomic<unsigned long long> counter{0};
     return counter.fetch_add(1) + 1;
 }
+
+std::atomic<int64_t> gates_late{0}, gates_unseen{0};
+
+// Opens the gate of a repetition, at the latest when it goes out of scope: whatever fails behind the gate's launch, what is
+// queued there is drained next, and is not to sit out the bound.
+struct GateOpener {
+    GateWord* word; unsigned long long seq;
+    void open() { __atomic_store_n(&word->go, seq, __ATOMIC_RELEASE); }
+    ~GateOpener() { open(); }
+};
 
 struct Events {
     std::vector<hipEvent_t> ev;
@@ -215,8 +229,8 @@ struct GroupPlan {
 };
 
 // Enqueues one repetition of the group: nl launches on sa, nc computations on sb.  The two enqueue
-// orders are merged so that an awaited event has always been recorded first; a dependency cycle
-// drains both streams and is LAGOM_EINVAL.  ga_start / gb_start may be null (no per-operator timing).
+// orders are merged so that an awaited event has always been recorded first; a dependency cycle is
+// LAGOM_EINVAL.  Behind a failure the caller drains both streams.  ga_start / gb_start may be null (no per-operator timing).
 int enqueue_group(const GroupPlan& plan, const lagom_comm_desc* launches, int nl, const lagom_cfg* cfgs,
                   const lagom_gemm_desc* comps, int nc, bool deps, hipStream_t sa, hipStream_t sb,
                   hipEvent_t* ga_start, hipEvent_t* ga_end, hipEvent_t* gb_start, hipEvent_t* gb_end) {
@@ -265,12 +279,7 @@ int enqueue_group(const GroupPlan& plan, const lagom_comm_desc* launches, int nl
                 progressed = true;
             }
         }
-        if (!progressed) {
-            // nothing of this repetition may stay queued: drain, then report
-            (void)hipStreamSynchronize(sa);
-            (void)hipStreamSynchronize(sb);
-            return lagom::fail(LAGOM_EINVAL, "the cross-stream dependencies form a cycle (launch %d, computation %d)", li, ci);
-        }
+        if (!progressed) return lagom::fail(LAGOM_EINVAL, "the cross-stream dependencies form a cycle (launch %d, computation %d)", li, ci);
     }
     return LAGOM_OK;
 }
@@ -367,25 +376,28 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
 
     std::vector<double> Ysums;
     // one repetition: gate, both streams enqueued, both drained
-    auto repetition = [&]() -> int {
-        const unsigned long long seq = next_gate_seq();
-        GateWord* word = words + seq % kGateWords;
+    auto repetition = [&](GateWord* word, unsigned long long seq) -> int {
+        GateOpener gate{word, seq};
         hipLaunchKernelGGL(gate_leader_kernel, dim3(1), dim3(64), 0, gate_stream, word, seq, ticks, lead_ticks, max_iter);
         HIP_TRY(hipGetLastError());
         if (run_comm && run_comp) {
             hipLaunchKernelGGL(gate_follower_kernel, dim3(1), dim3(64), 0, sb, word, seq, max_iter);
             HIP_TRY(hipGetLastError());
         }
-        const int rc = enqueue_group(plan, launches, run_comm ? nlaunch : 0, cfgs, comps, ncomp_run, deps, sa, sb,
-                                     ga_start, ga_end, gb_start, gb_end);
-        __atomic_store_n(&word->go, seq, __ATOMIC_RELEASE);       // also behind a failure: what is queued is to drain
-        if (rc) return rc;
+        if (int rc = enqueue_group(plan, launches, run_comm ? nlaunch : 0, cfgs, comps, ncomp_run, deps, sa, sb,
+                                   ga_start, ga_end, gb_start, gb_end)) return rc;
+        gate.open();
         if (run_comm) HIP_TRY(hipStreamSynchronize(sa));
         if (run_comp) HIP_TRY(hipStreamSynchronize(sb));
         return LAGOM_OK;
     };
     for (int it = 0; it < warmup + iters; ++it) {
-        if (int rc = drained(repetition(), sa, sb)) return rc;
+        const unsigned long long seq = next_gate_seq();
+        GateWord* word = words + seq % kGateWords;
+        const int rc = drained(repetition(word, seq), sa, sb);
+        if (__atomic_load_n(&word->late, __ATOMIC_RELAXED) == seq) ++gates_late;
+        if (__atomic_load_n(&word->unseen, __ATOMIC_RELAXED) == seq) ++gates_unseen;
+        if (rc) return rc;
         if (it < warmup) continue;
 
         // The common start: the start event of the stream whose first kernel follows its gate kernel directly.  With
@@ -434,6 +446,13 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
         if (out->x_mad_us) out->x_mad_us[j] = mad(xs[j], m);
     }
     if (out->y_us) for (int i = 0; i < ncomp; ++i) out->y_us[i] = median(ys[i]);
+    return LAGOM_OK;
+}
+
+extern "C" int lagom_gate_misses(int64_t* by_bound, int64_t* unseen) {
+    if (!by_bound || !unseen) return lagom::fail(LAGOM_EINVAL, "null output");
+    *by_bound = gates_late.load();
+    *unseen = gates_unseen.load();
     return LAGOM_OK;
 }
 
