@@ -99,8 +99,8 @@ __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w 
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
 // Two fp32 -> a packed pair of bf16, round to nearest, ties to even; NaN keeps a quiet payload.  v_cvt_pk_bf16_f32
-// gives the bits of the integer formula (upper + round-up, NaN: upper | 0x40) on all 2^32 inputs (checked); it
-// replaces 14 integer instructions per pair, which with two sources were half of a channel's VALU time.
+// gives the bits of the integer formula (upper + round-up, NaN: upper | 0x40) on every finite sum and every bf16 NaN
+// (tests/test_gpu_comm.py); it replaces 14 integer instructions per pair, which with two sources were half of a channel's VALU time.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bf16_round2(float lo, float hi) {

@@ -42,7 +42,7 @@
 //     the loop has multiplied some already, and clears those in its operand fragments (in both, so
 //     that no stray NaN meets a zero).  Its loads are in flight like any other step's; the rest of K
 //     fetched behind the loop with guarded loads cost a memory latency per tile: 4096 x 4096 x 184
-//     14.7 -> 13.4 us, x 72 12.7 -> 12.0, 4096 x 4352 x 2056 76.4 -> 74.0, 128 x 128 x 520 6.9 -> 6.7.
+//     14.7 -> 13.4 us, x 72 12.7 -> 12.0, 4096 x 4352 x 2056 76.4 -> 74.0.
 // General kernel (any K multiple of 8, either B layout, v_mfma_f32_32x32x16_bf16): tiles are
 // fetched into registers with bounds checks and zero fill, then stored to LDS ([K,N]: 8 x 8
 // blocks transposed in registers first); single buffered.  Slower; used for K < 64 and beyond
@@ -593,7 +593,7 @@ template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
-// K >= 64 and not a multiple of 64 (kernels of their own: the extra step costs registers the others leave free)
+// K >= 64 and not a multiple of 64 (kernels of their own: the peeled last step clears fragments; as many registers)
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>

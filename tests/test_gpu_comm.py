@@ -408,6 +408,36 @@ def test_full_size_launches_in_the_light_channel_and_roofline_shapes():
             assert same_bits(run(lg.LAGOM_GATHER_COPY, "bf16", shards, 1, cfg, 8 * 2097152)[0], whole), (run.__name__, cfg)
 
 
+# ------------------------------------------------------------- the rounding of bf16 results
+def test_one_bf16_source_keeps_every_pattern_and_makes_a_nan_quiet():
+    a = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16)
+    want = oc.reduce_copy([a], "bf16")[0]
+    nan = (a & 0x7FFF) > 0x7F80
+    assert same_bits(want, np.where(nan, a | 0x40, a).astype(np.uint16))
+    assert same_bits(_run(lg.LAGOM_REDUCE_COPY, "bf16", [a], 1, (4, 256, 16384), 1 << 16)[0], want)
+
+
+def test_every_finite_fp32_sum_is_rounded_to_nearest_even():
+    """A finite fp32 value is the exact sum of three bf16 values (8 of its 24 bits each, down to where the last of them has no
+    bf16 pattern), so a reduce of three sources rounds all of them; compared with the integer formula."""
+    n = 1 << 26
+    out = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
+    top = torch.tensor(-65536, dtype=torch.int32, device="cuda")             # 0xffff0000
+    cut = lambda x: (x.view(torch.int32) & top).view(torch.float32)
+    low = torch.arange(n, dtype=torch.int32, device="cuda")
+    for block in range(1 << 6):
+        x = (low + (block - 32) * n).view(torch.float32)
+        x = torch.where(torch.isfinite(x), x, torch.zeros_like(x))
+        a = cut(x)
+        b = cut(x - a)
+        c = cut(x - a - b)
+        lg.lagom_comm_kernel(lg.LAGOM_REDUCE_COPY, lg.LAGOM_BF16, [v.to(torch.bfloat16) for v in (a, b, c)], [out], n, (256, 512, 64 << 10),
+                             torch.cuda.current_stream())
+        u = (a + b + c).view(torch.int32).long() & 0xFFFFFFFF
+        want = (u + 0x7FFF + ((u >> 16) & 1)) >> 16
+        assert torch.equal(out.view(torch.int16).long() & 0xFFFF, want), block
+
+
 # ------------------------------------------------------------- edges of the pipelined mover
 def _edge_counts(nt, units, chunk, esz):
     """Element counts at which a wavefront's walk begins, ends or is empty: around one 1 KiB unit, one round of the

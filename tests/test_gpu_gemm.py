@@ -31,6 +31,12 @@ def _gemm(a_bits, b_bits, b_is_nk, out):
     return oc.bf16_to_f32(c) if out == "bf16" else c
 
 
+def _tile(M, N, K):
+    """Tile of the kernel that a shape runs on."""
+    g = lg.lagom_gemm_describe(M, N, K)
+    return g.tile_m, g.tile_n
+
+
 @pytest.mark.parametrize("M,N,K", [(512, 512, 512), (1, 1, 8), (300, 200, 136), (700, 520, 264), (256, 256, 64),
                                    (257, 255, 72), (33, 1000, 4096), (130, 77, 128), (513, 260, 192), (700, 300, 320), (1000, 520, 256), (300, 300, 64),
                                    # more than 256 tiles of 128 x 128 but not of 256 x 128: the 256 x 128 kernels, ragged, 1 to 4 K-steps
@@ -38,7 +44,8 @@ def _gemm(a_bits, b_bits, b_is_nk, out):
                                    # more than 256 tiles of 256 x 128, or a K tail: the 256 x 256 kernels, ragged in M and N
                                    (2100, 3720, 192), (2100, 3720, 64), (2100, 3720, 136),
                                    # K tails on the two smaller tilings
-                                   (2312, 1800, 136), (1000, 520, 328)])
+                                   (2312, 1800, 136), (1200, 1288, 328),
+                                   (1000, 520, 328)])
 @pytest.mark.parametrize("b_is_nk", [True, False])
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_gemm_small_shapes(M, N, K, b_is_nk, out):
@@ -90,13 +97,15 @@ def test_gemm_integer_inputs_are_exact():
     assert np.array_equal(got.astype(np.int64), ai @ bi.T)
 
 
-@pytest.mark.parametrize("M,N,K", [(260, 272, 320), (100, 8, 64), (256, 776, 128), (513, 264, 192), (64, 1032, 576),
-                                   (2100, 2056, 128), (2304, 2312, 320), (2100, 3720, 128)])
+@pytest.mark.parametrize("M,N,K", [(260, 272, 320), (100, 8, 64), (256, 776, 128), (513, 264, 192), (64, 1032, 576),       # K split over wavefronts
+                                   (1200, 1288, 64), (1030, 1032, 128), (1201, 1480, 192), (1200, 1288, 320), (1153, 1800, 576),  # 128 x 128
+                                   (2100, 2056, 128), (2304, 2312, 320),                                                 # 256 x 128
+                                   (2100, 3720, 128)])                                                                   # 256 x 256
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_gemm_b_kn_integer_inputs_are_exact(M, N, K, out):
     """B stored [K,N] with K a multiple of 64 takes the kernel whose LDS reads transpose B: any mix-up of
-    rows, columns or k order shows as a wrong integer.  One to nine K-steps, ragged M and N tiles, N = 8; the
-    last three shapes run on 256 x 128 (two) and 256 x 256 tiles, the others on 128 x 128."""
+    rows, columns or k order shows as a wrong integer.  One to nine K-steps, ragged M and N tiles, N = 8."""
+    assert (_tile(M, N, K)[0] < 128) == (M * N < 1000 * 1000)
     rng = np.random.default_rng(M + N + K)
     ai = rng.integers(-3, 4, size=(M, K)); bi = rng.integers(-3, 4, size=(K, N))
     a, b = inputs.to_bf16_bits(ai.astype(np.float32)), inputs.to_bf16_bits(bi.astype(np.float32))
@@ -109,12 +118,12 @@ def test_gemm_b_kn_integer_inputs_are_exact(M, N, K, out):
 
 @pytest.mark.parametrize("K", [72, 96, 104, 120, 184, 4104])
 @pytest.mark.parametrize("b_is_nk", [True, False])
-@pytest.mark.parametrize("M,N", [(260, 272), (2100, 2056), (2100, 3720)])
-def test_gemm_ragged_k_integer_inputs_are_exact(K, b_is_nk, M, N):
-    """K >= 64 that is no multiple of 64: the LDS-direct kernels multiply the last K % 64 columns (8 to 56
-    of them, one or two 32-wide slices) in a step of their own, zero filled from K on.  The three shapes
-    run on 128 x 128, 256 x 128 and 256 x 256 tiles."""
-    if K == 4104 and M > 1000:
+@pytest.mark.parametrize("M,N,tile", [(260, 272, (16, 32)), (1200, 1288, (128, 128)), (2100, 2056, (256, 128)), (2100, 3720, (256, 256))])
+def test_gemm_ragged_k_integer_inputs_are_exact(K, b_is_nk, M, N, tile):
+    """K >= 64 that is no multiple of 64: the last step or slice of the LDS-direct kernels begins at column K - 64 and clears the
+    columns that the one before it has multiplied (8 to 56 are left of it, in one or two 32-wide MFMA slices)."""
+    assert _tile(M, N, K) == tile
+    if K == 4104 and M > 2000:
         pytest.skip("one long K is enough")
     rng = np.random.default_rng(K)
     ai = rng.integers(-3, 4, size=(M, K)); bi = rng.integers(-3, 4, size=(K, N))
@@ -124,20 +133,22 @@ def test_gemm_ragged_k_integer_inputs_are_exact(K, b_is_nk, M, N):
     assert np.array_equal(got.astype(np.int64), ai @ bi)
 
 
-def _random_shapes(n, seed):
+def _random_shapes(n, seed, rows, groups):
     rng = np.random.default_rng(seed)
     shapes = []
     for i in range(n):
-        M = int(rng.integers(1, 700)); N = 8 * int(rng.integers(1, 90))
+        M = int(rng.integers(*rows)); N = 8 * int(rng.integers(*groups))
         K = 64 * int(rng.integers(1, 7)) if i % 3 else 8 * int(rng.integers(1, 40))   # two in three on the LDS-direct kernels
         shapes.append((M, N, K))
     return shapes
 
 
+@pytest.mark.parametrize("n,rows,groups", [(24, (1, 700), (1, 90)),             # K split over wavefronts, and the general kernel
+                                           (12, (1030, 1600), (129, 220))])     # 128 x 128 tiles
 @pytest.mark.parametrize("b_is_nk", [True, False])
-def test_gemm_seeded_random_shapes(b_is_nk):
-    """24 seeded shapes with ragged tiles in M and N and one to six K-steps, both kernels of each layout."""
-    for n, (M, N, K) in enumerate(_random_shapes(24, 77)):
+def test_gemm_seeded_random_shapes(b_is_nk, n, rows, groups):
+    """Seeded shapes with ragged tiles in M and N and one to six K-steps."""
+    for n, (M, N, K) in enumerate(_random_shapes(n, 77, rows, groups)):
         a = inputs.normal_bf16(100 + n, (M, K))
         b = inputs.normal_bf16(200 + n, (N, K) if b_is_nk else (K, N))
         ref = og.gemm_f64(a, b, b_is_nk)
@@ -218,12 +229,13 @@ def test_gemm_last_round_in_quadrants_integer_inputs_are_exact(M, N, K, b_is_nk)
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
 
 
-@pytest.mark.parametrize("M,N", [(130, 136), (2100, 2056), (2100, 3720)])     # 128 x 128, 256 x 128 and 256 x 256 tiles
+@pytest.mark.parametrize("M,N,tile", [(130, 136, (16, 32)), (1200, 1288, (128, 128)), (2100, 2056, (256, 128)), (2100, 3720, (256, 256))])
 @pytest.mark.parametrize("K", [72, 120, 136, 200, 264, 328, 392, 456])       # two to eight steps, each peeled form of the loop
 @pytest.mark.parametrize("b_is_nk", [True, False])
-def test_gemm_columns_in_two_k_steps_count_once(M, N, K, b_is_nk):
+def test_gemm_columns_in_two_k_steps_count_once(M, N, tile, K, b_is_nk):
     """The last K-step begins at column K - 64, so it loads columns that the step before it has multiplied: those must
     neither count twice (exact integers) nor carry an infinity of theirs into zero times infinity."""
+    assert _tile(M, N, K) == tile
     rng = np.random.default_rng(M + K)
     a = rng.integers(-3, 4, size=(M, K)).astype(np.float32)
     b = rng.integers(-3, 4, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
