@@ -117,6 +117,7 @@ struct Acc<LAGOM_F32> {
     __device__ __forceinline__ void init(u32x4 v) { a = __builtin_bit_cast(f32x4, v); }
     __device__ __forceinline__ void add(u32x4 v) { a = a + __builtin_bit_cast(f32x4, v); }
     __device__ __forceinline__ u32x4 result() const { return __builtin_bit_cast(u32x4, a); }
+    __device__ __forceinline__ void before(uint32_t& x) const { asm volatile("" : "+v"(x) : "v"(a)); }
 };
 
 // bf16: one 16-byte vector = 8 elements, accumulated as 8 fp32
@@ -137,6 +138,7 @@ struct Acc<LAGOM_BF16> {
         for (int i = 0; i < 4; ++i) r[i] = bf16_round2(a[2 * i], a[2 * i + 1]);
         return r;
     }
+    __device__ __forceinline__ void before(uint32_t& x) const { asm volatile("" : "+v"(x) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7])); }
 };
 
 // One element of a short tail (fewer than 16 bytes left at the end of the buffer).
@@ -369,42 +371,62 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
     put(b0);
 }
 
-// Many sources: a unit's sources are loaded in two halves, and while one half is added the other (of this unit, then of
-// the next one) is in flight.  Half the registers of two whole units.
-template <int DT, int S, bool STREAM, class IO>
-__device__ __forceinline__ void move_halves(Walk<REDUCE> w, const IO& io, uint32_t lane) {
-    constexpr int SA = (S + 1) / 2, SB = S - SA;
+// Many sources: a unit's sources are loaded in NG groups, and while one group is added the NB - 1 behind it (of this unit, then
+// of the next one) are in flight.  The registers of NB groups.
+template <int DT, int S, int NG, int NB, bool STREAM, class IO>
+__device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32_t lane) {
+    static_assert(NG % NB == 0 && NB > 1, "a group's buffer is the same in every unit");
     w.first();
     if (!w.more) return;
     const uint32_t lo = lane * 16;
-    u32x4 a[SA], b[SB];
-    auto clamped = [&]() { const uint32_t l = w.limit(); return lo < l ? lo : l; };
-    uint32_t o = clamped();
+    u32x4 buf[NB][(S + NG - 1) / NG];
+    // The unit that is loaded: its offset in a buffer, and the lane's in it.  Kept, as the compiler otherwise looks for the walk's end
+    // in front of each load: 16 x 1000003 bf16 at (32, 256, 64 KiB) 18.6 -> 16.2 us.
+    int64_t at;
+    uint32_t o;
+    auto clamp = [&]() { const uint32_t l = w.limit(); at = w.offset(); o = lo < l ? lo : l; };
+    auto load = [&](auto g) {
+        constexpr int G = decltype(g)::value % NG, FROM = S * G / NG, N = S * (G + 1) / NG - FROM;
 #pragma unroll
-    for (int s = 0; s < SA; ++s) a[s] = ld16<STREAM>(io.from(w, s) + o);
-    while (w.more) {
+        for (int s = 0; s < N; ++s) buf[G % NB][s] = ld16<STREAM>(io.src(FROM + s) + at + o);
+    };
+    Acc<DT> acc;
+    auto add = [&](auto g) {
+        constexpr int G = decltype(g)::value, N = S * (G + 1) / NG - S * G / NG;
+        if (G == 0) acc.init(buf[0][0]);
 #pragma unroll
-        for (int s = 0; s < SB; ++s) b[s] = ld16<STREAM>(io.from(w, SA + s) + o);
-        const int64_t off = io.to(w);
-        const bool mine = lo <= w.limit();
-        Acc<DT> acc;
-        acc.init(a[0]);
-#pragma unroll
-        for (int s = 1; s < SA; ++s) acc.add(a[s]);
-        auto finish = [&]() {
-#pragma unroll
-            for (int s = 0; s < SB; ++s) acc.add(b[s]);
-            const u32x4 r = acc.result();
-            if (mine) {
-                st16(io.dst(0) + off + lo, r);
-                for (int d = 1; d < io.ndst; ++d) st16(io.dst(d) + off + lo, r);
-            }
-        };
-        w.next(1);
-        o = clamped();
-#pragma unroll
-        for (int s = 0; s < SA; ++s) a[s] = ld16<STREAM>(io.from(w, s) + o);     // behind the end: unused
-        finish();
+        for (int s = G == 0; s < N; ++s) acc.add(buf[G % NB][s]);
+    };
+    int64_t off;
+    bool mine;
+    auto pass = [&](auto g) {
+        constexpr int G = decltype(g)::value;
+        if (G + NB - 1 == NG) {                     // on to the next unit (behind the end: loads that nobody uses)
+            off = at;
+            mine = lo <= w.limit();
+            w.next(1);
+            clamp();
+        }
+        load(std::integral_constant<int, G + NB - 1>{});
+        add(g);
+        // Left alone, the compiler loads every group in front of the additions, into registers of its own: a later group's
+        // addresses are therefore made to depend on the sums so far.
+        if (NG > 2) acc.before(o);
+    };
+    clamp();
+    load(std::integral_constant<int, 0>{});
+    if constexpr (NB > 2) load(std::integral_constant<int, 1>{});
+    static_assert(NB <= 3 && (NG == 2 || NG == 3 || NG == 6), "as written out here");
+    for (bool more = true; more; more = w.more) {
+        pass(std::integral_constant<int, 0>{});
+        pass(std::integral_constant<int, 1>{});
+        if constexpr (NG > 2) pass(std::integral_constant<int, 2>{});
+        if constexpr (NG > 3) { pass(std::integral_constant<int, 3>{}); pass(std::integral_constant<int, 4>{}); pass(std::integral_constant<int, 5>{}); }
+        const u32x4 r = acc.result();
+        if (mine) {
+            st16(io.dst(0) + off + lo, r);
+            for (int d = 1; d < io.ndst; ++d) st16(io.dst(d) + off + lo, r);
+        }
     }
 }
 
@@ -443,16 +465,26 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
 // the wavefronts beside it.  A channel of up to kDeepNT threads (one wavefront per SIMD) may use them all; with more threads
 // the wavefronts of a SIMD share them, and their number keeps the memory pipeline busy instead.  One memory latency per batch, the previous form
 // -> this one, us (data in the last-level cache): 64 MiB gather-copy at (8, 256, 2 MiB) 138.5 -> 86.3; 12 MiB two-source fp32
-// reduce at (4, 256, 128 KiB) 55.1 -> 33.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 18.9 (there
-// one source at a time in flight before); a ring share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 65.3; 72 MiB
+// reduce at (4, 256, 128 KiB) 55.1 -> 33.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 16.2 (there
+// one source at a time in flight before); a ring share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 61.1; 72 MiB
 // eight-source reduce at (256, 512, 32 KiB) 13.6 -> 12.9.
 constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
-constexpr bool in_halves(int S, bool deep) { return deep ? S > 8 : S > 4; }
+// The groups of move_groups (0: whole units).  With more than 256 threads a SIMD may hold two wavefronts of a channel, which fit
+// beside a product with up to 56 registers each.  Two whole halves of nine sources and more do not, and the channel then keeps its
+// compute unit from the product: makespan of three such reduces of 2 MiB sources beside 4096^3, us, halves -> three or six groups of
+// which three are in flight: 9 fp32 sources at (32, 512, 64 KiB) 115 -> 93 ([N,K]), 117 -> 95 ([K,N]); 16 bf16 131 -> 95, 134 -> 96; 12
+// fp32 at (8, 384, 256 KiB) 186 -> 146, 187 -> 147.  Alone 0.8 to 1.0 of the time, 1.03 at worst (9 fp32 at (8, 384, 256 KiB)).
+constexpr int groups(int DT, int S, bool deep) {
+    if (S <= (deep ? 8 : 4)) return 0;
+    if (deep || S <= 8) return 2;
+    return S <= (DT == LAGOM_F32 ? 11 : 9) ? 3 : 6;         // that many sources fit at a time
+}
 
 template <int DT, int S, bool STREAM, bool DEEP, class IO>
 __device__ __forceinline__ void move_reduce(const Walk<REDUCE>& w, const IO& io, uint32_t lane) {
-    if constexpr (in_halves(S, DEEP)) move_halves<DT, S, STREAM>(w, io, lane);
+    constexpr int NG = groups(DT, S, DEEP);
+    if constexpr (NG > 0) move_groups<DT, S, NG, NG == 2 ? 2 : 3, STREAM>(w, io, lane);
     else move_batches<DT, S, units_in_batch(S, DEEP), STREAM, false>(w, io, lane);
 }
 
@@ -511,7 +543,7 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) gather_copy_kernel(cons
 template <int DT, bool STREAM, bool DEEP, int S>
 void launch_reduce_s(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
     if constexpr (S > LAGOM_MAX_SRCS) return;
-    else if (a.nsrc == S) hipLaunchKernelGGL((reduce_copy_kernel<DT, S, STREAM, DEEP && !(in_halves(S, true))>), grid, block, 0, st, a);
+    else if (a.nsrc == S) hipLaunchKernelGGL((reduce_copy_kernel<DT, S, STREAM, DEEP>), grid, block, 0, st, a);
     else launch_reduce_s<DT, STREAM, DEEP, S + 1>(a, grid, block, st);
 }
 template <int DT>

@@ -450,7 +450,7 @@ def _edge_counts(nt, units, chunk, esz):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("nt", [64, 256, 320, 1024])           # one wavefront; the deepest; the first shallow; the most wavefronts
-@pytest.mark.parametrize("nsrc", [1, 2, 4, 7, 8, 9, 16])       # 8, 4, 2 units in flight, one unit, in halves
+@pytest.mark.parametrize("nsrc", [1, 2, 4, 7, 8, 9, 14, 16])   # 8, 4, 2 units in flight, one unit, in halves, in quarters
 def test_reduce_copy_at_the_edges_of_its_batches(dtype, nt, nsrc):
     esz = 4 if dtype == "f32" else 2
     for chunk, nc in [(16384, 2), (48 * 1024 + 16, 3)]:
