@@ -279,7 +279,8 @@ int lagom_streams_overlap(void* stream_a, void* stream_b, int* overlap);
  * Sec. 3.2): for every configuration of a list, applied to all communications of
  * the group, time the communications alone, the computations alone (once), and both
  * together, and derive the communication's global-memory bandwidth V (Eq. 6).  The computations
- * alone are re-timed every eighth point (the clock held under load drifts over a long sweep).
+ * alone are re-timed every eighth point (the clock held under load drifts over a long sweep), each
+ * time behind 40 ms of them untimed (behind light load products run slow for 20 ms and more).
  */
 typedef struct {
     lagom_cfg cfg;

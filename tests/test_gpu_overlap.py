@@ -121,6 +121,24 @@ def test_contention_sweep_on_the_tiny_grid(tiny):
     assert pts[2].comm_alone_us < pts[0].comm_alone_us
 
 
+def test_sweep_reference_is_the_steady_state_behind_light_points(tiny):
+    """Behind eight points of one channel the chip's power control lets a large product run 7 - 25 % longer for 20 ms and more;
+    the time alone that the ninth point is held against is the steady one.  The steady time repeats to 1 - 1.5 % on one chip, and a
+    sweep without its own warm-up is 10 % and more above it."""
+    n = 8192
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    A, B = (torch.randn((n, n), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    out = torch.empty((n, n), dtype=torch.bfloat16, device="cuda")
+    x, y, r = (torch.zeros(1 << 23, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    torch.cuda.synchronize()
+    launches = [lg.CommLaunch(lg.LAGOM_REDUCE_COPY, lg.LAGOM_BF16, [x, y], [r], 1 << 23, 0)]
+    comps = [lg.GemmDesc(A, B, out, n, n, n)]
+    pts = lg.lagom_contention_sweep(launches, 1, comps, [(1, 256, 64 << 10)] * 9, tiny["s1"], tiny["s2"], 1, 7)
+    steady = lg.lagom_overlap_run(launches, [(1, 256, 64 << 10)], comps, tiny["s1"], tiny["s2"], 60, 20, lg.LAGOM_ALONE_COMP).Y_us
+    print(f"\nalone: behind light points {pts[8].comp_alone_us:.1f} us, at the start {pts[0].comp_alone_us:.1f}, steady {steady:.1f}")
+    assert pts[8].comp_alone_us == pytest.approx(steady, rel=0.04)
+
+
 def test_measured_priority_search_stays_on_the_ladder_and_is_linear(tiny):
     space = lg.Space([1, 2, 4, 8, 16, 32], [256], [32768 << i for i in range(8)])
     prof = lg.OverlapProfile(tiny["launches"], tiny["comps"], tiny["s1"], tiny["s2"], 1, 3)
