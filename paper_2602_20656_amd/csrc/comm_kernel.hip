@@ -658,7 +658,7 @@ void launch_steps(const StepsArgs& a, dim3 grid, dim3 block, hipStream_t st) {
 
 // ------------------------------------------------------------------ staged through LDS
 // The same operators with every source vector staged through LDS by direct-to-LDS loads (global_load_lds, 16 bytes per
-// lane), the form the brief for this build sketches.  Each wavefront owns a ring of LDS_STAGES stages of LDS_U KiB and
+// lane).  Each wavefront owns a ring of LDS_STAGES stages of LDS_U KiB and
 // treats (batch of LDS_U KiB of the chunk, source) pairs as a stream of items: the loads of the next LDS_STAGES - 1 items
 // are in flight while the current one is read back (ds_read_b128) and folded into the lane's accumulators, in source
 // order, so the arithmetic and its order are exactly those of the register path; after the last source the batch is

@@ -1169,8 +1169,9 @@ Tiling choose_tiling(int64_t M, int64_t N, int64_t K) {
     return TILE_256x256;
 }
 
-// The smallest tile that covers C in one round is the fastest here too, whatever it loads in all: a compute unit loads
-// about 130 GB/s of (rows + columns of a tile) x K.  us, 128 x 128 tiles -> 64 x 64 | 64 x 32 | 32 x 32 | 16 x 32:
+// The smallest tile that covers C in one round is the fastest here too, whatever it loads in all: a workgroup's time is that
+// of its own loads, (rows + columns of its tile) x K at 60 - 110 GB/s with the launch in it (what follows, divided), less the
+// more compute units load.  us, 128 x 128 tiles -> 64 x 64 | 64 x 32 | 32 x 32 | 16 x 32:
 //   33 x 1000 x 4096    23.6 -> 11.5 |  8.9 |  6.9 |  5.9 (96 workgroups)     256 x 256 x 8192   43.1 -> 18.7 | 17.7 | 13.0 | 10.9 (128)
 //   512 x 512 x 512      6.3 ->  5.6 |  4.7 |  4.1 (256) |  6.3               640 x 640 x 4096   24.5 -> 14.9 | 12.0 (200) | 18.0 | 28.0
 //   1024 x 1024 x 4096  25.1 -> 16.8 (256) | 26.8 | 43.8 | 77.1               40 x 8192 x 8192   42.9 -> 24.1 | 22.6 (256) | 27.4 | 31.0
