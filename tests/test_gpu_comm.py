@@ -496,6 +496,22 @@ def test_gather_copy_of_shards_off_the_vector_grid(dtype, nt, P):
                 assert same_bits(got, want), (count, nc)
 
 
+@pytest.mark.parametrize("nt", [64, 256, 320, 1024])
+@pytest.mark.parametrize("per_wave", [1, 2, 3, 4, 5, 8, 9])
+def test_gather_copy_with_few_units_to_a_wavefront(nt, per_wave):
+    """Chunks of one to nine units a wavefront, the last unit whole or one vector long: every number of units per batch, with
+    loads streamed (200 channels, 240 chunks) and not, shards on and off the 16-byte grid."""
+    for short in (0, 1008):
+        chunk = per_wave * (nt // 64) * 1024 - short
+        for nc, P, chunks in ((3, 2, 3), (200, 3, 80)):
+            if nc == 200 and chunk > 40 * 1024:
+                continue
+            for count in (chunks * chunk // 2, chunks * chunk // 2 - 3):
+                shards = _sources("bf16", P, count, 1300)
+                got = _run(lg.LAGOM_GATHER_COPY, "bf16", shards, 1, (nc, nt, chunk), P * count)[0]
+                assert same_bits(got, np.concatenate(shards)), (short, nc, count)
+
+
 @pytest.mark.parametrize("nt", [64, 512])
 @pytest.mark.parametrize("busy", [1, 127, 128, 150])
 def test_wide_launches_with_few_busy_channels(nt, busy):
