@@ -67,6 +67,7 @@ struct GemmArgs {
     void* C;
     int64_t M, N, K;
     int32_t tiles_m, tiles_n;
+    int32_t rows;               // of the blocks that the list of tiles runs through (tile_in_list); 0: the list in columns of 8, XCDs in turn
 };
 
 __device__ __forceinline__ uint32_t bf16_round_bits(float f) {
@@ -79,24 +80,22 @@ __device__ __forceinline__ uint32_t bf16_round_bits(float f) {
 // index (in 16-byte units) of group `cg` of row `row` in a swizzled [rows][8] tile
 __device__ __forceinline__ int swz(int row, int cg) { return row * 8 + (cg ^ (row & 7)); }
 
-// Workgroup id -> (tile_m, tile_n).  Hardware deals consecutive ids round-robin to the 8 XCDs;
-// id = x + 8*q is given the q-th tile of the x-th eighth of the tile list, and the list itself
-// runs down columns of 8 tile-rows so that neighbours share B panels and reuse A panels.
-__device__ __forceinline__ void tile_in_list(int lin, int tiles_m, int tiles_n, int* tm, int* tn) {
-    constexpr int GROUP = 8;
-    const int per_group = GROUP * tiles_n;
+// Workgroup id -> (tile_m, tile_n).  Hardware deals consecutive ids round-robin to the 8 XCDs: XCD x is given the x-th eighth
+// of the list of tiles, and the list runs down columns of `rows` tile-rows, so that what an XCD works on at a time is a block of
+// tiles that shares A and B panels in its L2.
+__device__ __forceinline__ void tile_in_list(int lin, int tiles_m, int tiles_n, int rows, int* tm, int* tn) {
+    const int per_group = rows * tiles_n;
     const int grp = lin / per_group;
-    const int first_m = grp * GROUP;
-    const int rows = tiles_m - first_m < GROUP ? tiles_m - first_m : GROUP;
+    const int first_m = grp * rows;
+    const int high = tiles_m - first_m < rows ? tiles_m - first_m : rows;
     const int in = lin - grp * per_group;
-    *tm = first_m + in % rows;
-    *tn = in / rows;
+    *tm = first_m + in % high;
+    *tn = in / high;
 }
-__device__ __forceinline__ void tile_of(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
-    const int total = tiles_m * tiles_n;
-    int lin = id;
-    if ((total & 7) == 0) lin = (id & 7) * (total >> 3) + (id >> 3);
-    tile_in_list(lin, tiles_m, tiles_n, tm, tn);
+__device__ __forceinline__ void tile_of(int id, const GemmArgs& p, int* tm, int* tn) {
+    const int total = p.tiles_m * p.tiles_n, x = id & 7, over = total & 7;
+    const int lin = p.rows ? x * (total >> 3) + (x < over ? x : over) + (id >> 3) : id;
+    tile_in_list(lin, p.tiles_m, p.tiles_n, p.rows ? p.rows : 8, tm, tn);
 }
 
 template <bool B_NK, bool OUT_BF16>
@@ -109,7 +108,7 @@ __global__ void __launch_bounds__(THREADS) gemm_bf16_general_kernel(const GemmAr
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     int tm, tn;
-    tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn);
+    tile_of(blockIdx.x, p, &tm, &tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int64_t M = p.M, N = p.N, K = p.K;
 
@@ -590,14 +589,14 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
 // K >= 64 and not a multiple of 64 (kernels of their own: the peeled last step clears fragments; as many registers)
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); fast_gemm_body<true, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- small-tile kernels
 // 128 x 128 x 64 and 256 x 128 x 64 tiles for products with too few 256 x 256 tiles to fill the chip.
@@ -872,23 +871,23 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, false, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, true, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, true, OUT_BF16, false>(p, tm, tn); }
 // 256 x 128 tiles
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, false, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, true, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, OUT_BF16, false>(p, tm, tn); }
 // K >= 64 and not a multiple of 64
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, false, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<4, true, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, true, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, false, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p.tiles_m, p.tiles_n, &tm, &tn); small_gemm_body<8, true, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, OUT_BF16, true>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- large tiles, the last round in small ones
 // A product of more than 256 large tiles runs in rounds of 256 (one per compute unit), and the last round costs as much
@@ -913,7 +912,7 @@ __device__ __forceinline__ void mixed_gemm_body(const MixedArgs& p) {
     const int lin = large ? x * (p.nlarge >> 3) + (id >> 3) : p.nlarge + x * p.per_xcd + (j >> 2);
     const int inside = p.full_m * p.full_n, right = p.full_m * (p.g.tiles_n - p.full_n);
     int tm, tn;
-    if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, &tm, &tn);
+    if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, 8, &tm, &tn);
     else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
     else { tm = p.full_m; tn = lin - inside - right; }
     if (large) {
@@ -959,20 +958,32 @@ template <int NJ> __device__ __forceinline__ int kn_swz_split(int k) {
     return NJ == 4 ? (((k >> 3) & 1) << 2) | (((k >> 1) & 1) << 1) : ((k >> 3) & 1) << 1;
 }
 
+// tile_of() of at most 256 tiles.  A product of 4 us feels two divisions (0.1 us of 512 x 512 x 512): they are multiplications by
+// 2^32 / divisor, rounded up, exact as long as dividend x divisor is below 2^32.
+struct SplitOrder {
+    uint32_t rows, per_group, last;        // tile-rows of a group, its tiles, tile-rows of the last group
+    uint32_t by_group, by_rows, by_last;
+};
+__device__ __forceinline__ void tile_of(uint32_t id, const GemmArgs& p, const SplitOrder& o, int* tm, int* tn) {
+    const uint32_t total = p.tiles_m * p.tiles_n, x = id & 7, over = total & 7;
+    const uint32_t lin = x * (total >> 3) + (x < over ? x : over) + (id >> 3);
+    const uint32_t grp = o.per_group > 1 ? __umulhi(lin, o.by_group) : lin, in = lin - grp * o.per_group;
+    const bool last = (grp + 1) * o.rows >= (uint32_t)p.tiles_m;
+    const uint32_t high = last ? o.last : o.rows, col = high > 1 ? __umulhi(in, last ? o.by_last : o.by_rows) : in;
+    *tm = grp * o.rows + in - col * high;
+    *tn = col;
+}
+
 template <class T, bool B_KN, bool K_TAIL>
-__global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const GemmArgs p, const int out_bf16) {
+__global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const GemmArgs p, const SplitOrder order, const int out_bf16) {
     constexpr int MI = T::MI_, NJ = T::NJ_, WAVES = T::WAVES, SETS = T::SETS, LA = T::LA, LB = T::LB;
     static_assert(!B_KN || NJ == 2 || NJ == 4, "the [K,N] swizzle is for rows of 64 or 128 bytes");
     extern __shared__ u32x4 smem[];            // [wavefront][set][rows of A, B]; then [wavefront][ITEMS]
     __builtin_amdgcn_s_setprio(3);
     const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, r = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // XCD x takes the x-th eighth of the tiles, neighbours along the shorter side of C first: they share the longer panels
-    const int tiles = p.tiles_m * p.tiles_n, lin = (blockIdx.x & 7) * ((tiles + 7) >> 3) + (blockIdx.x >> 3);
-    if (lin >= tiles) return;
-    const bool m_first = p.tiles_m <= p.tiles_n;
-    const int inner = m_first ? p.tiles_m : p.tiles_n;
-    const int tm = m_first ? lin % inner : lin / inner, tn = m_first ? lin / inner : lin % inner;
+    int tm, tn;
+    tile_of(blockIdx.x, p, order, &tm, &tn);
     const int64_t m0 = (int64_t)tm * T::TM, n0 = (int64_t)tn * T::TN, M = p.M, N = p.N, K = p.K;
 
     const int slices = (int)((K + BK - 1) / BK);
@@ -1138,12 +1149,49 @@ int launch_fast(const ARGS& a, dim3 grid, hipStream_t st) {
     return LAGOM_OK;
 }
 
+// The block of tiles that an XCD works on at a time: n tiles, near to square in rows of A and of B; `rows` of them is the height of
+// the list's groups, all of (nearly) one height.  (A product of few tile-columns: whole tile-rows, rows = 1.)
+struct Block { int32_t rows; int64_t high, across; };
+Block block_of(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n, int64_t n) {
+    const int64_t square = n * tile_n / tile_m;
+    int64_t rows = 1;
+    while (rows * (rows + 1) < square) ++rows;          // to the nearest of the square root
+    if (rows * tiles_n < n) return {1, (n + tiles_n - 1) / tiles_n, tiles_n};
+    const int64_t groups = (tiles_m + rows / 2) / rows;
+    rows = groups > 1 ? (tiles_m + groups - 1) / groups : tiles_m;
+    const int64_t high = rows < n ? rows : n;
+    return {(int32_t)rows, high, (n + high - 1) / high};
+}
+// Up to this K what two XCDs both read is too little to matter, and the orders are the previous ones: columns of 8, dealt out to the
+// XCDs only where their number is a multiple of 8, and for split products the shorter side of C first.  us, those orders -> blocks:
+// split into 64 x 64 tiles 1024 x 1024 x 512 6.4 -> 6.3, x 1024 8.3 -> 7.6, x 4096 16.8 -> 15.2; 512 x 512 x 512 4.20 -> 4.20, x 4096 9.6 -> 8.9;
+// 384 x 512 x 7040 13.7 -> 12.8; 128 x 128 tiles 170 x 6953 x 1448 17.3 -> 16.0.
+constexpr int64_t kShortK = 512;
+int64_t at_a_time(int64_t tiles) { return tiles < 32 * 8 ? (tiles + 7) / 8 : 32; }      // tiles an XCD's 32 compute units work on
+Block tile_block(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n, int64_t K) {
+    const int64_t tiles = tiles_m * tiles_n, n = at_a_time(tiles);
+    if (K > kShortK && (tiles % 8 || tile_m != tile_n)) return block_of(tiles_m, tiles_n, tile_m, tile_n, n);
+    if (tiles % 8) return {0, 1, n};
+    const int64_t high = tiles_m < 8 ? tiles_m < n ? tiles_m : n : 8 < n ? 8 : n;
+    return {8, high, (n + high - 1) / high};
+}
+Block split_block(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n, int64_t K) {
+    const int64_t n = at_a_time(tiles_m * tiles_n);
+    if (K > kShortK) return block_of(tiles_m, tiles_n, tile_m, tile_n, n);
+    const bool m_first = tiles_m <= tiles_n;
+    const int64_t inner = m_first ? tiles_m : tiles_n, in = inner < n ? inner : n, across = (n + in - 1) / in;
+    return {(int32_t)(m_first ? tiles_m : 1), m_first ? in : across, m_first ? across : in};
+}
+
 template <class T, bool B_KN, bool K_TAIL>
 int launch_split_kernel(const GemmArgs& a, bool out_bf16, hipStream_t st) {
     constexpr auto kernel = gemm_bf16_split_kernel<T, B_KN, K_TAIL>;
     if (int rc = allow_lds<kernel>()) return rc;
-    const dim3 grid((unsigned)(((int64_t)a.tiles_m * a.tiles_n + 7) / 8 * 8));
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * T::WAVES), T::LDS_BYTES, st, a, out_bf16 ? 1 : 0);
+    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
+    const uint32_t rows = (uint32_t)split_block(a.tiles_m, a.tiles_n, T::TM, T::TN, a.K).rows, last = (uint32_t)a.tiles_m - (uint32_t)(a.tiles_m - 1) / rows * rows;
+    auto by = [](uint32_t d) { return (uint32_t)(((uint64_t{1} << 32) + d - 1) / d); };        // 2^32 does not fit: not used for d = 1
+    const SplitOrder order{rows, rows * (uint32_t)a.tiles_n, last, by(rows * (uint32_t)a.tiles_n), by(rows), by(last)};
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * T::WAVES), T::LDS_BYTES, st, a, order, out_bf16 ? 1 : 0);
     return LAGOM_OK;
 }
 template <class T>
@@ -1246,10 +1294,8 @@ extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype 
         out->mu = tm * tn;
         out->tile_m = split.tm; out->tile_n = split.tn; out->threads = split.threads;
         out->d_bytes = loads(split.tm, split.tn) + (double)split.tm * split.tn * out_bytes;
-        // an XCD takes an eighth of the tiles, along the shorter side of C first
-        const int64_t n = (out->mu + 7) / 8, inner = tm <= tn ? tm : tn, in = inner < n ? inner : n, across = (n + in - 1) / in;
-        const int64_t rows = tm <= tn ? in : across, cols = tm <= tn ? across : in;
-        out->d_bytes_past_l2 = loads(rows * split.tm, cols * split.tn) / (double)n + (double)split.tm * split.tn * out_bytes;
+        const Block block = split_block(tm, tn, split.tm, split.tn, K);
+        out->d_bytes_past_l2 = loads(block.high * split.tm, block.across * split.tn) / (double)at_a_time(out->mu) + (double)split.tm * split.tn * out_bytes;
         return LAGOM_OK;
     }
     const Tiling tiling = choose_tiling(M, N, K);
@@ -1259,24 +1305,13 @@ extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype 
     out->d_bytes = loads(bm, bn) + (double)bm * bn * out_bytes;
     out->tile_m = (int32_t)bm; out->tile_n = (int32_t)bn; out->threads = THREADS;
     const bool may_cut = tiling == TILE_256x256 && K >= BK && K <= FAST_MAX_K && M <= kMaxDim && N <= kMaxDim;
-    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn};
+    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn, 8};
     MixedArgs mixed;
     const int quadrants = may_cut ? choose_mixed(a, &mixed) : 0;
-    // the block of tiles an XCD works on at a time under tile_of() (32 compute units per XCD): n tiles in
-    // r tile-rows and c tile-columns need r A panels and c B panels between them
-    const int64_t total = tm * tn;
-    int64_t n, rows, cols;
-    if (total % 8 == 0 || quadrants) {
-        n = total / 8 < 32 ? total / 8 : 32;
-        rows = tm < 8 ? tm : 8;
-        if (rows > n) rows = n;
-        cols = (n + rows - 1) / rows;
-    } else {   // ids are not remapped: an XCD holds every eighth tile of the column-of-8 order
-        n = (total + 7) / 8 < 32 ? (total + 7) / 8 : 32;
-        rows = 1;
-        cols = n;
-    }
-    out->d_bytes_past_l2 = loads(rows * bm, cols * bn) / (double)n + (double)bm * bn * out_bytes;
+    // the block of tiles an XCD works on at a time (32 compute units per XCD): n tiles in r tile-rows and c tile-columns need
+    // r A panels and c B panels between them
+    const Block block = quadrants ? Block{8, tm < 8 ? tm : 8, (32 + (tm < 8 ? tm : 8) - 1) / (tm < 8 ? tm : 8)} : tile_block(tm, tn, bm, bn, K);
+    out->d_bytes_past_l2 = loads(block.high * bm, block.across * bn) / (double)at_a_time(tm * tn) + (double)bm * bn * out_bytes;
     if (quadrants) {   // means over the large tiles and the quadrants that hold something; the four of a tile share its panels
         const double quadrant_out = (double)SBM * SBN * out_bytes;
         out->mu = mixed.nlarge + quadrants;
@@ -1293,7 +1328,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (!b_is_nk && (N % 8)) return lagom::fail(LAGOM_EINVAL, "B stored [K,N] needs N to be a multiple of 8");
     const Tiling tiling = choose_tiling(M, N, K);
     if (const Split split = choose_split(M, N, K); split.launch) {
-        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0};
+        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0, 0};
         if (int rc = split.launch(a, b_is_nk != 0, out_dt == LAGOM_BF16, static_cast<hipStream_t>(hip_stream))) return rc;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "gemm launch: %s", hipGetErrorString(e));
@@ -1302,7 +1337,8 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (tiling != TILE_256x256) {
         const int bm = tiling == TILE_128x128 ? SBM : MBM;
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN)};
+                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0};
+        a.rows = tile_block(a.tiles_m, a.tiles_n, bm, SBN, K).rows;
         const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         const bool bf = out_dt == LAGOM_BF16;
@@ -1323,7 +1359,8 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         return LAGOM_OK;
     }
     GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-               (int32_t)((M + BM - 1) / BM), (int32_t)((N + BN - 1) / BN)};
+               (int32_t)((M + BM - 1) / BM), (int32_t)((N + BN - 1) / BN), 0};
+    a.rows = tile_block(a.tiles_m, a.tiles_n, BM, BN, K).rows;
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > (1 << 30)) return lagom::fail(LAGOM_EINVAL, "too many tiles");
     hipStream_t st = static_cast<hipStream_t>(hip_stream);

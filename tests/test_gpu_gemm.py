@@ -213,6 +213,26 @@ def test_gemm_more_tiles_than_compute_units_integer_inputs_are_exact(M, N, K, b_
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]} (tile {bad[0][0] // 256}, {bad[0][1] // 256})"
 
 
+@pytest.mark.parametrize("M,N,tile", [
+    (20, 30, (16, 32)), (250, 250, (16, 32)), (1000, 100, (16, 32)),        # fewer tiles than XCDs; 16 x 8; 63 x 4
+    (500, 500, (32, 32)), (2500, 80, (32, 32)),                             # 16 x 16; 79 x 3: whole tile-rows
+    (5400, 90, (64, 32)), (650, 600, (64, 32)), (90, 5400, (32, 64)),       # 85 x 3; 11 x 19; 3 x 85
+    (1000, 960, (64, 64)),                                                  # 16 x 15, a last group of another height
+    (1200, 1288, (128, 128)), (2100, 2056, (256, 128)), (2100, 3720, (256, 256))])      # 110, 153 and 135 tiles: no multiples of 8
+@pytest.mark.parametrize("b_is_nk", [True, False])
+def test_gemm_blocks_of_tiles_integer_inputs_are_exact(M, N, tile, b_is_nk):
+    """Above K = 512 the list of tiles runs through near-square blocks: every tile is taken once."""
+    K = 520
+    if not b_is_nk:
+        N = (N + 7) // 8 * 8
+    assert _tile(M, N, K) == tile
+    rng = np.random.default_rng(M + N)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+    got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
+    assert np.array_equal(got, a @ (b.T if b_is_nk else b))
+
+
 @pytest.mark.parametrize("M,N", [(3970, 4456),     # 16 x 18 tiles, 255 inside: an edge tile among the large ones
                                  (4096, 6144),     # two rounds of quadrants, none empty
                                  (4096, 6400),     # more than two rounds: large tiles only

@@ -82,6 +82,21 @@ def test_geometry_of_a_product_with_k_split_over_wavefronts(M, N, K, tile, mu, t
     assert g.d_bytes_past_l2 == (block[0] * tile[0] + block[1] * tile[1]) * K * 2 / -(-mu // 8) + out
 
 
+@pytest.mark.parametrize("M,N,K,tile,n,block", [
+    (1024, 1024, 576, (64, 64), 32, (6, 6)),          # 16 x 16 tiles in groups of 6, 6 and 4 rows, 32 of them at a time
+    (512, 512, 576, (32, 32), 32, (6, 6)),
+    (640, 640, 4096, (64, 32), 25, (4, 7)),           # 10 x 20
+    (5400, 90, 576, (64, 32), 32, (11, 3)),           # three tile-columns: whole tile-rows
+    (1152, 1280, 576, (128, 128), 12, (3, 4)),        # 90 tiles, no multiple of 8
+    (1024, 4096, 576, (128, 128), 32, (8, 4)),        # 256 tiles: columns of 8 as ever
+    (2048, 4096, 576, (256, 128), 32, (4, 8)),        # tiles twice as high as wide
+    (2100, 3720, 576, (256, 256), 17, (5, 4))])       # 9 x 15 = 135 tiles in groups of 5 and 4 rows
+def test_geometry_of_the_block_of_tiles_that_an_xcd_works_on_from_k_above_512(M, N, K, tile, n, block):
+    g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
+    assert (g.tile_m, g.tile_n) == tile
+    assert g.d_bytes_past_l2 == (block[0] * tile[0] + block[1] * tile[1]) * K * 2 / n + tile[0] * tile[1] * 4
+
+
 def test_geometry_where_k_is_not_split():
     """K too short for the tile, or one tile more than a round holds."""
     for M, N, K in [(640, 640, 64), (1024, 1024, 256), (1025, 1024, 4096)]:
