@@ -148,7 +148,8 @@ int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
  * What is left over behind whole rounds of 256 tiles of 256 x 256 runs as 128 x 128 quadrants where
  * they take at most two rounds ([K,N] with N > 2^23 apart): then mu counts the large tiles and the
  * quadrants that hold something, D and d_bytes_past_l2 are means over them, and tile_m x tile_n is the
- * large tile.  Host only. */
+ * large tile.  (Where it fits one round of 64 x 64 pieces and K > 256 a quadrant is up to four workgroups;
+ * it is counted as one, for it takes the time of one round either way.)  Host only. */
 typedef struct {
     int64_t mu;
     int32_t tb;

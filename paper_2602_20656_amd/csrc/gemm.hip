@@ -975,15 +975,13 @@ __device__ __forceinline__ void tile_of(uint32_t id, const GemmArgs& p, const Sp
 }
 
 template <class T, bool B_KN, bool K_TAIL>
-__global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const GemmArgs p, const SplitOrder order, const int out_bf16) {
+__device__ __forceinline__ void split_gemm_body(const GemmArgs& p, int tm, int tn, bool out_bf16) {
     constexpr int MI = T::MI_, NJ = T::NJ_, WAVES = T::WAVES, SETS = T::SETS, LA = T::LA, LB = T::LB;
     static_assert(!B_KN || NJ == 2 || NJ == 4, "the [K,N] swizzle is for rows of 64 or 128 bytes");
     extern __shared__ u32x4 smem[];            // [wavefront][set][rows of A, B]; then [wavefront][ITEMS]
     __builtin_amdgcn_s_setprio(3);
     const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, r = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int tm, tn;
-    tile_of(blockIdx.x, p, order, &tm, &tn);
     const int64_t m0 = (int64_t)tm * T::TM, n0 = (int64_t)tn * T::TN, M = p.M, N = p.N, K = p.K;
 
     const int slices = (int)((K + BK - 1) / BK);
@@ -1124,6 +1122,70 @@ __global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const Ge
         }
     }
 }
+
+template <class T, bool B_KN, bool K_TAIL>
+__global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const GemmArgs p, const SplitOrder order, const int out_bf16) {
+    int tm, tn;
+    tile_of(blockIdx.x, p, order, &tm, &tn);
+    split_gemm_body<T, B_KN, K_TAIL>(p, tm, tn, out_bf16 != 0);
+}
+
+// ------------------------------------------------------------------------- large tiles, the last round in split pieces
+// As above with 64 x 64 pieces of the left-over tiles, K split over a workgroup's wavefronts: where few tiles are left over, their
+// quadrants occupy a part of the chip and each is bound by what one compute unit loads.  The pieces inside C are numbered without
+// gaps: a tile at the edge may hold few of them.
+typedef SplitTile<4, 4, 4, 2> Piece;
+struct PiecesArgs {
+    GemmArgs g;                 // tiles_m, tiles_n: 256 x 256
+    int32_t full_m, full_n;     // tiles inside C altogether
+    int32_t nlarge;             // a multiple of 256
+    int32_t edge_m, edge_n;     // pieces across a tile that C's lower, right edge cuts through
+    int32_t inside, right;      // pieces of the tiles left over inside C and at its right edge; the lower edge's follow
+    int32_t first_right, first_low;     // tiles of either edge among the large ones
+    int32_t pieces;
+};
+constexpr int kPiecesAcross = BM / Piece::TM;
+
+template <bool B_KN, bool OUT_BF16, bool K_TAIL>
+__device__ __forceinline__ void pieces_gemm_body(const PiecesArgs& p) {
+    static_assert(64 * Piece::WAVES == THREADS && BM == BN && Piece::TM == Piece::TN, "pieces and large tiles in one launch");
+    const int id = blockIdx.x, x = id & 7;
+    if (id < p.nlarge) {
+        const int lin = x * (p.nlarge >> 3) + (id >> 3), inside = p.full_m * p.full_n, right = p.full_m * (p.g.tiles_n - p.full_n);
+        int tm, tn;
+        if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, 8, &tm, &tn);
+        else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
+        else { tm = p.full_m; tn = lin - inside - right; }
+        fast_gemm_body<B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
+        return;
+    }
+    constexpr int A = kPiecesAcross;
+    const int over = p.pieces & 7;
+    int j = x * (p.pieces >> 3) + (x < over ? x : over) + ((id - p.nlarge) >> 3);
+    int tm, tn;
+    if (j < p.inside) {
+        tile_in_list(p.nlarge + j / (A * A), p.full_m, p.full_n, 8, &tm, &tn);
+        tm = tm * A + j % A;
+        tn = tn * A + j / A % A;
+    } else if ((j -= p.inside) < p.right) {             // down the strip, then across
+        const int rows = (p.full_m - p.first_right) * A;
+        tm = p.first_right * A + j % rows;
+        tn = p.full_n * A + j / rows;
+    } else {                                            // along the strip, edge_m pieces high
+        j -= p.right;
+        tm = p.full_m * A + j % p.edge_m;
+        tn = p.first_low * A + j / p.edge_m;
+    }
+    split_gemm_body<Piece, B_KN, K_TAIL>(p.g, tm, tn, OUT_BF16);
+}
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_pieces_kernel(const PiecesArgs p) { pieces_gemm_body<false, OUT_BF16, false>(p); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_pieces_kernel(const PiecesArgs p) { pieces_gemm_body<true, OUT_BF16, false>(p); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_pieces_tail_kernel(const PiecesArgs p) { pieces_gemm_body<false, OUT_BF16, true>(p); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_pieces_tail_kernel(const PiecesArgs p) { pieces_gemm_body<true, OUT_BF16, true>(p); }
 
 // Lets a kernel have a compute unit's whole LDS: set once per kernel (and per device: a process may drive several); a
 // failure is not remembered.
@@ -1266,6 +1328,35 @@ int choose_mixed(const GemmArgs& g, MixedArgs* out) {
     return quadrants;
 }
 
+// Whether what is left over fits one round of pieces, and how.  A round of quadrants takes 0.39 of one of large tiles, one of pieces
+// 0.2 - 0.25 however few they are.  us, quadrants -> pieces: 4096 x 4352 x 4096 (256 pieces) 111.3 -> 102.3, x 512 24.1 -> 23.6, [K,N] x 1024 37.6
+// -> 35.2; 4352 x 4096 x 2048 [K,N] fp32 70.6 -> 64.9; 4100 x 4200 x 2056 (194) 75.7 -> 70.8, [K,N] fp32 80.9 -> 77.8; 4153 x 7768 x 3384 [K,N]
+// 187 -> 180.  As for a product of its own, 64 x 64 pieces need more than four slices of K: 4100 x 4200 x 320 22.5 -> 22.3.
+bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
+    const int rest = (int)(tiles % kRound);
+    if (g.K <= 4 * BK || tiles <= kRound || rest == 0) return false;
+    PiecesArgs a{g, (int32_t)(g.M / BM), (int32_t)(g.N / BN), (int32_t)(tiles - rest), 0, 0, 0, 0, 0, 0, 0};
+    auto across = [](int64_t size, int64_t tile) { return (int32_t)((size % tile + Piece::TM - 1) / Piece::TM); };
+    a.edge_m = across(g.M, BM);
+    a.edge_n = across(g.N, BN);
+    const int64_t inside = (int64_t)a.full_m * a.full_n, right = (int64_t)a.full_m * (g.tiles_n - a.full_n);
+    const int64_t in_right = a.nlarge - inside, in_low = in_right - right;       // large tiles behind those inside, behind those at the right
+    a.first_right = (int32_t)(in_right > 0 ? in_right < right ? in_right : right : 0);
+    a.first_low = (int32_t)(in_low > 0 ? in_low : 0);
+    const int64_t n_inside = in_right < 0 ? -in_right * kPiecesAcross * kPiecesAcross : 0;
+    const int64_t n_right = (right - a.first_right) * kPiecesAcross * a.edge_n;
+    int64_t n_low = 0;                                   // the lower edge's tiles, the corner last
+    if (g.tiles_m > a.full_m) {
+        const int64_t cols = (int64_t)a.full_n * kPiecesAcross + a.edge_n;
+        n_low = (cols - (int64_t)a.first_low * kPiecesAcross) * a.edge_m;
+    }
+    if (n_inside + n_right + n_low > kRound) return false;
+    a.inside = (int32_t)n_inside; a.right = (int32_t)n_right; a.pieces = (int32_t)(n_inside + n_right + n_low);
+    *out = a;
+    return true;
+}
+
 constexpr int64_t kMaxDim = 1 << 24;
 
 }  // namespace
@@ -1368,7 +1459,17 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     const bool bf = out_dt == LAGOM_BF16;
     const bool fast = K >= BK && K <= FAST_MAX_K && (b_is_nk || N <= FAST_MAX_N_KN);
     MixedArgs mixed;
-    if (fast && choose_mixed(a, &mixed)) {
+    PiecesArgs pieces;
+    if (fast && choose_pieces(a, &pieces)) {
+        const dim3 both((unsigned)(pieces.nlarge + pieces.pieces));
+        const bool tail = K % BK != 0;
+        int rc;
+#define LAGOM_PICK(NAME) (bf ? launch_fast<NAME<true>>(pieces, both, st) : launch_fast<NAME<false>>(pieces, both, st))
+        if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk_pieces_tail_kernel) : LAGOM_PICK(gemm_bf16_nk_pieces_kernel);
+        else rc = tail ? LAGOM_PICK(gemm_bf16_kn_pieces_tail_kernel) : LAGOM_PICK(gemm_bf16_kn_pieces_kernel);
+#undef LAGOM_PICK
+        if (rc) return rc;
+    } else if (fast && choose_mixed(a, &mixed)) {
         const dim3 both((unsigned)(mixed.nlarge + 32 * mixed.per_xcd));
         const bool tail = K % BK != 0;
         int rc;

@@ -172,3 +172,28 @@ def test_both_bodies_of_a_mixed_kernel_keep_their_accumulators(assembly, name):
                     assert not has_mfma and not falls_in and l.startswith(("v_accvgpr_mov_b32", "v_accvgpr_write_b32")), l
         start = nop + 3
     assert not any(l.startswith("v_mfma") for l in lines[start:])
+
+
+PIECES = tuple("gemm_bf16_%s_pieces%s_kernelILb%dE" % (k, t, o) for k in ("nk", "kn") for t in ("", "_tail") for o in (1, 0))
+
+
+@pytest.mark.parametrize("name", PIECES)
+def test_large_body_of_a_kernel_with_split_pieces_keeps_its_accumulators(assembly, name):
+    """The pieces' MFMAs are the compiler's own, in a body of their own."""
+    sym, _ = _body(assembly, name)
+    start = assembly.index("\n" + sym + ":")
+    lines = [l.split(";")[0].strip() for l in assembly[start:assembly.index(".Lfunc_end", start)].splitlines()[2:]]
+    lines = [l for l in lines if l]
+    meta = _metadata(assembly, sym)
+    assert meta["vgpr_spill_count"] == "0" and meta["sgpr_spill_count"] == "0" and meta["private_segment_fixed_size"] == "0", meta
+    waits = [i for i in range(len(lines) - 2) if all(l.startswith("s_nop 7") for l in lines[i:i + 3])]
+    assert len(waits) == 1
+    begin = max(i for i in range(waits[0]) if lines[i].startswith("s_setprio"))          # either body begins with it
+    first = next(i for i in range(begin, waits[0]) if lines[i].startswith("v_mfma"))
+    blocks = _blocks(lines[first:waits[0]])
+    assert sum(l.startswith("v_mfma") for _, b in blocks for l in b) >= 3 * 128
+    for falls_in, block in blocks:
+        has_mfma = any(l.startswith("v_mfma") for l in block)
+        for l in block:
+            if not l.startswith("v_mfma_f32_16x16x32_bf16") and AGPR.search(l):
+                assert not has_mfma and not falls_in and l.startswith(("v_accvgpr_mov_b32", "v_accvgpr_write_b32")), l

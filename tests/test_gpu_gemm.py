@@ -249,6 +249,24 @@ def test_gemm_last_round_in_quadrants_integer_inputs_are_exact(M, N, K, b_is_nk)
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
 
 
+@pytest.mark.parametrize("M,N", [(4100, 4200),     # 17 + 16 tiles at two edges left over: 194 pieces, most of the tiles' empty
+                                 (4096, 4352),     # 16 whole tiles, 256 pieces
+                                 (4352, 7704),     # one row of tiles behind two rounds, pieces 24 columns wide at its end
+                                 (130, 66000), (66000, 136),     # no tile inside C
+                                 (4096, 4357)])    # 5 columns of the last pieces, rows off the 16-byte grid
+@pytest.mark.parametrize("K", [264, 320])
+@pytest.mark.parametrize("b_is_nk", [True, False])
+def test_gemm_last_round_in_pieces_integer_inputs_are_exact(M, N, K, b_is_nk):
+    if not b_is_nk and N % 8:
+        pytest.skip("[K,N] layout needs N % 8 == 0")
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+    got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
+    bad = np.argwhere(got != (a @ (b.T if b_is_nk else b)))
+    assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
+
+
 @pytest.mark.parametrize("M,N,tile", [(130, 136, (16, 32)), (1200, 1288, (128, 128)), (2100, 2056, (256, 128)), (2100, 3720, (256, 256))])
 @pytest.mark.parametrize("K", [72, 120, 136, 200, 264, 328, 392, 456])       # two to eight steps, each peeled form of the loop
 @pytest.mark.parametrize("b_is_nk", [True, False])
