@@ -68,6 +68,7 @@ struct GemmArgs {
     int64_t M, N, K;
     int32_t tiles_m, tiles_n;
     int32_t rows;               // of the blocks that the list of tiles runs through (tile_in_list); 0: the list in columns of 8, XCDs in turn
+    int32_t cached;             // how C is stored (store_c)
 };
 
 __device__ __forceinline__ uint32_t bf16_round_bits(float f) {
@@ -266,6 +267,19 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
             if (OUT_BF16) reinterpret_cast<uint16_t*>(out)[k] = (uint16_t)(val[k >> 1] >> (16 * (k & 1)));
             else reinterpret_cast<uint32_t*>(out)[k] = val[k];
         }
+}
+
+// 16 bytes of a row of C on the 16-byte grid, past the L2s or into them (a rule of the sizes: cached_stores).  (Empty asm on both
+// sides: the compiler otherwise makes one store of the two, without the hint.  One choice for eight stores or for the whole epilogue
+// is no faster in the large tiles, up to 1 % slower.)
+__device__ __forceinline__ void store_c(char* out, u32x4 val, bool cached) {
+    if (cached) {
+        asm volatile("" ::: "memory");
+        *reinterpret_cast<u32x4*>(out) = val;
+        asm volatile("" ::: "memory");
+    } else {
+        __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(out));
+    }
 }
 
 // Clears an operand fragment in the lanes that do not keep theirs.
@@ -541,7 +555,7 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     const int r_in = lane & 15, c_q = 4 * (lane >> 4);
     char* st = reinterpret_cast<char*>(smem) + wave * SLOT_BYTES;
     const bool interior = m0 + BM <= M && n0 + BN <= N;
-    const bool vector_ok = (N % VEC) == 0;
+    const bool vector_ok = (N % VEC) == 0, cached = p.cached != 0;
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
     const int64_t gcol = n0 + wn * 128 + rd_cv * VEC;
 #pragma unroll
@@ -579,7 +593,7 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
                 const int64_t grow = row0 + ROWS_PER_READ * (tb * 8 + e);
                 char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
                 if (vector_ok) {
-                    if (interior || (grow < M && gcol < N)) __builtin_nontemporal_store(val[e], reinterpret_cast<u32x4*>(out));
+                    if (interior || (grow < M && gcol < N)) store_c(out, val[e], cached);
                 } else if (grow < M) {
                     store_ragged<OUT_BF16>(out, val[e], N - gcol);
                 }
@@ -852,7 +866,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
             }
         }
     const bool interior = m0 + T::BM_ <= M && n0 + SBN <= N;
-    const bool vector_ok = (N % VEC) == 0;
+    const bool vector_ok = (N % VEC) == 0, cached = NI > 4 && !OUT_BF16 && p.cached != 0;     // (the others cover 16 MiB at most)
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
     const int64_t gcol = n0 + wn * 64 + rd_cv * VEC;
     const int64_t row0 = m0 + wm * WROWS + rd_row;
@@ -863,7 +877,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         const int64_t grow = row0 + ROWS_PER_READ * e;
         char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
         if (vector_ok) {
-            if (interior || (grow < M && gcol < N)) __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(out));
+            if (interior || (grow < M && gcol < N)) store_c(out, val, cached);
         } else if (grow < M) {
             store_ragged<OUT_BF16>(out, val, N - gcol);
         }
@@ -1227,12 +1241,13 @@ Block block_of(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n,
 // Up to this K what two XCDs both read is too little to matter, and the orders are the previous ones: columns of 8, dealt out to the
 // XCDs only where their number is a multiple of 8, and for split products the shorter side of C first.  us, those orders -> blocks:
 // split into 64 x 64 tiles 1024 x 1024 x 512 6.4 -> 6.3, x 1024 8.3 -> 7.6, x 4096 16.8 -> 15.2; 512 x 512 x 512 4.20 -> 4.20, x 4096 9.6 -> 8.9;
-// 384 x 512 x 7040 13.7 -> 12.8; 128 x 128 tiles 170 x 6953 x 1448 17.3 -> 16.0.
+// 384 x 512 x 7040 13.7 -> 12.8; 128 x 128 tiles 170 x 6953 x 1448 17.3 -> 16.0.  Larger tiles, bound by their matrix cores, keep the previous orders
+// for every K: 3484 x 4296 x 2048 50.3 -> 48.2, but 3400 x 3400 x 4096 80.0 -> 81.8 and 5632 x 1280 x 7168 91.7 -> 94.0, 26 shapes 0.3 % in the mean.
 constexpr int64_t kShortK = 512;
 int64_t at_a_time(int64_t tiles) { return tiles < 32 * 8 ? (tiles + 7) / 8 : 32; }      // tiles an XCD's 32 compute units work on
 Block tile_block(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n, int64_t K) {
     const int64_t tiles = tiles_m * tiles_n, n = at_a_time(tiles);
-    if (K > kShortK && (tiles % 8 || tile_m != tile_n)) return block_of(tiles_m, tiles_n, tile_m, tile_n, n);
+    if (K > kShortK && tiles % 8 && tile_m == SBM) return block_of(tiles_m, tiles_n, tile_m, tile_n, n);
     if (tiles % 8) return {0, 1, n};
     const int64_t high = tiles_m < 8 ? tiles_m < n ? tiles_m : n : 8 < n ? 8 : n;
     return {8, high, (n + high - 1) / high};
@@ -1243,6 +1258,22 @@ Block split_block(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile
     const bool m_first = tiles_m <= tiles_n;
     const int64_t inner = m_first ? tiles_m : tiles_n, in = inner < n ? inner : n, across = (n + in - 1) / in;
     return {(int32_t)(m_first ? tiles_m : 1), m_first ? in : across, m_first ? across : in};
+}
+
+// Whether a tiled product stores C into the L2s (8 x 4 MiB) instead of past them.  Into them: where rows of C are off the 128-byte grid the
+// lines that two wavefronts share are put together there, and where the product goes on for a while the L2 takes a tile at once
+// and writes it back under later ones' loops.  Past them: what is in the L2s when the kernel ends is written back then, while
+// nothing else runs, and with bf16 results and a long K the panels of A and B need the place more.  us, past -> into:
+//   rows off the grid    3000 x 2600 x 512 fp32 17.1 -> 14.8, 3800 x 3900 x 1024 fp32 36.6 -> 32.4, 5000 x 5080 x 1024 54.6 -> 50.4, 3400 x 3400 x 256
+//                        fp32 18.1 -> 16.3, 4100 x 4200 x 2056 [K,N] fp32 77.3 -> 74.3; below 20 MiB 2100 x 2056 x 512 fp32 12.2 -> 13.1, 2749 x 3552 x
+//                        2648 53.5 -> 54.5
+//   on it, 48, 64 MiB    fp32 4096 x 4096 x 2048 58.6 -> 57.0, 8192 x 8192 x 1024 150 -> 140, x 4096 398 -> 390; bf16 6400 x 5632 x 128 25.1 -> 23.7, 8192 x
+//                        4096 x 1024 60.9 -> 59.7, but x 3072 144.7 -> 146.4 and x 4096 190 -> 192
+//   below                4096 x 4096 x 128 12.3 -> 13.7, 3072 x 3072 x 1024 fp32 25.6 -> 26.8, 2048 x 2048 x 512 fp32 9.8 -> 10.8
+bool cached_stores(int64_t M, int64_t N, int64_t K, int esize) {
+    const int64_t bytes = M * N * esize;
+    if (N * esize % 128) return bytes >= (int64_t)20 << 20;
+    return esize == 4 ? bytes >= (int64_t)48 << 20 : bytes >= (int64_t)64 << 20 && K <= 1024;
 }
 
 template <class T, bool B_KN, bool K_TAIL>
@@ -1396,7 +1427,7 @@ extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype 
     out->d_bytes = loads(bm, bn) + (double)bm * bn * out_bytes;
     out->tile_m = (int32_t)bm; out->tile_n = (int32_t)bn; out->threads = THREADS;
     const bool may_cut = tiling == TILE_256x256 && K >= BK && K <= FAST_MAX_K && M <= kMaxDim && N <= kMaxDim;
-    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn, 8};
+    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn, 8, 0};
     MixedArgs mixed;
     const int quadrants = may_cut ? choose_mixed(a, &mixed) : 0;
     // the block of tiles an XCD works on at a time (32 compute units per XCD): n tiles in r tile-rows and c tile-columns need
@@ -1419,7 +1450,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (!b_is_nk && (N % 8)) return lagom::fail(LAGOM_EINVAL, "B stored [K,N] needs N to be a multiple of 8");
     const Tiling tiling = choose_tiling(M, N, K);
     if (const Split split = choose_split(M, N, K); split.launch) {
-        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0, 0};
+        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0, 0, 0};
         if (int rc = split.launch(a, b_is_nk != 0, out_dt == LAGOM_BF16, static_cast<hipStream_t>(hip_stream))) return rc;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "gemm launch: %s", hipGetErrorString(e));
@@ -1428,7 +1459,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (tiling != TILE_256x256) {
         const int bm = tiling == TILE_128x128 ? SBM : MBM;
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0};
+                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0, cached_stores(M, N, K, lagom::elem_size(out_dt))};
         a.rows = tile_block(a.tiles_m, a.tiles_n, bm, SBN, K).rows;
         const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1450,7 +1481,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         return LAGOM_OK;
     }
     GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-               (int32_t)((M + BM - 1) / BM), (int32_t)((N + BN - 1) / BN), 0};
+               (int32_t)((M + BM - 1) / BM), (int32_t)((N + BN - 1) / BN), 0, cached_stores(M, N, K, lagom::elem_size(out_dt))};
     a.rows = tile_block(a.tiles_m, a.tiles_n, BM, BN, K).rows;
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > (1 << 30)) return lagom::fail(LAGOM_EINVAL, "too many tiles");

@@ -89,8 +89,8 @@ def test_geometry_of_a_product_with_k_split_over_wavefronts(M, N, K, tile, mu, t
     (5400, 90, 576, (64, 32), 32, (11, 3)),           # three tile-columns: whole tile-rows
     (1152, 1280, 576, (128, 128), 12, (3, 4)),        # 90 tiles, no multiple of 8
     (1024, 4096, 576, (128, 128), 32, (8, 4)),        # 256 tiles: columns of 8 as ever
-    (2048, 4096, 576, (256, 128), 32, (4, 8)),        # tiles twice as high as wide
-    (2100, 3720, 576, (256, 256), 17, (5, 4))])       # 9 x 15 = 135 tiles in groups of 5 and 4 rows
+    (2048, 4096, 576, (256, 128), 32, (8, 4)),        # larger tiles: columns of 8,
+    (2100, 3720, 576, (256, 256), 17, (1, 17))])      # dealt out one by one where their number (9 x 15) is no multiple of 8
 def test_geometry_of_the_block_of_tiles_that_an_xcd_works_on_from_k_above_512(M, N, K, tile, n, block):
     g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
     assert (g.tile_m, g.tile_n) == tile
