@@ -1,4 +1,4 @@
-"""ctypes binding of liblagom.so: argument marshalling only.
+"""Binding of liblagom.so: argument marshalling only, with ctypes, and natively (csrc/marshal.c) for the launches.
 
 Every function here has the name and the meaning of the C entry point it wraps
 (see include/lagom.h); all work is done by the native library.  Device buffers may be
@@ -155,11 +155,12 @@ PROFILE_FN = C.CFUNCTYPE(C.c_int, C.c_void_p, C.POINTER(lagom_cfg), C.c_int, C.P
 
 # --------------------------------------------------------------------------- loading
 _lib = None
+_launch = None      # the native marshalling of the launches, bound to _lib
 
 
 def lib() -> C.CDLL:
     """The loaded native library; raises if it has not been built."""
-    global _lib
+    global _lib, _launch
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2602_20656_amd.build` "
@@ -204,8 +205,15 @@ def lib() -> C.CDLL:
                                           C.POINTER(lagom_sweep_point), C.c_int, C.POINTER(C.c_int64), C.POINTER(C.c_int32)]
         for name in EXPORTS:
             getattr(L, name)
-        _lib = L
+        from . import _marshal
+        _marshal.bind(*(C.cast(f, C.c_void_p).value for f in (L.lagom_gemm, L.lagom_comm_kernel, L.lagom_comm_steps)), lagom_cfg)
+        _lib, _launch = L, _marshal
     return _lib
+
+
+def _launches():
+    lib()
+    return _launch
 
 
 def _check(rc: int) -> None:
@@ -246,10 +254,15 @@ def _cfg_array(cfgs: Sequence[CfgLike]):
 
 
 # ----------------------------------------------------------------------- entry points
+# The native marshalling answers None to arguments that it leaves to ctypes.
 def lagom_comm_kernel(op: int, dt: int, srcs, dsts, count: int, cfg: CfgLike, stream=None) -> None:
-    c = _cfg(cfg)
-    _check(lib().lagom_comm_kernel(op, dt, _ptr_array(srcs), len(srcs), _ptr_array(dsts), len(dsts),
-                                   int(count), C.byref(c), _stream(stream)))
+    rc = (_launch or _launches()).comm_kernel(op, dt, srcs, dsts, count, cfg, stream)
+    if rc is None:
+        c = _cfg(cfg)
+        rc = lib().lagom_comm_kernel(op, dt, _ptr_array(srcs), len(srcs), _ptr_array(dsts), len(dsts),
+                                     int(count), C.byref(c), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def lagom_comm_kernel_lds(op: int, dt: int, srcs, dsts, count: int, cfg: CfgLike, stream=None) -> None:
@@ -260,18 +273,26 @@ def lagom_comm_kernel_lds(op: int, dt: int, srcs, dsts, count: int, cfg: CfgLike
 
 def lagom_comm_steps(dt: int, steps: Sequence[Tuple[int, Sequence, Sequence]], count: int, cfg: CfgLike, stream=None) -> None:
     """steps: (op, srcs, dsts) per local step, all of `count` elements of dt; one kernel launch for all of them."""
-    c = _cfg(cfg)
-    arr = (lagom_comm_step * max(len(steps), 1))()
-    keep = []
-    for i, (op, srcs, dsts) in enumerate(steps):
-        a, b = _ptr_array(srcs), _ptr_array(dsts)
-        keep += [a, b]
-        arr[i] = lagom_comm_step(int(op), C.cast(a, C.POINTER(C.c_void_p)), len(srcs), C.cast(b, C.POINTER(C.c_void_p)), len(dsts))
-    _check(lib().lagom_comm_steps(dt, arr, len(steps), int(count), C.byref(c), _stream(stream)))
+    rc = (_launch or _launches()).comm_steps(dt, steps, count, cfg, stream)
+    if rc is None:
+        c = _cfg(cfg)
+        arr = (lagom_comm_step * max(len(steps), 1))()
+        keep = []
+        for i, (op, srcs, dsts) in enumerate(steps):
+            a, b = _ptr_array(srcs), _ptr_array(dsts)
+            keep += [a, b]
+            arr[i] = lagom_comm_step(int(op), C.cast(a, C.POINTER(C.c_void_p)), len(srcs), C.cast(b, C.POINTER(C.c_void_p)), len(dsts))
+        rc = lib().lagom_comm_steps(dt, arr, len(steps), int(count), C.byref(c), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def lagom_gemm(A, B, Cmat, M: int, N: int, K: int, b_is_nk: bool = True, out_dt: int = LAGOM_BF16, stream=None) -> None:
-    _check(lib().lagom_gemm(_ptr(A), _ptr(B), _ptr(Cmat), int(M), int(N), int(K), 1 if b_is_nk else 0, out_dt, _stream(stream)))
+    rc = (_launch or _launches()).gemm(A, B, Cmat, M, N, K, b_is_nk, out_dt, stream)
+    if rc is None:
+        rc = lib().lagom_gemm(_ptr(A), _ptr(B), _ptr(Cmat), int(M), int(N), int(K), 1 if b_is_nk else 0, out_dt, _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def lagom_gemm_describe(M: int, N: int, K: int, out_dt: int = LAGOM_BF16) -> lagom_gemm_geometry:
