@@ -87,6 +87,7 @@ __device__ __forceinline__ u32x4 ld16(const char* p) {
 }
 // from an element-aligned address (global loads need no more)
 typedef u32x4 u32x4_element_aligned __attribute__((aligned(2)));
+typedef uint32_t u32_aligned2 __attribute__((aligned(2)));
 template <bool STREAM>
 __device__ __forceinline__ u32x4 ld16_ragged(const char* p) {
     if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_element_aligned*>(p));
@@ -190,9 +191,12 @@ __device__ __forceinline__ void copy_rest(const char* src, const DST& dst, int n
 // ------------------------------------------------------------------ the pipelined mover
 // A gather-copy of shards that are no multiple of 16 bytes: shard r starts r * shard_bytes bytes behind a 16-byte boundary of
 // the destination.  Stores stay aligned: the shard's first `head` bytes and what is left behind its last whole vector are
-// copied apart (at most 30 bytes a shard), and the vectors between them are read from element-aligned addresses.  (A chunk's
-// last vector then reaches up to 14 bytes into the next chunk.)  Eight shards of 1000003 bf16 at (32, 256, 64 KiB): 18.9 us, as
-// much as aligned shards take; element by element, two bytes per lane and load, it was 310.9 us.
+// copied apart (at most 30 bytes a shard), and the vectors between them are read from element-aligned addresses, which on the 4-byte grid
+// cost 5 - 8 % against the 16-byte grid.  (A chunk's last vector then reaches up to 14 bytes into the next chunk.)
+// Of shards of an odd number of bf16 every second one starts off the 4-byte grid as well, and loads from there take 1.8 times as
+// long.  GATHER_HALVES reads its vectors two bytes early and shifts them: a lane's last two bytes are the first ones of the next lane's
+// vector (a DPP move), those of a unit's last vector are loaded apart, by one lane for each unit of the batch.
+// Eight shards of 1000003 bf16 at (32, 256, 64 KiB): 19.1 -> 15.0 us, of 1000000 13.4.
 __device__ __forceinline__ uint32_t ragged_head(uint32_t r, int64_t shard_bytes) { return (16u - ((r * (uint32_t)shard_bytes) & 15u)) & 15u; }
 
 // A wavefront's walk over its share: chunks blockIdx, blockIdx + NC, ... of every shard in turn, and in each chunk the
@@ -201,19 +205,24 @@ __device__ __forceinline__ uint32_t ragged_head(uint32_t r, int64_t shard_bytes)
 // a batch seems never to be waited for, and it drains the memory pipeline on each.  Which lane moves an element
 // depends on the sizes, NC, NT and C only, not on how many units are in flight: the steps of one launch rely on that.
 // STEPS: the walk of a reduce-copy taken nshards times, once for each of a run of steps.
-enum WalkKind { REDUCE, GATHER, GATHER_RAGGED, STEPS };
+enum WalkKind { REDUCE, GATHER, GATHER_RAGGED, GATHER_HALVES, STEPS };
+constexpr bool is_ragged(WalkKind k) { return k == GATHER_RAGGED || k == GATHER_HALVES; }
+constexpr bool is_gather(WalkKind k) { return k == GATHER || is_ragged(k); }
 template <WalkKind KIND>
 struct Walk {
+    static constexpr bool HALVES = KIND == GATHER_HALVES;
     Shape s;
     uint32_t wave, nw;
     uint32_t c, r;                              // current chunk of the shard, shard (0 in a reduce-copy; the step of a run)
     uint32_t n, units, rest;                    // unit, units of the chunk, bytes of whole vectors in its last unit
     bool more;                                  // the walk stands on something to move
-    // GATHER_RAGGED: bytes of the current shard in front of its first destination vector
-    __device__ __forceinline__ uint32_t head() const { return KIND == GATHER_RAGGED ? ragged_head(shard(), s.shard_bytes) : 0u; }
+    // ragged: bytes of the current shard in front of its first destination vector
+    __device__ __forceinline__ uint32_t head() const { return is_ragged(KIND) ? ragged_head(shard(), s.shard_bytes) : 0u; }
+    // GATHER_HALVES: how far the offset is off the 4-byte grid, 0 or 2
+    __device__ __forceinline__ uint32_t half() const { return KIND == GATHER_HALVES && !empty() ? head() & 2u : 0u; }
     __device__ __forceinline__ void open() {
         n = wave;
-        if (KIND == GATHER_RAGGED) {
+        if (is_ragged(KIND)) {
             const int64_t left = s.shard_bytes - ragged_head(r, s.shard_bytes) - (int64_t)c * s.chunk_bytes;
             const int64_t whole = (left < s.chunk_bytes ? left > 0 ? left : 0 : s.chunk_bytes) & ~(int64_t)15;
             units = (uint32_t)((whole + 1023) >> 10);
@@ -226,9 +235,9 @@ struct Walk {
     }
     __device__ __forceinline__ void first() {
         c = blockIdx.x; r = 0;
-        if (KIND == GATHER || KIND == GATHER_RAGGED) { r = c / s.chunks; c -= r * s.chunks; }
+        if (is_gather(KIND)) { r = c / s.chunks; c -= r * s.chunks; }
         open();
-        more = KIND == GATHER || KIND == GATHER_RAGGED ? r < s.nshards && s.full_units > 0 : c < s.chunks && n < units;
+        more = is_gather(KIND) ? r < s.nshards && s.full_units > 0 : c < s.chunks && n < units;
     }
     __device__ __forceinline__ void next(uint32_t batch) {
         n += batch * nw;
@@ -285,7 +294,7 @@ struct GatherIo {                               // shard r goes to r * shard_byt
     static constexpr bool SCALAR_OUT = false;
     const SRC& src; const DST& dst; int ndst;
     __device__ __forceinline__ const char* from(const Walk<KIND>& w, int) const { return src(w.shard()) + w.offset(); }
-    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return KIND == GATHER_RAGGED ? ld16_ragged<STREAM>(p) : ld16<STREAM>(p); }
+    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return is_ragged(KIND) ? ld16_ragged<STREAM>(p) : ld16<STREAM>(p); }
     __device__ __forceinline__ int64_t to(const Walk<KIND>& w) const { return w.shard() * w.s.shard_bytes + w.offset(); }
     __device__ __forceinline__ int copies(uint32_t) const { return ndst; }
     __device__ __forceinline__ char* out(uint32_t, int d) const { return dst(d); }
@@ -298,6 +307,7 @@ struct Batch {
     int64_t off;               // of the first unit in a destination
     uint32_t r;                // shard or step
     int32_t limit;             // lanes whose offset from there is larger store nothing
+    uint32_t shift, edge;      // GATHER_HALVES: bits that the vectors are off by; in lane u, the last four bytes of unit u
 };
 
 // Copies (S = 1) and reductions: while one batch is added and stored, the loads of the next one are in flight.  Loads and
@@ -321,6 +331,13 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         const char* from[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) from[s] = io.from(w, s);
+        if (WALK::HALVES) {
+            static_assert(!WALK::HALVES || (U & (U - 1)) == 0, "lanes beyond U repeat those below it");
+            const uint32_t unit_end = (((lane & (U - 1)) * w.nw) << 10) + 1024, end = unit_end < last + 16 ? unit_end : last + 16;
+            b.edge = *reinterpret_cast<const u32_aligned2*>(from[0] + (end - 4));       // (as a whole register: nothing to widen, early)
+            b.shift = w.half() * 8;
+            from[0] -= w.half();
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t o = at[u] < last ? at[u] : last;
@@ -331,6 +348,15 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
     // SCALAR_OUT: where the compiler sees that the offsets are the same in every batch, it holds them as 64-bit addresses, too.
     auto offset = [](uint32_t& o) { if (IO::SCALAR_OUT) asm volatile("" : "+v"(o)); return o; };
     auto finish = [&](const Batch<S, U>& b, int u) {
+        if (WALK::HALVES) {
+            // (No branch around it: the merged registers of a batch shifted and not would be more than a product leaves.)
+            const u32x4 x = b.v[u][0];
+            const uint32_t edge = (uint32_t)__builtin_amdgcn_readlane(b.edge, u) >> 16;
+            uint32_t next = __builtin_amdgcn_update_dpp(edge, x[0], 0x130 /* wave_shl:1: from the lane above, the last lane keeps the first */, 0xf, 0xf, false);
+            next = (int32_t)at[u] >= b.limit ? edge : next;
+            return u32x4{__builtin_amdgcn_alignbit(x[1], x[0], b.shift), __builtin_amdgcn_alignbit(x[2], x[1], b.shift),
+                         __builtin_amdgcn_alignbit(x[3], x[2], b.shift), __builtin_amdgcn_alignbit(next, x[3], b.shift)};
+        }
         if (COPY) return b.v[u][0];             // bytes are moved, never interpreted
         Acc<DT> acc;
         acc.init(b.v[u][0]);
@@ -339,6 +365,7 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         return acc.result();
     };
     auto put = [&](Batch<S, U>& b) {
+        if (WALK::HALVES) asm volatile("" : "+v"(b.edge)::"memory");      // read behind the next batch's loads, and not in front of them
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             b.v[u][0] = finish(b, u);
@@ -518,7 +545,7 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) reduce_copy_kernel(cons
 
 // KIND GATHER: every shard starts 16-byte aligned in the destination (shard_bytes % 16 == 0, or a single shard).
 template <WalkKind KIND, bool STREAM, int U>
-__global__ void __launch_bounds__(U == units_in_batch(1, true) ? kDeepNT : 1024) gather_copy_kernel(const CommArgs p) {
+__device__ __forceinline__ void gather_copy_body(const CommArgs& p) {
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
     const GatherIo<KIND, decltype(src), decltype(dst)> io{src, dst, p.ndst};
@@ -539,6 +566,12 @@ __global__ void __launch_bounds__(U == units_in_batch(1, true) ? kDeepNT : 1024)
         }
     }
 }
+
+template <WalkKind KIND, bool STREAM, int U>
+__global__ void __launch_bounds__(U == units_in_batch(1, true) ? kDeepNT : 1024) gather_copy_kernel(const CommArgs p) { gather_copy_body<KIND, STREAM, U>(p); }
+// shards of an odd number of two-byte elements
+template <bool STREAM, int U>
+__global__ void __launch_bounds__(U == units_in_batch(1, true) ? kDeepNT : 1024) gather_halves_kernel(const CommArgs p) { gather_copy_body<GATHER_HALVES, STREAM, U>(p); }
 
 template <int DT, bool STREAM, bool DEEP, int S>
 void launch_reduce_s(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
@@ -565,10 +598,24 @@ int gather_units(const Shape& s, uint32_t nt) {
     return units;
 }
 
+// Shards of an odd number of two-byte elements: two bytes early and shifted back, or as they lie, off the 4-byte grid.  What the shift
+// costs is its instructions, which one or two wavefronts cannot hide, and a load per batch for the units' last bytes, as many lines as
+// there are units: it takes four wavefronts, chunks of 32 KiB and batches of four units, and (as a chunk's units fill the last
+// batch badly otherwise) a power of two of wavefronts.  us, as they lie -> shifted, eight shards of 1000003 in the last-level cache: (16, 256,
+// 32 KiB) 33.5 -> 24.8, x 256 KiB 44.9 -> 26.0; (32, 256, 64 KiB) 19.1 -> 15.0; (128, 256, 64 KiB) 12.1 -> 10.2; (16, 512, 32 KiB) 31.4 -> 27.2; (16, 1024, 64 KiB) 32.5
+// -> 27.2, x 256 KiB 40.7 -> 27.2; but (16, 256, 16 KiB) 33.7 -> 33.9, (16, 512, 16 KiB) 36.0 -> 38.3, (16, 1024, 16 KiB) 52.3 -> 61.9, two wavefronts (16, 128,
+// 64 KiB) 37.9 -> 40.9, three (16, 192, 16 KiB) 53.4 -> 74.7, one (8, 64, 64 KiB) 184 -> 255.
+bool halves_pay(const Shape& s, uint32_t nt) {
+    const uint32_t nw = nt >> 6;
+    return (s.shard_bytes & 2) && nw >= 4 && (nw & (nw - 1)) == 0 && s.full_units >= (nw > 8 ? 4 * nw : 32);
+}
+
 template <WalkKind KIND, bool STREAM, int U>
 void launch_gather_u(const CommArgs& a, int units, dim3 grid, dim3 block, hipStream_t st) {
-    if (units == U) hipLaunchKernelGGL((gather_copy_kernel<KIND, STREAM, U>), grid, block, 0, st, a);
-    else if constexpr (U > 1) launch_gather_u<KIND, STREAM, U / 2>(a, units, grid, block, st);
+    if (units == U) {
+        if constexpr (KIND == GATHER_HALVES) hipLaunchKernelGGL((gather_halves_kernel<STREAM, U>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((gather_copy_kernel<KIND, STREAM, U>), grid, block, 0, st, a);
+    } else if constexpr (U > (KIND == GATHER_HALVES ? 4 : 1)) launch_gather_u<KIND, STREAM, U / 2>(a, units, grid, block, st);
 }
 template <WalkKind KIND>
 void launch_gather(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
@@ -847,6 +894,7 @@ extern "C" int lagom_comm_kernel(lagom_op op, lagom_dtype dt, const void* const*
     const dim3 grid((unsigned)cfg->nc), block((unsigned)cfg->nt);
     if (op == LAGOM_REDUCE_COPY) dt == LAGOM_F32 ? launch_reduce<LAGOM_F32>(a, grid, block, st) : launch_reduce<LAGOM_BF16>(a, grid, block, st);
     else if (nsrc == 1 || (a.shape.shard_bytes & 15) == 0) launch_gather<GATHER>(a, grid, block, st);
+    else if (halves_pay(a.shape, block.x)) launch_gather<GATHER_HALVES>(a, grid, block, st);
     else launch_gather<GATHER_RAGGED>(a, grid, block, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "comm kernel launch: %s", hipGetErrorString(e));

@@ -71,3 +71,11 @@ def test_reduces_and_gathers_fit_beside_a_product_up_to_512_threads(comm, left_b
         if re.search(r"reduce_copy_kernelILi1ELi8ELb[01]ELb0E", name):
             nt = 256
         assert _fits(meta, nt, left_by_product[layout]), (name, nt, meta["vgpr_count"], left_by_product)
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+def test_gathers_of_shifted_shards_fit_beside_a_product_up_to_512_threads(comm, left_by_product, layout):
+    kernels = {n: m for n, m in comm.items() if "gather_halves_kernel" in n}
+    assert len(kernels) == 2 * 2           # loads streamed or not; batches of four and of eight units
+    for name, meta in kernels.items():
+        assert _fits(meta, min(int(meta["max_flat_workgroup_size"]), 512), left_by_product[layout]), (name, meta["vgpr_count"], left_by_product)

@@ -496,6 +496,24 @@ def test_gather_copy_of_shards_off_the_vector_grid(dtype, nt, P):
                 assert same_bits(got, want), (count, nc)
 
 
+@pytest.mark.parametrize("nt", [128, 256, 512, 1024])
+@pytest.mark.parametrize("per_wave", [4, 8, 11, 17])
+def test_gather_copy_of_shards_of_an_odd_number_of_halves(nt, per_wave):
+    """Every second shard starts off the 4-byte grid: its vectors are read two bytes early and shifted.  Shard lengths around the ends
+    of units, batches and chunks, with the last whole vector at every place against a unit's end; loads streamed and not."""
+    chunk = per_wave * (nt // 64) * 1024
+    for base in (1024, 4 * (nt // 64) * 1024, chunk, 2 * chunk + 5 * 1024):
+        for e in (-9, -7, -1, 1, 3, 7, 9, 513):
+            count = (base // 2 + e) | 1
+            for P, nc in ((2, 1), (7, 3)):
+                shards = _sources("bf16", P, count, 1250)
+                for got in _run(lg.LAGOM_GATHER_COPY, "bf16", shards, P // 3 + 1, (nc, nt, chunk), P * count):
+                    assert same_bits(got, np.concatenate(shards)), (count, P, nc)
+    count = 67 * (chunk // 2) + 77                           # 2 x 68 chunks for 130 channels
+    shards = _sources("bf16", 2, count, 1251)
+    assert same_bits(_run(lg.LAGOM_GATHER_COPY, "bf16", shards, 1, (130, nt, chunk), 2 * count)[0], np.concatenate(shards))
+
+
 @pytest.mark.parametrize("nt", [64, 256, 320, 1024])
 @pytest.mark.parametrize("per_wave", [1, 2, 3, 4, 5, 8, 9])
 def test_gather_copy_with_few_units_to_a_wavefront(nt, per_wave):
