@@ -269,11 +269,15 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
         }
 }
 
-// 16 bytes of a row of C on the 16-byte grid, past the L2s or into them (a rule of the sizes: cached_stores).  (Empty asm on both
-// sides: the compiler otherwise makes one store of the two, without the hint.  One choice for eight stores or for the whole epilogue
-// is no faster in the large tiles, up to 1 % slower.)
+// 16 bytes of a row of C on the 16-byte grid, past the L2s or into them (a rule of the sizes: cached_stores).  BY_SIZE: empty asm on both
+// sides, as the compiler otherwise makes one store of the two, without the hint.  (The choice per store costs 8192 x 8192 x 8192 1 %, one
+// for eight stores or for the whole epilogue no less: the tilings whose rounds are all alike have kernels of their own.)
+enum Stores { PAST_L2, INTO_L2, BY_SIZE };       // the last where a kernel serves both: it reads GemmArgs.cached
+template <Stores STORES>
 __device__ __forceinline__ void store_c(char* out, u32x4 val, bool cached) {
-    if (cached) {
+    if (STORES == INTO_L2) {
+        *reinterpret_cast<u32x4*>(out) = val;
+    } else if (STORES == BY_SIZE && cached) {
         asm volatile("" ::: "memory");
         *reinterpret_cast<u32x4*>(out) = val;
         asm volatile("" ::: "memory");
@@ -304,7 +308,7 @@ typedef __attribute__((address_space(3))) char* lds_bytes;
 // B_KN = false: B stored [N,K]; true: B stored [K,N], its tiles kept in LDS as 64 rows (k) of 256 columns
 // and transposed by the LDS reads.
 // K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64, behind the start of the one before it.
-template <bool B_KN, bool OUT_BF16, bool K_TAIL>
+template <bool B_KN, bool OUT_BF16, bool K_TAIL, Stores STORES>
 __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn) {
     extern __shared__ u32x4 smem[];   // LDS_SLOTS operand tiles of 2048 16-byte slots
     // Wavefronts of a communication kernel may share this wavefront's SIMD (this kernel leaves them
@@ -555,7 +559,7 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     const int r_in = lane & 15, c_q = 4 * (lane >> 4);
     char* st = reinterpret_cast<char*>(smem) + wave * SLOT_BYTES;
     const bool interior = m0 + BM <= M && n0 + BN <= N;
-    const bool vector_ok = (N % VEC) == 0, cached = p.cached != 0;
+    const bool vector_ok = (N % VEC) == 0, cached = STORES == BY_SIZE && p.cached != 0;
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
     const int64_t gcol = n0 + wn * 128 + rd_cv * VEC;
 #pragma unroll
@@ -593,7 +597,7 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
                 const int64_t grow = row0 + ROWS_PER_READ * (tb * 8 + e);
                 char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
                 if (vector_ok) {
-                    if (interior || (grow < M && gcol < N)) store_c(out, val[e], cached);
+                    if (interior || (grow < M && gcol < N)) store_c<STORES>(out, val[e], cached);
                 } else if (grow < M) {
                     store_ragged<OUT_BF16>(out, val[e], N - gcol);
                 }
@@ -603,14 +607,24 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false, PAST_L2>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false, PAST_L2>(p, tm, tn); }
 // K >= 64 and not a multiple of 64 (kernels of their own: the peeled last step clears fragments; as many registers)
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true, PAST_L2>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true, PAST_L2>(p, tm, tn); }
+
+// C stored into the L2s
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false, INTO_L2>(p, tm, tn); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false, INTO_L2>(p, tm, tn); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true, INTO_L2>(p, tm, tn); }
+template <bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true, INTO_L2>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- small-tile kernels
 // 128 x 128 x 64 and 256 x 128 x 64 tiles for products with too few 256 x 256 tiles to fill the chip.
@@ -636,7 +650,7 @@ constexpr int SBM = SmallTile<4>::BM_, MBM = SmallTile<8>::BM_;
 __device__ __forceinline__ int kn_swz128(int k) { return (((k >> 3) & 1) << 3) | ((k & 3) << 1); }
 
 // K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64 (see the large kernel).
-template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL>
+template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL, Stores STORES = PAST_L2>
 __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int tn) {
     typedef SmallTile<NI> T;
     constexpr int S_STAGES = T::STAGES, S_AHEAD = T::AHEAD, S_STAGE_BYTES = T::STAGE_BYTES, S_OPERAND_BYTES = T::A_BYTES;
@@ -866,7 +880,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
             }
         }
     const bool interior = m0 + T::BM_ <= M && n0 + SBN <= N;
-    const bool vector_ok = (N % VEC) == 0, cached = NI > 4 && !OUT_BF16 && p.cached != 0;     // (the others cover 16 MiB at most)
+    const bool vector_ok = (N % VEC) == 0;
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
     const int64_t gcol = n0 + wn * 64 + rd_cv * VEC;
     const int64_t row0 = m0 + wm * WROWS + rd_row;
@@ -877,7 +891,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         const int64_t grow = row0 + ROWS_PER_READ * e;
         char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
         if (vector_ok) {
-            if (interior || (grow < M && gcol < N)) store_c(out, val, cached);
+            if (interior || (grow < M && gcol < N)) store_c<STORES>(out, val, false);
         } else if (grow < M) {
             store_ragged<OUT_BF16>(out, val, N - gcol);
         }
@@ -902,6 +916,12 @@ template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, OUT_BF16, true>(p, tm, tn); }
+
+// fp32 results stored into the L2s (bf16 ones of one round of these tiles, and any of 128 x 128 tiles, are too small for that: 16 MiB)
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, false, false, INTO_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, false, false, INTO_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, false, true, INTO_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, false, true, INTO_L2>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- large tiles, the last round in small ones
 // A product of more than 256 large tiles runs in rounds of 256 (one per compute unit), and the last round costs as much
@@ -930,7 +950,7 @@ __device__ __forceinline__ void mixed_gemm_body(const MixedArgs& p) {
     else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
     else { tm = p.full_m; tn = lin - inside - right; }
     if (large) {
-        fast_gemm_body<B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
+        fast_gemm_body<B_KN, OUT_BF16, K_TAIL, BY_SIZE>(p.g, tm, tn);
         return;
     }
     if (lin >= p.g.tiles_m * p.g.tiles_n) return;
@@ -1170,7 +1190,7 @@ __device__ __forceinline__ void pieces_gemm_body(const PiecesArgs& p) {
         if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, 8, &tm, &tn);
         else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
         else { tm = p.full_m; tn = lin - inside - right; }
-        fast_gemm_body<B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
+        fast_gemm_body<B_KN, OUT_BF16, K_TAIL, BY_SIZE>(p.g, tm, tn);
         return;
     }
     constexpr int A = kPiecesAcross;
@@ -1459,7 +1479,8 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (tiling != TILE_256x256) {
         const int bm = tiling == TILE_128x128 ? SBM : MBM;
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0, cached_stores(M, N, K, lagom::elem_size(out_dt))};
+                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0, 0};
+        a.cached = out_dt == LAGOM_F32 && tiling == TILE_256x128 && cached_stores(M, N, K, 4);
         a.rows = tile_block(a.tiles_m, a.tiles_n, bm, SBN, K).rows;
         const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1470,6 +1491,9 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         if (tiling == TILE_128x128) {
             if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk128_tail_kernel) : LAGOM_PICK(gemm_bf16_nk128_kernel);
             else rc = tail ? LAGOM_PICK(gemm_bf16_kn128_tail_kernel) : LAGOM_PICK(gemm_bf16_kn128_kernel);
+        } else if (a.cached) {               // fp32
+            if (b_is_nk) rc = tail ? launch_fast<gemm_bf16_nk256x128_cached_tail_kernel>(a, grid, st) : launch_fast<gemm_bf16_nk256x128_cached_kernel>(a, grid, st);
+            else rc = tail ? launch_fast<gemm_bf16_kn256x128_cached_tail_kernel>(a, grid, st) : launch_fast<gemm_bf16_kn256x128_cached_kernel>(a, grid, st);
         } else {
             if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk256x128_tail_kernel) : LAGOM_PICK(gemm_bf16_nk256x128_kernel);
             else rc = tail ? LAGOM_PICK(gemm_bf16_kn256x128_tail_kernel) : LAGOM_PICK(gemm_bf16_kn256x128_kernel);
@@ -1510,14 +1534,17 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
 #undef LAGOM_PICK
         if (rc) return rc;
     } else if (fast) {
+        const bool tail = K % BK != 0;
         int rc;
-        if (K % BK == 0) {
-            if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_nk_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_nk_kernel<false>>(a, grid, st);
-            else rc = bf ? launch_fast<gemm_bf16_kn_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_kn_kernel<false>>(a, grid, st);
+#define LAGOM_PICK(NAME) (bf ? launch_fast<NAME<true>>(a, grid, st) : launch_fast<NAME<false>>(a, grid, st))
+        if (a.cached) {
+            if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk_cached_tail_kernel) : LAGOM_PICK(gemm_bf16_nk_cached_kernel);
+            else rc = tail ? LAGOM_PICK(gemm_bf16_kn_cached_tail_kernel) : LAGOM_PICK(gemm_bf16_kn_cached_kernel);
         } else {
-            if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_nk_tail_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_nk_tail_kernel<false>>(a, grid, st);
-            else rc = bf ? launch_fast<gemm_bf16_kn_tail_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_kn_tail_kernel<false>>(a, grid, st);
+            if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk_tail_kernel) : LAGOM_PICK(gemm_bf16_nk_kernel);
+            else rc = tail ? LAGOM_PICK(gemm_bf16_kn_tail_kernel) : LAGOM_PICK(gemm_bf16_kn_kernel);
         }
+#undef LAGOM_PICK
         if (rc) return rc;
     } else if (b_is_nk) {
         if (bf) hipLaunchKernelGGL((gemm_bf16_general_kernel<true, true>), grid, block, 0, st, a);

@@ -197,3 +197,22 @@ def test_large_body_of_a_kernel_with_split_pieces_keeps_its_accumulators(assembl
         for l in block:
             if not l.startswith("v_mfma_f32_16x16x32_bf16") and AGPR.search(l):
                 assert not has_mfma and not falls_in and l.startswith(("v_accvgpr_mov_b32", "v_accvgpr_write_b32")), l
+
+
+CACHED = tuple("gemm_bf16_%s_cached%s_kernelILb%dE" % (k, t, o) for k in ("nk", "kn") for t in ("", "_tail") for o in (1, 0)) + \
+    tuple("gemm_bf16_%s256x128_cached%s_kernelE" % (k, t) for k in ("nk", "kn") for t in ("", "_tail"))            # fp32
+
+
+@pytest.mark.parametrize("name", CACHED)
+def test_kernels_that_store_into_the_l2_are_those_that_store_past_it(assembly, name):
+    """Instruction for instruction, but for the stores' hint: what holds for the accumulators of the one holds for the other."""
+    def text(n):
+        sym, _ = _body(assembly, n)
+        start = assembly.index("\n" + sym + ":")
+        lines = assembly[start:assembly.index(".Lfunc_end", start)].splitlines()[2:]
+        lines = [re.sub(r"(\.L\w+?)\d+_", r"\1", l.split(";")[0]).strip() for l in lines]
+        return [l for l in lines if l and not l.startswith(".")]
+    cached, past = text(name), text(name.replace("_cached", "").replace("kernelE", "kernelILb0E"))
+    assert not any(l.startswith("global_store_dwordx4") and l.endswith(" nt") for l in cached)
+    first, last = (lambda t: [i for i, l in enumerate(t) if l.startswith("v_mfma")][::len([l for l in t if l.startswith("v_mfma")]) - 1])(past)
+    assert cached[:last] == past[:last] and last - first > 3 * 64

@@ -249,6 +249,24 @@ def test_gemm_last_round_in_quadrants_integer_inputs_are_exact(M, N, K, b_is_nk)
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
 
 
+@pytest.mark.parametrize("M,N,out", [(2304, 2312, "f32"),                         # 256 x 128 tiles, rows of C off the 128-byte grid, 20.3 MiB
+                                     (3400, 3400, "bf16"), (3400, 3400, "f32"),   # 256 x 256 tiles
+                                     (3584, 3584, "f32"),                         # on the grid, 49 MiB
+                                     (8192, 4104, "bf16")])                       # off it, with quadrants behind the large tiles
+@pytest.mark.parametrize("K", [64, 136])
+@pytest.mark.parametrize("b_is_nk", [True, False])
+def test_gemm_results_stored_into_the_l2_integer_inputs_are_exact(M, N, out, K, b_is_nk):
+    if not b_is_nk:
+        N = (N + 7) // 8 * 8
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+    want = a @ (b.T if b_is_nk else b)
+    if out == "bf16":
+        want = oc.bf16_to_f32(oc.f32_to_bf16(want))
+    assert np.array_equal(_gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, out), want)
+
+
 @pytest.mark.parametrize("M,N", [(4100, 4200),     # 17 + 16 tiles at two edges left over: 194 pieces, most of the tiles' empty
                                  (4096, 4352),     # 16 whole tiles, 256 pieces
                                  (4352, 7704),     # one row of tiles behind two rounds, pieces 24 columns wide at its end
