@@ -9,7 +9,8 @@
 // wavefront n mod (NT/64), and the sequence runs on from chunk to chunk.  The walk over it lives in scalar
 // registers, and the loads of the next batch of units are issued before the current batch is added and stored
 // (see "the pipelined mover" below), so that a channel is bound by what a compute unit's memory pipeline
-// moves (100 - 116 GB/s, loads and stores together, from 8 wavefronts up) and not by one memory latency per batch.
+// moves (100 - 127 GB/s, loads and stores together, from 8 wavefronts up) and not by one memory latency per batch.
+// With fewer wavefronts it is bound by their instructions, of which one wavefront issues one in five cycles.
 // Every byte is touched once, so stores always carry the non-temporal hint (measured on MI355X: +3..7 % and no
 // write-allocate traffic in the L2 that a co-running GEMM depends on).  Loads carry it only
 // when at least kStreamLoadsFromNC channels have work: with that many channels the
@@ -23,6 +24,7 @@
 #include <hip/hip_runtime.h>
 #include <atomic>
 #include <type_traits>
+#include <utility>
 #include "common.h"
 
 namespace {
@@ -35,8 +37,7 @@ struct Shape {
     uint32_t nshards;          // of a gather-copy; 1 for a reduce-copy
     uint32_t chunks;           // per shard
     uint32_t step_shards, step_chunks;   // NC chunks further: that many shards and chunks
-    uint32_t full_units, full_rest;   // of a whole chunk: units, and bytes of whole 16-byte vectors in the last of them
-    uint32_t last_units, last_rest;   // of a shard's last chunk (0 units: it holds no whole vector)
+    uint32_t full_bytes, last_bytes;  // whole 16-byte vectors of a chunk, and of a shard's last one (0: it holds none)
 };
 struct CommArgs {
     const char* src[LAGOM_MAX_SRCS];
@@ -48,8 +49,9 @@ struct CommArgs {
 Shape make_shape(int64_t shard_bytes, int64_t chunk_bytes, int nshards, int nc) {
     Shape s{};
     if (chunk_bytes > shard_bytes) chunk_bytes = (shard_bytes + 15) & ~(int64_t)15;
-    // chunk numbers are 32-bit on the device: more than 2^30 of them (64 GiB in 16-byte chunks at the least, and then the
-    // result is the same) are taken as larger chunks
+    // Offsets in a chunk and chunk numbers are 32-bit on the device: chunks of more than 1 GiB are taken as chunks of that, and more than
+    // 2^30 of them (in 16-byte chunks those of 16 GiB) as larger ones.  The result is the same.
+    if (chunk_bytes > (int64_t)1 << 30) chunk_bytes = (int64_t)1 << 30;
     while ((shard_bytes + chunk_bytes - 1) / chunk_bytes * nshards > (int64_t)1 << 30) chunk_bytes *= 2;
     s.shard_bytes = shard_bytes;
     s.chunk_bytes = chunk_bytes;
@@ -57,13 +59,8 @@ Shape make_shape(int64_t shard_bytes, int64_t chunk_bytes, int nshards, int nc) 
     s.chunks = (uint32_t)((shard_bytes + chunk_bytes - 1) / chunk_bytes);
     s.step_shards = (uint32_t)nc / s.chunks;
     s.step_chunks = (uint32_t)nc % s.chunks;
-    auto cut = [](int64_t bytes, uint32_t* units, uint32_t* rest) {
-        const int64_t whole = bytes & ~(int64_t)15;
-        *units = (uint32_t)((whole + 1023) >> 10);
-        *rest = (uint32_t)(whole - ((int64_t)*units - 1) * 1024);
-    };
-    cut(chunk_bytes < shard_bytes ? chunk_bytes : shard_bytes, &s.full_units, &s.full_rest);
-    cut(shard_bytes - (int64_t)(s.chunks - 1) * chunk_bytes, &s.last_units, &s.last_rest);
+    s.full_bytes = (uint32_t)(chunk_bytes < shard_bytes ? chunk_bytes : shard_bytes) & ~15u;
+    s.last_bytes = (uint32_t)(shard_bytes - (int64_t)(s.chunks - 1) * chunk_bytes) & ~15u;
     return s;
 }
 
@@ -93,6 +90,10 @@ __device__ __forceinline__ u32x4 ld16_ragged(const char* p) {
     if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_element_aligned*>(p));
     return *reinterpret_cast<const u32x4_element_aligned*>(p);
 }
+// Bytes [0, bytes) at p as a buffer: lanes beyond them store nothing, without a branch.
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer buffer(char* p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000 /* raw, 32-bit data */); }
+__device__ __forceinline__ void st16(Buffer b, uint32_t at, u32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, b, at, 0, 2 /* non-temporal */); }
 __device__ __forceinline__ void st16(char* p, u32x4 v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p)); }
 
 // bf16 is the upper half of an fp32 pattern.
@@ -204,68 +205,79 @@ __device__ __forceinline__ uint32_t ragged_head(uint32_t r, int64_t shard_bytes)
 // scalar compare), and a step is straight-line code -- with loops in it the compiler's control flow holds paths on which
 // a batch seems never to be waited for, and it drains the memory pipeline on each.  Which lane moves an element
 // depends on the sizes, NC, NT and C only, not on how many units are in flight: the steps of one launch rely on that.
+// Within a chunk a step is an addition to the offset and a subtraction from what is left; all else is done once a chunk, and stores
+// go through buffers that end where the chunk does.  With the offset multiplied out for every unit, its end looked for in front of
+// every load and store, and the destinations' pointers loaded behind them, a unit of eight bf16 sources took 249 instructions, 105 of them
+// scalar, at five cycles each.  us, that -> this, sources of 1000000 elements at (8, NT, 32 KiB): eight bf16, NT 64 128 -> 92, 128 66.7
+// -> 50.8, 256 34.4 -> 25.3, 512 20.5 -> 19.9; six fp32, 128 74.2 -> 42.5, 256 39.0 -> 29.5; sixteen bf16, 128 110 -> 81, 256 57.0 -> 43.9;
+// two fp32, 64 37.1 -> 25.9; a gather of eight, 64 76.9 -> 55.3, 256 35.3 -> 32.8.  One shape of a hundred and fifty lost more than 3 %: two
+// destinations written by twenty channels of 2 MiB, 65 -> 68.
 // STEPS: the walk of a reduce-copy taken nshards times, once for each of a run of steps.
 enum WalkKind { REDUCE, GATHER, GATHER_RAGGED, GATHER_HALVES, STEPS };
 constexpr bool is_ragged(WalkKind k) { return k == GATHER_RAGGED || k == GATHER_HALVES; }
 constexpr bool is_gather(WalkKind k) { return k == GATHER || is_ragged(k); }
 template <WalkKind KIND>
 struct Walk {
-    static constexpr bool HALVES = KIND == GATHER_HALVES;
+    static constexpr bool RAGGED = is_ragged(KIND), HALVES = KIND == GATHER_HALVES;
     Shape s;
     uint32_t wave, nw;
-    uint32_t c, r;                              // current chunk of the shard, shard (0 in a reduce-copy; the step of a run)
-    uint32_t n, units, rest;                    // unit, units of the chunk, bytes of whole vectors in its last unit
-    bool more;                                  // the walk stands on something to move
-    // ragged: bytes of the current shard in front of its first destination vector
-    __device__ __forceinline__ uint32_t head() const { return is_ragged(KIND) ? ragged_head(shard(), s.shard_bytes) : 0u; }
+    uint32_t c, r;                              // current chunk of the shard, shard (0 in a reduce-copy; the step of a run; behind the end s.nshards or more)
+    int32_t left;                               // bytes of whole vectors from the unit to the chunk's end, none or fewer where it holds no unit
+    int64_t off;                                // of the unit in the shard
+    // The walk stands on something to move.  (Not a variable of its own: the compiler keeps truth values that loops hand on as masks
+    // of lanes, and what depends on them in vector registers.)
+    __device__ __forceinline__ bool more() const { return r < s.nshards; }
+    __device__ __forceinline__ uint32_t shard() const { return more() ? r : 0; }
+    __device__ __forceinline__ uint32_t room() const { return left > 0 ? left : 0; }
+    __device__ __forceinline__ uint32_t last() const { return left > 0 ? left - 16 : 0; }     // from the unit to the chunk's last vector
     // GATHER_HALVES: how far the offset is off the 4-byte grid, 0 or 2
-    __device__ __forceinline__ uint32_t half() const { return KIND == GATHER_HALVES && !empty() ? head() & 2u : 0u; }
+    __device__ __forceinline__ uint32_t half() const { return HALVES && left > 0 ? ragged_head(r, s.shard_bytes) & 2u : 0u; }
     __device__ __forceinline__ void open() {
-        n = wave;
-        if (is_ragged(KIND)) {
-            const int64_t left = s.shard_bytes - ragged_head(r, s.shard_bytes) - (int64_t)c * s.chunk_bytes;
-            const int64_t whole = (left < s.chunk_bytes ? left > 0 ? left : 0 : s.chunk_bytes) & ~(int64_t)15;
-            units = (uint32_t)((whole + 1023) >> 10);
-            rest = (uint32_t)(whole - ((int64_t)units - 1) * 1024);
-            return;
+        uint32_t head = 0;                      // bytes of the shard in front of its first destination vector
+        if (RAGGED) {
+            head = ragged_head(r, s.shard_bytes);
+            const int64_t rem = s.shard_bytes - head - (int64_t)c * s.chunk_bytes;
+            left = (int32_t)(rem < s.chunk_bytes ? rem > 0 ? rem : 0 : s.chunk_bytes) & ~15;
+        } else {
+            left = (int32_t)(c + 1 == s.chunks ? s.last_bytes : s.full_bytes);
         }
-        const bool end = c + 1 == s.chunks;
-        units = end ? s.last_units : s.full_units;
-        rest = end ? s.last_rest : s.full_rest;
+        left = more() ? left - (int32_t)(wave << 10) : 0;
+        // Where there is nothing to move the walk points at the start of a shard, for loads that nobody uses.
+        off = left > 0 ? (int64_t)c * s.chunk_bytes + head + (wave << 10) : 0;
     }
     __device__ __forceinline__ void first() {
         c = blockIdx.x; r = 0;
-        if (is_gather(KIND)) { r = c / s.chunks; c -= r * s.chunks; }
+        if (is_gather(KIND)) {
+            r = c / s.chunks; c -= r * s.chunks;
+            if (s.full_bytes == 0) r = s.nshards;
+            open();
+        } else stop_at_end();
+    }
+    // reduce-copies: behind the last chunk (only that one can have fewer units) nothing is left
+    __device__ __forceinline__ void stop_at_end() {
+        if (c >= s.chunks) r = s.nshards;
         open();
-        more = is_gather(KIND) ? r < s.nshards && s.full_units > 0 : c < s.chunks && n < units;
+        if (left <= 0) r = s.nshards;
     }
     __device__ __forceinline__ void next(uint32_t batch) {
-        n += batch * nw;
-        if (n >= units) {
-            if (KIND == STEPS) {
-                c += gridDim.x;
-                if (c >= s.chunks) { c = blockIdx.x; ++r; }
-            } else if (KIND != REDUCE) {
-                // a shard's short last chunk may hold no unit for this wavefront; the walk still stops there (and moves nothing)
-                c += s.step_chunks; r += s.step_shards;
-                if (c >= s.chunks) { c -= s.chunks; ++r; }
-            } else {
-                c += gridDim.x;                 // at most 2^30 + 65535
-            }
-            open();
-            more = more && (KIND != REDUCE ? r < s.nshards : c < s.chunks && n < units);   // only the last chunk can have fewer units
+        const uint32_t bytes = (batch * nw) << 10;
+        off += bytes;
+        left -= (int32_t)bytes;
+        if (left > 0) return;
+        if (KIND == REDUCE) {
+            c += gridDim.x;                     // at most 2^30 + 65535
+            stop_at_end();
+            return;
         }
-    }
-    // Where there is nothing to move the walk points at the start of a shard, for loads that nobody uses.
-    __device__ __forceinline__ uint32_t shard() const { return more ? r : 0; }
-    __device__ __forceinline__ bool empty() const { return !more || (KIND != REDUCE && n >= units); }
-    __device__ __forceinline__ int64_t offset() const {         // byte in the shard
-        return empty() ? 0 : (int64_t)c * s.chunk_bytes + ((int64_t)n << 10) + head();
-    }
-    // offset from offset() of the chunk's last vector (from 2^20 units on: larger than any offset in a batch)
-    __device__ __forceinline__ uint32_t limit() const {
-        const uint32_t left = units - 1 - n;
-        return empty() ? 0u : (left < (1u << 20) ? left << 10 : 1u << 30) + rest - 16;
+        if (KIND == STEPS) {
+            c += gridDim.x;
+            if (c >= s.chunks) { c = blockIdx.x; ++r; }
+        } else {
+            // a shard's short last chunk may hold no unit for this wavefront; the walk still stops there (and moves nothing)
+            c += s.step_chunks; r += s.step_shards;
+            if (c >= s.chunks) { c -= s.chunks; ++r; }
+        }
+        open();
     }
 };
 
@@ -281,42 +293,41 @@ __device__ __forceinline__ Walk<KIND> make_walk(const Shape& s) {
 // Where the walk reads and writes.
 template <class SRC, class DST>
 struct ReduceIo {                               // src(s) and dst(d) at the same offset
-    static constexpr bool SCALAR_OUT = false;
     const SRC& src; const DST& dst; int ndst;
-    __device__ __forceinline__ const char* from(const Walk<REDUCE>& w, int s) const { return src(s) + w.offset(); }
-    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return ld16<STREAM>(p); }
-    __device__ __forceinline__ int64_t to(const Walk<REDUCE>& w) const { return w.offset(); }
+    __device__ __forceinline__ const char* from(const Walk<REDUCE>& w, int s) const { return src(s) + w.off; }
+    __device__ __forceinline__ int64_t to(const Walk<REDUCE>& w) const { return w.off; }
     __device__ __forceinline__ int copies(uint32_t) const { return ndst; }
     __device__ __forceinline__ char* out(uint32_t, int d) const { return dst(d); }
 };
 template <WalkKind KIND, class SRC, class DST>
 struct GatherIo {                               // shard r goes to r * shard_bytes
-    static constexpr bool SCALAR_OUT = false;
     const SRC& src; const DST& dst; int ndst;
-    __device__ __forceinline__ const char* from(const Walk<KIND>& w, int) const { return src(w.shard()) + w.offset(); }
-    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* p) { return is_ragged(KIND) ? ld16_ragged<STREAM>(p) : ld16<STREAM>(p); }
-    __device__ __forceinline__ int64_t to(const Walk<KIND>& w) const { return w.shard() * w.s.shard_bytes + w.offset(); }
+    __device__ __forceinline__ const char* from(const Walk<KIND>& w, int) const { return src(w.shard()) + w.off; }
+    __device__ __forceinline__ int64_t to(const Walk<KIND>& w) const { return w.shard() * w.s.shard_bytes + w.off; }
     __device__ __forceinline__ int copies(uint32_t) const { return ndst; }
     __device__ __forceinline__ char* out(uint32_t, int d) const { return dst(d); }
 };
+
+// f(0), f(1), ... with their numbers as constants, for as long as they return true.  (A loop that may be left from its middle is not unrolled.)
+template <class F, int... I>
+__device__ __forceinline__ bool while_true(const F& f, std::integer_sequence<int, I...>) { return (f(std::integral_constant<int, I>{}) && ...); }
 
 // A batch: U units of one chunk, S sources each.
 template <int S, int U>
 struct Batch {
     u32x4 v[U][S];
-    int64_t off;               // of the first unit in a destination
-    uint32_t r;                // shard or step
-    int32_t limit;             // lanes whose offset from there is larger store nothing
+    char* to;                  // the first unit in the first destination
+    uint32_t r, room;          // the walk's shard or step, and bytes from there to the chunk's end
     uint32_t shift, edge;      // GATHER_HALVES: bits that the vectors are off by; in lane u, the last four bytes of unit u
 };
 
-// Copies (S = 1) and reductions: while one batch is added and stored, the loads of the next one are in flight.  Loads and
+// Copies (S = 1) and reductions of NB batches: while one is added and stored, the loads of the others are in flight.  Loads and
 // stores share one in-order counter, so issuing the next loads in front of the stores also keeps the stores'
 // acknowledgements off the path.  U: units per batch.
-template <int DT, int S, int U, bool STREAM, bool COPY, class WALK, class IO>
+template <int DT, int S, int U, int NB, bool STREAM, bool COPY, class WALK, class IO>
 __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane) {
     w.first();
-    if (!w.more) return;
+    if (!w.more()) return;
     // The compiler must not see that the walks of a fused launch have their lanes' offsets in common: it would compute those of
     // every kind of step in front of the loop over the steps and hold them all, in registers that a product beside the kernel needs.
     asm volatile("" : "+v"(lane));
@@ -324,10 +335,10 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
 #pragma unroll
     for (int u = 0; u < U; ++u) at[u] = lane * 16 + ((u * w.nw) << 10);
     auto fetch = [&](Batch<S, U>& b) {          // past the chunk's end its last vector is read again (and not stored)
-        b.off = io.to(w);
-        b.r = w.shard();
-        const uint32_t last = w.limit();
-        b.limit = w.empty() ? -1 : (int32_t)last;
+        b.to = io.out(w.shard(), 0) + io.to(w);
+        b.r = w.r;
+        b.room = w.room();
+        const uint32_t last = w.last();
         const char* from[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) from[s] = io.from(w, s);
@@ -342,18 +353,17 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         for (int u = 0; u < U; ++u) {
             const uint32_t o = at[u] < last ? at[u] : last;
 #pragma unroll
-            for (int s = 0; s < S; ++s) b.v[u][s] = IO::template load<STREAM>(from[s] + o);
+            for (int s = 0; s < S; ++s) b.v[u][s] = WALK::RAGGED ? ld16_ragged<STREAM>(from[s] + o) : ld16<STREAM>(from[s] + o);
         }
+        w.next(U);
     };
-    // SCALAR_OUT: where the compiler sees that the offsets are the same in every batch, it holds them as 64-bit addresses, too.
-    auto offset = [](uint32_t& o) { if (IO::SCALAR_OUT) asm volatile("" : "+v"(o)); return o; };
     auto finish = [&](const Batch<S, U>& b, int u) {
         if (WALK::HALVES) {
             // (No branch around it: the merged registers of a batch shifted and not would be more than a product leaves.)
             const u32x4 x = b.v[u][0];
             const uint32_t edge = (uint32_t)__builtin_amdgcn_readlane(b.edge, u) >> 16;
             uint32_t next = __builtin_amdgcn_update_dpp(edge, x[0], 0x130 /* wave_shl:1: from the lane above, the last lane keeps the first */, 0xf, 0xf, false);
-            next = (int32_t)at[u] >= b.limit ? edge : next;
+            next = at[u] + 16 >= b.room ? edge : next;
             return u32x4{__builtin_amdgcn_alignbit(x[1], x[0], b.shift), __builtin_amdgcn_alignbit(x[2], x[1], b.shift),
                          __builtin_amdgcn_alignbit(x[3], x[2], b.shift), __builtin_amdgcn_alignbit(next, x[3], b.shift)};
         }
@@ -366,56 +376,45 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
     };
     auto put = [&](Batch<S, U>& b) {
         if (WALK::HALVES) asm volatile("" : "+v"(b.edge)::"memory");      // read behind the next batch's loads, and not in front of them
+        const Buffer to = buffer(b.to, b.room);
+        const int copies = b.r < w.s.nshards ? io.copies(b.r) : 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             b.v[u][0] = finish(b, u);
-            // Used here, in front of the branch: where the compiler sees a path on which a load is never waited for, it
-            // drains the memory pipeline before the register is loaded again.
-            asm volatile("" ::"v"(b.v[u][0]));
+            st16(to, at[u], b.v[u][0]);
         }
-        if (b.limit >= (int32_t)((((U - 1) * w.nw) << 10) + 1008)) {      // whole units
-            for (int d = 0; d < io.copies(b.r); ++d)
+        for (int d = 1; d < copies; ++d) {
+            const Buffer other = buffer(io.out(b.r, d) + (b.to - io.out(b.r, 0)), b.room);
 #pragma unroll
-                for (int u = 0; u < U; ++u) st16(io.out(b.r, d) + b.off + offset(at[u]), b.v[u][0]);
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if ((int32_t)at[u] <= b.limit)
-                    for (int d = 0; d < io.copies(b.r); ++d) st16(io.out(b.r, d) + b.off + offset(at[u]), b.v[u][0]);
+            for (int u = 0; u < U; ++u) st16(other, at[u], b.v[u][0]);
         }
     };
-    Batch<S, U> b0, b1;
-    fetch(b0);
-    w.next(U);
-    while (w.more) {
-        fetch(b1);
-        put(b0);
-        w.next(U);
-        fetch(b0);          // behind the end: empty
-        put(b1);
-        w.next(U);
-    }
-    put(b0);
+    // NB - 1 batches are in flight while one is added and stored.  Behind the end: empty ones.
+    Batch<S, U> b[NB];
+#pragma unroll
+    for (int i = 0; i < NB - 1; ++i) fetch(b[i]);
+    while (while_true([&](auto i) {
+        constexpr int I = decltype(i)::value;
+        fetch(b[(I + NB - 1) % NB]);
+        put(b[I]);
+        return b[(I + 1) % NB].r < w.s.nshards;
+    }, std::make_integer_sequence<int, NB>{})) {}
 }
 
 // Many sources: a unit's sources are loaded in NG groups, and while one group is added the NB - 1 behind it (of this unit, then
 // of the next one) are in flight.  The registers of NB groups.
 template <int DT, int S, int NG, int NB, bool STREAM, class IO>
 __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32_t lane) {
-    static_assert(NG % NB == 0 && NB > 1, "a group's buffer is the same in every unit");
+    static_assert(NG % NB == 0 && (NB == 2 || NB == 3), "a group's buffer is the same in every unit");
     w.first();
-    if (!w.more) return;
+    if (!w.more()) return;
     const uint32_t lo = lane * 16;
     u32x4 buf[NB][(S + NG - 1) / NG];
-    // The unit that is loaded: its offset in a buffer, and the lane's in it.  Kept, as the compiler otherwise looks for the walk's end
-    // in front of each load: 16 x 1000003 bf16 at (32, 256, 64 KiB) 18.6 -> 16.2 us.
-    int64_t at;
-    uint32_t o;
-    auto clamp = [&]() { const uint32_t l = w.limit(); at = w.offset(); o = lo < l ? lo : l; };
+    uint32_t o = lo < w.last() ? lo : w.last();
     auto load = [&](auto g) {
         constexpr int G = decltype(g)::value % NG, FROM = S * G / NG, N = S * (G + 1) / NG - FROM;
 #pragma unroll
-        for (int s = 0; s < N; ++s) buf[G % NB][s] = ld16<STREAM>(io.src(FROM + s) + at + o);
+        for (int s = 0; s < N; ++s) buf[G % NB][s] = ld16<STREAM>(io.from(w, FROM + s) + o);
     };
     Acc<DT> acc;
     auto add = [&](auto g) {
@@ -424,37 +423,31 @@ __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32
 #pragma unroll
         for (int s = G == 0; s < N; ++s) acc.add(buf[G % NB][s]);
     };
-    int64_t off;
-    bool mine;
+    char* to;                                   // the unit that is added: where it goes, and its bytes
+    uint32_t room;
     auto pass = [&](auto g) {
         constexpr int G = decltype(g)::value;
         if (G + NB - 1 == NG) {                     // on to the next unit (behind the end: loads that nobody uses)
-            off = at;
-            mine = lo <= w.limit();
+            to = io.dst(0) + w.off;
+            room = w.room();
             w.next(1);
-            clamp();
+            o = lo < w.last() ? lo : w.last();
         }
         load(std::integral_constant<int, G + NB - 1>{});
         add(g);
         // Left alone, the compiler loads every group in front of the additions, into registers of its own: a later group's
         // addresses are therefore made to depend on the sums so far.
         if (NG > 2) acc.before(o);
+        return true;
     };
-    clamp();
     load(std::integral_constant<int, 0>{});
     if constexpr (NB > 2) load(std::integral_constant<int, 1>{});
-    static_assert(NB <= 3 && (NG == 2 || NG == 3 || NG == 6), "as written out here");
-    for (bool more = true; more; more = w.more) {
-        pass(std::integral_constant<int, 0>{});
-        pass(std::integral_constant<int, 1>{});
-        if constexpr (NG > 2) pass(std::integral_constant<int, 2>{});
-        if constexpr (NG > 3) { pass(std::integral_constant<int, 3>{}); pass(std::integral_constant<int, 4>{}); pass(std::integral_constant<int, 5>{}); }
+    do {
+        while_true(pass, std::make_integer_sequence<int, NG>{});
         const u32x4 r = acc.result();
-        if (mine) {
-            st16(io.dst(0) + off + lo, r);
-            for (int d = 1; d < io.ndst; ++d) st16(io.dst(d) + off + lo, r);
-        }
-    }
+        st16(buffer(to, room), lo, r);
+        for (int d = 1; d < io.ndst; ++d) st16(buffer(io.dst(d) + (to - io.dst(0)), room), lo, r);
+    } while (w.more());
 }
 
 // Any number of sources, up to four loads in flight: the steps of more than two sources of a fused launch.  The first group
@@ -462,8 +455,8 @@ __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32
 template <int DT, bool STREAM, class IO>
 __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc, uint32_t lane) {
     const uint32_t lo = lane * 16;
-    for (w.first(); w.more; w.next(1)) {
-        if (lo > w.limit()) continue;
+    for (w.first(); w.more(); w.next(1)) {
+        if (lo >= w.room()) continue;
         Acc<DT> acc;
         auto first = [&](auto n) {                // added in source order
             u32x4 x[decltype(n)::value];
@@ -484,7 +477,7 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
             acc.add(x0); acc.add(x1); acc.add(x2); acc.add(x3);
         }
         const u32x4 r = acc.result();
-        for (int d = 0; d < io.ndst; ++d) st16(io.dst(d) + w.offset() + lo, r);
+        for (int d = 0; d < io.ndst; ++d) st16(io.dst(d) + w.off + lo, r);
     }
 }
 
@@ -497,6 +490,9 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
 // eight-source reduce at (256, 512, 32 KiB) 13.6 -> 12.9.
 constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
+// Eight sources come in three batches: eight fp32 of 1000000 at (8, 128, 32 KiB) 69.6 -> 61.2 us, at 256 threads 44.8 -> 45.3; of fewer
+// sources a third one gains nothing.
+constexpr int batches(int S, bool deep) { return S == 8 && deep ? 3 : 2; }
 // The groups of move_groups (0: whole units).  With more than 256 threads a SIMD may hold two wavefronts of a channel, which fit
 // beside a product with up to 56 registers each.  Two whole halves of nine sources and more do not, and the channel then keeps its
 // compute unit from the product: makespan of three such reduces of 2 MiB sources beside 4096^3, us, halves -> three or six groups of
@@ -512,7 +508,7 @@ template <int DT, int S, bool STREAM, bool DEEP, class IO>
 __device__ __forceinline__ void move_reduce(const Walk<REDUCE>& w, const IO& io, uint32_t lane) {
     constexpr int NG = groups(DT, S, DEEP);
     if constexpr (NG > 0) move_groups<DT, S, NG, NG == 2 ? 2 : 3, STREAM>(w, io, lane);
-    else move_batches<DT, S, units_in_batch(S, DEEP), STREAM, false>(w, io, lane);
+    else move_batches<DT, S, units_in_batch(S, DEEP), batches(S, DEEP), STREAM, false>(w, io, lane);
 }
 
 // The channel of a buffer's last chunk moves what is left behind the last whole vector.
@@ -549,7 +545,7 @@ __device__ __forceinline__ void gather_copy_body(const CommArgs& p) {
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
     const GatherIo<KIND, decltype(src), decltype(dst)> io{src, dst, p.ndst};
-    move_batches<LAGOM_F32, 1, U, STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
+    move_batches<LAGOM_F32, 1, U, 2, STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
     if (KIND == GATHER) {
         if (p.nsrc == 1) copy_tail<uint8_t>(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
         return;
@@ -593,7 +589,7 @@ void launch_reduce(const CommArgs& a, dim3 grid, dim3 block, hipStream_t st) {
 // threads and 16 to 64 KiB got slower.  Half as many units where loads are streamed: up to 9 % slower at 64 KiB.
 int gather_units(const Shape& s, uint32_t nt) {
     int units = units_in_batch(1, nt <= kDeepNT);
-    const uint32_t nw = nt >> 6, mine = (s.full_units + nw - 1) / nw;
+    const uint32_t nw = nt >> 6, full_units = (s.full_bytes + 1023) >> 10, mine = (full_units + nw - 1) / nw;
     while (units > 1 && (uint32_t)units / 2 >= mine) units /= 2;
     return units;
 }
@@ -607,7 +603,7 @@ int gather_units(const Shape& s, uint32_t nt) {
 // 64 KiB) 37.9 -> 40.9, three (16, 192, 16 KiB) 53.4 -> 74.7, one (8, 64, 64 KiB) 184 -> 255.
 bool halves_pay(const Shape& s, uint32_t nt) {
     const uint32_t nw = nt >> 6;
-    return (s.shard_bytes & 2) && nw >= 4 && (nw & (nw - 1)) == 0 && s.full_units >= (nw > 8 ? 4 * nw : 32);
+    return (s.shard_bytes & 2) && nw >= 4 && (nw & (nw - 1)) == 0 && s.full_bytes > ((nw > 8 ? 4 * nw : 32) - 1) << 10;
 }
 
 template <WalkKind KIND, bool STREAM, int U>
@@ -653,11 +649,9 @@ static_assert(kMaxStepPtrs <= 256 && LAGOM_MAX_SRCS < 256 && LAGOM_MAX_DSTS < 25
 
 template <bool DEEP>
 struct StepsIo {                      // step r of the walk is step st + r of the launch
-    static constexpr bool SCALAR_OUT = !DEEP;
     const StepsArgs& p; uint32_t st;
-    __device__ __forceinline__ const char* from(const Walk<STEPS>& w, int s) const { return p.src(st + w.shard(), s) + w.offset(); }
-    template <bool STREAM> static __device__ __forceinline__ u32x4 load(const char* q) { return ld16<STREAM>(q); }
-    __device__ __forceinline__ int64_t to(const Walk<STEPS>& w) const { return w.offset(); }
+    __device__ __forceinline__ const char* from(const Walk<STEPS>& w, int s) const { return p.src(st + w.shard(), s) + w.off; }
+    __device__ __forceinline__ int64_t to(const Walk<STEPS>& w) const { return w.off; }
     __device__ __forceinline__ int copies(uint32_t r) const { return p.ndst(st + r); }
     __device__ __forceinline__ char* out(uint32_t r, int d) const { return p.dst(st + r, d); }
 };
@@ -683,13 +677,13 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const
         int run = 1;
         if (p.kind(st) == StepsArgs::kind_of(LAGOM_GATHER_COPY, 1)) {        // a plain copy to every destination
             run = steps_in_walk(p, st, U1, w);
-            move_batches<DT, 1, U1, STREAM, true>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+            move_batches<DT, 1, U1, 2, STREAM, true>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
         } else if (DT == LAGOM_BF16 && p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 1)) {     // (of fp32: a copy)
             run = steps_in_walk(p, st, U1, w);
-            move_batches<DT, 1, U1, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+            move_batches<DT, 1, U1, 2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
         } else if (p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 2)) {
             run = steps_in_walk(p, st, U2, w);
-            move_batches<DT, 2, U2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+            move_batches<DT, 2, U2, 2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
         } else {
             const auto src = [&p, st](int s) { return p.src(st, s); };
             const auto dst = [&p, st](int d) { return p.dst(st, d); };

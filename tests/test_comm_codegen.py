@@ -79,3 +79,14 @@ def test_gathers_of_shifted_shards_fit_beside_a_product_up_to_512_threads(comm, 
     assert len(kernels) == 2 * 2           # loads streamed or not; batches of four and of eight units
     for name, meta in kernels.items():
         assert _fits(meta, min(int(meta["max_flat_workgroup_size"]), 512), left_by_product[layout]), (name, meta["vgpr_count"], left_by_product)
+
+
+def test_walks_keep_to_scalar_registers(tmp_path):
+    """A store whose buffer the compiler holds in vector registers becomes a loop over that buffer's values, and scalars that do not fit
+    are written to lanes of vector registers: either costs a wavefront more instructions than the unit it moves."""
+    text = open(lb.device_assembly("comm_kernel.hip", str(tmp_path))).read()
+    bodies = re.findall(r"^(_ZN\S*(?:reduce_copy|gather_copy|gather_halves|comm_steps)_kernel\S*):(.*?)s_endpgm", text, re.S | re.M)
+    assert len(bodies) == 2 * (2 * 16 * 2 + 2 * 4) + 2 * 2 + 2 * 2 * 2
+    for name, body in bodies:
+        assert "v_writelane" not in body, name
+        assert "s_xor_b64 exec, exec" not in body, name          # how such a loop takes its lanes off

@@ -583,3 +583,27 @@ def test_fused_reduces_of_one_source_keep_loads_in_flight(dtype, cfg):
     count = (12 << 20) // (4 if dtype == "f32" else 2)
     copy, reduce = (_fused_us(dtype, op, 1, count, cfg) for op in (lg.LAGOM_GATHER_COPY, lg.LAGOM_REDUCE_COPY))
     assert reduce < 2.0 * copy, (reduce, copy)
+
+
+@pytest.mark.parametrize("op,nsrc,nbytes,cfg", [
+    ("gather", 1, (5 << 30) + 48, (64, 256, 1 << 20)),            # offsets beyond 32 bits
+    ("gather", 1, (5 << 29) + 16, (2, 512, 5 << 28)),             # chunks of more than 1 GiB, the last one short
+    ("gather", 3, (3 << 29) + 2, (64, 256, 3 << 20)),             # shards off the 16-byte grid, the last beyond 2^31 of the destination
+    ("reduce", 2, (5 << 29) + 16, (128, 256, 16 << 20)),
+    ("reduce", 9, (9 << 28) + 4, (256, 128, 1 << 30)),            # in halves; more channels than chunks
+])
+def test_buffers_of_gigabytes(op, nsrc, nbytes, cfg):
+    count = nbytes // 2
+    srcs = [torch.randint(0, 256, (nbytes,), dtype=torch.uint8, device="cuda").view(torch.int16) for _ in range(nsrc)]
+    if op == "reduce":                                            # multiples of 1/4 below 64: sums are exact in any order
+        srcs = [(x.bitwise_and(255).to(torch.bfloat16) / 4).view(torch.int16) for x in srcs]
+    dst = torch.zeros(count * (nsrc if op == "gather" else 1) + 8, dtype=torch.int16, device="cuda")
+    lg.lagom_comm_kernel(lg.LAGOM_GATHER_COPY if op == "gather" else lg.LAGOM_REDUCE_COPY, lg.LAGOM_BF16, srcs, [dst], count, cfg, torch.cuda.current_stream())
+    if op == "gather":
+        for s, src in enumerate(srcs):
+            assert torch.equal(dst[s * count:(s + 1) * count], src)
+    else:
+        for at in range(0, count, 1 << 28):
+            part = [x[at:at + (1 << 28)].view(torch.bfloat16).float() for x in srcs]
+            assert torch.equal(dst[:count][at:at + (1 << 28)].view(torch.bfloat16), sum(part[1:], part[0]).to(torch.bfloat16))
+    assert not dst[-8:].any()
