@@ -405,7 +405,7 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
 // of the next one) are in flight.  The registers of NB groups.
 template <int DT, int S, int NG, int NB, bool STREAM, class IO>
 __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32_t lane) {
-    static_assert(NG % NB == 0 && (NB == 2 || NB == 3), "a group's buffer is the same in every unit");
+    static_assert(NG % NB == 0 && NB > 1, "a group's buffer is the same in every unit");
     w.first();
     if (!w.more()) return;
     const uint32_t lo = lane * 16;
@@ -415,6 +415,7 @@ __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32
         constexpr int G = decltype(g)::value % NG, FROM = S * G / NG, N = S * (G + 1) / NG - FROM;
 #pragma unroll
         for (int s = 0; s < N; ++s) buf[G % NB][s] = ld16<STREAM>(io.from(w, FROM + s) + o);
+        return true;
     };
     Acc<DT> acc;
     auto add = [&](auto g) {
@@ -440,8 +441,7 @@ __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32
         if (NG > 2) acc.before(o);
         return true;
     };
-    load(std::integral_constant<int, 0>{});
-    if constexpr (NB > 2) load(std::integral_constant<int, 1>{});
+    while_true(load, std::make_integer_sequence<int, NB - 1>{});
     do {
         while_true(pass, std::make_integer_sequence<int, NG>{});
         const u32x4 r = acc.result();
@@ -498,16 +498,24 @@ constexpr int batches(int S, bool deep) { return S == 8 && deep ? 3 : 2; }
 // compute unit from the product: makespan of three such reduces of 2 MiB sources beside 4096^3, us, halves -> three or six groups of
 // which three are in flight: 9 fp32 sources at (32, 512, 64 KiB) 115 -> 93 ([N,K]), 117 -> 95 ([K,N]); 16 bf16 131 -> 95, 134 -> 96; 12
 // fp32 at (8, 384, 256 KiB) 186 -> 146, 187 -> 147.  Alone 0.8 to 1.0 of the time, 1.03 at worst (9 fp32 at (8, 384, 256 KiB)).
+// Up to 256 threads: from ten sources on six groups, of which five are in flight.  us, halves -> this, sources of 1000000 at (8, NT, 32 KiB):
+// twelve bf16, NT 64 128 -> 122, 128 67.0 -> 63.5, 256 36.2 -> 33.5; sixteen fp32, 64 200 -> 185, 128 105.5 -> 98.2, 256 85.0 -> 83.8.  Of two whole units
+// there (up to twelve fit) nine sources are faster still (fp32, 128 98.6 -> 73.7; 90.0 in six groups), twelve bf16 are slower (74.5).
 constexpr int groups(int DT, int S, bool deep) {
-    if (S <= (deep ? 8 : 4)) return 0;
-    if (deep || S <= 8) return 2;
+    if (S <= (deep ? 9 : 4)) return 0;
+    if (deep) return 6;
+    if (S <= 8) return 2;
     return S <= (DT == LAGOM_F32 ? 11 : 9) ? 3 : 6;         // that many sources fit at a time
+}
+constexpr int groups_held(int DT, int S, bool deep) {
+    const int ng = groups(DT, S, deep);
+    return deep || ng == 2 ? ng : 3;
 }
 
 template <int DT, int S, bool STREAM, bool DEEP, class IO>
 __device__ __forceinline__ void move_reduce(const Walk<REDUCE>& w, const IO& io, uint32_t lane) {
     constexpr int NG = groups(DT, S, DEEP);
-    if constexpr (NG > 0) move_groups<DT, S, NG, NG == 2 ? 2 : 3, STREAM>(w, io, lane);
+    if constexpr (NG > 0) move_groups<DT, S, NG, groups_held(DT, S, DEEP), STREAM>(w, io, lane);
     else move_batches<DT, S, units_in_batch(S, DEEP), batches(S, DEEP), STREAM, false>(w, io, lane);
 }
 
