@@ -210,15 +210,15 @@ __device__ __forceinline__ uint32_t ragged_head(uint32_t r, int64_t shard_bytes)
 // every load and store, and the destinations' pointers loaded behind them, a unit of eight bf16 sources took 249 instructions, 105 of them
 // scalar, at five cycles each.  us, that -> this, sources of 1000000 elements at (8, NT, 32 KiB): eight bf16, NT 64 128 -> 92, 128 66.7
 // -> 50.8, 256 34.4 -> 25.3, 512 20.5 -> 19.9; six fp32, 128 74.2 -> 42.5, 256 39.0 -> 29.5; sixteen bf16, 128 110 -> 81, 256 57.0 -> 43.9;
-// two fp32, 64 37.1 -> 25.9; a gather of eight, 64 76.9 -> 55.3, 256 35.3 -> 32.8.  One shape of a hundred and fifty lost more than 3 %: two
-// destinations written by twenty channels of 2 MiB, 65 -> 68.
+// two fp32, 64 37.1 -> 25.9; a gather of eight, 64 76.9 -> 55.3, 256 35.3 -> 32.8.  (Two destinations
+// written by twenty channels of 256 threads and 2 MiB, ten shards of 1250232 bf16: 65 -> 62.)
 // STEPS: the walk of a reduce-copy taken nshards times, once for each of a run of steps.
 enum WalkKind { REDUCE, GATHER, GATHER_RAGGED, GATHER_HALVES, STEPS };
 constexpr bool is_ragged(WalkKind k) { return k == GATHER_RAGGED || k == GATHER_HALVES; }
 constexpr bool is_gather(WalkKind k) { return k == GATHER || is_ragged(k); }
 template <WalkKind KIND>
 struct Walk {
-    static constexpr bool RAGGED = is_ragged(KIND), HALVES = KIND == GATHER_HALVES;
+    static constexpr bool GATHERS = is_gather(KIND), RAGGED = is_ragged(KIND), HALVES = KIND == GATHER_HALVES;
     Shape s;
     uint32_t wave, nw;
     uint32_t c, r;                              // current chunk of the shard, shard (0 in a reduce-copy; the step of a run; behind the end s.nshards or more)
@@ -308,9 +308,9 @@ struct GatherIo {                               // shard r goes to r * shard_byt
     __device__ __forceinline__ char* out(uint32_t, int d) const { return dst(d); }
 };
 
-// f(0), f(1), ... with their numbers as constants, for as long as they return true.  (A loop that may be left from its middle is not unrolled.)
+// f(0), f(1), ... with their numbers as constants
 template <class F, int... I>
-__device__ __forceinline__ bool while_true(const F& f, std::integer_sequence<int, I...>) { return (f(std::integral_constant<int, I>{}) && ...); }
+__device__ __forceinline__ void for_each(const F& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 
 // A batch: U units of one chunk, S sources each.
 template <int S, int U>
@@ -379,26 +379,38 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         const Buffer to = buffer(b.to, b.room);
         const int copies = b.r < w.s.nshards ? io.copies(b.r) : 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            b.v[u][0] = finish(b, u);
-            st16(to, at[u], b.v[u][0]);
+        for (int u = 0; u < U; ++u) b.v[u][0] = finish(b, u);
+        if (WALK::GATHERS && copies == 2) {         // unit by unit: us, destination by destination -> this, ten shards of 1250232 bf16 at (256, 256, 2 MiB) 68.6 -> 62.3
+            const Buffer second = buffer(io.out(b.r, 1) + (b.to - io.out(b.r, 0)), b.room);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                st16(to, at[u], b.v[u][0]);
+                st16(second, at[u], b.v[u][0]);
+            }
+            return;
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) st16(to, at[u], b.v[u][0]);
         for (int d = 1; d < copies; ++d) {
             const Buffer other = buffer(io.out(b.r, d) + (b.to - io.out(b.r, 0)), b.room);
 #pragma unroll
             for (int u = 0; u < U; ++u) st16(other, at[u], b.v[u][0]);
         }
     };
-    // NB - 1 batches are in flight while one is added and stored.  Behind the end: empty ones.
+    // NB - 1 batches are in flight while one is added and stored.  Behind the end: empty ones.  The end is looked for once for all NB: a way
+    // out of the loop's middle shares a block with the way back, on which the compiler then drains the memory pipeline.
     Batch<S, U> b[NB];
 #pragma unroll
     for (int i = 0; i < NB - 1; ++i) fetch(b[i]);
-    while (while_true([&](auto i) {
-        constexpr int I = decltype(i)::value;
-        fetch(b[(I + NB - 1) % NB]);
-        put(b[I]);
-        return b[(I + 1) % NB].r < w.s.nshards;
-    }, std::make_integer_sequence<int, NB>{})) {}
+    while (w.more()) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            fetch(b[(i + NB - 1) % NB]);
+            put(b[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NB - 1; ++i) put(b[i]);
 }
 
 // Many sources: a unit's sources are loaded in NG groups, and while one group is added the NB - 1 behind it (of this unit, then
@@ -415,7 +427,6 @@ __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32
         constexpr int G = decltype(g)::value % NG, FROM = S * G / NG, N = S * (G + 1) / NG - FROM;
 #pragma unroll
         for (int s = 0; s < N; ++s) buf[G % NB][s] = ld16<STREAM>(io.from(w, FROM + s) + o);
-        return true;
     };
     Acc<DT> acc;
     auto add = [&](auto g) {
@@ -439,11 +450,10 @@ __device__ __forceinline__ void move_groups(Walk<REDUCE> w, const IO& io, uint32
         // Left alone, the compiler loads every group in front of the additions, into registers of its own: a later group's
         // addresses are therefore made to depend on the sums so far.
         if (NG > 2) acc.before(o);
-        return true;
     };
-    while_true(load, std::make_integer_sequence<int, NB - 1>{});
+    for_each(load, std::make_integer_sequence<int, NB - 1>{});
     do {
-        while_true(pass, std::make_integer_sequence<int, NG>{});
+        for_each(pass, std::make_integer_sequence<int, NG>{});
         const u32x4 r = acc.result();
         st16(buffer(to, room), lo, r);
         for (int d = 1; d < io.ndst; ++d) st16(buffer(io.dst(d) + (to - io.dst(0)), room), lo, r);
@@ -490,19 +500,30 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
 // eight-source reduce at (256, 512, 32 KiB) 13.6 -> 12.9.
 constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
-// Eight sources come in three batches: eight fp32 of 1000000 at (8, 128, 32 KiB) 69.6 -> 61.2 us, at 256 threads 44.8 -> 45.3; of fewer
-// sources a third one gains nothing.
-constexpr int batches(int S, bool deep) { return S == 8 && deep ? 3 : 2; }
+// Reductions of up to 256 threads: three batches.  us, two -> three, sources of 1000000 at (8, NT, 32 KiB): six fp32, NT 64 80.6 -> 76.6, 128 42.9 -> 40.7,
+// 256 29.6 -> 29.3, at (128, 128, 64 KiB) 9.1 -> 7.3; eight fp32, 64 111 -> 93.4, 128 59.8 -> 49.9; six bf16 of 4194304 at (32, 128, 32 KiB) 40.8 -> 38.3.
+// Of seven and eight bf16 sources three batches do not fit beside a product.  Copies gain nothing: a gather of eight 4 MiB shards at (256, 256, 32 KiB) 13.4 -> 13.8.
+constexpr int batches(int DT, int S, bool deep) { return deep && S <= (DT == LAGOM_F32 ? 8 : 6) ? 3 : 2; }
+// Units per batch where a wavefront has at most half a batch of them in a chunk: what a batch holds beyond them costs its loads' and stores'
+// time for nothing.  us, whole batches -> this: ring shares of four 554264 at (8, 1024, 16 KiB) fp32 103 -> 68.7, bf16
+// 56 -> 38.8; at (16, 1024, 16 KiB) two fp32 sources of 1625440 20.4 -> 14.6, one 24 -> 11.4.
+constexpr int few_units_in_batch(int S, bool deep) { return units_in_batch(S, deep) / 4 > 0 ? units_in_batch(S, deep) / 4 : 1; }
+template <int S, bool DEEP>
+__device__ __forceinline__ bool few_units(const Shape& s, uint32_t nw) {
+    constexpr int U = units_in_batch(S, DEEP);
+    return U > 1 && (s.full_bytes + 1023) >> 10 <= nw * (U / 2);
+}
 // The groups of move_groups (0: whole units).  With more than 256 threads a SIMD may hold two wavefronts of a channel, which fit
 // beside a product with up to 56 registers each.  Two whole halves of nine sources and more do not, and the channel then keeps its
 // compute unit from the product: makespan of three such reduces of 2 MiB sources beside 4096^3, us, halves -> three or six groups of
 // which three are in flight: 9 fp32 sources at (32, 512, 64 KiB) 115 -> 93 ([N,K]), 117 -> 95 ([K,N]); 16 bf16 131 -> 95, 134 -> 96; 12
 // fp32 at (8, 384, 256 KiB) 186 -> 146, 187 -> 147.  Alone 0.8 to 1.0 of the time, 1.03 at worst (9 fp32 at (8, 384, 256 KiB)).
-// Up to 256 threads: from ten sources on six groups, of which five are in flight.  us, halves -> this, sources of 1000000 at (8, NT, 32 KiB):
-// twelve bf16, NT 64 128 -> 122, 128 67.0 -> 63.5, 256 36.2 -> 33.5; sixteen fp32, 64 200 -> 185, 128 105.5 -> 98.2, 256 85.0 -> 83.8.  Of two whole units
-// there (up to twelve fit) nine sources are faster still (fp32, 128 98.6 -> 73.7; 90.0 in six groups), twelve bf16 are slower (74.5).
+// Up to 256 threads: six groups, of which five are in flight, or, of up to twelve fp32 sources, two whole units.  us, halves -> six groups |
+// whole units, sources of 1000000 at (8, NT, 32 KiB): nine bf16, NT 128 55.8 -> 51.4 | 54.7; twelve bf16, 64 128 -> 122 | 125, 128 67.0 -> 63.5 | 71.1, 256 36.2 ->
+// 33.5 | 41.9; ten fp32, 64 185 -> 173 | 120, 128 101 -> 90.9 | 66.4, 256 55.7 -> 54.7 | 56.0; twelve fp32, 64 189 -> 175 | 127, 128 104.5 -> 91.0 | 79.6, 256
+// 65.4 -> 65.3 | 66.6; sixteen fp32, 64 200 -> 185, 128 105.5 -> 98.2, 256 85.0 -> 83.8.
 constexpr int groups(int DT, int S, bool deep) {
-    if (S <= (deep ? 9 : 4)) return 0;
+    if (S <= (!deep ? 4 : DT == LAGOM_F32 ? 12 : 8)) return 0;
     if (deep) return 6;
     if (S <= 8) return 2;
     return S <= (DT == LAGOM_F32 ? 11 : 9) ? 3 : 6;         // that many sources fit at a time
@@ -516,7 +537,8 @@ template <int DT, int S, bool STREAM, bool DEEP, class IO>
 __device__ __forceinline__ void move_reduce(const Walk<REDUCE>& w, const IO& io, uint32_t lane) {
     constexpr int NG = groups(DT, S, DEEP);
     if constexpr (NG > 0) move_groups<DT, S, NG, groups_held(DT, S, DEEP), STREAM>(w, io, lane);
-    else move_batches<DT, S, units_in_batch(S, DEEP), batches(S, DEEP), STREAM, false>(w, io, lane);
+    else if (S <= 2 && few_units<S, DEEP>(w.s, w.nw)) move_batches<DT, S, few_units_in_batch(S, DEEP), 2, STREAM, false>(w, io, lane);
+    else move_batches<DT, S, units_in_batch(S, DEEP), batches(DT, S, DEEP), STREAM, false>(w, io, lane);
 }
 
 // The channel of a buffer's last chunk moves what is left behind the last whole vector.
@@ -655,7 +677,6 @@ struct StepsArgs {
 };
 static_assert(kMaxStepPtrs <= 256 && LAGOM_MAX_SRCS < 256 && LAGOM_MAX_DSTS < 256, "a step is packed in bytes");
 
-template <bool DEEP>
 struct StepsIo {                      // step r of the walk is step st + r of the launch
     const StepsArgs& p; uint32_t st;
     __device__ __forceinline__ const char* from(const Walk<STEPS>& w, int s) const { return p.src(st + w.shard(), s) + w.off; }
@@ -678,20 +699,31 @@ __device__ __forceinline__ int steps_in_walk(const StepsArgs& p, int st, uint32_
 
 template <int DT, bool STREAM, bool DEEP>
 __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const StepsArgs p) {
-    Walk<STEPS> w = make_walk<STEPS>(p.shape);
+    const Walk<STEPS> w = make_walk<STEPS>(p.shape);
     const uint32_t lane = threadIdx.x & 63;
-    constexpr int U1 = units_in_batch(1, DEEP), U2 = units_in_batch(2, DEEP);
+    auto walk = [&](int st, auto s, auto u, auto copy) {
+        constexpr int S = decltype(s)::value, U = decltype(u)::value;
+        // (As with the lane in move_batches: what every kind of walk needs of the wavefronts' number would be held for all of them at once.)
+        Walk<STEPS> mine = w;
+        asm volatile("" : "+s"(mine.nw), "+s"(mine.wave));
+        const int run = steps_in_walk(p, st, U, mine);
+        move_batches<DT, S, U, 2, STREAM, decltype(copy)::value>(mine, StepsIo{p, (uint32_t)st}, lane);
+        return run;
+    };
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, units_in_batch(1, DEEP)> u1{};
+    constexpr std::integral_constant<int, few_units_in_batch(1, DEEP)> f1{};
+    constexpr std::integral_constant<int, units_in_batch(2, DEEP)> u2{};
+    constexpr std::integral_constant<int, few_units_in_batch(2, DEEP)> f2{};
     for (int st = 0; st < p.nsteps;) {
         int run = 1;
         if (p.kind(st) == StepsArgs::kind_of(LAGOM_GATHER_COPY, 1)) {        // a plain copy to every destination
-            run = steps_in_walk(p, st, U1, w);
-            move_batches<DT, 1, U1, 2, STREAM, true>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+            run = few_units<1, DEEP>(p.shape, w.nw) ? walk(st, one, f1, std::true_type{}) : walk(st, one, u1, std::true_type{});
         } else if (DT == LAGOM_BF16 && p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 1)) {     // (of fp32: a copy)
-            run = steps_in_walk(p, st, U1, w);
-            move_batches<DT, 1, U1, 2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+            run = few_units<1, DEEP>(p.shape, w.nw) ? walk(st, one, f1, std::false_type{}) : walk(st, one, u1, std::false_type{});
         } else if (p.kind(st) == StepsArgs::kind_of(LAGOM_REDUCE_COPY, 2)) {
-            run = steps_in_walk(p, st, U2, w);
-            move_batches<DT, 2, U2, 2, STREAM, false>(w, StepsIo<DEEP>{p, (uint32_t)st}, lane);
+            run = few_units<2, DEEP>(p.shape, w.nw) ? walk(st, two, f2, std::false_type{}) : walk(st, two, u2, std::false_type{});
         } else {
             const auto src = [&p, st](int s) { return p.src(st, s); };
             const auto dst = [&p, st](int d) { return p.dst(st, d); };

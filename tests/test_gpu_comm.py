@@ -607,3 +607,13 @@ def test_buffers_of_gigabytes(op, nsrc, nbytes, cfg):
             part = [x[at:at + (1 << 28)].view(torch.bfloat16).float() for x in srcs]
             assert torch.equal(dst[:count][at:at + (1 << 28)].view(torch.bfloat16), sum(part[1:], part[0]).to(torch.bfloat16))
     assert not dst[-8:].any()
+
+
+@pytest.mark.parametrize("nt", [64, 256, 1024])
+@pytest.mark.parametrize("count", [8 * 1024, 40 * 1024 + 8, 40 * 1024 + 4, 70 * 1024 + 3])     # on the 16-byte grid, off it, an odd number of halves
+def test_gather_copy_into_several_destinations(nt, count):
+    shards = _sources("bf16", 3, count, 1700)
+    for chunk, nc in [(16384, 2), (32 * 1024, 3), (1 << 20, 8)]:
+        for ndst in (2, 3):
+            for got in _run(lg.LAGOM_GATHER_COPY, "bf16", shards, ndst, (nc, nt, chunk), 3 * count):
+                assert same_bits(got, np.concatenate(shards)), (chunk, nc, ndst)
