@@ -493,11 +493,10 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
 
 // How much a lane keeps in flight.  A GEMM workgroup of large tiles leaves 120 registers of a SIMD ([N,K]) or 112 ([K,N]) to
 // the wavefronts beside it.  A channel of up to kDeepNT threads (one wavefront per SIMD) may use them all; with more threads
-// the wavefronts of a SIMD share them, and their number keeps the memory pipeline busy instead.  One memory latency per batch, the previous form
-// -> this one, us (data in the last-level cache): 64 MiB gather-copy at (8, 256, 2 MiB) 138.5 -> 86.3; 12 MiB two-source fp32
-// reduce at (4, 256, 128 KiB) 55.1 -> 33.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 16.2 (there
-// one source at a time in flight before); a ring share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 61.1; 72 MiB
-// eight-source reduce at (256, 512, 32 KiB) 13.6 -> 12.9.
+// the wavefronts of a SIMD share them, and their number keeps the memory pipeline busy instead.  One memory latency per batch ->
+// loads in flight while a batch is stored -> with the walk's short steps, us: 64 MiB gather-copy at (8, 256, 2 MiB) 138.5 -> 87.8 -> 81.8; 12 MiB
+// two-source fp32 reduce at (4, 256, 128 KiB) 55.1 -> 32.6 -> 32.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 16.2 -> 13.1; a ring
+// share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 61.6 -> 58.8; 72 MiB eight-source reduce at (256, 512, 32 KiB) 13.6 -> 13.1 -> 13.0.
 constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
 // Reductions of up to 256 threads: three batches.  us, two -> three, sources of 1000000 at (8, NT, 32 KiB): six fp32, NT 64 80.6 -> 76.6, 128 42.9 -> 40.7,
