@@ -501,7 +501,9 @@ constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
 // Reductions of up to 256 threads: three batches.  us, two -> three, sources of 1000000 at (8, NT, 32 KiB): six fp32, NT 64 80.6 -> 76.6, 128 42.9 -> 40.7,
 // 256 29.6 -> 29.3, at (128, 128, 64 KiB) 9.1 -> 7.3; eight fp32, 64 111 -> 93.4, 128 59.8 -> 49.9; six bf16 of 4194304 at (32, 128, 32 KiB) 40.8 -> 38.3.
-// Of seven and eight bf16 sources three batches do not fit beside a product.  Copies gain nothing: a gather of eight 4 MiB shards at (256, 256, 32 KiB) 13.4 -> 13.8.
+// Of seven and eight bf16 sources three batches do not fit beside a product.  Gathers of whole shards
+// in batches of eight units take three as well: six layers' gathers on 8 channels beside products of 2176 x 3328 x 1408 418 -> 409 us, eight 4 MiB shards
+// at (32, 256, 64 KiB) 24.2 -> 23.7.
 constexpr int batches(int DT, int S, bool deep) { return deep && S <= (DT == LAGOM_F32 ? 8 : 6) ? 3 : 2; }
 // Units per batch where a wavefront has at most half a batch of them in a chunk: what a batch holds beyond them costs its loads' and stores'
 // time for nothing.  us, whole batches -> this: ring shares of four 554264 at (8, 1024, 16 KiB) fp32 103 -> 68.7, bf16
@@ -574,7 +576,7 @@ __device__ __forceinline__ void gather_copy_body(const CommArgs& p) {
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
     const GatherIo<KIND, decltype(src), decltype(dst)> io{src, dst, p.ndst};
-    move_batches<LAGOM_F32, 1, U, 2, STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
+    move_batches<LAGOM_F32, 1, U, KIND == GATHER && U == units_in_batch(1, true) ? 3 : 2, STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
     if (KIND == GATHER) {
         if (p.nsrc == 1) copy_tail<uint8_t>(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
         return;
