@@ -1065,7 +1065,13 @@ __device__ __forceinline__ void split_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NJ; ++j) {
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // Where the compiler sees constants it takes the loop's vectors apart into single registers and puts each together again for
+            // the next slice: 64 x 64 tiles then took up to 252 registers (now 152 - 172), and large tiles with such pieces behind
+            // them 428 (now 388 and 396, like the other large ones), which channels beside a product did not fit with.
+            asm volatile("" : "+v"(acc[i][j]));
+        }
     u32x4 fa[2][MI], fb[2][NJ];
     auto read = [&](int set) {
         const u32x4* sa = reinterpret_cast<const u32x4*>(mine + set * SET_BYTES);
