@@ -68,7 +68,6 @@ struct GemmArgs {
     int64_t M, N, K;
     int32_t tiles_m, tiles_n;
     int32_t rows;               // of the blocks that the list of tiles runs through (tile_in_list); 0: the list in columns of 8, XCDs in turn
-    int32_t cached;             // how C is stored (store_c)
 };
 
 __device__ __forceinline__ uint32_t bf16_round_bits(float f) {
@@ -269,23 +268,6 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
         }
 }
 
-// 16 bytes of a row of C on the 16-byte grid, past the L2s or into them (a rule of the sizes: cached_stores).  BY_SIZE: empty asm on both
-// sides, as the compiler otherwise makes one store of the two, without the hint.  (The choice per store costs 8192 x 8192 x 8192 1 %, one
-// for eight stores or for the whole epilogue no less: the tilings whose rounds are all alike have kernels of their own.)
-enum Stores { PAST_L2, INTO_L2, BY_SIZE };       // the last where a kernel serves both: it reads GemmArgs.cached
-template <Stores STORES>
-__device__ __forceinline__ void store_c(char* out, u32x4 val, bool cached) {
-    if (STORES == INTO_L2) {
-        *reinterpret_cast<u32x4*>(out) = val;
-    } else if (STORES == BY_SIZE && cached) {
-        asm volatile("" ::: "memory");
-        *reinterpret_cast<u32x4*>(out) = val;
-        asm volatile("" ::: "memory");
-    } else {
-        __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(out));
-    }
-}
-
 // Clears an operand fragment in the lanes that do not keep theirs.
 template <class FRAG>
 __device__ __forceinline__ void keep_frag(FRAG& f, bool keep) {
@@ -308,7 +290,7 @@ typedef __attribute__((address_space(3))) char* lds_bytes;
 // B_KN = false: B stored [N,K]; true: B stored [K,N], its tiles kept in LDS as 64 rows (k) of 256 columns
 // and transposed by the LDS reads.
 // K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64, behind the start of the one before it.
-template <bool B_KN, bool OUT_BF16, bool K_TAIL, Stores STORES>
+template <bool B_KN, bool OUT_BF16, bool K_TAIL>
 __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn) {
     extern __shared__ u32x4 smem[];   // LDS_SLOTS operand tiles of 2048 16-byte slots
     // Wavefronts of a communication kernel may share this wavefront's SIMD (this kernel leaves them
@@ -559,7 +541,7 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     const int r_in = lane & 15, c_q = 4 * (lane >> 4);
     char* st = reinterpret_cast<char*>(smem) + wave * SLOT_BYTES;
     const bool interior = m0 + BM <= M && n0 + BN <= N;
-    const bool vector_ok = (N % VEC) == 0, cached = STORES == BY_SIZE && p.cached != 0;
+    const bool vector_ok = (N % VEC) == 0;
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
     const int64_t gcol = n0 + wn * 128 + rd_cv * VEC;
 #pragma unroll
@@ -592,12 +574,16 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
                 const int r = rd_row + ROWS_PER_READ * (tb * 8 + e);
                 val[e] = *reinterpret_cast<const u32x4*>(st + r * ROW_BYTES + ((rd_cv ^ (r & 15)) << 4));
             }
+            // Past the L2s, also where rows of C are off the 64-byte grid and two wavefronts write parts of a line.  Into them such products
+            // alone are faster (5000 x 5080 x 512 fp32 45 -> 42 us over 16 results, 37 over one), but rows on the grid lose (6400 x 5632 x 2056
+            // fp32 132 -> 144, 8192 x 8448 x 256 fp32 73 -> 81), and what runs beside a product finds its data gone from the last-level
+            // cache: a 64 MiB gather on 8 channels beside three of 5000 x 5080 x 512 fp32 166 -> 253.
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int64_t grow = row0 + ROWS_PER_READ * (tb * 8 + e);
                 char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
                 if (vector_ok) {
-                    if (interior || (grow < M && gcol < N)) store_c<STORES>(out, val[e], cached);
+                    if (interior || (grow < M && gcol < N)) __builtin_nontemporal_store(val[e], reinterpret_cast<u32x4*>(out));
                 } else if (grow < M) {
                     store_ragged<OUT_BF16>(out, val[e], N - gcol);
                 }
@@ -607,24 +593,14 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false, PAST_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false, PAST_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
 // K >= 64 and not a multiple of 64 (kernels of their own: the peeled last step clears fragments; as many registers)
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true, PAST_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true, PAST_L2>(p, tm, tn); }
-
-// C stored into the L2s
-template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false, INTO_L2>(p, tm, tn); }
-template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false, INTO_L2>(p, tm, tn); }
-template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true, INTO_L2>(p, tm, tn); }
-template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true, INTO_L2>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- small-tile kernels
 // 128 x 128 x 64 and 256 x 128 x 64 tiles for products with too few 256 x 256 tiles to fill the chip.
@@ -650,7 +626,7 @@ constexpr int SBM = SmallTile<4>::BM_, MBM = SmallTile<8>::BM_;
 __device__ __forceinline__ int kn_swz128(int k) { return (((k >> 3) & 1) << 3) | ((k & 3) << 1); }
 
 // K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64 (see the large kernel).
-template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL, Stores STORES = PAST_L2>
+template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL>
 __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int tn) {
     typedef SmallTile<NI> T;
     constexpr int S_STAGES = T::STAGES, S_AHEAD = T::AHEAD, S_STAGE_BYTES = T::STAGE_BYTES, S_OPERAND_BYTES = T::A_BYTES;
@@ -891,7 +867,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         const int64_t grow = row0 + ROWS_PER_READ * e;
         char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
         if (vector_ok) {
-            if (interior || (grow < M && gcol < N)) store_c<STORES>(out, val, false);
+            if (interior || (grow < M && gcol < N)) __builtin_nontemporal_store(val, reinterpret_cast<u32x4*>(out));
         } else if (grow < M) {
             store_ragged<OUT_BF16>(out, val, N - gcol);
         }
@@ -916,12 +892,6 @@ template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, OUT_BF16, true>(p, tm, tn); }
-
-// fp32 results stored into the L2s (bf16 ones of one round of these tiles, and any of 128 x 128 tiles, are too small for that: 16 MiB)
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, false, false, INTO_L2>(p, tm, tn); }
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_cached_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, false, false, INTO_L2>(p, tm, tn); }
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, false, true, INTO_L2>(p, tm, tn); }
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_cached_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, false, true, INTO_L2>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- large tiles, the last round in small ones
 // A product of more than 256 large tiles runs in rounds of 256 (one per compute unit), and the last round costs as much
@@ -950,7 +920,7 @@ __device__ __forceinline__ void mixed_gemm_body(const MixedArgs& p) {
     else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
     else { tm = p.full_m; tn = lin - inside - right; }
     if (large) {
-        fast_gemm_body<B_KN, OUT_BF16, K_TAIL, BY_SIZE>(p.g, tm, tn);
+        fast_gemm_body<B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
         return;
     }
     if (lin >= p.g.tiles_m * p.g.tiles_n) return;
@@ -1196,7 +1166,7 @@ __device__ __forceinline__ void pieces_gemm_body(const PiecesArgs& p) {
         if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, 8, &tm, &tn);
         else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
         else { tm = p.full_m; tn = lin - inside - right; }
-        fast_gemm_body<B_KN, OUT_BF16, K_TAIL, BY_SIZE>(p.g, tm, tn);
+        fast_gemm_body<B_KN, OUT_BF16, K_TAIL>(p.g, tm, tn);
         return;
     }
     constexpr int A = kPiecesAcross;
@@ -1284,22 +1254,6 @@ Block split_block(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile
     const bool m_first = tiles_m <= tiles_n;
     const int64_t inner = m_first ? tiles_m : tiles_n, in = inner < n ? inner : n, across = (n + in - 1) / in;
     return {(int32_t)(m_first ? tiles_m : 1), m_first ? in : across, m_first ? across : in};
-}
-
-// Whether a tiled product stores C into the L2s (8 x 4 MiB) instead of past them.  Into them: where rows of C are off the 128-byte grid the
-// lines that two wavefronts share are put together there, and where the product goes on for a while the L2 takes a tile at once
-// and writes it back under later ones' loops.  Past them: what is in the L2s when the kernel ends is written back then, while
-// nothing else runs, and with bf16 results and a long K the panels of A and B need the place more.  us, past -> into:
-//   rows off the grid    3000 x 2600 x 512 fp32 17.1 -> 14.8, 3800 x 3900 x 1024 fp32 36.6 -> 32.4, 5000 x 5080 x 1024 54.6 -> 50.4, 3400 x 3400 x 256
-//                        fp32 18.1 -> 16.3, 4100 x 4200 x 2056 [K,N] fp32 77.3 -> 74.3; below 20 MiB 2100 x 2056 x 512 fp32 12.2 -> 13.1, 2749 x 3552 x
-//                        2648 53.5 -> 54.5
-//   on it, 48, 64 MiB    fp32 4096 x 4096 x 2048 58.6 -> 57.0, 8192 x 8192 x 1024 150 -> 140, x 4096 398 -> 390; bf16 6400 x 5632 x 128 25.1 -> 23.7, 8192 x
-//                        4096 x 1024 60.9 -> 59.7, but x 3072 144.7 -> 146.4 and x 4096 190 -> 192
-//   below                4096 x 4096 x 128 12.3 -> 13.7, 3072 x 3072 x 1024 fp32 25.6 -> 26.8, 2048 x 2048 x 512 fp32 9.8 -> 10.8
-bool cached_stores(int64_t M, int64_t N, int64_t K, int esize) {
-    const int64_t bytes = M * N * esize;
-    if (N * esize % 128) return bytes >= (int64_t)20 << 20;
-    return esize == 4 ? bytes >= (int64_t)48 << 20 : bytes >= (int64_t)64 << 20 && K <= 1024;
 }
 
 template <class T, bool B_KN, bool K_TAIL>
@@ -1453,7 +1407,7 @@ extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype 
     out->d_bytes = loads(bm, bn) + (double)bm * bn * out_bytes;
     out->tile_m = (int32_t)bm; out->tile_n = (int32_t)bn; out->threads = THREADS;
     const bool may_cut = tiling == TILE_256x256 && K >= BK && K <= FAST_MAX_K && M <= kMaxDim && N <= kMaxDim;
-    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn, 8, 0};
+    const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn, 8};
     MixedArgs mixed;
     const int quadrants = may_cut ? choose_mixed(a, &mixed) : 0;
     // the block of tiles an XCD works on at a time (32 compute units per XCD): n tiles in r tile-rows and c tile-columns need
@@ -1476,7 +1430,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (!b_is_nk && (N % 8)) return lagom::fail(LAGOM_EINVAL, "B stored [K,N] needs N to be a multiple of 8");
     const Tiling tiling = choose_tiling(M, N, K);
     if (const Split split = choose_split(M, N, K); split.launch) {
-        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0, 0, 0};
+        const GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K, 0, 0, 0};
         if (int rc = split.launch(a, b_is_nk != 0, out_dt == LAGOM_BF16, static_cast<hipStream_t>(hip_stream))) return rc;
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return lagom::fail(LAGOM_EHIP, "gemm launch: %s", hipGetErrorString(e));
@@ -1485,8 +1439,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
     if (tiling != TILE_256x256) {
         const int bm = tiling == TILE_128x128 ? SBM : MBM;
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0, 0};
-        a.cached = out_dt == LAGOM_F32 && tiling == TILE_256x128 && cached_stores(M, N, K, 4);
+                   (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0};
         a.rows = tile_block(a.tiles_m, a.tiles_n, bm, SBN, K).rows;
         const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1497,9 +1450,6 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         if (tiling == TILE_128x128) {
             if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk128_tail_kernel) : LAGOM_PICK(gemm_bf16_nk128_kernel);
             else rc = tail ? LAGOM_PICK(gemm_bf16_kn128_tail_kernel) : LAGOM_PICK(gemm_bf16_kn128_kernel);
-        } else if (a.cached) {               // fp32
-            if (b_is_nk) rc = tail ? launch_fast<gemm_bf16_nk256x128_cached_tail_kernel>(a, grid, st) : launch_fast<gemm_bf16_nk256x128_cached_kernel>(a, grid, st);
-            else rc = tail ? launch_fast<gemm_bf16_kn256x128_cached_tail_kernel>(a, grid, st) : launch_fast<gemm_bf16_kn256x128_cached_kernel>(a, grid, st);
         } else {
             if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk256x128_tail_kernel) : LAGOM_PICK(gemm_bf16_nk256x128_kernel);
             else rc = tail ? LAGOM_PICK(gemm_bf16_kn256x128_tail_kernel) : LAGOM_PICK(gemm_bf16_kn256x128_kernel);
@@ -1511,7 +1461,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         return LAGOM_OK;
     }
     GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
-               (int32_t)((M + BM - 1) / BM), (int32_t)((N + BN - 1) / BN), 0, cached_stores(M, N, K, lagom::elem_size(out_dt))};
+               (int32_t)((M + BM - 1) / BM), (int32_t)((N + BN - 1) / BN), 0};
     a.rows = tile_block(a.tiles_m, a.tiles_n, BM, BN, K).rows;
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > (1 << 30)) return lagom::fail(LAGOM_EINVAL, "too many tiles");
@@ -1540,17 +1490,14 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
 #undef LAGOM_PICK
         if (rc) return rc;
     } else if (fast) {
-        const bool tail = K % BK != 0;
         int rc;
-#define LAGOM_PICK(NAME) (bf ? launch_fast<NAME<true>>(a, grid, st) : launch_fast<NAME<false>>(a, grid, st))
-        if (a.cached) {
-            if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk_cached_tail_kernel) : LAGOM_PICK(gemm_bf16_nk_cached_kernel);
-            else rc = tail ? LAGOM_PICK(gemm_bf16_kn_cached_tail_kernel) : LAGOM_PICK(gemm_bf16_kn_cached_kernel);
+        if (K % BK == 0) {
+            if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_nk_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_nk_kernel<false>>(a, grid, st);
+            else rc = bf ? launch_fast<gemm_bf16_kn_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_kn_kernel<false>>(a, grid, st);
         } else {
-            if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk_tail_kernel) : LAGOM_PICK(gemm_bf16_nk_kernel);
-            else rc = tail ? LAGOM_PICK(gemm_bf16_kn_tail_kernel) : LAGOM_PICK(gemm_bf16_kn_kernel);
+            if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_nk_tail_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_nk_tail_kernel<false>>(a, grid, st);
+            else rc = bf ? launch_fast<gemm_bf16_kn_tail_kernel<true>>(a, grid, st) : launch_fast<gemm_bf16_kn_tail_kernel<false>>(a, grid, st);
         }
-#undef LAGOM_PICK
         if (rc) return rc;
     } else if (b_is_nk) {
         if (bf) hipLaunchKernelGGL((gemm_bf16_general_kernel<true, true>), grid, block, 0, st, a);

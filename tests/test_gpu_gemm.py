@@ -249,13 +249,13 @@ def test_gemm_last_round_in_quadrants_integer_inputs_are_exact(M, N, K, b_is_nk)
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
 
 
-@pytest.mark.parametrize("M,N,out", [(2304, 2312, "f32"),                         # 256 x 128 tiles, rows of C off the 128-byte grid, 20.3 MiB
+@pytest.mark.parametrize("M,N,out", [(2304, 2312, "f32"),                         # 256 x 128 tiles, rows of C off the 128-byte grid
                                      (3400, 3400, "bf16"), (3400, 3400, "f32"),   # 256 x 256 tiles
-                                     (3584, 3584, "f32"),                         # on the grid, 49 MiB
+                                     (3584, 3584, "f32"),                         # on the grid
                                      (8192, 4104, "bf16")])                       # off it, with quadrants behind the large tiles
 @pytest.mark.parametrize("K", [64, 136])
 @pytest.mark.parametrize("b_is_nk", [True, False])
-def test_gemm_results_stored_into_the_l2_integer_inputs_are_exact(M, N, out, K, b_is_nk):
+def test_gemm_large_results_integer_inputs_are_exact(M, N, out, K, b_is_nk):
     if not b_is_nk:
         N = (N + 7) // 8 * 8
     rng = np.random.default_rng(M + N + K)
