@@ -380,7 +380,9 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         const int copies = b.r < w.s.nshards ? io.copies(b.r) : 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) b.v[u][0] = finish(b, u);
-        if (WALK::GATHERS && copies == 2) {         // unit by unit: us, destination by destination -> this, ten shards of 1250232 bf16 at (256, 256, 2 MiB) 68.6 -> 62.3
+        // Unit by unit, from four wavefronts on.  us, destination by destination -> this: ten shards of 1250232 bf16 at (256, 256, 2 MiB) 68.6 -> 62.3,
+        // eight 4 MiB ones at (16, 256, 64 KiB) 62.5 -> 60.9, but at (256, 64, 32 KiB) 19.4 -> 20.9, (16, 128, 64 KiB) 60.5 -> 61.9.
+        if (WALK::GATHERS && copies == 2 && w.nw >= 4) {
             const Buffer second = buffer(io.out(b.r, 1) + (b.to - io.out(b.r, 0)), b.room);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
