@@ -90,9 +90,11 @@ __device__ __forceinline__ u32x4 ld16_ragged(const char* p) {
     if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_element_aligned*>(p));
     return *reinterpret_cast<const u32x4_element_aligned*>(p);
 }
-// Bytes [0, bytes) at p as a buffer: lanes beyond them store nothing, without a branch.
+// Bytes [0, bytes) at p as a buffer: lanes beyond them store nothing and load zeros, without a branch or an access to memory.
 typedef __amdgpu_buffer_rsrc_t Buffer;
 __device__ __forceinline__ Buffer buffer(char* p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000 /* raw, 32-bit data */); }
+template <bool STREAM>
+__device__ __forceinline__ u32x4 ld16(Buffer b, uint32_t at) { return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, STREAM ? 2 : 0)); }
 __device__ __forceinline__ void st16(Buffer b, uint32_t at, u32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, b, at, 0, 2 /* non-temporal */); }
 __device__ __forceinline__ void st16(char* p, u32x4 v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p)); }
 
@@ -334,6 +336,10 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
     uint32_t at[U];                             // a lane's offsets in a batch
 #pragma unroll
     for (int u = 0; u < U; ++u) at[u] = lane * 16 + ((u * w.nw) << 10);
+    // Whole shards on 128 channels and more, whose walks are short: nothing is read behind the walk's end.  us, the start of a shard read
+    // there -> this, bf16 at (256, 256, 32 KiB): three chunks a channel 9.8 -> 9.7, into two destinations 13.4 -> 12.9, eight 4 MiB shards
+    // into two 18.9 -> 17.6.  On few channels it costs more than it saves: eight 4 MiB shards at (8, 256, 2 MiB) 81.9 -> 87.5.
+    constexpr bool BOUNDED = STREAM && WALK::GATHERS && !WALK::RAGGED;
     auto fetch = [&](Batch<S, U>& b) {          // past the chunk's end its last vector is read again (and not stored)
         b.to = io.out(w.shard(), 0) + io.to(w);
         b.r = w.r;
@@ -351,6 +357,10 @@ __device__ __forceinline__ void move_batches(WALK w, const IO& io, uint32_t lane
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if constexpr (BOUNDED) {
+                b.v[u][0] = ld16<STREAM>(buffer(const_cast<char*>(from[0]), b.room), at[u]);
+                continue;
+            }
             const uint32_t o = at[u] < last ? at[u] : last;
 #pragma unroll
             for (int s = 0; s < S; ++s) b.v[u][s] = WALK::RAGGED ? ld16_ragged<STREAM>(from[s] + o) : ld16<STREAM>(from[s] + o);
@@ -503,9 +513,7 @@ constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
 // Reductions of up to 256 threads: three batches.  us, two -> three, sources of 1000000 at (8, NT, 32 KiB): six fp32, NT 64 80.6 -> 76.6, 128 42.9 -> 40.7,
 // 256 29.6 -> 29.3, at (128, 128, 64 KiB) 9.1 -> 7.3; eight fp32, 64 111 -> 93.4, 128 59.8 -> 49.9; six bf16 of 4194304 at (32, 128, 32 KiB) 40.8 -> 38.3.
-// Of seven and eight bf16 sources three batches do not fit beside a product.  Gathers of whole shards
-// in batches of eight units take three as well: six layers' gathers on 8 channels beside products of 2176 x 3328 x 1408 418 -> 409 us, eight 4 MiB shards
-// at (32, 256, 64 KiB) 24.2 -> 23.7.
+// Of seven and eight bf16 sources three batches do not fit beside a product.
 constexpr int batches(int DT, int S, bool deep) { return deep && S <= (DT == LAGOM_F32 ? 8 : 6) ? 3 : 2; }
 // Units per batch where a wavefront has at most half a batch of them in a chunk: what a batch holds beyond them costs its loads' and stores'
 // time for nothing.  us, whole batches -> this: ring shares of four 554264 at (8, 1024, 16 KiB) fp32 103 -> 68.7, bf16
@@ -572,13 +580,22 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) reduce_copy_kernel(cons
     reduce_tail<DT>(src, dst, S, p.ndst, p.shape.shard_bytes, p.shape.chunks);
 }
 
+// Gathers of whole shards in batches of eight units take three of them, but on 128 channels and more (streamed loads) only with up to three
+// wavefronts.  us, two -> three: six layers' gathers on 8 channels beside products of 2176 x 3328 x 1408 418 -> 409, eight 4 MiB shards at (16, 128, 64
+// KiB) 46.5 -> 41.4, (32, 256, 64 KiB) 24.2 -> 23.7, (256, 128, 32 KiB) 13.2 -> 12.7.  Three are walked at a time, with empty ones behind the end, and
+// with four wavefronts two are as fast: (256, 256, 32 KiB) 13.6 -> 13.9; with three chunks a channel 9.8 -> 11.0, nine at (128, 256, 32 KiB) 16.7 -> 17.4.
+template <WalkKind KIND, bool STREAM, int U>
+__device__ __forceinline__ bool three_batches(uint32_t nw) { return KIND == GATHER && U == units_in_batch(1, true) && (!STREAM || nw < 4); }
+
 // KIND GATHER: every shard starts 16-byte aligned in the destination (shard_bytes % 16 == 0, or a single shard).
 template <WalkKind KIND, bool STREAM, int U>
 __device__ __forceinline__ void gather_copy_body(const CommArgs& p) {
     const auto src = [&p](int s) { return p.src[s]; };
     const auto dst = [&p](int d) { return p.dst[d]; };
     const GatherIo<KIND, decltype(src), decltype(dst)> io{src, dst, p.ndst};
-    move_batches<LAGOM_F32, 1, U, KIND == GATHER && U == units_in_batch(1, true) ? 3 : 2, STREAM, true>(make_walk<KIND>(p.shape), io, threadIdx.x & 63);
+    const Walk<KIND> w = make_walk<KIND>(p.shape);
+    if (three_batches<KIND, STREAM, U>(w.nw)) move_batches<LAGOM_F32, 1, U, 3, STREAM, true>(w, io, threadIdx.x & 63);
+    else move_batches<LAGOM_F32, 1, U, 2, STREAM, true>(w, io, threadIdx.x & 63);
     if (KIND == GATHER) {
         if (p.nsrc == 1) copy_tail<uint8_t>(p.src[0], dst, p.ndst, p.shape.shard_bytes, p.shape.chunks);
         return;

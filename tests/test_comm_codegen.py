@@ -90,3 +90,13 @@ def test_walks_keep_to_scalar_registers(tmp_path):
     for name, body in bodies:
         assert "v_writelane" not in body, name
         assert "s_xor_b64 exec, exec" not in body, name          # how such a loop takes its lanes off
+
+
+def test_streamed_gathers_of_whole_shards_read_nothing_behind_the_end(tmp_path):
+    """Their walks are short, and the batches behind the end a large part of them: loads are bounded by the chunk, like the stores."""
+    text = open(lb.device_assembly("comm_kernel.hip", str(tmp_path))).read()
+    bodies = re.findall(r"^_ZN\S*gather_copy_kernelILNS_8WalkKindE1ELb([01])ELi(\d+)E\S*:(.*?)s_endpgm", text, re.S | re.M)
+    assert sorted((s, int(u)) for s, u, _ in bodies) == [(s, u) for s in "01" for u in (1, 2, 4, 8)]
+    for streamed, units, body in bodies:
+        assert ("global_load_dwordx4" in body) == (streamed == "0"), (streamed, units)
+        assert ("buffer_load_dwordx4" in body) == (streamed == "1"), (streamed, units)

@@ -617,3 +617,18 @@ def test_gather_copy_into_several_destinations(nt, count):
         for ndst in (2, 3):
             for got in _run(lg.LAGOM_GATHER_COPY, "bf16", shards, ndst, (nc, nt, chunk), 3 * count):
                 assert same_bits(got, np.concatenate(shards)), (chunk, nc, ndst)
+
+
+@pytest.mark.parametrize("nt", [64, 192, 256])
+@pytest.mark.parametrize("ndst", [1, 2, 3])
+def test_gather_copy_of_few_chunks_to_each_of_many_channels(nt, ndst):
+    """One to seven batches of a walk, a chunk each: whole ones, and with a last chunk of one vector."""
+    chunk, nc = 8 * (nt // 64) * 1024, 130
+    values = np.random.default_rng(1800 + nt).integers(0, 1 << 16, size=(2, 7 * nc * chunk // 4 + 8), dtype=np.uint16)      # bytes are moved: any pattern
+    for per_channel in (1, 2, 3, 4, 5, 7):
+        for e in (0, 8):
+            shard = per_channel * nc // 2 * (chunk // 2) + e
+            for P in (1, 2):
+                shards = [v[:shard] for v in values[:P]]
+                for got in _run(lg.LAGOM_GATHER_COPY, "bf16", shards, ndst, (nc, nt, chunk), P * shard):
+                    assert same_bits(got, np.concatenate(shards)), (per_channel, e, P)
