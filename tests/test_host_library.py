@@ -97,6 +97,18 @@ def test_geometry_of_the_block_of_tiles_that_an_xcd_works_on_from_k_above_512(M,
     assert g.d_bytes_past_l2 == (block[0] * tile[0] + block[1] * tile[1]) * K * 2 / n + tile[0] * tile[1] * 4
 
 
+@pytest.mark.parametrize("M,N,K,tile,n,block", [
+    (37, 240, 4048, (16, 32), 3, (3, 1)),             # 3 x 8 tiles: near-square blocks of 2 x 2 would read more
+    (208, 64, 6592, (16, 32), 4, (2, 2)),             # 13 x 2: as much
+    (768, 256, 8192, (32, 32), 24, (3, 8)),           # 24 x 8: 0.91 of it
+    (256, 128, 8192, (16, 32), 8, (4, 2)),            # 16 x 4: 0.8
+    (960, 600, 4096, (64, 64), 19, (4, 5))])          # 15 x 10: 0.72
+def test_split_products_take_blocks_where_they_read_at_most_four_fifths(M, N, K, tile, n, block):
+    g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
+    assert (g.tile_m, g.tile_n) == tile
+    assert g.d_bytes_past_l2 == (block[0] * tile[0] + block[1] * tile[1]) * K * 2 / n + tile[0] * tile[1] * 4
+
+
 def test_geometry_where_k_is_not_split():
     """K too short for the tile, or one tile more than a round holds."""
     for M, N, K in [(640, 640, 64), (1024, 1024, 256), (1025, 1024, 4096)]:
