@@ -145,11 +145,12 @@ int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int6
  *                                      over the workgroup's wavefronts
  *   else                               the smallest of 128 x 128, 256 x 128 and 256 x 256 of which at
  *                                      most 256 cover C, 256 x 256 if none does
- * What is left over behind whole rounds of 256 tiles of 256 x 256 runs as 128 x 128 quadrants where
- * they take at most two rounds ([K,N] with N > 2^23 apart): then mu counts the large tiles and the
- * quadrants that hold something, D and d_bytes_past_l2 are means over them, and tile_m x tile_n is the
- * large tile.  (Where it fits one round of 64 x 64 pieces and K > 256 a quadrant is up to four workgroups;
- * it is counted as one, for it takes the time of one round either way.)  Host only. */
+ * What is left over behind whole rounds of 256 tiles of 256 x 256 ([K,N] with N > 2^23 apart) runs as
+ * 64 x 64 pieces, K split over the workgroup's wavefronts, where K > 256 and they take at most one
+ * round, else as 128 x 128 quadrants where they take at most two: then mu counts the large tiles and
+ * the pieces or quadrants that hold something, D and d_bytes_past_l2 are means over them, and
+ * tile_m x tile_n is the large tile.  (The cost model takes workgroups to be alike: a round of
+ * pieces costs it a round of the mean, which is more than it takes.)  Host only. */
 typedef struct {
     int64_t mu;
     int32_t tb;

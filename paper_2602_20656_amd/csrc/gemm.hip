@@ -1415,11 +1415,28 @@ extern "C" int lagom_gemm_describe(int64_t M, int64_t N, int64_t K, lagom_dtype 
     const bool may_cut = tiling == TILE_256x256 && K >= BK && K <= FAST_MAX_K && M <= kMaxDim && N <= kMaxDim;
     const GemmArgs a{nullptr, nullptr, nullptr, M, N, K, (int32_t)tm, (int32_t)tn, 8};
     MixedArgs mixed;
-    const int quadrants = may_cut ? choose_mixed(a, &mixed) : 0;
+    PiecesArgs cut;
+    const bool pieces = may_cut && choose_pieces(a, &cut);
+    const int quadrants = may_cut && !pieces ? choose_mixed(a, &mixed) : 0;
     // the block of tiles an XCD works on at a time (32 compute units per XCD): n tiles in r tile-rows and c tile-columns need
     // r A panels and c B panels between them
-    const Block block = quadrants ? Block{8, tm < 8 ? tm : 8, (32 + (tm < 8 ? tm : 8) - 1) / (tm < 8 ? tm : 8)} : tile_block(tm, tn, bm, bn, K);
+    const Block block = quadrants || pieces ? Block{8, tm < 8 ? tm : 8, (32 + (tm < 8 ? tm : 8) - 1) / (tm < 8 ? tm : 8)} : tile_block(tm, tn, bm, bn, K);
     out->d_bytes_past_l2 = loads(block.high * bm, block.across * bn) / (double)at_a_time(tm * tn) + (double)bm * bn * out_bytes;
+    if (pieces) {      // means over the large tiles and the pieces; a tile's sixteen share its panels, and so does what an XCD takes of a strip
+        const double piece_out = (double)Piece::TM * Piece::TN * out_bytes;
+        const int64_t n = (cut.pieces + 7) / 8;
+        auto of_strip = [&](int64_t high) {      // pieces across, the other way
+            high = high < n ? high : n;
+            return loads(high * Piece::TM, (n + high - 1) / high * Piece::TN) / (double)n;
+        };
+        const double past_l2 = (cut.inside ? cut.inside * loads(BM, BN) / (kPiecesAcross * kPiecesAcross) : 0.0) +
+                               (cut.right ? cut.right * of_strip((int64_t)(cut.full_m - cut.first_right) * kPiecesAcross) : 0.0) +
+                               (cut.pieces > cut.inside + cut.right ? (cut.pieces - cut.inside - cut.right) * of_strip(cut.edge_m) : 0.0);
+        out->mu = cut.nlarge + cut.pieces;
+        auto mean = [&](double large, double all_pieces) { return (cut.nlarge * large + all_pieces + cut.pieces * piece_out) / (double)out->mu; };
+        out->d_bytes = mean(out->d_bytes, cut.pieces * loads(Piece::TM, Piece::TN));
+        out->d_bytes_past_l2 = mean(out->d_bytes_past_l2, past_l2);
+    }
     if (quadrants) {   // means over the large tiles and the quadrants that hold something; the four of a tile share its panels
         const double quadrant_out = (double)SBM * SBN * out_bytes;
         out->mu = mixed.nlarge + quadrants;

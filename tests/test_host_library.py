@@ -115,19 +115,35 @@ def test_geometry_where_k_is_not_split():
         assert lg.lagom_gemm_describe(M, N, K).tile_m == 128
 
 
-@pytest.mark.parametrize("M,N,large,quadrants", [
-    (4096, 4352, 256, 4 * 16),
-    (4100, 4200, 256, 65),          # 33 tiles left over: 16 + 17 at two edges, half or a quarter of each in C
-    (4096, 6144, 256, 4 * 128),
-    (3970, 4456, 256, 14 * 2 + 17 * 4 + 2),       # 16 x 18 tiles, 255 inside; 14 of the right edge's, the lower edge's and the corner
-    (4096, 6400, 400, 0)])          # 144 tiles left over are more than two rounds of quadrants: whole tiles
-def test_geometry_of_a_product_with_its_last_round_in_quadrants(M, N, large, quadrants):
-    K = 2048
+@pytest.mark.parametrize("M,N,K,large,quadrants", [
+    (4096, 4352, 256, 256, 4 * 16),
+    (4100, 4200, 256, 256, 65),          # 33 tiles left over: 16 + 17 at two edges, half or a quarter of each in C
+    (4096, 6144, 2048, 256, 4 * 128),
+    (3970, 4456, 2048, 256, 14 * 2 + 17 * 4 + 2),       # 16 x 18 tiles, 255 inside; 14 of the right edge's, the lower edge's and the corner
+    (4096, 6400, 2048, 400, 0)])         # 144 tiles left over are more than two rounds of quadrants: whole tiles
+def test_geometry_of_a_product_with_its_last_round_in_quadrants(M, N, K, large, quadrants):
     g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
     whole, quarter = (256 + 256) * K * 2 + 256 * 256 * 4, (128 + 128) * K * 2 + 128 * 128 * 4
     assert (g.tile_m, g.tile_n, g.threads, g.mu) == (256, 256, 256, large + quadrants)
     assert g.d_bytes == pytest.approx((large * whole + quadrants * quarter) / g.mu, rel=1e-12)
     assert g.d_bytes_past_l2 < g.d_bytes
+
+
+@pytest.mark.parametrize("M,N,large,pieces,panels", [
+    (4096, 4352, 256, 16 * 16, 16 * 16 * (256 + 256) / 16),               # whole tiles
+    (4100, 4200, 256, 64 * 2 + 66,                                        # strips two pieces wide and one high: 25 of a strip to an XCD
+     64 * 2 * (25 * 64 + 64) / 25 + 66 * (64 + 25 * 64) / 25),
+    (4352, 7704, 512, 15 * 4, 60 * (8 * 64 + 64) / 8),                    # 15 of the right edge's 17 tiles, one piece wide
+    (130, 66000, 256, 2 * 4 * 3, 24 * (3 * 64 + 64) / 3)])                # no tile inside C; the last two, three pieces high
+def test_geometry_of_a_product_with_its_last_round_in_pieces(M, N, large, pieces, panels):
+    K = 2048
+    g = lg.lagom_gemm_describe(M, N, K, lg.LAGOM_F32)
+    whole, piece = (256 + 256) * K * 2 + 256 * 256 * 4, (64 + 64) * K * 2 + 64 * 64 * 4
+    assert (g.tile_m, g.tile_n, g.threads, g.mu) == (256, 256, 256, large + pieces)
+    assert g.d_bytes == pytest.approx((large * whole + pieces * piece) / g.mu, rel=1e-12)
+    high = min(8, -(-M // 256))           # of the large tiles' block
+    past = ((high + -(-32 // high)) * 256 / 32 * large + panels) * K * 2 + 256 * 256 * 4 * large + 64 * 64 * 4 * pieces
+    assert g.d_bytes_past_l2 == pytest.approx(past / g.mu, rel=1e-12)
 
 
 def test_argument_errors_are_reported_before_any_gpu_work():
