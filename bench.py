@@ -164,13 +164,17 @@ def comm_bytes(launches):
 
 
 def gemm_kernel_name(geo, M, N, K):
-    """The kernel lagom_gemm dispatches for an [N,K] product (names as they appear in a kernel trace)."""
+    """The kernel lagom_gemm dispatches for an [N,K] product with a bf16 result (names as they appear in a kernel trace)."""
     if geo.tile_m * geo.tile_n <= 64 * 64:
         return "gemm_bf16_split_kernel"
     if K < 64 or K > 1 << 22:
         return "gemm_bf16_general_kernel"
     tiles = -(-M // geo.tile_m) * -(-N // geo.tile_n)
-    kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "" if geo.mu == tiles else "_mixed")
+    kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "")
+    if not kind and geo.mu != tiles:       # whole rounds of large tiles, and the rest in smaller ones: whose loads tell which
+        large = tiles // LAMBDA * LAMBDA
+        of_rest = (geo.mu * geo.d_bytes - large * ((256 + 256) * K * 2 + 256 * 256 * 2)) / (geo.mu - large)
+        kind = "_pieces" if of_rest < (128 + 128) * K * 2 else "_mixed"
     return f"gemm_bf16_nk{kind}{'_tail' if K % 64 else ''}_kernel"
 
 

@@ -208,3 +208,15 @@ def test_results_go_past_the_l2(assembly):
         body = body[:body.index(".Lfunc_end")]
         hinted = len(re.findall(r"^\s*global_store_dwordx4 .* nt\b", body, re.M))
         assert hinted >= (8 if "128" in sym else 32), (sym, hinted)
+
+
+@pytest.mark.parametrize("M,N,K,name", [
+    (512, 512, 512, "split"), (512, 512, 56, "general"), (1200, 1288, 320, "nk128"), (1200, 1288, 72, "nk128_tail"), (2048, 4096, 4096, "nk256x128"),
+    (4096, 4096, 4096, "nk"), (4096, 4096, 4104, "nk_tail"), (4096, 4352, 4096, "nk_pieces"), (4100, 4200, 2056, "nk_pieces_tail"),
+    (4096, 4352, 256, "nk_mixed"), (4096, 6144, 72, "nk_mixed_tail"), (4096, 6400, 4096, "nk")])
+def test_bench_names_the_kernel_that_runs(assembly, M, N, K, name):
+    import bench
+    from paper_2602_20656_amd import binding as lg
+    got = bench.gemm_kernel_name(lg.lagom_gemm_describe(M, N, K, lg.LAGOM_BF16), M, N, K)
+    assert got == f"gemm_bf16_{name}_kernel"
+    assert re.search(r"^\S*\d%sI?\S*:" % got, assembly, re.M)
