@@ -269,19 +269,23 @@ def test_gemm_large_results_integer_inputs_are_exact(M, N, out, K, b_is_nk):
 
 @pytest.mark.parametrize("M,N", [(4100, 4200),     # 17 + 16 tiles at two edges left over: 194 pieces, most of the tiles' empty
                                  (4096, 4352),     # 16 whole tiles, 256 pieces
-                                 (4352, 7704),     # one row of tiles behind two rounds, pieces 24 columns wide at its end
+                                 (4352, 7704),     # 15 of the right edge's tiles behind two rounds, pieces 24 columns wide
                                  (130, 66000), (66000, 136),     # no tile inside C
-                                 (4096, 4357)])    # 5 columns of the last pieces, rows off the 16-byte grid
+                                 (4096, 4101),     # pieces 5 columns wide, rows off the 16-byte grid
+                                 (4096, 4357)])    # as wide, 320 of them: quadrants
 @pytest.mark.parametrize("K", [264, 320])
 @pytest.mark.parametrize("b_is_nk", [True, False])
-def test_gemm_last_round_in_pieces_integer_inputs_are_exact(M, N, K, b_is_nk):
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+def test_gemm_last_round_in_pieces_integer_inputs_are_exact(M, N, K, b_is_nk, out):
     if not b_is_nk and N % 8:
         pytest.skip("[K,N] layout needs N % 8 == 0")
     rng = np.random.default_rng(M + N + K)
     a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
     b = rng.integers(-4, 5, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
-    got = _gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, "f32")
-    bad = np.argwhere(got != (a @ (b.T if b_is_nk else b)))
+    want = a @ (b.T if b_is_nk else b)
+    if out == "bf16":
+        want = oc.bf16_to_f32(oc.f32_to_bf16(want))
+    bad = np.argwhere(_gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), b_is_nk, out) != want)
     assert bad.size == 0, f"{len(bad)} wrong elements, first at {bad[0]}"
 
 
