@@ -205,7 +205,11 @@ def lib() -> C.CDLL:
                                           C.POINTER(lagom_sweep_point), C.c_int, C.POINTER(C.c_int64), C.POINTER(C.c_int32)]
         for name in EXPORTS:
             getattr(L, name)
-        from . import _marshal
+        try:
+            from . import _marshal
+        except ImportError as e:
+            raise ImportError(f"{LIB_PATH} is there, but the module _marshal beside it is not, or not for this Python: build both with "
+                              "`python -m paper_2602_20656_amd.build`") from e
         _marshal.bind(*(C.cast(f, C.c_void_p).value for f in (L.lagom_gemm, L.lagom_comm_kernel, L.lagom_comm_steps)), lagom_cfg)
         _lib, _launch = L, _marshal
     return _lib

@@ -1,4 +1,4 @@
-"""Builds liblagom.so (HIP kernels + host model/search + C ABI) for gfx950 and _marshal.so (its launches for Python), in-tree.
+"""Builds liblagom.so (HIP kernels + host model/search + C ABI) for gfx950 and the module _marshal (its launches for Python), in-tree.
 
     python -m paper_2602_20656_amd.build
 
@@ -17,10 +17,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblagom.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")          # the Python side of the launches, a module of its own: the library knows no Python
+# The Python side of the launches, a module of its own: the library knows no Python.  It holds this interpreter's object layouts, so
+# it carries its tag, without which any other would load it.
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["errors.cpp", "cost_model.cpp", "tune.cpp", "model_fill.cpp", "comm_kernel.hip", "gemm.hip", "overlap.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-CC = os.environ.get("CC", "gcc")
+CC = os.environ.get("CC", os.path.join(os.path.dirname(HIPCC), "amdclang"))
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
           "-Wall", "-Wno-unused-function"]
@@ -46,6 +48,9 @@ def build(verbose: bool = True) -> str:
             print(out)
     link = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     subprocess.check_call(link)
+    untagged = os.path.join(HERE, "_marshal.so")
+    if os.path.exists(untagged) and untagged != MARSHAL:       # of an earlier build
+        os.remove(untagged)
     subprocess.check_call([CC, "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter", "-I", sysconfig.get_paths()["include"],
                            "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.c"), "-o", MARSHAL])
     if verbose:

@@ -2,6 +2,10 @@
 
 No GPU: it is bound to recorders in place of the library's functions."""
 import ctypes as C
+import os
+import subprocess
+import sys
+import sysconfig
 from types import SimpleNamespace
 
 import numpy as np
@@ -131,3 +135,16 @@ def test_what_ctypes_refused_is_refused():
     with pytest.raises(lg.LagomError) as e:
         lg.lagom_comm_kernel(0, 0, [P[0]] * 65, P[1:2], 1, (1, 64, 16))
     assert e.value.code == lg.LAGOM_EINVAL
+
+
+def test_the_module_is_for_this_interpreter_only():
+    assert lg._launches().__file__.endswith("_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_without_the_module_the_error_names_the_build():
+    code = ("import sys; sys.modules['paper_2602_20656_amd._marshal'] = None\n"
+            "from paper_2602_20656_amd import binding\n"
+            "try: binding.lib()\n"
+            "except ImportError as e: assert 'python -m paper_2602_20656_amd.build' in str(e), e\n"
+            "else: raise AssertionError('loaded')")
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=120, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
