@@ -21,7 +21,8 @@ static comm_fn comm_call;
 static steps_fn steps_call;
 static PyObject *cfg_type, *data_ptr_name, *cuda_stream_name;
 
-/* Each: 1 if the object is one of the above, else 0 with no exception set. */
+/* Each: 1 if the object is one of the above, else 0, with no exception set but what ends the program (KeyboardInterrupt and its like, from
+ * an object's own code). */
 static int take_int(PyObject* o, long long lo, long long hi, long long* out) {
     int overflow;
     if (!PyLong_Check(o)) return 0;
@@ -50,7 +51,10 @@ static int take_address(PyObject* o, void** out) {
 }
 static int take_owned_address(PyObject* v, void** out) {         /* a new reference, or null with an exception */
     int ok;
-    if (!v) { PyErr_Clear(); return 0; }
+    if (!v) {
+        if (PyErr_ExceptionMatches(PyExc_Exception)) PyErr_Clear();
+        return 0;
+    }
     ok = take_address(v, out);
     Py_DECREF(v);
     return ok;
@@ -100,14 +104,19 @@ static int take_pointers(PyObject* o, void** out, int room, int* n) {
     return 1;
 }
 
+static PyObject* leave(void) {
+    if (PyErr_Occurred()) return NULL;
+    Py_RETURN_NONE;
+}
+
 static PyObject* gemm(PyObject* self, PyObject* const* a, Py_ssize_t n) {
     void *A, *B, *C, *stream;
     int64_t M, N, K;
     int nk, dt, rc;
     (void)self;
-    if (n != 9 || !gemm_call) Py_RETURN_NONE;
+    if (n != 9 || !gemm_call) return leave();
     if (!take_pointer(a[0], &A) || !take_pointer(a[1], &B) || !take_pointer(a[2], &C) || !take_int64(a[3], &M) || !take_int64(a[4], &N) ||
-        !take_int64(a[5], &K) || !take_int32(a[7], &dt) || !take_stream(a[8], &stream)) Py_RETURN_NONE;
+        !take_int64(a[5], &K) || !take_int32(a[7], &dt) || !take_stream(a[8], &stream)) return leave();
     nk = PyObject_IsTrue(a[6]);
     if (nk < 0) return NULL;
     Py_BEGIN_ALLOW_THREADS
@@ -123,9 +132,9 @@ static PyObject* comm_kernel(PyObject* self, PyObject* const* a, Py_ssize_t n) {
     int64_t count;
     lagom_cfg cfg;
     (void)self;
-    if (n != 7 || !comm_call) Py_RETURN_NONE;
+    if (n != 7 || !comm_call) return leave();
     if (!take_int32(a[0], &op) || !take_int32(a[1], &dt) || !take_pointers(a[2], srcs, ROOM, &nsrc) || !take_pointers(a[3], dsts, ROOM, &ndst) ||
-        !take_int64(a[4], &count) || !take_cfg(a[5], &cfg) || !take_stream(a[6], &stream)) Py_RETURN_NONE;
+        !take_int64(a[4], &count) || !take_cfg(a[5], &cfg) || !take_stream(a[6], &stream)) return leave();
     Py_BEGIN_ALLOW_THREADS
     rc = comm_call((lagom_op)op, (lagom_dtype)dt, (const void* const*)srcs, nsrc, dsts, ndst, count, &cfg, stream);
     Py_END_ALLOW_THREADS
@@ -140,15 +149,15 @@ static PyObject* comm_steps(PyObject* self, PyObject* const* a, Py_ssize_t n) {
     int64_t count;
     lagom_cfg cfg;
     (void)self;
-    if (n != 5 || !steps_call) Py_RETURN_NONE;
-    if (!take_int32(a[0], &dt) || (!PyList_CheckExact(a[1]) && !PyTuple_CheckExact(a[1]))) Py_RETURN_NONE;
+    if (n != 5 || !steps_call) return leave();
+    if (!take_int32(a[0], &dt) || (!PyList_CheckExact(a[1]) && !PyTuple_CheckExact(a[1]))) return leave();
     for (; nsteps < PySequence_Fast_GET_SIZE(a[1]); ++nsteps) {
         PyObject* s;
         lagom_comm_step* t = &steps[nsteps];
         int op = 0, ok;
-        if (nsteps >= ROOM) Py_RETURN_NONE;
+        if (nsteps >= ROOM) return leave();
         s = PySequence_Fast_GET_ITEM(a[1], nsteps);
-        if (!PyTuple_CheckExact(s) || PyTuple_GET_SIZE(s) != 3) Py_RETURN_NONE;
+        if (!PyTuple_CheckExact(s) || PyTuple_GET_SIZE(s) != 3) return leave();
         Py_INCREF(s);
         ok = take_int32(PyTuple_GET_ITEM(s, 0), &op);
         t->op = op;
@@ -159,9 +168,9 @@ static PyObject* comm_steps(PyObject* self, PyObject* const* a, Py_ssize_t n) {
         ok = ok && take_pointers(PyTuple_GET_ITEM(s, 2), &ptr[used], STEPS_ROOM - used, &t->ndst);
         if (ok) used += t->ndst;
         Py_DECREF(s);
-        if (!ok) Py_RETURN_NONE;
+        if (!ok) return leave();
     }
-    if (!take_int64(a[2], &count) || !take_cfg(a[3], &cfg) || !take_stream(a[4], &stream)) Py_RETURN_NONE;
+    if (!take_int64(a[2], &count) || !take_cfg(a[3], &cfg) || !take_stream(a[4], &stream)) return leave();
     Py_BEGIN_ALLOW_THREADS
     rc = steps_call((lagom_dtype)dt, steps, nsteps, count, &cfg, stream);
     Py_END_ALLOW_THREADS

@@ -105,6 +105,27 @@ def test_comm_steps_leaves_the_rest_to_ctypes(calls, steps):
     assert lg._launch.comm_steps(0, steps, 1, (1, 64, 16), None) is None and calls.got == []
 
 
+class Interrupted:
+    calls = 0
+
+    def data_ptr(self):
+        Interrupted.calls += 1
+        raise KeyboardInterrupt
+
+    cuda_stream = property(data_ptr)
+
+
+@pytest.mark.parametrize("call", [
+    lambda x: lg.lagom_gemm(x, P[1], P[2], 4, 4, 8), lambda x: lg.lagom_gemm(*P, 4, 4, 8, stream=x), lambda x: lg.lagom_comm_kernel(0, 0, [P[0], x], P[1:2], 1, (1, 64, 16)),
+    lambda x: lg.lagom_comm_steps(0, [(0, P[:1], [x])], 1, (1, 64, 16)), lambda x: lg.lagom_comm_steps(0, [(0, P[:1], P[1:2])], 1, (1, 64, 16), x)])
+def test_an_interrupt_is_no_wrong_argument(calls, call):
+    """It ends the call where it comes up, and the object is not asked again through ctypes."""
+    before = Interrupted.calls
+    with pytest.raises(KeyboardInterrupt):
+        call(Interrupted())
+    assert Interrupted.calls == before + 1 and calls.got == []
+
+
 class Shrinks:
     """data_ptr() empties the list it is in."""
     def __init__(self, inside):
