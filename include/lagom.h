@@ -130,6 +130,9 @@ int lagom_comm_steps(lagom_dtype dt, const lagom_comm_step* steps, int nsteps, i
  *   C : device, row-major [M,N], bf16 (round-to-nearest-even) or fp32 per out_dt.
  *   M, N, K >= 1; K a multiple of 8 (16-byte rows); [K,N] also needs N a multiple of 8;
  *   pointers 16-byte aligned.  Fastest when K is a multiple of 64; K < 64 takes a slow path.
+ *   The order in which an element's products are added depends on the sizes and on where the element lies
+ *   (a last round in pieces, see lagom_gemm_describe): results are the same from call to call, equal rows of
+ *   A may give rows of C that differ in the rounding of fp32 sums.
  * Enqueue only on hip_stream.  Errors: LAGOM_EINVAL, LAGOM_EALIGN, LAGOM_EHIP.
  */
 int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int64_t N, int64_t K,

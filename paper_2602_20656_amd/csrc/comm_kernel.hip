@@ -503,36 +503,47 @@ __device__ __forceinline__ void move_any(Walk<REDUCE> w, const IO& io, int nsrc,
     }
 }
 
-// How much a lane keeps in flight.  A GEMM workgroup of large tiles leaves 120 registers of a SIMD ([N,K]) or 112 ([K,N]) to
-// the wavefronts beside it.  A channel of up to kDeepNT threads (one wavefront per SIMD) may use them all; with more threads
-// the wavefronts of a SIMD share them, and their number keeps the memory pipeline busy instead.  One memory latency per batch ->
-// loads in flight while a batch is stored -> with the walk's short steps, us: 64 MiB gather-copy at (8, 256, 2 MiB) 138.5 -> 87.8 -> 81.8; 12 MiB
-// two-source fp32 reduce at (4, 256, 128 KiB) 55.1 -> 32.6 -> 32.0; sixteen sources of 1000003 bf16 at (32, 256, 64 KiB) 47.6 -> 16.2 -> 13.1; a ring
-// share of fourteen 3 MiB steps at (32, 256, 64 KiB) 159.6 -> 61.6 -> 58.8; 72 MiB eight-source reduce at (256, 512, 32 KiB) 13.6 -> 13.1 -> 13.0.
+// How much a lane keeps in flight: all that a product beside it leaves, 120 registers of a SIMD ([N,K]) or 112 ([K,N]), in
+// channels of up to kDeepNT threads, one wavefront per SIMD; half of that with more threads, whose number keeps the memory
+// pipeline busy instead.  us, one memory latency per batch -> loads in flight while a batch is stored -> with the walk's short
+// steps:
+//   64 MiB gather-copy at (8, 256, 2 MiB)                                  138.5 -> 87.8 -> 81.8
+//   12 MiB two-source fp32 reduce at (4, 256, 128 KiB)                      55.1 -> 32.6 -> 32.0
+//   sixteen sources of 1000003 bf16 at (32, 256, 64 KiB)                    47.6 -> 16.2 -> 13.1
+//   ring share of fourteen 3 MiB steps at (32, 256, 64 KiB)                159.6 -> 61.6 -> 58.8
+//   72 MiB eight-source reduce at (256, 512, 32 KiB)                        13.6 -> 13.1 -> 13.0
 constexpr int kDeepNT = 256;
 constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) : S == 2 ? (deep ? 4 : 2) : S <= 4 ? (deep ? 2 : 1) : 1; }
-// Reductions of up to 256 threads: three batches.  us, two -> three, sources of 1000000 at (8, NT, 32 KiB): six fp32, NT 64 80.6 -> 76.6, 128 42.9 -> 40.7,
-// 256 29.6 -> 29.3, at (128, 128, 64 KiB) 9.1 -> 7.3; eight fp32, 64 111 -> 93.4, 128 59.8 -> 49.9; six bf16 of 4194304 at (32, 128, 32 KiB) 40.8 -> 38.3.
-// Of seven and eight bf16 sources three batches do not fit beside a product.
+// Reductions of up to 256 threads: three batches, but two of seven and eight bf16 sources, of which three do not fit beside a
+// product.  us, two -> three, sources of 1000000 at (8, NT, 32 KiB):
+//   six fp32      NT 64 80.6 -> 76.6   128 42.9 -> 40.7   256 29.6 -> 29.3   at (128, 128, 64 KiB) 9.1 -> 7.3
+//   eight fp32    NT 64 111 -> 93.4    128 59.8 -> 49.9
+//   six bf16 of 4194304 at (32, 128, 32 KiB) 40.8 -> 38.3
 constexpr int batches(int DT, int S, bool deep) { return deep && S <= (DT == LAGOM_F32 ? 8 : 6) ? 3 : 2; }
-// Units per batch where a wavefront has at most half a batch of them in a chunk: what a batch holds beyond them costs its loads' and stores'
-// time for nothing.  us, whole batches -> this: ring shares of four 554264 at (8, 1024, 16 KiB) fp32 103 -> 68.7, bf16
-// 56 -> 38.8; at (16, 1024, 16 KiB) two fp32 sources of 1625440 20.4 -> 14.6, one 24 -> 11.4.
+// A quarter of the units per batch where a wavefront has at most half a batch of them in a chunk: what a batch holds beyond
+// them costs its loads' and stores' time for nothing.  us, whole batches -> this: ring shares of four 554264 at (8, 1024, 16
+// KiB) fp32 103 -> 68.7, bf16 56 -> 38.8; at (16, 1024, 16 KiB) two fp32 sources of 1625440 20.4 -> 14.6, one 24 -> 11.4.
 constexpr int few_units_in_batch(int S, bool deep) { return units_in_batch(S, deep) / 4 > 0 ? units_in_batch(S, deep) / 4 : 1; }
 template <int S, bool DEEP>
 __device__ __forceinline__ bool few_units(const Shape& s, uint32_t nw) {
     constexpr int U = units_in_batch(S, DEEP);
     return U > 1 && (s.full_bytes + 1023) >> 10 <= nw * (U / 2);
 }
-// The groups of move_groups (0: whole units).  With more than 256 threads a SIMD may hold two wavefronts of a channel, which fit
-// beside a product with up to 56 registers each.  Two whole halves of nine sources and more do not, and the channel then keeps its
-// compute unit from the product: makespan of three such reduces of 2 MiB sources beside 4096^3, us, halves -> three or six groups of
-// which three are in flight: 9 fp32 sources at (32, 512, 64 KiB) 115 -> 93 ([N,K]), 117 -> 95 ([K,N]); 16 bf16 131 -> 95, 134 -> 96; 12
-// fp32 at (8, 384, 256 KiB) 186 -> 146, 187 -> 147.  Alone 0.8 to 1.0 of the time, 1.03 at worst (9 fp32 at (8, 384, 256 KiB)).
-// Up to 256 threads: six groups, of which five are in flight, or, of up to twelve fp32 sources, two whole units.  us, halves -> six groups |
-// whole units, sources of 1000000 at (8, NT, 32 KiB): nine bf16, NT 128 55.8 -> 51.4 | 54.7; twelve bf16, 64 128 -> 122 | 125, 128 67.0 -> 63.5 | 71.1, 256 36.2 ->
-// 33.5 | 41.9; ten fp32, 64 185 -> 173 | 120, 128 101 -> 90.9 | 66.4, 256 55.7 -> 54.7 | 56.0; twelve fp32, 64 189 -> 175 | 127, 128 104.5 -> 91.0 | 79.6, 256
-// 65.4 -> 65.3 | 66.6; sixteen fp32, 64 200 -> 185, 128 105.5 -> 98.2, 256 85.0 -> 83.8.
+// The groups of move_groups (0: whole units).
+// Up to 256 threads: six groups, of which five are in flight, but two whole units of up to twelve fp32 sources.  us, halves ->
+// six groups | whole units, sources of 1000000 at (8, NT, 32 KiB):
+//   nine bf16       NT 128 55.8 -> 51.4 | 54.7
+//   twelve bf16     NT 64 128 -> 122 | 125     128 67.0 -> 63.5 | 71.1     256 36.2 -> 33.5 | 41.9
+//   ten fp32        NT 64 185 -> 173 | 120     128 101 -> 90.9 | 66.4      256 55.7 -> 54.7 | 56.0
+//   twelve fp32     NT 64 189 -> 175 | 127     128 104.5 -> 91.0 | 79.6    256 65.4 -> 65.3 | 66.6
+//   sixteen fp32    NT 64 200 -> 185           128 105.5 -> 98.2           256 85.0 -> 83.8
+// With more threads a SIMD may hold two wavefronts of a channel, which fit beside a product with up to 56 registers each: from
+// nine sources on three or six groups, of which three are in flight.  Two whole halves of them do not fit, and the channel then
+// keeps its compute unit from the product.  Makespan of three reduces of 2 MiB sources beside 4096^3, us, halves -> this:
+//   9 fp32 at (32, 512, 64 KiB)     115 -> 93 ([N,K])    117 -> 95 ([K,N])
+//   16 bf16 at (32, 512, 64 KiB)    131 -> 95            134 -> 96
+//   12 fp32 at (8, 384, 256 KiB)    186 -> 146           187 -> 147
+// Alone they take 0.8 to 1.0 of the time, 1.03 at worst (9 fp32 at (8, 384, 256 KiB)).
 constexpr int groups(int DT, int S, bool deep) {
     if (S <= (!deep ? 4 : DT == LAGOM_F32 ? 12 : 8)) return 0;
     if (deep) return 6;

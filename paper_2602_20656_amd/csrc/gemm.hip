@@ -1143,7 +1143,8 @@ __global__ void __launch_bounds__(64 * T::WAVES) gemm_bf16_split_kernel(const Ge
 // ------------------------------------------------------------------------- large tiles, the last round in split pieces
 // As above with 64 x 64 pieces of the left-over tiles, K split over a workgroup's wavefronts: where few tiles are left over, their
 // quadrants occupy a part of the chip and each is bound by what one compute unit loads.  The pieces inside C are numbered without
-// gaps: a tile at the edge may hold few of them.
+// gaps: a tile at the edge may hold few of them.  Their sums are added wavefront by wavefront, the large tiles' along K: equal rows of A
+// give rows of C that may differ in the fp32 sums' rounding where one of them lies in a piece (rel 5e-8).
 typedef SplitTile<4, 4, 4, 2> Piece;
 struct PiecesArgs {
     GemmArgs g;                 // tiles_m, tiles_n: 256 x 256
@@ -1234,11 +1235,14 @@ Block block_of(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n,
     const int64_t high = rows < n ? rows : n;
     return {(int32_t)rows, high, (n + high - 1) / high};
 }
-// Up to this K what two XCDs both read is too little to matter, and the orders are the previous ones: columns of 8, dealt out to the
-// XCDs only where their number is a multiple of 8, and for split products the shorter side of C first.  us, those orders -> blocks:
-// split into 64 x 64 tiles 1024 x 1024 x 512 6.4 -> 6.3, x 1024 8.3 -> 7.6, x 4096 16.8 -> 15.2; 512 x 512 x 512 4.20 -> 4.20, x 4096 9.6 -> 8.9;
-// 384 x 512 x 7040 13.7 -> 12.8; 128 x 128 tiles 170 x 6953 x 1448 17.3 -> 16.0.  Larger tiles, bound by their matrix cores, keep the previous orders
-// for every K: 3484 x 4296 x 2048 50.3 -> 48.2, but 3400 x 3400 x 4096 80.0 -> 81.8 and 5632 x 1280 x 7168 91.7 -> 94.0, 26 shapes 0.3 % in the mean.
+// Up to this K what two XCDs both read is too little to matter, and the orders are the previous ones: columns of 8, dealt out to
+// the XCDs only where their number is a multiple of 8, and for split products the shorter side of C first.  us, those orders ->
+// blocks:
+//   64 x 64 split tiles      1024 x 1024 x 512 6.4 -> 6.3, x 1024 8.3 -> 7.6, x 4096 16.8 -> 15.2; 384 x 512 x 7040 13.7 -> 12.8
+//   32 x 32 split tiles      512 x 512 x 512 4.20 -> 4.20, x 4096 9.6 -> 8.9
+//   128 x 128 tiles          170 x 6953 x 1448 17.3 -> 16.0; 1152 x 1408 x 3968 26.4 -> 24.9
+// Larger tiles, bound by their matrix cores, keep the previous orders for every K: 3484 x 4296 x 2048 50.3 -> 48.2, but 3400 x
+// 3400 x 4096 80.0 -> 81.8 and 5632 x 1280 x 7168 91.7 -> 94.0, 26 shapes 0.3 % in the mean.
 constexpr int64_t kShortK = 512;
 int64_t at_a_time(int64_t tiles) { return tiles < 32 * 8 ? (tiles + 7) / 8 : 32; }      // tiles an XCD's 32 compute units work on
 Block tile_block(int64_t tiles_m, int64_t tiles_n, int64_t tile_m, int64_t tile_n, int64_t K) {
@@ -1345,10 +1349,15 @@ int choose_mixed(const GemmArgs& g, MixedArgs* out) {
     return quadrants;
 }
 
-// Whether what is left over fits one round of pieces, and how.  A round of quadrants takes 0.39 of one of large tiles, one of pieces
-// 0.2 - 0.25 however few they are.  us, quadrants -> pieces: 4096 x 4352 x 4096 (256 pieces) 111.3 -> 102.3, x 512 24.1 -> 23.6, [K,N] x 1024 37.6
-// -> 35.2; 4352 x 4096 x 2048 [K,N] fp32 70.6 -> 64.9; 4100 x 4200 x 2056 (194) 75.7 -> 70.8, [K,N] fp32 80.9 -> 77.8; 4153 x 7768 x 3384 [K,N]
-// 187 -> 180.  As for a product of its own, 64 x 64 pieces need more than four slices of K: 4100 x 4200 x 320 22.5 -> 22.3.
+// Whether what is left over fits one round of pieces, and how.  A round of quadrants takes 0.39 of one of large tiles, one of
+// pieces 0.2 - 0.25 however few they are.  us, quadrants -> pieces:
+//   4096 x 4352 x 4096 (256 pieces) 112.7 -> 103.5, x 512 24.1 -> 23.6, [K,N] x 1024 38.1 -> 35.6
+//   4352 x 4096 x 2048 [K,N] 63.4 -> 58.3, fp32 70.6 -> 64.9
+//   4100 x 4200 x 2056 (194 pieces) 75.7 -> 70.8, [K,N] fp32 80.9 -> 75.0
+//   4153 x 7768 x 3384 [K,N] 187 -> 182
+// Beside communication, which shares the compute units that all the pieces need at once, nothing is gained: makespans with ring
+// shares on 8 to 64 channels 0.97 - 1.04 of the quadrants'.  As for a product of its own, 64 x 64 pieces need more than four
+// slices of K: 4100 x 4200 x 320 22.5 -> 22.3.
 bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
     const int rest = (int)(tiles % kRound);

@@ -590,7 +590,7 @@ def test_fused_reduces_of_one_source_keep_loads_in_flight(dtype, cfg):
     ("gather", 1, (5 << 29) + 16, (2, 512, 5 << 28)),             # chunks of more than 1 GiB, the last one short
     ("gather", 3, (3 << 29) + 2, (64, 256, 3 << 20)),             # shards off the 16-byte grid, the last beyond 2^31 of the destination
     ("reduce", 2, (5 << 29) + 16, (128, 256, 16 << 20)),
-    ("reduce", 9, (9 << 28) + 4, (256, 128, 1 << 30)),            # in halves; more channels than chunks
+    ("reduce", 9, (9 << 28) + 4, (256, 128, 1 << 30)),            # in six groups; more channels than chunks
 ])
 def test_buffers_of_gigabytes(op, nsrc, nbytes, cfg):
     count = nbytes // 2
