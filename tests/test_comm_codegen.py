@@ -63,13 +63,10 @@ def test_fused_steps_fit_beside_a_product_up_to_512_threads(comm, left_by_produc
 
 @pytest.mark.parametrize("layout", ["nk", "kn"])
 def test_reduces_and_gathers_fit_beside_a_product_up_to_512_threads(comm, left_by_product, layout):
-    """All but eight bf16 sources, of which two wavefronts with two halves each take 128 registers: up to 256 threads only."""
     kernels = {n: m for n, m in comm.items() if "reduce_copy_kernel" in n or "gather_copy_kernel" in n}
     assert len(kernels) == 2 * (2 * 16 * 2 + 2 * 4)         # loads streamed or not; types, sources and depths; a gather's kinds and units per batch
     for name, meta in kernels.items():
         nt = min(int(meta["max_flat_workgroup_size"]), 512)
-        if re.search(r"reduce_copy_kernelILi1ELi8ELb[01]ELb0E", name):
-            nt = 256
         assert _fits(meta, nt, left_by_product[layout]), (name, nt, meta["vgpr_count"], left_by_product)
 
 
