@@ -9,7 +9,7 @@
 // wavefront n mod (NT/64), and the sequence runs on from chunk to chunk.  The walk over it lives in scalar
 // registers, and the loads of the next batch of units are issued before the current batch is added and stored
 // (see "the pipelined mover" below), so that a channel is bound by what a compute unit's memory pipeline
-// moves (100 - 127 GB/s, loads and stores together, from 8 wavefronts up) and not by one memory latency per batch.
+// moves (93 - 117 GB/s, loads and stores together) and not by one memory latency per batch.
 // With fewer wavefronts it is bound by their instructions, of which one wavefront issues one in five cycles.
 // Every byte is touched once, so stores always carry the non-temporal hint (measured on MI355X: +3..7 % and no
 // write-allocate traffic in the L2 that a co-running GEMM depends on).  Loads carry it only
@@ -522,7 +522,7 @@ constexpr int units_in_batch(int S, bool deep) { return S == 1 ? (deep ? 8 : 4) 
 constexpr int batches(int DT, int S, bool deep) { return deep && S <= (DT == LAGOM_F32 ? 8 : 6) ? 3 : 2; }
 // A quarter of the units per batch where a wavefront has at most half a batch of them in a chunk: what a batch holds beyond
 // them costs its loads' and stores' time for nothing.  us, whole batches -> this: ring shares of four 554264 at (8, 1024, 16
-// KiB) fp32 103 -> 68.7, bf16 56 -> 38.8; at (16, 1024, 16 KiB) two fp32 sources of 1625440 20.4 -> 14.6, one 24 -> 11.4.
+// KiB) fp32 95.7 -> 68.4, bf16 51.4 -> 38.5; at (16, 1024, 16 KiB) two fp32 sources of 1625440 20.4 -> 14.6, one 24 -> 11.4.
 constexpr int few_units_in_batch(int S, bool deep) { return units_in_batch(S, deep) / 4 > 0 ? units_in_batch(S, deep) / 4 : 1; }
 template <int S, bool DEEP>
 __device__ __forceinline__ bool few_units(const Shape& s, uint32_t nw) {
