@@ -1154,15 +1154,16 @@ struct PiecesArgs {
     int32_t inside, right;      // pieces of the tiles left over inside C and at its right edge; the lower edge's follow
     int32_t first_right, first_low;     // tiles of either edge among the large ones
     int32_t pieces;
+    int32_t lead;               // pieces in front of the large tiles, a multiple of 8; the others follow them
 };
 constexpr int kPiecesAcross = BM / Piece::TM;
 
 template <bool B_KN, bool OUT_BF16, bool K_TAIL>
 __device__ __forceinline__ void pieces_gemm_body(const PiecesArgs& p) {
     static_assert(64 * Piece::WAVES == THREADS && BM == BN && Piece::TM == Piece::TN, "pieces and large tiles in one launch");
-    const int id = blockIdx.x, x = id & 7;
-    if (id < p.nlarge) {
-        const int lin = x * (p.nlarge >> 3) + (id >> 3), inside = p.full_m * p.full_n, right = p.full_m * (p.g.tiles_n - p.full_n);
+    const int id = blockIdx.x, x = id & 7, behind = id - p.lead;
+    if (behind >= 0 && behind < p.nlarge) {
+        const int lin = x * (p.nlarge >> 3) + (behind >> 3), inside = p.full_m * p.full_n, right = p.full_m * (p.g.tiles_n - p.full_n);
         int tm, tn;
         if (lin < inside) tile_in_list(lin, p.full_m, p.full_n, 8, &tm, &tn);
         else if (lin < inside + right) { tm = lin - inside; tn = p.full_n; }
@@ -1172,7 +1173,7 @@ __device__ __forceinline__ void pieces_gemm_body(const PiecesArgs& p) {
     }
     constexpr int A = kPiecesAcross;
     const int over = p.pieces & 7;
-    int j = x * (p.pieces >> 3) + (x < over ? x : over) + ((id - p.nlarge) >> 3);
+    int j = x * (p.pieces >> 3) + (x < over ? x : over) + ((behind < 0 ? id : id - p.nlarge) >> 3);
     int tm, tn;
     if (j < p.inside) {
         tile_in_list(p.nlarge + j / (A * A), p.full_m, p.full_n, 8, &tm, &tn);
@@ -1358,11 +1359,17 @@ int choose_mixed(const GemmArgs& g, MixedArgs* out) {
 // Beside communication, which shares the compute units that all the pieces need at once, nothing is gained: makespans with ring
 // shares on 8 to 64 channels 0.97 - 1.04 of the quadrants'.  As for a product of its own, 64 x 64 pieces need more than four
 // slices of K: 4100 x 4200 x 320 22.5 -> 22.3.
+// Half of the chip begins with a piece each, so that its large tiles store a piece's time behind the others': the results of a
+// round, stored by all at one moment, cost what the memory takes for them (64 MiB of fp32 results 14 us of 78).  us, all pieces
+// behind -> 128 in front: 4100 x 4200 x 2056 72.9 -> 67.6, [K,N] fp32 78.9 -> 75.0, 4096 x 4352 x 4096 109.5 -> 109.0, 4352 x 4096 x 2048
+// [K,N] fp32 67.7 -> 66.8 (64 in front 77.5 of the 78.9, 192 77.8, 256 77.0).  Quadrants in front of large tiles gain nothing (4096
+// x 6144 x 2048 fp32 91.4 -> 93.0).
+constexpr int kLead = kRound / 2;
 bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
     const int rest = (int)(tiles % kRound);
     if (g.K <= 4 * BK || tiles <= kRound || rest == 0) return false;
-    PiecesArgs a{g, (int32_t)(g.M / BM), (int32_t)(g.N / BN), (int32_t)(tiles - rest), 0, 0, 0, 0, 0, 0, 0};
+    PiecesArgs a{g, (int32_t)(g.M / BM), (int32_t)(g.N / BN), (int32_t)(tiles - rest), 0, 0, 0, 0, 0, 0, 0, 0};
     auto across = [](int64_t size, int64_t tile) { return (int32_t)((size % tile + Piece::TM - 1) / Piece::TM); };
     a.edge_m = across(g.M, BM);
     a.edge_n = across(g.N, BN);
@@ -1379,6 +1386,7 @@ bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     }
     if (n_inside + n_right + n_low > kRound) return false;
     a.inside = (int32_t)n_inside; a.right = (int32_t)n_right; a.pieces = (int32_t)(n_inside + n_right + n_low);
+    a.lead = (a.pieces < kLead ? a.pieces : kLead) & ~7;
     *out = a;
     return true;
 }
