@@ -16,7 +16,7 @@
 // when at least kStreamLoadsFromNC channels have work: with that many channels the
 // kernel is bandwidth-bound and streams from HBM (+6..13 %), while with few channels it is
 // latency-bound and its sources are usually still in the last-level cache, where the hint
-// costs 15..30 %.
+// costs 15..30 %; and so are what a ring's steps read, on any number of channels (launch_steps).
 //
 // Arithmetic (reduce-copy): fp32 additions in source order, bf16 widened exactly by a
 // 16-bit shift, one round-to-nearest-even at the store.  Only additions are used, so no
@@ -769,9 +769,27 @@ __global__ void __launch_bounds__(DEEP ? kDeepNT : 1024) comm_steps_kernel(const
     }
 }
 
+// Whether a step reads what another one reads or writes as well: a ring's steps take turns with a few wire buffers.
+bool reads_again(const StepsArgs& a) {
+    auto first = [&](int st) { return a.step[st] & 255; };
+    auto nsrc = [&](int st) { return a.step[st] >> 8 & 255; };
+    auto end = [&](int st) { return first(st) + nsrc(st) + (a.step[st] >> 16 & 255); };
+    for (int st = 0; st < a.nsteps; ++st)
+        for (uint32_t s = first(st); s < first(st) + nsrc(st); ++s)
+            for (int other = 0; other < a.nsteps; ++other)
+                for (uint32_t q = first(other); other != st && q < end(other); ++q)
+                    if (a.ptr[q] == a.ptr[s]) return true;
+    return false;
+}
+
+// Loads that carry the non-temporal hint leave nothing behind in the last-level cache: not for steps that read it again.  us, with the hint ->
+// without, ring shares, buffers of the same share each time | of another one each time: eight ranks of 1051544 bf16 at (256, 256, 16 KiB) 22.3 -> 14.8 |
+// 24.7 -> 23.1, sixteen of 1295728 fp32 at (256, 128, 32 KiB) 85.5 -> 66.2 | 87.5 -> 66.8, four of 1873712 fp32 at (128, 128, 32 KiB) 32.6 -> 24.9 | 34.3 -> 28.3, two of
+// 1417128 fp32 at (128, 256, 32 KiB) 8.9 -> 7.5 | 12.0 -> 11.8; thirty shares 0.80 | 0.89 in the mean, 1.02 at worst.  (A reduce or gather of
+// its own gains as much where its sources are those of the call before, but loses 4 - 9 % where they come from HBM.)
 template <int DT>
 void launch_steps(const StepsArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    const bool stream = stream_loads(grid.x, a.shape), deep = block.x <= kDeepNT;
+    const bool stream = stream_loads(grid.x, a.shape) && !reads_again(a), deep = block.x <= kDeepNT;
     if (stream) {
         if (deep) hipLaunchKernelGGL((comm_steps_kernel<DT, true, true>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((comm_steps_kernel<DT, true, false>), grid, block, 0, st, a);

@@ -544,6 +544,20 @@ def test_wide_launches_with_few_busy_channels(nt, busy):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("nt", [64, 512])
+@pytest.mark.parametrize("again", [(), ("a",), ("e",)])           # a source read twice; a destination read by a later step
+def test_wide_steps_that_do_and_do_not_read_anything_again(dtype, nt, again):
+    """130 channels with a chunk each: loads are streamed only where no step reads what another one reads or writes."""
+    count = 129 * 1024 + 7
+    bufs = dict(zip("abcdefgh", _sources(dtype, 8, count, 1450)))
+    steps = [("reduce_copy", ["a", "b"], ["e"]), ("reduce_copy", ["c", "d"], ["f"]), ("gather_copy", [*again, "g"][:1], ["h"])]
+    want = oc.comm_steps(bufs, steps, dtype)
+    got = _steps_case(dtype, count, (130, nt, 4096 if dtype == "f32" else 2048), steps, bufs)
+    for k in bufs:
+        assert same_bits(got[k], want[k]), k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("nt", [64, 320])
 def test_fused_reduces_of_many_sources(dtype, nt):
     """Three to sixteen sources: a first group of one to four, then groups of four, added in source order."""
