@@ -625,12 +625,34 @@ constexpr int SBM = SmallTile<4>::BM_, MBM = SmallTile<8>::BM_;
 // c ^ kn_swz128(k), which spreads the rows of a transposing read over the 8 32-byte windows of a row.
 __device__ __forceinline__ int kn_swz128(int k) { return (((k >> 3) & 1) << 3) | ((k & 3) << 1); }
 
-// K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64 (see the large kernel).
-template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL>
+// K_TAIL: K is not a multiple of 64, and rows start anywhere between two 128-byte lines: 64 columns of a row reach into two lines, and
+// the compute unit's cache, which looks up one line at a time, takes twice the time.  LINES: tile t holds line t of every row
+// instead, counted from the one that the row starts in, so a row that starts s groups (of 16 bytes) behind a line has the last s groups of
+// K-step t in tile t + 1: the lanes that need those read there.  A group's place in its row in LDS is the one it would have without the
+// shift.  One tile more is loaded, and one more has to be there.  The last K-step's columns behind K are cleared in the fragments.
+// Without LINES: the last tile begins at column K - 64 (see the large kernel).
+constexpr int LINE = BK * 2;
+// How many groups of 16 bytes a row starts behind a line.  Rows 8 apart start alike.
+__device__ __forceinline__ int skew(const uint16_t* base, int row, int64_t K) { return (int)(((uintptr_t)base >> 4) + (uint32_t)row * (uint32_t)(K / 8)) & 7; }
+enum TileKind { USUAL_TILE, LAST_TILE, END_TILE };
+// A lane's offset against its group's in the columns of a K-step, which count from one line in front of them.  Lanes with nothing to load read
+// what lies in a line that others of their row read.
+struct LinesOf {
+    uint32_t usual;             // part of the offset as it is held: the group of K-step t in tile t, or of the one before, if it lies behind the line
+    uint32_t first, last, end;  // against that: in tile 0 (nothing in front of the row), in the last K-step's tile, and in the one behind
+                                // it, from the same place (nothing behind the row)
+    __device__ __forceinline__ LinesOf(bool behind, int group, int last_groups)
+        : usual(behind ? 0u : LINE), first(behind ? LINE - 16u * group : 0u),
+          last(!behind && group >= last_groups ? 16u * (uint32_t)(last_groups - 1 - group) : 0u),
+          end((behind && group < last_groups ? LINE : LINE + 16u * (uint32_t)(last_groups - 1 - group)) - usual) {}
+};
+template <int NI, bool B_KN, bool OUT_BF16, bool K_TAIL, bool LINES = false>
 __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int tn) {
     typedef SmallTile<NI> T;
     constexpr int S_STAGES = T::STAGES, S_AHEAD = T::AHEAD, S_STAGE_BYTES = T::STAGE_BYTES, S_OPERAND_BYTES = T::A_BYTES;
     constexpr int LA = T::LA, LB = T::LB, PER_TILE = LA + LB;
+    static_assert(!LINES || (K_TAIL && NI == 4), "of three tiles in LDS none would be left to wait for ahead");
+    constexpr bool LINES_B = LINES && !B_KN;
     extern __shared__ u32x4 smem[];
     __builtin_amdgcn_s_setprio(3);
     const int tid = threadIdx.x;
@@ -647,18 +669,22 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    const int nk = (int)(K_TAIL ? (K + BK - 1) / BK : K / BK);
     // load d of an operand tile: rows (d*4 + wave)*8 + lane/8, as in the large kernel
     const int srow = wave * 8 + (lane >> 3);
     const int scg = (lane & 7) ^ ((srow >> 1) & 7);
-    const char* g_a = reinterpret_cast<const char*>(p.A + m0 * K);
-    const char* g_b = reinterpret_cast<const char*>(B_KN ? p.B + n0 : p.B + n0 * K);
+    const char* g_a = reinterpret_cast<const char*>(p.A + m0 * K) - (LINES ? LINE : 0);
+    const char* g_b = reinterpret_cast<const char*>(B_KN ? p.B + n0 : p.B + n0 * K) - (LINES_B ? LINE : 0);
+    const int last_groups = (int)(K / 8) - 8 * (nk - 1);
+    const LinesOf lines_a(scg + skew(p.A, srow, K) >= 8, scg, last_groups), lines_b(scg + skew(p.B, srow, K) >= 8, scg, last_groups);
     const int64_t b_step = B_KN ? 2 * BK * N : 2 * BK;
     uint32_t a_off[LA], b_off[LB];
 #pragma unroll
     for (int d = 0; d < LA; ++d) {
         const int64_t r = srow + 32 * d, last_a = M - 1 - m0;
-        a_off[d] = (uint32_t)(((r < last_a ? r : last_a) * K + scg * 8) * 2);
+        a_off[d] = (uint32_t)(((r < last_a ? r : last_a) * K + scg * 8) * 2) + (LINES ? lines_a.usual : 0u);
     }
+    uint32_t b_row[LB];          // [K,N] with LINES: to the first row, which rows behind K re-read
 #pragma unroll
     for (int d = 0; d < LB; ++d) {
         const int64_t r = srow + 32 * d, last_b = N - 1 - n0;
@@ -666,40 +692,49 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
             const int krow = 16 * d + 4 * wave + (lane >> 4);
             const int64_t grp = (lane & 15) ^ kn_swz128(krow), last_grp = (N - n0) / 8 - 1;
             b_off[d] = (uint32_t)((krow * N + (grp < last_grp ? grp : last_grp) * 8) * 2);
+            b_row[d] = krow < 8 * last_groups ? 0u : (uint32_t)(krow * N * 2);
         } else {
-            b_off[d] = (uint32_t)(((r < last_b ? r : last_b) * K + scg * 8) * 2);
+            b_off[d] = (uint32_t)(((r < last_b ? r : last_b) * K + scg * 8) * 2) + (LINES ? lines_b.usual : 0u);
         }
     }
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
-    const int nk = (int)(K_TAIL ? (K + BK - 1) / BK : K / BK);
-    const int again = K_TAIL ? (int)((int64_t)nk * BK - K) : 0;      // columns of the last tile that the one before it holds as well
+    const int nl = LINES ? nk + 1 : nk;         // tiles that are loaded
+    const int again = K_TAIL && !LINES ? (int)((int64_t)nk * BK - K) : 0;      // columns of the last tile that the one before it holds as well
     const int64_t again_a = 2 * again, again_b = B_KN ? 2 * again * N : 2 * again;   // in bytes
     // g_a / g_b from the tile in front of `t` to tile t.  (The compiler must not know `t`: it would peel the loop's last
     // iterations for this comparison, and copy accumulators between them.)
-    auto is_last = [&](int t) { asm volatile("" : "+s"(t)); return t == nk - 1; };
-    auto next_a = [&](int t) { g_a += BK * 2; if (K_TAIL) g_a -= is_last(t) ? again_a : 0; };
-    auto next_b = [&](int t) { g_b += b_step; if (K_TAIL) g_b -= is_last(t) ? again_b : 0; };
+    auto is_last = [&](int t) { asm volatile("" : "+s"(t)); return t == nl - 1; };
+    auto next_a = [&](int t) { g_a += BK * 2; if (K_TAIL) g_a -= is_last(t) ? (LINES ? LINE : again_a) : 0; };
+    auto next_b = [&](int t) { g_b += b_step; if (K_TAIL) g_b -= is_last(t) ? (LINES ? b_step : again_b) : 0; };
+    // the lane's offsets in load d of tile t
+    auto from_a = [&](TileKind kind, int d) { return a_off[d] + (!LINES || kind == USUAL_TILE ? 0u : kind == LAST_TILE ? lines_a.last : lines_a.end); };
+    auto from_b = [&](TileKind kind, int d) {
+        if (!LINES || kind == USUAL_TILE) return b_off[d];
+        return B_KN ? b_off[d] - b_row[d] : b_off[d] + (kind == LAST_TILE ? lines_b.last : lines_b.end);
+    };
+    auto kind_of = [&](int t) { return t < nk - 1 ? USUAL_TILE : t == nk - 1 ? LAST_TILE : END_TILE; };
     auto load_tile = [&](int stage) {   // the tile g_a / g_b point at (tile `stage`), then advance them one K-step
         const uint32_t base = lds0 + stage * S_STAGE_BYTES;
+        const uint32_t first_a = LINES && stage == 0 ? lines_a.first : 0u, first_b = LINES_B && stage == 0 ? lines_b.first : 0u;
 #pragma unroll
         for (int d = 0; d < LA; ++d)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base + d * 4096), "v"(a_off[d]), "s"(g_a) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base + d * 4096), "v"(from_a(kind_of(stage), d) + first_a), "s"(g_a) : "memory");
 #pragma unroll
         for (int d = 0; d < LB; ++d)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base + S_OPERAND_BYTES + d * 4096), "v"(b_off[d]), "s"(g_b) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base + S_OPERAND_BYTES + d * 4096), "v"(from_b(kind_of(stage), d) + first_b), "s"(g_b) : "memory");
         next_a(stage + 1);
         next_b(stage + 1);
     };
 
-    for (int t = 0; t < S_AHEAD && t < nk; ++t) load_tile(t);
+    for (int t = 0; t < S_AHEAD && t < nl; ++t) load_tile(t);
     // Tile t >= AHEAD is loaded in two halves: A behind the barrier of step t-STAGES, B in the first half of
     // step t-AHEAD (g_a / g_b point at the next tile to load of their operand).
     auto set_m0 = [&](uint32_t lds) { asm volatile("s_mov_b32 m0, %0" ::"s"(lds) : "memory"); };
     auto load_m0 = [&](const char* sbase, uint32_t voff) { asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory"); };
-    if (S_AHEAD < nk) {
+    if (S_AHEAD < nl) {
 #pragma unroll
         for (int d = 0; d < LA; ++d)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + S_AHEAD * S_STAGE_BYTES + d * 4096), "v"(a_off[d]), "s"(g_a) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + S_AHEAD * S_STAGE_BYTES + d * 4096), "v"(from_a(kind_of(S_AHEAD), d)), "s"(g_a) : "memory");
         next_a(S_AHEAD + 1);
     }
 
@@ -719,9 +754,11 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
     }
     constexpr int UNITS = NI + 4;
     // read unit u of a slice, in the order the MFMAs consume them: A0, B0, B1, B2, B3, A1, A2, ...
-    auto read_unit = [&](uint32_t stage_bytes, int ks, int u) {
-        const u32x4* sa = reinterpret_cast<const u32x4*>(smem_bytes + stage_bytes);
-        const u32x4* sb = sa + S_OPERAND_BYTES / 16;
+    const bool behind_a[2] = {kq + skew(p.A, arow, K) >= 8, 4 + kq + skew(p.A, arow, K) >= 8};     // LINES: the lane's groups lie in the next tile
+    const bool behind_b[2] = {kq + skew(p.B, brow, K) >= 8, 4 + kq + skew(p.B, brow, K) >= 8};
+    auto read_unit = [&](uint32_t stage_bytes, uint32_t next_bytes, int ks, int u) {
+        const u32x4* sa = reinterpret_cast<const u32x4*>(smem_bytes + (LINES && behind_a[ks] ? next_bytes : stage_bytes));
+        const u32x4* sb = reinterpret_cast<const u32x4*>(smem_bytes + (LINES_B && behind_b[ks] ? next_bytes : stage_bytes)) + S_OPERAND_BYTES / 16;
         if (u == 0 || u >= 5) {
             const int r = u == 0 ? 0 : u - 4;
             fa[ks][r] = __builtin_bit_cast(bf16x8, sa[swz64(arow + r * 16, ks * 4 + kq)]);
@@ -745,10 +782,11 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         else if (tiles >= 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
-    wait_all_but(nk - 1 < S_AHEAD - 1 ? nk - 1 : S_AHEAD - 1);   // tile 0 (the A half of tile AHEAD, if any, may fly on as well)
+    // tile 0 (LINES: and tile 1; the A half of tile AHEAD, if any, may fly on as well)
+    wait_all_but((nl < S_AHEAD ? nl : S_AHEAD) - (LINES ? 2 : 1));
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) read_unit(0, 0, u);
+    for (int u = 0; u < UNITS; ++u) read_unit(0, S_STAGE_BYTES, 0, u);
 
     // One K-step = 2 k-slices x 4*NI MFMAs, each MFMA followed by at most one side instruction (a B fragment
     // of the [K,N] layout being two reads):
@@ -759,22 +797,25 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
     //   second half  NI + 4 fragment reads of slice 0 of tile kt+1; then the A half of tile kt+STAGES
     // LOAD_B / LOAD_A / NEXT: tiles kt+AHEAD / kt+STAGES / kt+1 exist (compile time: no branch inside a step).
     uint32_t o_cur = 0, o_next = S_STAGE_BYTES, o_b4 = S_AHEAD * S_STAGE_BYTES;   // byte offsets of the slots of tiles kt, kt+1, kt+4
+    uint32_t o_third = 2 * S_STAGE_BYTES;       // LINES: of tile kt+2
+    auto behind = [&](uint32_t o) { return o + S_STAGE_BYTES == S_STAGES * S_STAGE_BYTES ? 0 : o + S_STAGE_BYTES; };
     int kt = 0;
-    auto step = [&](auto load_b_c, auto load_a_c, auto next_c) {
+    auto step = [&](auto load_b_c, auto load_a_c, auto next_c, auto kind_b_c, auto kind_a_c) {
+        constexpr TileKind KIND_B = decltype(kind_b_c)::value, KIND_A = decltype(kind_a_c)::value;     // of the tiles it loads
         constexpr bool LOAD_B = decltype(load_b_c)::value, LOAD_A = decltype(load_a_c)::value, NEXT = decltype(next_c)::value;
         const uint32_t l_b = lds0 + o_b4 + S_OPERAND_BYTES, l_a = lds0 + o_cur;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             if (ks == 1) {
-                // issued and not needed yet: the whole tiles kt+2 .. kt+AHEAD that exist
-                if (LOAD_B) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S_AHEAD - 1) * PER_TILE) : "memory");
+                // issued and not needed yet: the whole tiles kt+2 (LINES: kt+3) .. kt+AHEAD that exist
+                if (LOAD_B) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S_AHEAD - (LINES ? 2 : 1)) * PER_TILE) : "memory");
                 else if (NEXT) wait_all_but(nk - 2 - kt);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (K_TAIL && !NEXT) {
-                const bool keep = ks * 4 + kq >= again / 8;
+                const bool keep = LINES ? ks * 4 + kq < last_groups : ks * 4 + kq >= again / 8;
 #pragma unroll
                 for (int i = 0; i < NI; ++i) keep_frag(fa[ks][i], keep);
 #pragma unroll
@@ -793,12 +834,12 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
                     LAGOM_MFMA_16x16x32(acc[i][j], b_frag(ks, j), fa[ks][i]);
                     __builtin_amdgcn_sched_barrier(0);
                     if (sl < UNITS) {
-                        if (ks == 0) read_unit(o_cur, 1, sl);
-                        else if (NEXT) read_unit(o_next, 0, sl);
+                        if (ks == 0) read_unit(o_cur, o_next, 1, sl);
+                        else if (NEXT) read_unit(o_next, o_third, 0, sl);
                     } else {
                         const int d = (sl - UNITS) >> 1, odd = (sl - UNITS) & 1;
-                        if (ks == 0 && LOAD_B && d < LB) { if (odd) load_m0(g_b, b_off[d]); else set_m0(l_b + d * 4096); }
-                        if (ks == 1 && LOAD_A && d < LA) { if (odd) load_m0(g_a, a_off[d]); else set_m0(l_a + d * 4096); }
+                        if (ks == 0 && LOAD_B && d < LB) { if (odd) load_m0(g_b, from_b(KIND_B, d)); else set_m0(l_b + d * 4096); }
+                        if (ks == 1 && LOAD_A && d < LA) { if (odd) load_m0(g_a, from_a(KIND_A, d)); else set_m0(l_a + d * 4096); }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -806,20 +847,30 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         if (LOAD_B) next_b(kt + S_AHEAD + 1);
         if (LOAD_A) next_a(kt + S_STAGES + 1);
         o_cur = o_next;
-        o_next = o_next + S_STAGE_BYTES == S_STAGES * S_STAGE_BYTES ? 0 : o_next + S_STAGE_BYTES;
-        o_b4 = o_b4 + S_STAGE_BYTES == S_STAGES * S_STAGE_BYTES ? 0 : o_b4 + S_STAGE_BYTES;
+        o_next = LINES ? o_third : behind(o_next);
+        if (LINES) o_third = behind(o_third);
+        o_b4 = behind(o_b4);
         ++kt;
     };
-    while (kt + S_STAGES < nk) step(std::true_type{}, std::true_type{}, std::true_type{});
-    // at most STAGES steps are left, peeled in straight-line code (a loop over step variants makes the register
-    // allocator copy accumulators between them, with none of the wait states a copy behind an MFMA needs)
-    if (kt + S_AHEAD < nk) step(std::true_type{}, std::false_type{}, std::true_type{});
-    if (kt + 1 < nk) step(std::false_type{}, std::false_type{}, std::true_type{});
-    if (S_AHEAD > 2) {
-        if (kt + 1 < nk) step(std::false_type{}, std::false_type{}, std::true_type{});
-        if (kt + 1 < nk) step(std::false_type{}, std::false_type{}, std::true_type{});
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr std::integral_constant<TileKind, USUAL_TILE> usual{};
+    constexpr std::integral_constant<TileKind, LAST_TILE> last{};
+    constexpr std::integral_constant<TileKind, END_TILE> end{};
+    while (kt + S_STAGES < nk - (LINES ? 1 : 0)) step(yes, yes, yes, usual, usual);
+    // at most STAGES steps are left (LINES: and the two that load the last tiles), peeled in straight-line code (a loop over step variants makes
+    // the register allocator copy accumulators between them, with none of the wait states a copy behind an MFMA needs)
+    if (LINES) {
+        if (kt + S_STAGES == nk - 1) step(yes, yes, yes, usual, last);
+        if (kt + S_STAGES == nk) step(yes, yes, yes, last, end);
     }
-    if (kt < nk) step(std::false_type{}, std::false_type{}, std::false_type{});
+    if (kt + S_AHEAD < nl) step(yes, no, yes, end, usual);
+    if (kt + 1 < nk) step(no, no, yes, usual, usual);
+    if (S_AHEAD > 2) {
+        if (kt + 1 < nk) step(no, no, yes, usual, usual);
+        if (kt + 1 < nk) step(no, no, yes, usual, usual);
+    }
+    if (kt < nk) step(no, no, no, usual, usual);
     // wait states behind the last inline-asm MFMA, as in the large kernel
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll
@@ -883,6 +934,9 @@ template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, OUT_BF16, false>(p, tm, tn); }
+// K not a multiple of 64, lines of A and B as they lie in memory
+template <bool B_KN, bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_lines128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, B_KN, OUT_BF16, true, true>(p, tm, tn); }
 // K >= 64 and not a multiple of 64
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, false, OUT_BF16, true>(p, tm, tn); }
@@ -1391,6 +1445,18 @@ bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     return true;
 }
 
+// 128 x 128 tiles of a product whose K is no multiple of 64, in lines as they lie in memory.  One tile more to load and one more to wait for
+// cost 0.8 us, and as long as A and B stay in the L2s their lines may as well be asked for twice.  us, 64 columns from wherever they
+// begin -> lines, N x K stored [N,K] | [K,N], whose rows of B begin where they began:
+//   1025 x 1024 (72 tiles)    x 1304 11.5 -> 12.2 | 12.2 -> 12.9    x 1800 19.9 -> 15.5 | 17.3 -> 16.6    x 3080 31.4 -> 22.4 | 27.0 -> 24.4
+//   1053 x 1536 (108)         x 1304 11.8 -> 12.1 | 12.4 -> 13.0    x 1800 18.5 -> 15.3 | 16.0 -> 16.4    x 3080 30.9 -> 22.5 | 25.2 -> 24.4
+//   200 x 8000 (126)          x 1304 11.4 -> 12.1 | 12.4 -> 13.0    x 1800 18.0 -> 15.4 | 15.9 -> 16.5    x 3080 28.6 -> 22.5 | 24.7 -> 24.4
+//   1300 x 2304 (198)         x 776  10.2 -> 9.7  | 9.5 -> 10.0     x 1544 17.3 -> 14.3 | 15.2 -> 15.1    x 3080 31.6 -> 24.1 | 26.3 -> 24.7
+//   1024 x 4096 (256)         x 520  8.7 -> 8.7   | 8.5 -> 8.8      x 1544 19.4 -> 15.7 | 17.1 -> 16.1    x 3080 33.6 -> 26.4 | 29.2 -> 27.7
+// The same way through products with K split over wavefronts, which then take neighbouring slices, gains 7 - 18 % at K = 5288 and loses 5 - 20 %
+// up to 3000; tiles of 256 rows have no room in LDS for a third tile to be there.
+bool lines_pay(int64_t tiles, int64_t K, bool b_is_nk) { return b_is_nk ? K >= 1800 || tiles * K >= 166000 : K >= 2048 || tiles * K >= 300000; }
+
 constexpr int64_t kMaxDim = 1 << 24;
 
 }  // namespace
@@ -1481,13 +1547,17 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
                    (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0};
         a.rows = tile_block(a.tiles_m, a.tiles_n, bm, SBN, K).rows;
-        const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
+        const int tiles = a.tiles_m * a.tiles_n;
+        const dim3 grid((unsigned)tiles);
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         const bool bf = out_dt == LAGOM_BF16;
         const bool tail = K % BK != 0;
         int rc;
 #define LAGOM_PICK(NAME) (bf ? launch_fast<NAME<true>>(a, grid, st) : launch_fast<NAME<false>>(a, grid, st))
-        if (tiling == TILE_128x128) {
+        if (tiling == TILE_128x128 && tail && lines_pay(tiles, K, b_is_nk)) {
+            if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_lines128_kernel<false, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<false, false>>(a, grid, st);
+            else rc = bf ? launch_fast<gemm_bf16_lines128_kernel<true, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<true, false>>(a, grid, st);
+        } else if (tiling == TILE_128x128) {
             if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk128_tail_kernel) : LAGOM_PICK(gemm_bf16_nk128_kernel);
             else rc = tail ? LAGOM_PICK(gemm_bf16_kn128_tail_kernel) : LAGOM_PICK(gemm_bf16_kn128_kernel);
         } else {

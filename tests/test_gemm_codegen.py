@@ -220,3 +220,43 @@ def test_bench_names_the_kernel_that_runs(assembly, M, N, K, name):
     got = bench.gemm_kernel_name(lg.lagom_gemm_describe(M, N, K, lg.LAGOM_BF16), M, N, K)
     assert got == f"gemm_bf16_{name}_kernel"
     assert re.search(r"^\S*\d%sI?\S*:" % got, assembly, re.M)
+
+
+LINES = tuple("gemm_bf16_lines128_kernelILb%dELb%dE" % (k, o) for k in (0, 1) for o in (1, 0))
+
+
+@pytest.mark.parametrize("name", LINES)
+def test_tiles_in_lines_keep_their_accumulators_and_one_side_instruction_per_mfma(assembly, name):
+    sym, lines = _body(assembly, name)
+    meta = _metadata(assembly, sym)
+    assert meta["vgpr_spill_count"] == "0" and meta["sgpr_spill_count"] == "0" and meta["private_segment_fixed_size"] == "0", meta
+    assert meta["agpr_count"] == "64", meta
+    lines = [l for l in lines if l]
+    mfma = [i for i, l in enumerate(lines) if l.startswith("v_mfma_f32_16x16x32_bf16")]
+    nop = next(i for i in range(mfma[-1], len(lines)) if lines[i].startswith("s_nop 7"))
+    assert all(l.startswith("s_nop 7") for l in lines[nop:nop + 3])
+    for falls_in, block in _blocks(lines[mfma[0]:nop]):
+        for l in block:
+            if AGPR.search(l) and not l.startswith("v_mfma_f32_16x16x32_bf16"):
+                assert not falls_in and not any(b.startswith("v_mfma") for b in block) and l.startswith(("v_accvgpr_mov_b32", "v_accvgpr_write_b32")), l
+    back = next(i for i in range(mfma[0], len(lines)) if lines[i].startswith("s_cbranch"))
+    label = lines[back].split()[-1] + ":"
+    head = max(i for i in range(mfma[0]) if lines[i].startswith(label))
+    body = [l for l in lines[head + 1:back] if not l.endswith(":")]
+    assert sum(l.startswith("v_mfma") for l in body) == 32 and sum(l.startswith("s_barrier") for l in body) == 1
+    assert sum(l.startswith("global_load_lds_dwordx4") for l in body) == 8
+    run, worst, seen = 0, 0, False
+    for l in body:
+        if l.startswith("v_mfma"):
+            worst, seen, run = max(worst, run) if seen else 0, True, 0
+        elif not l.startswith(("s_waitcnt", "s_barrier")):
+            run += 1
+    assert worst <= 5, worst        # two selects, an address add and a read
+
+
+@pytest.mark.parametrize("M,N,K,name", [(1200, 1288, 1032, "nk128_tail"), (1200, 1288, 1512, "lines128"), (933, 1226, 1736, "nk128_tail"), (933, 1226, 1800, "lines128"), (933, 1226, 1856, "nk128")])
+def test_bench_names_the_kernel_of_tiles_in_lines(assembly, M, N, K, name):
+    import bench
+    from paper_2602_20656_amd import binding as lg
+    got = bench.gemm_kernel_name(lg.lagom_gemm_describe(M, N, K, lg.LAGOM_BF16), M, N, K)
+    assert got == f"gemm_bf16_{name}_kernel" and re.search(r"^\S*\d%sI?\S*:" % got, assembly, re.M)

@@ -346,3 +346,34 @@ def test_gemm_rows_off_the_16_byte_grid(M, N, K, out):
     if out == "bf16":
         want = oc.bf16_to_f32(oc.f32_to_bf16(want))
     assert np.array_equal(_gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), True, out), want)
+
+
+@pytest.mark.parametrize("M,N", [(1025, 1032), (1153, 1800), (4001, 1000)])      # 81, 150 and 256 tiles of 128 x 128, one row or column in the last ones
+@pytest.mark.parametrize("K", [1800, 1864, 1992, 2056, 2088, 2104, 2152, 2168])  # from the first K on, 8 to 56 columns behind the last whole step, rows 1 to 7 groups off the line
+@pytest.mark.parametrize("b_is_nk", [True, False])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_gemm_lines_of_rows_anywhere_integer_inputs_are_exact(M, N, K, b_is_nk, shift):
+    """Tiles hold the lines that rows lie in, which begin `shift` groups of 16 bytes behind a line and K / 8 more from row to row.  The last columns
+    of a row and the first of the next lie in one line: what is infinite there reaches its own row and column only."""
+    assert _tile(M, N, K) == (128, 128)
+    rng = np.random.default_rng(M + K)
+    a = rng.integers(-3, 4, size=(M, K)).astype(np.float32)
+    b = rng.integers(-3, 4, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
+    want = a @ (b.T if b_is_nk else b)
+    bad_rows, bad_col = (1, M - 1), N - 2
+    a[bad_rows[0], 0], a[bad_rows[1], K - 1] = np.inf, np.inf
+    if b_is_nk: b[bad_col, K - 1] = np.inf
+    else: b[K - 1, bad_col] = np.inf
+    def placed(x):
+        flat = torch.zeros(x.size + 64, dtype=torch.bfloat16, device="cuda")
+        flat[8 * shift:8 * shift + x.size] = torch.from_numpy(x.reshape(-1)).to(torch.bfloat16).cuda()
+        return flat, flat.data_ptr() + 16 * shift
+    (fa, pa), (fb, pb), c = placed(a), placed(b), torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    lg.lagom_gemm(pa, pb, c, M, N, K, b_is_nk, lg.LAGOM_F32, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    got = c.cpu().numpy()
+    clean = np.ones((M, N), bool)
+    clean[list(bad_rows)] = False
+    clean[:, bad_col] = False
+    assert np.array_equal(got[clean], want[clean])
+    assert not np.isfinite(got[list(bad_rows)]).any() and not np.isfinite(got[:, bad_col]).any()
