@@ -170,7 +170,7 @@ def gemm_kernel_name(geo, M, N, K):
     if K < 64 or K > 1 << 22:
         return "gemm_bf16_general_kernel"
     tiles = -(-M // geo.tile_m) * -(-N // geo.tile_n)
-    if (geo.tile_m, geo.tile_n) == (128, 128) and K % 64 and (K >= 1800 or tiles * K >= 166000):
+    if (geo.tile_m, geo.tile_n) == (128, 128) and K % 64 and K >= 640:
         return "gemm_bf16_lines128_kernel"
     kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "")
     if not kind and geo.mu != tiles:       # whole rounds of large tiles, and the rest in smaller ones: whose loads tell which

@@ -1446,16 +1446,17 @@ bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
 }
 
 // 128 x 128 tiles of a product whose K is no multiple of 64, in lines as they lie in memory.  One tile more to load and one more to wait for
-// cost 0.8 us, and as long as A and B stay in the L2s their lines may as well be asked for twice.  us, 64 columns from wherever they
-// begin -> lines, N x K stored [N,K] | [K,N], whose rows of B begin where they began:
-//   1025 x 1024 (72 tiles)    x 1304 11.5 -> 12.2 | 12.2 -> 12.9    x 1800 19.9 -> 15.5 | 17.3 -> 16.6    x 3080 31.4 -> 22.4 | 27.0 -> 24.4
-//   1053 x 1536 (108)         x 1304 11.8 -> 12.1 | 12.4 -> 13.0    x 1800 18.5 -> 15.3 | 16.0 -> 16.4    x 3080 30.9 -> 22.5 | 25.2 -> 24.4
-//   200 x 8000 (126)          x 1304 11.4 -> 12.1 | 12.4 -> 13.0    x 1800 18.0 -> 15.4 | 15.9 -> 16.5    x 3080 28.6 -> 22.5 | 24.7 -> 24.4
-//   1300 x 2304 (198)         x 776  10.2 -> 9.7  | 9.5 -> 10.0     x 1544 17.3 -> 14.3 | 15.2 -> 15.1    x 3080 31.6 -> 24.1 | 26.3 -> 24.7
-//   1024 x 4096 (256)         x 520  8.7 -> 8.7   | 8.5 -> 8.8      x 1544 19.4 -> 15.7 | 17.1 -> 16.1    x 3080 33.6 -> 26.4 | 29.2 -> 27.7
-// The same way through products with K split over wavefronts, which then take neighbouring slices, gains 7 - 18 % at K = 5288 and loses 5 - 20 %
-// up to 3000; tiles of 256 rows have no room in LDS for a third tile to be there.
-bool lines_pay(int64_t tiles, int64_t K, bool b_is_nk) { return b_is_nk ? K >= 1800 || tiles * K >= 166000 : K >= 2048 || tiles * K >= 300000; }
+// cost 0.8 us, and where A and B lie in the L2s already their lines may as well be asked for twice.  us, 64 columns from wherever they
+// begin -> lines, [N,K] | [K,N], whose rows of B begin where they began; inputs in the last-level cache, others from call to call:
+//   1053 x 1536 (108 tiles)  x 520  8.7 -> 8.2 | 8.3 -> 8.5    x 776 11.2 -> 9.7  | 10.0 -> 10.2   x 1304 16.0 -> 12.6 | 13.7 -> 13.3
+//   200 x 8000 (126)         x 520  8.0 -> 8.2 | 8.1 -> 8.5    x 776 10.9 -> 9.7  | 9.9 -> 10.2    x 1304 15.6 -> 12.5 | 13.4 -> 13.3
+//   1024 x 4096 (256)        x 520 10.1 -> 9.1 | 9.2 -> 9.2    x 776 12.2 -> 10.6 | 11.4 -> 10.9   x 1304 17.6 -> 14.6 | 15.4 -> 14.8
+// The same inputs from call to call, in the L2s where they fit: 1053 x 1536 x 776 8.8 -> 9.4, x 1544 16.5 -> 13.7 | 14.2 -> 14.8, x 3080 30.9 -> 22.5 |
+// 25.2 -> 24.4; 1024 x 4096 x 776 11.1 -> 10.1 | 10.0 -> 10.3, x 3080 33.6 -> 26.4 | 29.2 -> 27.7.  Inputs from HBM: 1053 x 1536 x 776 12.5 -> 11.1 |
+// 11.8 -> 11.4, x 3080 39.1 -> 31.0 | 34.9 -> 30.1.
+// The same way through products with K split over wavefronts, which then take neighbouring slices and a line more each, gains 7 - 20 % from K = 3000
+// on and loses as much up to 2000; tiles of 256 rows have no room in LDS for a third tile to be there.
+bool lines_pay(int64_t K, bool b_is_nk) { return K >= (b_is_nk ? 640 : 1280); }
 
 constexpr int64_t kMaxDim = 1 << 24;
 
@@ -1547,14 +1548,13 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         GemmArgs a{static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), C, M, N, K,
                    (int32_t)((M + bm - 1) / bm), (int32_t)((N + SBN - 1) / SBN), 0};
         a.rows = tile_block(a.tiles_m, a.tiles_n, bm, SBN, K).rows;
-        const int tiles = a.tiles_m * a.tiles_n;
-        const dim3 grid((unsigned)tiles);
+        const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         const bool bf = out_dt == LAGOM_BF16;
         const bool tail = K % BK != 0;
         int rc;
 #define LAGOM_PICK(NAME) (bf ? launch_fast<NAME<true>>(a, grid, st) : launch_fast<NAME<false>>(a, grid, st))
-        if (tiling == TILE_128x128 && tail && lines_pay(tiles, K, b_is_nk)) {
+        if (tiling == TILE_128x128 && tail && lines_pay(K, b_is_nk)) {
             if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_lines128_kernel<false, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<false, false>>(a, grid, st);
             else rc = bf ? launch_fast<gemm_bf16_lines128_kernel<true, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<true, false>>(a, grid, st);
         } else if (tiling == TILE_128x128) {

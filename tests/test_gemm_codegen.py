@@ -254,7 +254,7 @@ def test_tiles_in_lines_keep_their_accumulators_and_one_side_instruction_per_mfm
     assert worst <= 5, worst        # two selects, an address add and a read
 
 
-@pytest.mark.parametrize("M,N,K,name", [(1200, 1288, 1032, "nk128_tail"), (1200, 1288, 1512, "lines128"), (933, 1226, 1736, "nk128_tail"), (933, 1226, 1800, "lines128"), (933, 1226, 1856, "nk128")])
+@pytest.mark.parametrize("M,N,K,name", [(1200, 1288, 632, "nk128_tail"), (1200, 1288, 648, "lines128"), (1200, 1288, 704, "nk128"), (2100, 2056, 648, "nk256x128_tail")])
 def test_bench_names_the_kernel_of_tiles_in_lines(assembly, M, N, K, name):
     import bench
     from paper_2602_20656_amd import binding as lg
