@@ -170,8 +170,9 @@ def gemm_kernel_name(geo, M, N, K):
     if K < 64 or K > 1 << 22:
         return "gemm_bf16_general_kernel"
     tiles = -(-M // geo.tile_m) * -(-N // geo.tile_n)
-    if (geo.tile_m, geo.tile_n) == (128, 128) and K % 64 and K >= 640:
-        return "gemm_bf16_lines128_kernel"
+    lines = {(128, 128): ("128", 640), (256, 128): ("256x128", 1536)}.get((geo.tile_m, geo.tile_n))
+    if lines and K % 64 and K >= lines[1]:
+        return f"gemm_bf16_lines{lines[0]}_kernel"
     kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "")
     if not kind and geo.mu != tiles:       # whole rounds of large tiles, and the rest in smaller ones: whose loads tell which
         large = tiles // LAMBDA * LAMBDA

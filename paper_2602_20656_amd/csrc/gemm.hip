@@ -629,7 +629,8 @@ __device__ __forceinline__ int kn_swz128(int k) { return (((k >> 3) & 1) << 3) |
 // the compute unit's cache, which looks up one line at a time, takes twice the time.  LINES: tile t holds line t of every row
 // instead, counted from the one that the row starts in, so a row that starts s groups (of 16 bytes) behind a line has the last s groups of
 // K-step t in tile t + 1: the lanes that need those read there.  A group's place in its row in LDS is the one it would have without the
-// shift.  One tile more is loaded, and one more has to be there.  The last K-step's columns behind K are cleared in the fragments.
+// shift.  One tile more is loaded, and one more has to be there.  The last K-step's columns behind K are cleared in the fragments.  256 x 128 tiles,
+// with three in LDS, hold A in lines and B in K-steps.
 // Without LINES: the last tile begins at column K - 64 (see the large kernel).
 constexpr int LINE = BK * 2;
 // How many groups of 16 bytes a row starts behind a line.  Rows 8 apart start alike.
@@ -651,8 +652,8 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
     typedef SmallTile<NI> T;
     constexpr int S_STAGES = T::STAGES, S_AHEAD = T::AHEAD, S_STAGE_BYTES = T::STAGE_BYTES, S_OPERAND_BYTES = T::A_BYTES;
     constexpr int LA = T::LA, LB = T::LB, PER_TILE = LA + LB;
-    static_assert(!LINES || (K_TAIL && NI == 4), "of three tiles in LDS none would be left to wait for ahead");
-    constexpr bool LINES_B = LINES && !B_KN;
+    static_assert(!LINES || K_TAIL);
+    constexpr bool LINES_B = LINES && !B_KN && NI == 4;
     extern __shared__ u32x4 smem[];
     __builtin_amdgcn_s_setprio(3);
     const int tid = threadIdx.x;
@@ -685,6 +686,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         a_off[d] = (uint32_t)(((r < last_a ? r : last_a) * K + scg * 8) * 2) + (LINES ? lines_a.usual : 0u);
     }
     uint32_t b_row[LB];          // [K,N] with LINES: to the first row, which rows behind K re-read
+    const uint32_t b_past_k = scg < last_groups ? 0u : 16u * (uint32_t)(scg - last_groups + 1);      // [N,K] with LINES of A only: to the last group
 #pragma unroll
     for (int d = 0; d < LB; ++d) {
         const int64_t r = srow + 32 * d, last_b = N - 1 - n0;
@@ -694,7 +696,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
             b_off[d] = (uint32_t)((krow * N + (grp < last_grp ? grp : last_grp) * 8) * 2);
             b_row[d] = krow < 8 * last_groups ? 0u : (uint32_t)(krow * N * 2);
         } else {
-            b_off[d] = (uint32_t)(((r < last_b ? r : last_b) * K + scg * 8) * 2) + (LINES ? lines_b.usual : 0u);
+            b_off[d] = (uint32_t)(((r < last_b ? r : last_b) * K + scg * 8) * 2) + (LINES_B ? lines_b.usual : 0u);
         }
     }
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
@@ -710,7 +712,7 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
     auto from_a = [&](TileKind kind, int d) { return a_off[d] + (!LINES || kind == USUAL_TILE ? 0u : kind == LAST_TILE ? lines_a.last : lines_a.end); };
     auto from_b = [&](TileKind kind, int d) {
         if (!LINES || kind == USUAL_TILE) return b_off[d];
-        return B_KN ? b_off[d] - b_row[d] : b_off[d] + (kind == LAST_TILE ? lines_b.last : lines_b.end);
+        return B_KN ? b_off[d] - b_row[d] : !LINES_B ? b_off[d] - b_past_k : b_off[d] + (kind == LAST_TILE ? lines_b.last : lines_b.end);
     };
     auto kind_of = [&](int t) { return t < nk - 1 ? USUAL_TILE : t == nk - 1 ? LAST_TILE : END_TILE; };
     auto load_tile = [&](int stage) {   // the tile g_a / g_b point at (tile `stage`), then advance them one K-step
@@ -782,8 +784,8 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         else if (tiles >= 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_TILE) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
-    // tile 0 (LINES: and tile 1; the A half of tile AHEAD, if any, may fly on as well)
-    wait_all_but((nl < S_AHEAD ? nl : S_AHEAD) - (LINES ? 2 : 1));
+    // tile 0 (LINES: and tile 1, or its A half; the A half of tile AHEAD, if any, may fly on as well)
+    wait_all_but((nl < S_AHEAD ? nl : S_AHEAD) - (LINES && NI == 4 ? 2 : 1));
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) read_unit(0, S_STAGE_BYTES, 0, u);
@@ -807,8 +809,8 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             if (ks == 1) {
-                // issued and not needed yet: the whole tiles kt+2 (LINES: kt+3) .. kt+AHEAD that exist
-                if (LOAD_B) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S_AHEAD - (LINES ? 2 : 1)) * PER_TILE) : "memory");
+                // issued and not needed yet: the whole tiles kt+2 (LINES: kt+3; of three tiles the B half of kt+2) .. kt+AHEAD that exist
+                if (LOAD_B) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(!LINES ? (S_AHEAD - 1) * PER_TILE : S_AHEAD > 2 ? (S_AHEAD - 2) * PER_TILE : LB) : "memory");
                 else if (NEXT) wait_all_but(nk - 2 - kt);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
@@ -934,9 +936,11 @@ template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_kn256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, true, OUT_BF16, false>(p, tm, tn); }
-// K not a multiple of 64, lines of A and B as they lie in memory
+// K not a multiple of 64, lines of A and B, or of A alone, as they lie in memory
 template <bool B_KN, bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_lines128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, B_KN, OUT_BF16, true, true>(p, tm, tn); }
+template <bool B_KN, bool OUT_BF16>
+__global__ void __launch_bounds__(THREADS) gemm_bf16_lines256x128_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<8, B_KN, OUT_BF16, true, true>(p, tm, tn); }
 // K >= 64 and not a multiple of 64
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(THREADS) gemm_bf16_nk128_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); small_gemm_body<4, false, OUT_BF16, true>(p, tm, tn); }
@@ -1455,8 +1459,15 @@ bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
 // 25.2 -> 24.4; 1024 x 4096 x 776 11.1 -> 10.1 | 10.0 -> 10.3, x 3080 33.6 -> 26.4 | 29.2 -> 27.7.  Inputs from HBM: 1053 x 1536 x 776 12.5 -> 11.1 |
 // 11.8 -> 11.4, x 3080 39.1 -> 31.0 | 34.9 -> 30.1.
 // The same way through products with K split over wavefronts, which then take neighbouring slices and a line more each, gains 7 - 20 % from K = 3000
-// on and loses as much up to 2000; tiles of 256 rows have no room in LDS for a third tile to be there.
+// on and loses as much up to 2000.
 bool lines_pay(int64_t K, bool b_is_nk) { return K >= (b_is_nk ? 640 : 1280); }
+// 256 x 128 tiles, of which LDS holds three: A alone in lines, whose loads are half a K-step in front of B's.  us, the same inputs from call
+// to call | inputs from HBM:
+//   2048 x 4096 (256 tiles)  x 776 17.9 -> 17.4 | 19.6 -> 18.4    x 2056 38.4 -> 34.8 | 48.3 -> 41.8    [K,N] 35.1 -> 33.9 | 43.4 -> 40.2
+//   2100 x 2200 (162)        x 776 14.8 -> 15.0 | 19.7 -> 19.6    x 2056 29.8 -> 29.9 | 42.1 -> 40.8    [K,N] 30.6 -> 29.9 | 42.8 -> 40.2
+//   713 x 5672 (135)         x 776 16.1 -> 15.7 | 20.7 -> 20.3    x 2056 33.5 -> 30.6 | 42.9 -> 40.4    [K,N] 33.3 -> 31.8 | 43.1 -> 39.9
+// x 1032 0.94 - 1.01 ([K,N] 0.96 - 1.03), x 520 0.97 - 1.06, x 1544 0.90 - 1.00.
+bool lines_of_a_pay(int64_t K) { return K >= 1536; }
 
 constexpr int64_t kMaxDim = 1 << 24;
 
@@ -1557,6 +1568,9 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         if (tiling == TILE_128x128 && tail && lines_pay(K, b_is_nk)) {
             if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_lines128_kernel<false, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<false, false>>(a, grid, st);
             else rc = bf ? launch_fast<gemm_bf16_lines128_kernel<true, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<true, false>>(a, grid, st);
+        } else if (tiling == TILE_256x128 && tail && lines_of_a_pay(K)) {
+            if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_lines256x128_kernel<false, true>>(a, grid, st) : launch_fast<gemm_bf16_lines256x128_kernel<false, false>>(a, grid, st);
+            else rc = bf ? launch_fast<gemm_bf16_lines256x128_kernel<true, true>>(a, grid, st) : launch_fast<gemm_bf16_lines256x128_kernel<true, false>>(a, grid, st);
         } else if (tiling == TILE_128x128) {
             if (b_is_nk) rc = tail ? LAGOM_PICK(gemm_bf16_nk128_tail_kernel) : LAGOM_PICK(gemm_bf16_nk128_kernel);
             else rc = tail ? LAGOM_PICK(gemm_bf16_kn128_tail_kernel) : LAGOM_PICK(gemm_bf16_kn128_kernel);

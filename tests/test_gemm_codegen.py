@@ -222,7 +222,7 @@ def test_bench_names_the_kernel_that_runs(assembly, M, N, K, name):
     assert re.search(r"^\S*\d%sI?\S*:" % got, assembly, re.M)
 
 
-LINES = tuple("gemm_bf16_lines128_kernelILb%dELb%dE" % (k, o) for k in (0, 1) for o in (1, 0))
+LINES = tuple("gemm_bf16_lines%s_kernelILb%dELb%dE" % (t, k, o) for t in ("128", "256x128") for k in (0, 1) for o in (1, 0))
 
 
 @pytest.mark.parametrize("name", LINES)
@@ -230,7 +230,8 @@ def test_tiles_in_lines_keep_their_accumulators_and_one_side_instruction_per_mfm
     sym, lines = _body(assembly, name)
     meta = _metadata(assembly, sym)
     assert meta["vgpr_spill_count"] == "0" and meta["sgpr_spill_count"] == "0" and meta["private_segment_fixed_size"] == "0", meta
-    assert meta["agpr_count"] == "64", meta
+    ni = 8 if "256x128" in name else 4
+    assert meta["agpr_count"] == str(16 * ni), meta
     lines = [l for l in lines if l]
     mfma = [i for i, l in enumerate(lines) if l.startswith("v_mfma_f32_16x16x32_bf16")]
     nop = next(i for i in range(mfma[-1], len(lines)) if lines[i].startswith("s_nop 7"))
@@ -243,8 +244,8 @@ def test_tiles_in_lines_keep_their_accumulators_and_one_side_instruction_per_mfm
     label = lines[back].split()[-1] + ":"
     head = max(i for i in range(mfma[0]) if lines[i].startswith(label))
     body = [l for l in lines[head + 1:back] if not l.endswith(":")]
-    assert sum(l.startswith("v_mfma") for l in body) == 32 and sum(l.startswith("s_barrier") for l in body) == 1
-    assert sum(l.startswith("global_load_lds_dwordx4") for l in body) == 8
+    assert sum(l.startswith("v_mfma") for l in body) == 8 * ni and sum(l.startswith("s_barrier") for l in body) == 1
+    assert sum(l.startswith("global_load_lds_dwordx4") for l in body) == ni + 4
     run, worst, seen = 0, 0, False
     for l in body:
         if l.startswith("v_mfma"):
@@ -254,7 +255,7 @@ def test_tiles_in_lines_keep_their_accumulators_and_one_side_instruction_per_mfm
     assert worst <= 5, worst        # two selects, an address add and a read
 
 
-@pytest.mark.parametrize("M,N,K,name", [(1200, 1288, 632, "nk128_tail"), (1200, 1288, 648, "lines128"), (1200, 1288, 704, "nk128"), (2100, 2056, 648, "nk256x128_tail")])
+@pytest.mark.parametrize("M,N,K,name", [(1200, 1288, 632, "nk128_tail"), (1200, 1288, 648, "lines128"), (1200, 1288, 704, "nk128"), (2100, 2056, 1528, "nk256x128_tail"), (2100, 2056, 1544, "lines256x128")])
 def test_bench_names_the_kernel_of_tiles_in_lines(assembly, M, N, K, name):
     import bench
     from paper_2602_20656_amd import binding as lg

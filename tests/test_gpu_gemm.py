@@ -348,14 +348,16 @@ def test_gemm_rows_off_the_16_byte_grid(M, N, K, out):
     assert np.array_equal(_gemm(oc.f32_to_bf16(a), oc.f32_to_bf16(b), True, out), want)
 
 
-@pytest.mark.parametrize("M,N", [(1025, 1032), (1153, 1800), (4001, 1000)])      # 81, 150 and 256 tiles of 128 x 128, one row or column in the last ones
+@pytest.mark.parametrize("M,N,more", [(1025, 1032, 0), (1153, 1800, 0), (4001, 1000, 0),      # 81, 150 and 256 tiles of 128 x 128, one row or column in the last ones
+                                      (2100, 2056, 960)])                                     # 256 x 128, from K = 1536 on
 @pytest.mark.parametrize("K", [648, 1288, 1304, 1320, 1336, 1352, 1368, 1384, 1400])  # 8 to 56 columns behind the last whole step, rows 1 to 7 groups apart on the line
 @pytest.mark.parametrize("b_is_nk", [True, False])
 @pytest.mark.parametrize("shift", [0, 3])
-def test_gemm_lines_of_rows_anywhere_integer_inputs_are_exact(M, N, K, b_is_nk, shift):
+def test_gemm_lines_of_rows_anywhere_integer_inputs_are_exact(M, N, more, K, b_is_nk, shift):
     """Tiles hold the lines that rows lie in, which begin `shift` groups of 16 bytes behind a line and K / 8 more from row to row.  The last columns
     of a row and the first of the next lie in one line: what is infinite there reaches its own row and column only."""
-    assert _tile(M, N, K) == (128, 128)
+    K += more
+    assert _tile(M, N, K) == ((256, 128) if more else (128, 128))
     rng = np.random.default_rng(M + K)
     a = rng.integers(-3, 4, size=(M, K)).astype(np.float32)
     b = rng.integers(-3, 4, size=(N, K) if b_is_nk else (K, N)).astype(np.float32)
