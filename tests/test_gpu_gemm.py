@@ -379,3 +379,28 @@ def test_gemm_lines_of_rows_anywhere_integer_inputs_are_exact(M, N, more, K, b_i
     clean[:, bad_col] = False
     assert np.array_equal(got[clean], want[clean])
     assert not np.isfinite(got[list(bad_rows)]).any() and not np.isfinite(got[:, bad_col]).any()
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(300, 192, 200, (16, 32)), (640, 640, 136, (64, 32)), (90, 5400, 128, (32, 64)), (1000, 960, 320, (64, 64)),
+                                        (1200, 1280, 72, (128, 128)), (2100, 2112, 128, (256, 128)), (2100, 3712, 128, (256, 256)), (4100, 4224, 320, (256, 256))])
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+@pytest.mark.parametrize("shift", [0, 1, 4])          # groups of 16 bytes that C begins behind a 128-byte line
+def test_gemm_results_on_and_off_the_lines_integer_inputs_are_exact(M, N, K, tile, out, shift):
+    """Rows of C on 128-byte lines, and off them by where C begins: stored past the L2, or through it; nothing beside C is written."""
+    assert _tile(M, N, K) == tile
+    rng = np.random.default_rng(M + K)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K)).astype(np.float32)
+    want = a @ b.T
+    if out == "bf16":
+        want = oc.bf16_to_f32(oc.f32_to_bf16(want))
+    dt, esz = (torch.bfloat16, 2) if out == "bf16" else (torch.float32, 4)
+    room = torch.full((M * N + 512,), 123.0, dtype=dt, device="cuda")
+    first = 128 // esz + 16 * shift // esz
+    assert room.data_ptr() % 128 == 0
+    lg.lagom_gemm(torch.from_numpy(a).cuda().to(torch.bfloat16), torch.from_numpy(b).cuda().to(torch.bfloat16), room.data_ptr() + first * esz, M, N, K, True,
+                  lg.LAGOM_BF16 if out == "bf16" else lg.LAGOM_F32, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    h = room.float().cpu().numpy()
+    assert np.array_equal(h[first:first + M * N].reshape(M, N), want)
+    assert (h[:first] == 123.0).all() and (h[first + M * N:] == 123.0).all()
