@@ -269,10 +269,10 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
 }
 
 // A store through the L2 to memory: nothing of it is left to be written back when the kernel ends.  (The compiler has no such store of this
-// size; its registers may be written again one wait state later.)  For results whose rows begin and end inside 128-byte lines, of which two
-// wavefronts write parts, and for products with K split over wavefronts, whose lines four write; results of whole lines go past the
-// L2 (us, past -> through: 2048 x 2048 x 256 fp32 7.5 -> 7.9, x 1024 13.0 -> 13.6), and so do those of more than one round, which end in another
-// round's shadow (4100 x 4200 x 2056 [K,N] fp32 67.9 -> 73.8).  us, past -> through: 2048 x 2040 x 256 fp32 8.6 -> 7.3, 5742 x 1000 x 128 [K,N] 7.8 -> 7.0,
+// size; its registers may be written again one wait state later.)  For results of 128 and 256 x 128 tiles whose rows begin and end inside 128-byte
+// lines, of which two wavefronts write parts, and for products with K split over wavefronts, whose lines four write; results of whole lines go past
+// the L2 (us, past -> through: 2048 x 2048 x 256 fp32 7.5 -> 7.9, x 1024 13.0 -> 13.6), and so do those of 256 x 256 tiles (4100 x 4200 x 2056 [K,N] fp32
+// 67.9 -> 73.8; 4096 x 4000 x 2048 fp32, one round, 55.3 -> 55.4).  us, past -> through: 2048 x 2040 x 256 fp32 8.6 -> 7.3, 5742 x 1000 x 128 [K,N] 7.8 -> 7.0,
 // 713 x 5672 x 640 fp32 13.6 -> 12.6, 1100 x 3000 x 512 [K,N] 8.8 -> 8.4, 3000 x 3064 x 512 16.8 -> 15.3, 1841 x 4392 x 376 [K,N] fp32 17.5 -> 16.8; in the L2 -> through:
 // 512 x 1920 x 1024 [K,N] fp32 7.7 -> 7.3, 1024 x 1024 x 1024 7.3 -> 7.1, fp32 7.5 -> 7.1.  Rows off the 16-byte grid (store_ragged) stay in the
 // L2, which puts their pieces together: 933 x 1226 x 1032 fp32 12.7 -> 15.8, 7456 x 542 x 824 17.0 -> 21.4.
@@ -302,8 +302,7 @@ typedef __attribute__((address_space(3))) char* lds_bytes;
 // B_KN = false: B stored [N,K]; true: B stored [K,N], its tiles kept in LDS as 64 rows (k) of 256 columns
 // and transposed by the LDS reads.
 // K_TAIL: K is not a multiple of 64; the last tile begins at column K - 64, behind the start of the one before it.
-// ONE_ROUND: the launch may hold no more tiles than there are compute units.
-template <bool B_KN, bool OUT_BF16, bool K_TAIL, bool ONE_ROUND = false>
+template <bool B_KN, bool OUT_BF16, bool K_TAIL>
 __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn) {
     extern __shared__ u32x4 smem[];   // LDS_SLOTS operand tiles of 2048 16-byte slots
     // Wavefronts of a communication kernel may share this wavefront's SIMD (this kernel leaves them
@@ -555,7 +554,6 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
     char* st = reinterpret_cast<char*>(smem) + wave * SLOT_BYTES;
     const bool interior = m0 + BM <= M && n0 + BN <= N;
     const bool vector_ok = (N % VEC) == 0;
-    const bool through = ONE_ROUND && rows_off_line(p, ESZ) && p.tiles_m * p.tiles_n <= 256;
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
     const int64_t gcol = n0 + wn * 128 + rd_cv * VEC;
 #pragma unroll
@@ -592,33 +590,29 @@ __device__ __forceinline__ void fast_gemm_body(const GemmArgs& p, int tm, int tn
             // alone are faster (5000 x 5080 x 512 fp32 45 -> 42 us over 16 results, 37 over one), but rows on the grid lose (6400 x 5632 x 2056
             // fp32 132 -> 144, 8192 x 8448 x 256 fp32 73 -> 81), and what runs beside a product finds its data gone from the last-level
             // cache: a 64 MiB gather on 8 channels beside three of 5000 x 5080 x 512 fp32 166 -> 253.
-            auto store = [&](auto how) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int64_t grow = row0 + ROWS_PER_READ * (tb * 8 + e);
-                    char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
-                    if (vector_ok) {
-                        if (interior || (grow < M && gcol < N)) how(out, val[e]);
-                    } else if (grow < M) {
-                        store_ragged<OUT_BF16>(out, val[e], N - gcol);
-                    }
+            for (int e = 0; e < 8; ++e) {
+                const int64_t grow = row0 + ROWS_PER_READ * (tb * 8 + e);
+                char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
+                if (vector_ok) {
+                    if (interior || (grow < M && gcol < N)) __builtin_nontemporal_store(val[e], reinterpret_cast<u32x4*>(out));
+                } else if (grow < M) {
+                    store_ragged<OUT_BF16>(out, val[e], N - gcol);
                 }
-            };
-            if (through) store([](char* out, u32x4 v) { store_through(out, v); });
-            else store([](char* out, u32x4 v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out)); });
+            }
         }
     }
 }
 
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, false>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, false>(p, tm, tn); }
 // K >= 64 and not a multiple of 64 (kernels of their own: the peeled last step clears fragments; as many registers)
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_nk_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<false, OUT_BF16, true>(p, tm, tn); }
 template <bool OUT_BF16>
-__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true, true>(p, tm, tn); }
+__global__ void __launch_bounds__(THREADS) gemm_bf16_kn_tail_kernel(const GemmArgs p) { int tm, tn; tile_of(blockIdx.x, p, &tm, &tn); fast_gemm_body<true, OUT_BF16, true>(p, tm, tn); }
 
 // ------------------------------------------------------------------------- small-tile kernels
 // 128 x 128 x 64 and 256 x 128 x 64 tiles for products with too few 256 x 256 tiles to fill the chip.
@@ -926,27 +920,28 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
                 *reinterpret_cast<f32x4*>(dst) = acc[i][j];
             }
         }
-    const bool interior = m0 + T::BM_ <= M && n0 + SBN <= N;
-    const bool vector_ok = (N % VEC) == 0;
     const int rd_row = lane / GROUPS, rd_cv = lane % GROUPS;
-    const int64_t gcol = n0 + wn * 64 + rd_cv * VEC;
-    const int64_t row0 = m0 + wm * WROWS + rd_row;
-    auto store = [&](auto how) {
-#pragma unroll
-        for (int e = 0; e < WROWS / ROWS_PER_READ; ++e) {   // each read covers ROWS_PER_READ whole rows of the block
-            const int r = rd_row + ROWS_PER_READ * e;
-            const u32x4 val = *reinterpret_cast<const u32x4*>(st + r * ROW_BYTES + ((rd_cv ^ (r & (GROUPS - 1))) << 4));
-            const int64_t grow = row0 + ROWS_PER_READ * e;
-            char* out = reinterpret_cast<char*>(p.C) + (grow * N + gcol) * ESZ;
-            if (vector_ok) {
-                if (interior || (grow < M && gcol < N)) how(out, val);
-            } else if (grow < M) {
-                store_ragged<OUT_BF16>(out, val, N - gcol);
-            }
-        }
+    const int64_t gcol = n0 + wn * 64 + rd_cv * VEC, row0 = m0 + wm * WROWS + rd_row;
+    const int rows = gcol < N ? (int)(M - row0 < WROWS ? M - row0 : WROWS) : 0;   // of the block and of C from this lane's first one on
+    char* out = reinterpret_cast<char*>(p.C) + (row0 * N + gcol) * ESZ;
+    const int64_t rows_on = ROWS_PER_READ * N * ESZ;
+    const auto read = [&](int e) {   // ROWS_PER_READ whole rows of the block
+        const int r = rd_row + ROWS_PER_READ * e;
+        return *reinterpret_cast<const u32x4*>(st + r * ROW_BYTES + ((rd_cv ^ (r & (GROUPS - 1))) << 4));
     };
-    if (rows_off_line(p, ESZ)) store([](char* out, u32x4 v) { store_through(out, v); });
-    else store([](char* out, u32x4 v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out)); });
+    if (__builtin_expect(N % VEC == 0 && !rows_off_line(p, ESZ), 1)) {
+#pragma unroll
+        for (int e = 0; e < WROWS / ROWS_PER_READ; ++e, out += rows_on)
+            if (ROWS_PER_READ * e < rows) __builtin_nontemporal_store(read(e), reinterpret_cast<u32x4*>(out));
+    } else if (N % VEC == 0) {
+#pragma unroll
+        for (int e = 0; e < WROWS / ROWS_PER_READ; ++e, out += rows_on)
+            if (ROWS_PER_READ * e < rows) store_through(out, read(e));
+    } else {   // rolled: unrolled, the code alone, which a launch has to fetch, costs 2 to 7 % (3001 x 1001 x 512 8.9 us, so 8.25)
+#pragma unroll 1
+        for (int e = 0; e < WROWS / ROWS_PER_READ; ++e, out += rows_on)
+            if (ROWS_PER_READ * e < rows) store_ragged<OUT_BF16>(out, read(e), N - gcol);
+    }
 }
 
 template <bool OUT_BF16>
