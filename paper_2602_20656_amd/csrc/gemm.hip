@@ -878,7 +878,8 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         if (kt + S_STAGES == nk - 1) step(yes, yes, yes, usual, last);
         if (kt + S_STAGES == nk) step(yes, yes, yes, last, end);
     }
-    if (kt + S_AHEAD < nl) step(yes, no, yes, end, usual);
+    // (tile nk of B in K-steps, of which nothing is read, is not loaded where it would still be under way behind the last step)
+    if ((!LINES || LINES_B || S_AHEAD > 2) && kt + S_AHEAD < nl) step(yes, no, yes, end, usual);
     if (kt + 1 < nk) step(no, no, yes, usual, usual);
     if (S_AHEAD > 2) {
         if (kt + 1 < nk) step(no, no, yes, usual, usual);
@@ -891,7 +892,8 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
     for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
-    __builtin_amdgcn_s_barrier();   // every wavefront is past its last LDS read before the ring is reused below
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();   // every wavefront is past its last LDS read, and no load is on its way there, before the ring is reused below
 
     // Epilogue: acc[i][j][v] is row 16*i + lane%16, column 16*j + 4*(lane/16) + v of the wavefront's 16*NI x 64
     // block, staged in the wavefront's own LDS as rows of ROW_BYTES (16-byte group c of row r at c ^ (r % GROUPS))

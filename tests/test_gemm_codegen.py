@@ -261,3 +261,17 @@ def test_bench_names_the_kernel_of_tiles_in_lines(assembly, M, N, K, name):
     from paper_2602_20656_amd import binding as lg
     got = bench.gemm_kernel_name(lg.lagom_gemm_describe(M, N, K, lg.LAGOM_BF16), M, N, K)
     assert got == f"gemm_bf16_{name}_kernel" and re.search(r"^\S*\d%sI?\S*:" % got, assembly, re.M)
+
+
+@pytest.mark.parametrize("name", SMALL + MEDIUM + LINES)
+def test_no_load_into_lds_is_in_flight_when_results_are_staged_there(assembly, name):
+    """Results pass through the LDS that the tiles lie in: behind the last step, on every path, all loads have landed and all wavefronts know."""
+    _, lines = _body(assembly, name)
+    lines = [l for l in lines if l]
+    mfma = max(i for i, l in enumerate(lines) if l.startswith("v_mfma_f32_16x16x32_bf16"))
+    write = next(i for i in range(mfma, len(lines)) if lines[i].startswith("ds_write"))
+    nop = next(i for i in range(mfma, write) if lines[i].startswith("s_nop 7"))
+    behind = lines[nop:write]              # one block: every path from the steps to the first write runs through all of it
+    assert not any(l.endswith(":") or l.startswith(("s_cbranch", "s_branch")) for l in behind)
+    wait = next((i for i, l in enumerate(behind) if l.startswith("s_waitcnt vmcnt(0)")), None)
+    assert wait is not None and any(l.startswith("s_barrier") for l in behind[wait:])
