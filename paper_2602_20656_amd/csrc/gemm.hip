@@ -269,7 +269,7 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
 }
 
 // A store through the L2 to memory: nothing of it is left to be written back when the kernel ends.  (The compiler has no such store of this
-// size; its registers may be written again one wait state later.)  For results of 128 and 256 x 128 tiles whose rows begin and end inside 128-byte
+// size; behind one of 16 bytes a vector instruction may write its registers two wait states later, which the compiler does not see to.)  For results of 128 and 256 x 128 tiles whose rows begin and end inside 128-byte
 // lines, of which two wavefronts write parts, and for products with K split over wavefronts, whose lines four write; results of whole lines go past
 // the L2 (us, past -> through: 2048 x 2048 x 256 fp32 7.5 -> 7.9, x 1024 13.0 -> 13.6), and so do those of 256 x 256 tiles (4100 x 4200 x 2056 [K,N] fp32
 // 67.9 -> 73.8; 4096 x 4000 x 2048 fp32, one round, 55.3 -> 55.4).  us, past -> through: 2048 x 2040 x 256 fp32 8.6 -> 7.3, 5742 x 1000 x 128 [K,N] 7.8 -> 7.0,
@@ -277,8 +277,8 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
 // 512 x 1920 x 1024 [K,N] fp32 7.7 -> 7.3, 1024 x 1024 x 1024 7.3 -> 7.1, fp32 7.5 -> 7.1.  Rows off the 16-byte grid (store_ragged) stay in the
 // L2, which puts their pieces together: 933 x 1226 x 1032 fp32 12.7 -> 15.8, 7456 x 542 x 824 17.0 -> 21.4.
 __device__ __forceinline__ bool rows_off_line(const GemmArgs& p, int element) { return (((uintptr_t)p.C | (uintptr_t)(p.N * element)) & 127) != 0; }
-__device__ __forceinline__ void store_through(char* out, u32x4 val) { asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(out), "v"(val) : "memory"); }
-__device__ __forceinline__ void store_through(char* out, uint2 val) { asm volatile("global_store_dwordx2 %0, %1, off sc1\n\ts_nop 0" ::"v"(out), "v"(val) : "memory"); }
+__device__ __forceinline__ void store_through(char* out, u32x4 val) { asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(out), "v"(val) : "memory"); }
+__device__ __forceinline__ void store_through(char* out, uint2 val) { asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(out), "v"(val) : "memory"); }
 
 // Clears an operand fragment in the lanes that do not keep theirs.
 template <class FRAG>

@@ -275,3 +275,13 @@ def test_no_load_into_lds_is_in_flight_when_results_are_staged_there(assembly, n
     assert not any(l.endswith(":") or l.startswith(("s_cbranch", "s_branch")) for l in behind)
     wait = next((i for i, l in enumerate(behind) if l.startswith("s_waitcnt vmcnt(0)")), None)
     assert wait is not None and any(l.startswith("s_barrier") for l in behind[wait:])
+
+
+def test_stores_through_the_l2_keep_their_registers_for_two_wait_states(assembly):
+    """A vector instruction may write the registers of a store of more than 8 bytes two wait states behind it; the compiler does not look into inline asm."""
+    lines = [l for l in (l.split(";")[0].strip() for l in assembly.splitlines()) if l]
+    stores = [i for i, l in enumerate(lines) if re.match(r"global_store_dwordx4 .* sc1\b", l)]
+    assert stores
+    for i in stores:
+        nop = re.match(r"s_nop (\d+)", lines[i + 1])
+        assert nop and int(nop.group(1)) >= 1, lines[i:i + 3]
