@@ -427,15 +427,7 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
         if (__atomic_load_n(&word->late, __ATOMIC_RELAXED) == seq) ++gates_late;
         if (__atomic_load_n(&word->unseen, __ATOMIC_RELAXED) == seq) ++gates_unseen;
     };
-    for (int it = 0; it < total; ++it) {
-        // (behind a failure the streams are drained: every repetition that was begun has ended)
-        int rc = it == 0 ? drained(repetition(0), sa, sb) : LAGOM_OK;
-        if (rc) { count_misses(0); return rc; }
-        if (it + 1 < total) rc = drained(repetition(it + 1), sa, sb);
-        if (!rc) rc = drained(ended(it), sa, sb);
-        count_misses(it);
-        if (rc) { if (it + 1 < total) count_misses(it + 1); return rc; }
-        if (it < warmup) continue;
+    auto read_out = [&](int it) -> int {
         const auto [ga_start, ga_end, gb_start, gb_end] = marks(it);
 
         // The common start: the start event of the stream whose first kernel follows its gate kernel directly.  With
@@ -469,6 +461,17 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
             HIP_TRY(hipEventElapsedTime(&ms, origin, gb_start[0])); startsB.push_back((double)ms * 1000.0);
         }
         Xs.push_back(X); Ys.push_back(Y); Zs.push_back(endA > endB ? endA : endB); Ysums.push_back(ysum);
+        return LAGOM_OK;
+    };
+    for (int it = 0; it < total; ++it) {
+        // (behind a failure the streams are drained: every repetition that was begun has ended)
+        int rc = it == 0 ? drained(repetition(0), sa, sb) : LAGOM_OK;
+        if (rc) { count_misses(0); return rc; }
+        if (it + 1 < total) rc = drained(repetition(it + 1), sa, sb);
+        if (!rc) rc = drained(ended(it), sa, sb);
+        count_misses(it);
+        if (!rc && it >= warmup) rc = drained(read_out(it), sa, sb);
+        if (rc) { if (it + 1 < total) count_misses(it + 1); return rc; }
     }
     out->X_us = median(Xs);
     out->Y_us = median(Ys);

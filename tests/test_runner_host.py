@@ -1,0 +1,37 @@
+"""The host side of lagom_overlap_run on a model of the runtime (tests/runner_host.cpp): what is queued when, and what is left behind a failure."""
+import json
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2602_20656_amd import binding as lg
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PACKAGE = os.path.join(ROOT, "paper_2602_20656_amd")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def runner(tmp_path_factory):
+    lg.lib()                       # built
+    exe = str(tmp_path_factory.mktemp("runner") / "runner_host")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROCM, "include"),
+                           os.path.join(ROOT, "tests", "runner_host.cpp"), lg.LIB_PATH, "-Wl,-rpath," + PACKAGE, "-Wl,--allow-shlib-undefined", "-o", exe])
+    def run(fail=0, comm_us=1.0, comp_us=1.0, warmup=0, iters=1, mode=lg.LAGOM_CORUN):
+        r = subprocess.run([exe, *map(str, (fail, comm_us, comp_us, warmup, iters, mode))], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return json.loads(r.stdout)
+    return run
+
+
+@pytest.mark.parametrize("mode", [lg.LAGOM_CORUN, lg.LAGOM_ALONE_COMM, lg.LAGOM_ALONE_COMP])
+def test_a_failed_read_out_leaves_nothing_in_flight(runner, mode):
+    """The repetition behind the one that is read out is queued already: it has ended before the events it waits on go and the call returns."""
+    reads = runner(warmup=1, iters=3, mode=mode)["reads"]
+    for fail in range(1, reads + 1):
+        r = runner(fail=fail, warmup=1, iters=3, mode=mode)
+        assert r["rc"] == lg.LAGOM_EHIP and "made to fail" in r["error"]
+        assert r["destroyed_in_flight"] == 0 and r["in_flight"] == 0 and r["alive"] == 0, (fail, r)
