@@ -270,7 +270,7 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
 
 // A store through the L2 to memory: nothing of it is left to be written back when the kernel ends.  (The compiler has no such store of this
 // size; behind one of 16 bytes a vector instruction may write its registers two wait states later, which the compiler does not see to.)  For results of 128 and 256 x 128 tiles whose rows begin and end inside 128-byte
-// lines, of which two wavefronts write parts, and for products with K split over wavefronts, whose lines four write; results of whole lines go past
+// lines, of which two wavefronts write parts, and for some products with K split over wavefronts, whose lines four write (split_gemm_body); results of whole lines go past
 // the L2 (us, past -> through: 2048 x 2048 x 256 fp32 7.5 -> 7.9, x 1024 13.0 -> 13.6), and so do those of 256 x 256 tiles (4100 x 4200 x 2056 [K,N] fp32
 // 67.9 -> 73.8; 4096 x 4000 x 2048 fp32, one round, 55.3 -> 55.4).  us, past -> through: 2048 x 2040 x 256 fp32 8.6 -> 7.3, 5742 x 1000 x 128 [K,N] 7.8 -> 7.0,
 // 713 x 5672 x 640 fp32 13.6 -> 12.6, 1100 x 3000 x 512 [K,N] 8.8 -> 8.4, 3000 x 3064 x 512 16.8 -> 15.3, 1841 x 4392 x 376 [K,N] fp32 17.5 -> 16.8; in the L2 -> through:
@@ -1181,6 +1181,11 @@ __device__ __forceinline__ void split_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
         for (int j = 0; j < NJ; ++j) partial[wave * T::ITEMS + (i * NJ + j) * 64 + lane] = acc[i][j];
     __syncthreads();
+    // Through the L2 to memory (store_through) where that pays, else into the L2, which puts the pieces of a line together.  Off the grid of four
+    // elements through the L2 costs 0 - 20 % (1000 x 958 x 320 5.58 -> 6.69); on it, us, in the L2 -> through: 64 rows 1000 x 960 x 320 5.59 -> 5.33, fp32 5.77 -> 5.30, 512 x 1920 x 1024 [K,N]
+    // 7.14 -> 6.88, 640 x 644 x 136 fp32 4.34 -> 4.25 (bf16 4.23 -> 4.23); 32 rows fp32 512 x 512 x 512 3.95 -> 3.88, but 512 x 508 x 512 3.97 -> 4.05, bf16 3.89 ->
+    // 3.89 and 3.92 -> 4.04, 90 x 5404 x 128 4.09 -> 4.17; 16 rows 33 x 1000 x 4096 5.85 -> 5.90.
+    const bool through = T::TM == 64 ? N % 4 == 0 : T::TM == 32 && !out_bf16 && N % 8 == 0;
     for (int item = tid; item < T::ITEMS; item += 64 * WAVES) {
         f32x4 x = partial[item];
 #pragma unroll
@@ -1194,14 +1199,16 @@ __device__ __forceinline__ void split_gemm_body(const GemmArgs& p, int tm, int t
             u32x2_aligned2 v;
             v[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[0], x[1]}, bf16x2));
             v[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[2], x[3]}, bf16x2));
-            if (col + 4 <= N) store_through(reinterpret_cast<char*>(out), uint2{v[0], v[1]});
+            if (T::TM == 64 && through) store_through(reinterpret_cast<char*>(out), uint2{v[0], v[1]});
+            else if (col + 4 <= N) *reinterpret_cast<u32x2_aligned2*>(out) = v;
             else
 #pragma unroll
                 for (int e = 0; e < 3; ++e)
                     if (col + e < N) out[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
         } else {
             float* out = reinterpret_cast<float*>(p.C) + row * N + col;
-            if (col + 4 <= N) store_through(reinterpret_cast<char*>(out), __builtin_bit_cast(u32x4, x));
+            if (through) store_through(reinterpret_cast<char*>(out), __builtin_bit_cast(u32x4, x));
+            else if (col + 4 <= N) *reinterpret_cast<u32x4_aligned2*>(out) = __builtin_bit_cast(u32x4, x);
             else
 #pragma unroll
                 for (int e = 0; e < 3; ++e)

@@ -285,3 +285,16 @@ def test_stores_through_the_l2_keep_their_registers_for_two_wait_states(assembly
     for i in stores:
         nop = re.match(r"s_nop (\d+)", lines[i + 1])
         assert nop and int(nop.group(1)) >= 1, lines[i:i + 3]
+
+
+@pytest.mark.parametrize("tile,through", [((1, 2), ()), ((2, 2), ("x4",)), ((2, 4), ("x4",)), ((4, 2), ("x4", "x2")), ((4, 4), ("x4", "x2"))])
+def test_split_products_store_through_the_l2_by_a_rule_only(assembly, tile, through):
+    """Whole vectors of four results leave tiles of 16 rows into the L2; of 32 (fp32 alone) and 64 rows through it, and into it where rows of C lie off the grid."""
+    bodies = re.findall(r"^\S*gemm_bf16_split_kernelINS_9SplitTileILi%dELi%dE\S*:.*?^\.Lfunc_end" % tile, assembly, re.M | re.S)
+    assert len(bodies) == 4          # both layouts of B, K a multiple of 64 or not
+    for body in bodies:
+        lines = [l.split(";")[0].strip() for l in body.splitlines()]
+        for size in ("x4", "x2"):
+            stores = [l for l in lines if l.startswith("global_store_dword%s " % size)]
+            assert any("sc1" not in l for l in stores)
+            assert any("sc1" in l for l in stores) == (size in through), (size, stores)

@@ -334,6 +334,27 @@ def test_gemm_few_tiles_integer_inputs_are_exact(M, N, Ks, b_is_nk, out):
         assert np.array_equal(got, want, equal_nan=True), (K, np.argwhere(got != want)[:3])
 
 
+@pytest.mark.parametrize("M,N,K", [(33, 1002, 136), (500, 500, 128), (500, 502, 128), (500, 504, 72), (64, 5404, 136), (90, 5402, 128), (640, 636, 136), (640, 634, 128),
+                                   (1000, 956, 320), (1000, 958, 328), (4100, 4196, 328), (4100, 4198, 320)])      # 16 to 64 rows, and 64 x 64 pieces beside large tiles
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+def test_gemm_split_rows_on_and_off_the_grids_of_four_and_eight(M, N, K, out):
+    """Vectors of four results go through the L2 or into it by where rows of C begin; nothing beside C is written."""
+    assert _tile(M, N, K)[0] in (16, 32, 64, 256)
+    rng = np.random.default_rng(M + N + K)
+    a = rng.integers(-4, 5, size=(M, K)).astype(np.float32)
+    b = rng.integers(-4, 5, size=(N, K)).astype(np.float32)
+    want = a @ b.T
+    if out == "bf16":
+        want = oc.bf16_to_f32(oc.f32_to_bf16(want))
+    room = torch.full((M * N + 128,), 123.0, dtype=torch.bfloat16 if out == "bf16" else torch.float32, device="cuda")
+    lg.lagom_gemm(torch.from_numpy(a).cuda().to(torch.bfloat16), torch.from_numpy(b).cuda().to(torch.bfloat16), room.data_ptr() + 64 * room.element_size(), M, N, K, True,
+                  lg.LAGOM_BF16 if out == "bf16" else lg.LAGOM_F32, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    h = room.float().cpu().numpy()
+    assert np.array_equal(h[64:64 + M * N].reshape(M, N), want)
+    assert (h[:64] == 123.0).all() and (h[64 + M * N:] == 123.0).all()
+
+
 @pytest.mark.parametrize("M,N", [(1201, 1203), (1202, 1285), (2100, 2201), (2065, 2308), (2100, 3725), (4100, 4198)])   # 128 x 128, 256 x 128, 256 x 256 tiles, and with quadrants
 @pytest.mark.parametrize("K", [64, 136])
 @pytest.mark.parametrize("out", ["bf16", "f32"])
