@@ -787,9 +787,14 @@ bool reads_again(const StepsArgs& a) {
 // 24.7 -> 23.1, sixteen of 1295728 fp32 at (256, 128, 32 KiB) 85.5 -> 66.2 | 87.5 -> 66.8, four of 1873712 fp32 at (128, 128, 32 KiB) 32.6 -> 24.9 | 34.3 -> 28.3, two of
 // 1417128 fp32 at (128, 256, 32 KiB) 8.9 -> 7.5 | 12.0 -> 11.8; thirty shares 0.80 | 0.89 in the mean, 1.02 at worst.  (A reduce or gather of
 // its own gains as much where its sources are those of the call before, but loses 4 - 9 % where they come from HBM.)
+// Not so where a buffer fills that cache (256 MiB) by itself: what is read again is gone by then.  us, with the hint -> without, two ranks of bf16 and four of
+// fp32 at (256, 256, 128 KiB), eight of bf16 at (256, 512, 128 KiB), four of bf16 at (128, 256, 64 KiB): buffers of 160 MiB 183 -> 149, 544 -> 539, 1275 -> 1204,
+// 614 -> 619; 192 MiB 219 -> 219, 650 -> 653, 1538 -> 1476, 737 -> 748; 224 MiB 256 -> 261, 768 -> 777, 1819 -> 1753, 863 -> 875; 320 MiB 369 -> 378, 1108 -> 1133,
+// 2648 -> 2653, 1235 -> 1255.
+constexpr int64_t kReadAgainBelow = 224ll << 20;
 template <int DT>
 void launch_steps(const StepsArgs& a, dim3 grid, dim3 block, hipStream_t st) {
-    const bool stream = stream_loads(grid.x, a.shape) && !reads_again(a), deep = block.x <= kDeepNT;
+    const bool kept = a.shape.shard_bytes < kReadAgainBelow && reads_again(a), stream = stream_loads(grid.x, a.shape) && !kept, deep = block.x <= kDeepNT;
     if (stream) {
         if (deep) hipLaunchKernelGGL((comm_steps_kernel<DT, true, true>), grid, block, 0, st, a);
         else hipLaunchKernelGGL((comm_steps_kernel<DT, true, false>), grid, block, 0, st, a);
