@@ -163,22 +163,24 @@ def comm_bytes(launches):
     return [lg.lagom_comm_bytes(l.op, l.dtype, len(l.srcs), len(l.dsts), l.count) for l in launches]
 
 
-def gemm_kernel_name(geo, M, N, K):
-    """The kernel lagom_gemm dispatches for an [N,K] product with a bf16 result (names as they appear in a kernel trace)."""
+def gemm_kernel_name(geo, M, N, K, b_is_nk=True, out_dt=None):
+    """The kernel lagom_gemm dispatches for a product (names as they appear in a kernel trace); its result is bf16 if not said."""
+    from paper_2602_20656_amd import binding as lg
+    out_bytes = 4 if out_dt == lg.LAGOM_F32 else 2
     if geo.tile_m * geo.tile_n <= 64 * 64:
         return "gemm_bf16_split_kernel"
     if K < 64 or K > 1 << 22:
         return "gemm_bf16_general_kernel"
     tiles = -(-M // geo.tile_m) * -(-N // geo.tile_n)
-    lines = {(128, 128): ("128", 640), (256, 128): ("256x128", 1536)}.get((geo.tile_m, geo.tile_n))
+    lines = {(128, 128): ("128", 640 if b_is_nk else 1280), (256, 128): ("256x128", 1536)}.get((geo.tile_m, geo.tile_n))
     if lines and K % 64 and K >= lines[1]:
         return f"gemm_bf16_lines{lines[0]}_kernel"
     kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "")
     if not kind and geo.mu != tiles:       # whole rounds of large tiles, and the rest in smaller ones: whose loads tell which
         large = tiles // LAMBDA * LAMBDA
-        of_rest = (geo.mu * geo.d_bytes - large * ((256 + 256) * K * 2 + 256 * 256 * 2)) / (geo.mu - large)
+        of_rest = (geo.mu * geo.d_bytes - large * ((256 + 256) * K * 2 + 256 * 256 * out_bytes)) / (geo.mu - large)
         kind = "_pieces" if of_rest < (128 + 128) * K * 2 else "_mixed"
-    return f"gemm_bf16_nk{kind}{'_tail' if K % 64 else ''}_kernel"
+    return f"gemm_bf16_{'nk' if b_is_nk else 'kn'}{kind}{'_tail' if K % 64 else ''}_kernel"
 
 
 def rotating_comm_roofline(st1, st2, op, dt_name, nsrc, count, cfgs, iters, final_iters=20):

@@ -1,6 +1,7 @@
-// Prints the kernel that lagom_comm_steps launches, without a GPU: the HIP entry points that a launch calls are defined here and found
-// before the real ones.  Buffers are addresses that nothing reads.
-//   steps_host <dtype> <count> <nc> <nt> <chunk bytes> <op>:<sources>-<destinations> ...        (a buffer is a letter)
+// Prints the kernels that lagom_comm_steps and lagom_gemm launch, without a GPU: the HIP entry points that a launch calls are defined here
+// and found before the real ones.  Buffers are addresses that nothing reads.
+//   launch_host steps <dtype> <count> <nc> <nt> <chunk bytes> <op>:<sources>-<destinations> ...        (a buffer is a letter)
+//   launch_host gemm <M>,<N>,<K>,<b_is_nk>,<out dtype> ...
 #define __HIP_PLATFORM_AMD__
 #include <hip/hip_runtime_api.h>
 #include <cstdio>
@@ -27,25 +28,43 @@ void __hipUnregisterFatBinary(void**) {}
 void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { names()[host] = name; }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, hipStream_t st) { g_grid = g; g_block = b; g_lds = s; g_stream = st; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* st) { *g = g_grid; *b = g_block; *s = g_lds; *st = g_stream; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return ""; }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void**, size_t, hipStream_t) { std::printf("%s %u %u\n", names()[f].c_str(), g.x, b.x); return hipSuccess; }
 }  // extern "C"
 
-int main(int argc, char** argv) {
-    if (argc < 7) return 2;
+int steps(int argc, char** argv) {
+    if (argc < 6) return 2;
     std::vector<std::vector<void*>> held;
-    std::vector<lagom_comm_step> steps;
-    for (int i = 6; i < argc; ++i) {
+    std::vector<lagom_comm_step> list;
+    for (int i = 5; i < argc; ++i) {
         const char *from = std::strchr(argv[i], ':') + 1, *arrow = std::strchr(from, '-');
         held.push_back(buffers(from, arrow));
         held.push_back(buffers(arrow + 1, arrow + std::strlen(arrow)));
-        steps.push_back({atoi(argv[i]), nullptr, (int32_t)held[held.size() - 2].size(), nullptr, (int32_t)held.back().size()});
+        list.push_back({atoi(argv[i]), nullptr, (int32_t)held[held.size() - 2].size(), nullptr, (int32_t)held.back().size()});
     }
-    for (size_t i = 0; i < steps.size(); ++i) { steps[i].srcs = held[2 * i].data(); steps[i].dsts = held[2 * i + 1].data(); }
+    for (size_t i = 0; i < list.size(); ++i) { list[i].srcs = held[2 * i].data(); list[i].dsts = held[2 * i + 1].data(); }
     lagom_cfg cfg{};
-    cfg.nc = atoi(argv[3]); cfg.nt = atoi(argv[4]); cfg.chunk_bytes = atoll(argv[5]);
-    const int rc = lagom_comm_steps((lagom_dtype)atoi(argv[1]), steps.data(), (int)steps.size(), atoll(argv[2]), &cfg, nullptr);
+    cfg.nc = atoi(argv[2]); cfg.nt = atoi(argv[3]); cfg.chunk_bytes = atoll(argv[4]);
+    return lagom_comm_steps((lagom_dtype)atoi(argv[0]), list.data(), (int)list.size(), atoll(argv[1]), &cfg, nullptr);
+}
+
+int gemm(int argc, char** argv) {
+    const std::vector<void*> m = buffers("abc", "abc" + 3);
+    for (int i = 0; i < argc; ++i) {
+        long long M, N, K;
+        int nk, out;
+        if (std::sscanf(argv[i], "%lld,%lld,%lld,%d,%d", &M, &N, &K, &nk, &out) != 5) return 2;
+        if (int rc = lagom_gemm(m[0], m[1], m[2], M, N, K, nk, (lagom_dtype)out, nullptr)) return rc;
+    }
+    return 0;
+}
+
+int main(int argc, char** argv) {
+    if (argc < 2) return 2;
+    const int rc = argv[1][0] == 's' ? steps(argc - 2, argv + 2) : gemm(argc - 2, argv + 2);
     if (rc) std::fprintf(stderr, "%s\n", lagom_last_error());
     return rc ? 1 : 0;
 }

@@ -547,7 +547,7 @@ def test_wide_launches_with_few_busy_channels(nt, busy):
 @pytest.mark.parametrize("nt", [64, 512])
 @pytest.mark.parametrize("again", [(), ("a",), ("e",)])           # a source read twice; a destination read by a later step
 def test_wide_steps_that_do_and_do_not_read_anything_again(dtype, nt, again):
-    """130 channels with a chunk each: the same bits with the loads' hint and without it (tests/test_steps_host.py says which a launch takes)."""
+    """130 channels with a chunk each: the same bits with the loads' hint and without it (tests/test_launch_host.py says which a launch takes)."""
     count = 129 * 1024 + 7
     bufs = dict(zip("abcdefgh", _sources(dtype, 8, count, 1450)))
     steps = [("reduce_copy", ["a", "b"], ["e"]), ("reduce_copy", ["c", "d"], ["f"]), ("gather_copy", [*again, "g"][:1], ["h"])]

@@ -1,4 +1,5 @@
-"""Which kernel lagom_comm_steps launches, on a model of the runtime (tests/steps_host.cpp): loads carry the non-temporal hint or not."""
+"""Which kernels lagom_comm_steps and lagom_gemm launch, on a model of the runtime (tests/launch_host.cpp): loads with the non-temporal hint or without,
+and the names that the benchmark gives."""
 import os
 import re
 import shutil
@@ -17,17 +18,25 @@ MiB = 1 << 20
 
 
 @pytest.fixture(scope="module")
-def streamed(tmp_path_factory):
+def launched(tmp_path_factory):
     lg.lib()                       # built
-    exe = str(tmp_path_factory.mktemp("steps") / "steps_host")
+    exe = str(tmp_path_factory.mktemp("launch") / "launch_host")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROCM, "include"),
-                           os.path.join(ROOT, "tests", "steps_host.cpp"), lg.LIB_PATH, "-Wl,-rpath," + PACKAGE, "-Wl,--allow-shlib-undefined", "-o", exe])
+                           os.path.join(ROOT, "tests", "launch_host.cpp"), lg.LIB_PATH, "-Wl,-rpath," + PACKAGE, "-Wl,--allow-shlib-undefined", "-o", exe])
+    def run(*args):
+        r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return r.stdout.splitlines()
+    return run
+
+
+@pytest.fixture(scope="module")
+def streamed(launched):
     def run(steps, dtype=lg.LAGOM_F32, nbytes=32 * MiB, nc=128, nt=256, chunk=65536):
         count = nbytes // (4 if dtype == lg.LAGOM_F32 else 2)
-        r = subprocess.run([exe, *map(str, (dtype, count, nc, nt, chunk)), *steps], capture_output=True, text=True, timeout=60)
-        assert r.returncode == 0, r.stdout + r.stderr
-        m = re.fullmatch(r"\S*comm_steps_kernelILi(\d)ELb(\d)ELb(\d)E\S* (\d+) (\d+)\n", r.stdout)
-        assert m and (int(m[1]), int(m[4]), int(m[5])) == (dtype, nc, nt), r.stdout
+        (line,) = launched("steps", dtype, count, nc, nt, chunk, *steps)
+        m = re.fullmatch(r"\S*comm_steps_kernelILi(\d)ELb(\d)ELb(\d)E\S* (\d+) (\d+)", line)
+        assert m and (int(m[1]), int(m[4]), int(m[5])) == (dtype, nc, nt), line
         return m[2] == "1"
     return run
 
@@ -51,3 +60,19 @@ def test_steps_that_read_again_load_without_the_hint(streamed, steps, again, dty
 def test_buffers_that_fill_the_last_level_cache_are_streamed_all_the_same(streamed, nbytes, hint):
     assert streamed([REDUCE + "ab-e", REDUCE + "ad-f"], nbytes=nbytes) == hint
     assert streamed([REDUCE + "ab-e", REDUCE + "cd-f"], nbytes=nbytes)
+
+
+def test_the_benchmark_names_the_kernels_that_are_launched(launched):
+    """Both layouts of B, on either side of every line of the dispatch, and products anywhere."""
+    import random
+    import bench
+    rng = random.Random(3)
+    shapes = [(512, 512, 512), (512, 512, 56), (1200, 1288, 320), (1200, 1288, 72), (2048, 4096, 4096), (4096, 4096, 4096), (4096, 4096, 4104), (4096, 4352, 4096), (4100, 4200, 2056),
+              (4096, 4352, 256), (4096, 6144, 72), (4096, 6400, 4096), *((1200, 1288, k) for k in (632, 640, 648, 1272, 1280, 1288)), *((2100, 2056, k) for k in (1528, 1536, 1544))]
+    shapes += [tuple(int(2 ** rng.uniform(5, 13.3)) // 8 * 8 for _ in range(3)) for _ in range(200)]
+    asked = [(*s, nk, out) for s in shapes for nk in (True, False) for out in (lg.LAGOM_BF16, lg.LAGOM_F32)]
+    lines = launched("gemm", *("%d,%d,%d,%d,%d" % a for a in asked))
+    assert len(lines) == len(asked)
+    for (M, N, K, nk, out), line in zip(asked, lines):
+        name = re.search(r"\d(gemm_bf16_\w+?_kernel)[IE]", line)[1]
+        assert bench.gemm_kernel_name(lg.lagom_gemm_describe(M, N, K, out), M, N, K, nk, out) == name, (M, N, K, nk, out)
