@@ -666,7 +666,7 @@ def main():
     ap.add_argument("--profile-max-iters", type=int, default=100)
     ap.add_argument("--dependent", action="store_true",
                     help="fsdp_chain only: GEMM i (i > 0) consumes the weight gathered by communication i-1 and waits for it")
-    ap.add_argument("--dump", default=None, help="directory for per-workload JSON files with the sweep tables, tuner traces and profile logs")
+    ap.add_argument("--dump", default=None, help="directory for record.json (the printed line with everything of each workload) and per-workload JSON files with the sweep tables, tuner traces and profile logs")
     ap.add_argument("--standalone-only", action="store_true",
                     help="run every kernel alone and nothing that needs two kernels at once: the form for rocprofv3 --pmc")
     args = ap.parse_args()
@@ -733,7 +733,19 @@ def main():
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(headline)
-    print(json.dumps(out))
+    if args.dump:
+        with open(os.path.join(args.dump, "record.json"), "w") as f:
+            json.dump(out, f, indent=1, default=str)
+    print(json.dumps(short_line(out)))
+
+
+def short_line(record):
+    """The record with little of each workload: one line of some 5000 characters.  (What reads it keeps the end of the output only; whole, it was cut.)"""
+    def short(v):
+        return float(f"{v:.4g}") if isinstance(v, float) else [short(x) for x in v] if isinstance(v, (list, tuple)) else v
+    kept = ("speedup_tuned_vs_default", "verdict", "z_default_us", "z_tuned_us", "z_tuned_free_steps_us", "z_comm_descent_us", "z_best_swept_us",
+            "z_best_swept_extended_us", "gemm_alone_us", "seconds")
+    return {**record, "configs": {name: {k: short(c[k]) for k in kept} for name, c in record["configs"].items()}}
 
 
 if __name__ == "__main__":

@@ -67,6 +67,33 @@ def test_gates_open_over_more_repetitions_than_there_are_gate_words(tiny, mode):
     assert abs(t.comm_start_us - t.comp_start_us) <= 4.0
 
 
+@pytest.mark.parametrize("longer", ["communication", "computation"])
+def test_repetitions_are_disjoint_where_one_stream_takes_far_longer(longer):
+    """Each repetition is queued while the one before runs.  The reduction adds into one of its own sources, so its result counts the
+    repetitions; the makespan is that of the longer side."""
+    s1, s2 = lg.overlapping_streams()
+    n, warmup, iters = 1 << 20, 2, 9
+    total, one = torch.full((n,), 5.0, device="cuda"), torch.ones(n, device="cuda")
+    M = 512 if longer == "communication" else 4096
+    A, B = torch.randn(M, M, device="cuda").to(torch.bfloat16), torch.randn(M, M, device="cuda").to(torch.bfloat16)
+    C, want = torch.zeros(M, M, dtype=torch.bfloat16, device="cuda"), torch.zeros(M, M, dtype=torch.bfloat16, device="cuda")
+    lg.lagom_gemm(A, B, want, M, M, M, True, lg.LAGOM_BF16, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    cfg = (1, 256, 64 << 10) if longer == "communication" else (64, 256, 64 << 10)      # one channel: some 100 us
+    launches = [lg.CommLaunch(lg.LAGOM_REDUCE_COPY, lg.LAGOM_F32, [total, one], [total], n, 0)]
+    before = lg.lagom_gate_misses()
+    t = lg.lagom_overlap_run(launches, [cfg], [lg.GemmDesc(A, B, C, M, M, M)], s1, s2, warmup, iters, lg.LAGOM_CORUN)
+    torch.cuda.synchronize()
+    late, unseen = (b - a for a, b in zip(before, lg.lagom_gate_misses()))
+    assert late <= 3 and unseen == 0
+    assert torch.equal(total, torch.full_like(total, 5.0 + warmup + iters))
+    assert torch.equal(C, want)
+    x, y = t.X_us, t.Y_us
+    assert (x > 3 * y) if longer == "communication" else (y > 3 * x), (x, y)
+    assert abs(t.comm_start_us - t.comp_start_us) <= 4.0
+    assert max(x, y) - 3.0 <= t.Z_us <= max(x, y) + 7.0          # medians of different repetitions, released at most 4 us apart
+
+
 def test_a_failed_group_does_not_sit_out_the_gate(tiny):
     """A dependency cycle is found behind the gate's launch: the gate is opened before the streams are drained."""
     cyc_l = [lg.CommLaunch(lg.LAGOM_REDUCE_COPY, lg.LAGOM_F32, [tiny["da"], tiny["db"]], [tiny["dout"]], 1 << 20, 0, after_comp=0)]

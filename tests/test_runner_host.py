@@ -35,3 +35,15 @@ def test_a_failed_read_out_leaves_nothing_in_flight(runner, mode):
         r = runner(fail=fail, warmup=1, iters=3, mode=mode)
         assert r["rc"] == lg.LAGOM_EHIP and "made to fail" in r["error"]
         assert r["destroyed_in_flight"] == 0 and r["in_flight"] == 0 and r["alive"] == 0, (fail, r)
+
+
+@pytest.mark.parametrize("comm_us,comp_us", [(100.0, 3.0), (3.0, 100.0), (50.0, 40.0)])
+@pytest.mark.parametrize("warmup,iters", [(0, 1), (1, 1), (2, 4)])
+@pytest.mark.parametrize("mode", [lg.LAGOM_CORUN, lg.LAGOM_ALONE_COMM, lg.LAGOM_ALONE_COMP])
+def test_repetitions_do_not_reach_into_each_other(runner, comm_us, comp_us, warmup, iters, mode):
+    """A repetition is queued while the one before runs: it begins when that has ended on both streams, however much longer one of them takes."""
+    r = runner(comm_us=comm_us, comp_us=comp_us, warmup=warmup, iters=iters, mode=mode)
+    comm, comp = mode != lg.LAGOM_ALONE_COMP, mode != lg.LAGOM_ALONE_COMM
+    assert r["rc"] == lg.LAGOM_OK and r["early"] == 0 and r["in_flight"] == 0 and r["alive"] == 0
+    assert (r["comms"], r["comps"]) == ((warmup + iters) * comm, (warmup + iters) * comp)
+    assert (r["X"], r["Y"], r["Z"]) == pytest.approx((comm_us * comm, comp_us * comp, max(comm_us * comm, comp_us * comp)), abs=0.01)
