@@ -362,13 +362,11 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
     const int ncomp_run = run_comp ? ncomp : 0;
     const bool deps = run_comm && run_comp;        // dependencies only matter when both streams run
     Events E;
-    const int nevents = 2 * ngroups + 2 * ncomp_run;        // of a repetition, of which two are under way
-    if (int rc = E.make(2 * nevents)) return rc;
-    struct Marks { hipEvent_t *ga_start, *ga_end, *gb_start, *gb_end; };
-    auto marks = [&](int it) {
-        hipEvent_t* first = E.ev.data() + (it & 1) * nevents;
-        return Marks{first, first + ngroups, first + 2 * ngroups, first + 2 * ngroups + ncomp_run};
-    };
+    if (int rc = E.make(2 * ngroups + 2 * ncomp_run)) return rc;
+    hipEvent_t* ga_start = E.ev.data();
+    hipEvent_t* ga_end = ga_start + ngroups;
+    hipEvent_t* gb_start = ga_end + ngroups;
+    hipEvent_t* gb_end = gb_start + ncomp_run;
 
     int dev = 0, clock_khz = 100000;
     HIP_TRY(hipGetDevice(&dev));
@@ -390,45 +388,33 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
     hipStream_t gate_stream = run_comm ? sa : sb;
 
     std::vector<double> Ysums;
-    // One repetition: gate, both streams enqueued.  It starts when the one before has ended on both streams, which wait for each other
-    // on the device: the host enqueues it meanwhile, behind the closed gate, and reads the times of the one before when that has ended.
-    // us, enqueued when the streams are drained -> this, a ring share of 25 MiB beside 4096^3 (makespan 133): a repetition 172 -> 157, of which
-    // the gate's lead is 12 and the streams' wait for each other 5 (a wait inside the gates would have no bound but the computation's
-    // length), six of them and what surrounds them 1084 -> 1049.
-    const int total = warmup + iters;
-    unsigned long long seqs[2];
-    auto repetition = [&](int it) -> int {
-        const unsigned long long seq = seqs[it & 1] = next_gate_seq();
-        GateWord* const word = words + seq % kGateWords;
+    // One repetition: gate, both streams enqueued, both drained.  Enqueued while the one before runs, behind waits of the streams for each other, six
+    // repetitions of a ring share of 25 MiB beside 4096^3 and what surrounds them take 1058 us instead of 1093; but the streams are then released 1.7 us
+    // apart in most of them (0.2 us so), whatever the gates' lead, and X, Y and Z read that much more: 64 channels beside 512^3 9.2 -> 10 - 11.8, a
+    // stream alone 7.2 -> 7.6.
+    auto repetition = [&](GateWord* word, unsigned long long seq) -> int {
         GateOpener gate{word, seq};
-        const Marks m = marks(it), before = marks(it - 1);
-        if (run_comm && run_comp && it > 0) {
-            HIP_TRY(hipStreamWaitEvent(sa, before.gb_end[ncomp_run - 1], 0));
-            HIP_TRY(hipStreamWaitEvent(sb, before.ga_end[ngroups - 1], 0));
-        }
         hipLaunchKernelGGL(gate_leader_kernel, dim3(1), dim3(64), 0, gate_stream, word, seq, ticks, lead_ticks, max_iter);
         HIP_TRY(hipGetLastError());
         if (run_comm && run_comp) {
             hipLaunchKernelGGL(gate_follower_kernel, dim3(1), dim3(64), 0, sb, word, seq, max_iter);
             HIP_TRY(hipGetLastError());
         }
-        return enqueue_group(plan, launches, run_comm ? nlaunch : 0, cfgs, comps, ncomp_run, deps, sa, sb,
-                             m.ga_start, m.ga_end, m.gb_start, m.gb_end);
-    };
-    auto ended = [&](int it) -> int {
-        const Marks m = marks(it);
-        if (run_comm) HIP_TRY(hipEventSynchronize(m.ga_end[ngroups - 1]));
-        if (run_comp) HIP_TRY(hipEventSynchronize(m.gb_end[ncomp_run - 1]));
+        if (int rc = enqueue_group(plan, launches, run_comm ? nlaunch : 0, cfgs, comps, ncomp_run, deps, sa, sb,
+                                   ga_start, ga_end, gb_start, gb_end)) return rc;
+        gate.open();
+        if (run_comm) HIP_TRY(hipStreamSynchronize(sa));
+        if (run_comp) HIP_TRY(hipStreamSynchronize(sb));
         return LAGOM_OK;
     };
-    auto count_misses = [&](int it) {
-        const unsigned long long seq = seqs[it & 1];
-        GateWord* const word = words + seq % kGateWords;
+    for (int it = 0; it < warmup + iters; ++it) {
+        const unsigned long long seq = next_gate_seq();
+        GateWord* word = words + seq % kGateWords;
+        const int rc = drained(repetition(word, seq), sa, sb);
         if (__atomic_load_n(&word->late, __ATOMIC_RELAXED) == seq) ++gates_late;
         if (__atomic_load_n(&word->unseen, __ATOMIC_RELAXED) == seq) ++gates_unseen;
-    };
-    auto read_out = [&](int it) -> int {
-        const auto [ga_start, ga_end, gb_start, gb_end] = marks(it);
+        if (rc) return rc;
+        if (it < warmup) continue;
 
         // The common start: the start event of the stream whose first kernel follows its gate kernel directly.  With
         // cross-stream dependencies the other stream's first start event is recorded behind a wait; without them the
@@ -461,17 +447,6 @@ extern "C" int lagom_overlap_run(const lagom_comm_desc* launches, int nlaunch, c
             HIP_TRY(hipEventElapsedTime(&ms, origin, gb_start[0])); startsB.push_back((double)ms * 1000.0);
         }
         Xs.push_back(X); Ys.push_back(Y); Zs.push_back(endA > endB ? endA : endB); Ysums.push_back(ysum);
-        return LAGOM_OK;
-    };
-    for (int it = 0; it < total; ++it) {
-        // (behind a failure the streams are drained: every repetition that was begun has ended)
-        int rc = it == 0 ? drained(repetition(0), sa, sb) : LAGOM_OK;
-        if (rc) { count_misses(0); return rc; }
-        if (it + 1 < total) rc = drained(repetition(it + 1), sa, sb);
-        if (!rc) rc = drained(ended(it), sa, sb);
-        count_misses(it);
-        if (!rc && it >= warmup) rc = drained(read_out(it), sa, sb);
-        if (rc) { if (it + 1 < total) count_misses(it + 1); return rc; }
     }
     out->X_us = median(Xs);
     out->Y_us = median(Ys);
@@ -634,7 +609,7 @@ extern "C" int lagom_contention_sweep(const lagom_comm_desc* launches, int nlaun
         comp_alone = sum(yi);
         return rc;
     };
-    auto settle = [&]() { return (int)(kSettleUs / (comp_alone + 10.0)); };     // repetitions, each with 10 us and more between products
+    auto settle = [&]() { return (int)(kSettleUs / (comp_alone + 40.0)); };     // repetitions, each with 40 us of the host's
     if (int rc = reference(0)) return rc;
     if (int rc = reference(settle())) return rc;
     for (int p = 0; p < npoints; ++p) {

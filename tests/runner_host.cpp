@@ -1,6 +1,6 @@
 // Drives lagom_overlap_run on a model of the runtime, without a GPU: the HIP entry points that the library calls are defined here and
 // found before the real ones.  Streams are clocks in virtual time, a launch moves its stream's clock by the kernel's duration, an
-// event is the clock of the stream that recorded it.
+// event is the clock of the stream that recorded it.  The host's clock stands still but for its waits; nothing begins before it was queued.
 //   runner_host <fail> <comm us> <comp us> <warmup> <iters> <mode>
 // Call <fail> of hipEventElapsedTime fails (0: none).  Prints what the runner returned and measured, and counts what must not happen.
 #define __HIP_PLATFORM_AMD__
@@ -22,9 +22,11 @@ std::map<hipStream_t, double> clock_of;
 std::map<hipStream_t, int> queued;                       // operations behind the last synchronisation
 std::set<Event*> alive;
 std::vector<Op> ops;
-int reads = 0, fail_at = 0, created = 0, destroyed_in_flight = 0;
-double comm_us = 1.0, comp_us = 1.0;
+int reads = 0, fail_at = 0, created = 0, destroyed_in_flight = 0, ahead = 0;
+double comm_us = 1.0, comp_us = 1.0, host = 0.0;
 hipStream_t sa = reinterpret_cast<hipStream_t>(16), sb = reinterpret_cast<hipStream_t>(32);
+double& queue(hipStream_t st) { ++queued[st]; double& c = clock_of[st]; if (host > c) c = host; return c; }
+void wait_until(double at) { if (at > host) host = at; }
 bool idle() { return !queued[sa] && !queued[sb]; }
 }  // namespace
 
@@ -42,18 +44,19 @@ const char* hipGetErrorString(hipError_t) { return "made to fail"; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = aligned_alloc(64, (n + 63) / 64 * 64); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { Event* x = new Event; alive.insert(x); ++created; *e = reinterpret_cast<hipEvent_t>(x); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { if (!idle()) ++destroyed_in_flight; Event* x = reinterpret_cast<Event*>(e); alive.erase(x); delete x; return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t st) { reinterpret_cast<Event*>(e)->at = clock_of[st]; ++queued[st]; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t st) { reinterpret_cast<Event*>(e)->at = queue(st); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t e, unsigned) {
     const double at = reinterpret_cast<Event*>(e)->at;
-    if (at > clock_of[st]) clock_of[st] = at;
-    ++queued[st];
+    double& clock = queue(st);
+    if (at > clock) clock = at;
     return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {          // a stream whose clock has not moved since is idle
+    wait_until(reinterpret_cast<Event*>(e)->at);
     for (auto& [st, n] : queued) if (clock_of[st] <= reinterpret_cast<Event*>(e)->at) n = 0;
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t st) { queued[st] = 0; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t st) { wait_until(clock_of[st]); queued[st] = 0; return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
     if (++reads == fail_at) return hipErrorInvalidHandle;
     *ms = (float)((reinterpret_cast<Event*>(b)->at - reinterpret_cast<Event*>(a)->at) / 1000.0);
@@ -69,11 +72,12 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
         unsigned long long* word = *static_cast<unsigned long long**>(args[0]);
         word[1] = *static_cast<unsigned long long*>(args[1]);
     }
+    if (has("gate_leader") && !idle()) ++ahead;         // a repetition that is queued while another one runs
     const bool gate = has("gate_") || has("meet_");
-    const double begin = clock_of[st];
-    clock_of[st] += gate ? 1.0 : has("gemm") ? comp_us : comm_us;
-    ops.push_back({st == sa ? 0 : 1, gate, begin, clock_of[st]});
-    ++queued[st];
+    double& clock = queue(st);
+    const double begin = clock;
+    clock += gate ? 1.0 : has("gemm") ? comp_us : comm_us;
+    ops.push_back({st == sa ? 0 : 1, gate, begin, clock});
     return hipSuccess;
 }
 }  // extern "C"
@@ -106,8 +110,8 @@ int main(int argc, char** argv) {
         ++seen[o.stream];
         ended[o.stream] = o.end;
     }
-    std::printf("{\"rc\": %d, \"error\": \"%s\", \"X\": %.3f, \"Y\": %.3f, \"Z\": %.3f, \"comms\": %d, \"comps\": %d, \"early\": %d, \"reads\": %d, \"created\": %d, "
-                "\"destroyed_in_flight\": %d, \"in_flight\": %d, \"alive\": %zu}\n", rc, rc ? lagom_last_error() : "", t.X_us, t.Y_us, t.Z_us, comms, comps, early, reads,
+    std::printf("{\"rc\": %d, \"error\": \"%s\", \"X\": %.3f, \"Y\": %.3f, \"Z\": %.3f, \"comms\": %d, \"comps\": %d, \"early\": %d, \"ahead\": %d, \"reads\": %d, \"created\": %d, "
+                "\"destroyed_in_flight\": %d, \"in_flight\": %d, \"alive\": %zu}\n", rc, rc ? lagom_last_error() : "", t.X_us, t.Y_us, t.Z_us, comms, comps, early, ahead, reads,
                 created, destroyed_in_flight, idle() ? 0 : 1, alive.size());
     return 0;
 }

@@ -69,7 +69,7 @@ def test_gates_open_over_more_repetitions_than_there_are_gate_words(tiny, mode):
 
 @pytest.mark.parametrize("longer", ["communication", "computation"])
 def test_repetitions_are_disjoint_where_one_stream_takes_far_longer(longer):
-    """Each repetition is queued while the one before runs.  The reduction adds into one of its own sources, so its result counts the
+    """Each repetition begins when the one before has ended on both streams.  The reduction adds into one of its own sources, so its result counts the
     repetitions; the makespan is that of the longer side."""
     s1, s2 = lg.overlapping_streams()
     n, warmup, iters = 1 << 20, 2, 9
