@@ -172,8 +172,8 @@ def gemm_kernel_name(geo, M, N, K, b_is_nk=True, out_dt=None):
     if K < 64 or K > 1 << 22:
         return "gemm_bf16_general_kernel"
     tiles = -(-M // geo.tile_m) * -(-N // geo.tile_n)
-    lines = {(128, 128): ("128", 640 if b_is_nk else 1280), (256, 128): ("256x128", 1536)}.get((geo.tile_m, geo.tile_n))
-    if lines and K % 64 and K >= lines[1]:
+    lines = {(128, 128): ("128", 640 if b_is_nk else 1280, 64 if b_is_nk else 32), (256, 128): ("256x128", 1536, 32 if b_is_nk else 16)}.get((geo.tile_m, geo.tile_n))
+    if lines and K >= lines[1] and K % lines[2]:
         return f"gemm_bf16_lines{lines[0]}_kernel"
     kind = {(128, 128): "128", (256, 128): "256x128"}.get((geo.tile_m, geo.tile_n), "")
     if not kind and geo.mu != tiles:       # whole rounds of large tiles, and the rest in smaller ones: whose loads tell which

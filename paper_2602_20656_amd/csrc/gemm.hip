@@ -1445,9 +1445,16 @@ int choose_mixed(const GemmArgs& g, MixedArgs* out) {
 // slices of K: 4100 x 4200 x 320 22.5 -> 22.3.
 // Half of the chip begins with a piece each, so that its large tiles store a piece's time behind the others': the results of a
 // round, stored by all at one moment, cost what the memory takes for them (64 MiB of fp32 results 14 us of 78).  us, all pieces
-// behind -> 128 in front: 4100 x 4200 x 2056 72.9 -> 67.6, [K,N] fp32 78.9 -> 75.0, 4096 x 4352 x 4096 109.5 -> 109.0, 4352 x 4096 x 2048
-// [K,N] fp32 67.7 -> 66.8 (64 in front 77.5 of the 78.9, 192 77.8, 256 77.0).  Quadrants in front of large tiles gain nothing (4096
-// x 6144 x 2048 fp32 91.4 -> 93.0).
+// behind -> 64 | 128 | 192 in front, bf16, fp32:
+//   one round   4100 x 4200 x 2056 [K,N] 68.9 -> 67.2 | 65.0 | 67.4, 75.8 -> 72.8 | 68.6 | 71.6   4352 x 4096 x 2048 [K,N] 61.3 -> 59.4 | 58.7 | 60.1, 66.5 -> 64.6 | 65.6 | 65.9
+//               4096 x 4160 x 1024 33.6 -> 31.7 | 31.8 | 31.8, 38.4 -> 34.9 | 35.1 | 35.0         4096 x 4352 x 4096 106.1 -> 106.4 | 105.7 | 106.4, 111.6 -> 111.2 | 108.2 | 110.8
+//   two         4100 x 8200 x 1024 66.6 -> 63.5 | 60.8 | 63.8, 77.7 -> 75.7 | 71.1 | 72.5         4153 x 7768 x 3384 180 -> 182 | 182 | 183, 190 -> 191 | 191 | 191
+//   three       8200 x 6200 x 2048 166 -> 158 | 155 | 161, 183 -> 174 | 168 | 173                 12300 x 4100 x 1536 136 -> 136 | 137 | 137, 150 -> 150 | 150 | 151
+// Beside communication a unit that hosts a channel and begins with a piece ends a piece's time later than it did, and behind a single round
+// nothing is left to make up for it.  Makespans beside a ring share of eight 3.1 MiB buffers on 8 | 32 | 64 channels, all behind -> 128 in front, bf16:
+//   one round   4100 x 4200 x 2056 [K,N] 253 -> 258 | 123 -> 129 | 95 -> 104    4352 x 4096 x 2048 227 -> 232 | 108 -> 115 | 81 -> 88
+//   two, three  4100 x 8200 x 1024 243 -> 240 | 117 -> 113 | 90 -> 86           8200 x 6200 x 2048 296 -> 296 | 193 -> 181 | 171 -> 182
+// (with the pieces behind the first 128 large tiles the same).  Quadrants in front of large tiles gain nothing (4096 x 6144 x 2048 fp32 91.4 -> 93.0).
 constexpr int kLead = kRound / 2;
 bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
@@ -1486,14 +1493,19 @@ bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
 // 11.8 -> 11.4, x 3080 39.1 -> 31.0 | 34.9 -> 30.1.
 // The same way through products with K split over wavefronts, which then take neighbouring slices and a line more each, gains 7 - 20 % from K = 3000
 // on and loses as much up to 2000.
-bool lines_pay(int64_t K, bool b_is_nk) { return K >= (b_is_nk ? 640 : 1280); }
+// Rows that start alike gain less: of a K that is a multiple of 16 every fourth row starts at a line, of one that is a multiple of 32 every other one.
+// K = 1288 to 7224 in every class, three shapes, others' time = 1: odd multiples of 8 [N,K] 0.68 - 0.82, [K,N] 0.92 - 1.00; of 16 0.71 - 0.87 and 0.94 - 1.02; of 32
+// 0.81 - 0.98 and 0.97 - 1.04.
+bool lines_pay(int64_t K, bool b_is_nk) { return K >= (b_is_nk ? 640 : 1280) && (b_is_nk || K % 32 != 0); }
 // 256 x 128 tiles, of which LDS holds three: A alone in lines, whose loads are half a K-step in front of B's.  us, the same inputs from call
 // to call | inputs from HBM:
 //   2048 x 4096 (256 tiles)  x 776 17.9 -> 17.4 | 19.6 -> 18.4    x 2056 38.4 -> 34.8 | 48.3 -> 41.8    [K,N] 35.1 -> 33.9 | 43.4 -> 40.2
 //   2100 x 2200 (162)        x 776 14.8 -> 15.0 | 19.7 -> 19.6    x 2056 29.8 -> 29.9 | 42.1 -> 40.8    [K,N] 30.6 -> 29.9 | 42.8 -> 40.2
 //   713 x 5672 (135)         x 776 16.1 -> 15.7 | 20.7 -> 20.3    x 2056 33.5 -> 30.6 | 42.9 -> 40.4    [K,N] 33.3 -> 31.8 | 43.1 -> 39.9
 // x 1032 0.94 - 1.01 ([K,N] 0.96 - 1.03), x 520 0.97 - 1.06, x 1544 0.90 - 1.00.
-bool lines_of_a_pay(int64_t K) { return K >= 1536; }
+// Those are odd multiples of 8.  K = 1544 to 6584 in every class, 2048 x 4096, 2100 x 2176, 713 x 5632 and 2966 x 1536, others' time = 1: odd multiples of 8 [N,K]
+// 0.88 - 0.96, [K,N] 0.95 - 1.03; of 16 0.89 - 1.01 and 0.97 - 1.08; of 32 0.95 - 1.08 and 1.01 - 1.17.
+bool lines_of_a_pay(int64_t K, bool b_is_nk) { return K >= 1536 && K % (b_is_nk ? 32 : 16) != 0; }
 
 constexpr int64_t kMaxDim = 1 << 24;
 
@@ -1594,7 +1606,7 @@ extern "C" int lagom_gemm(const void* A, const void* B, void* C, int64_t M, int6
         if (tiling == TILE_128x128 && tail && lines_pay(K, b_is_nk)) {
             if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_lines128_kernel<false, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<false, false>>(a, grid, st);
             else rc = bf ? launch_fast<gemm_bf16_lines128_kernel<true, true>>(a, grid, st) : launch_fast<gemm_bf16_lines128_kernel<true, false>>(a, grid, st);
-        } else if (tiling == TILE_256x128 && tail && lines_of_a_pay(K)) {
+        } else if (tiling == TILE_256x128 && tail && lines_of_a_pay(K, b_is_nk)) {
             if (b_is_nk) rc = bf ? launch_fast<gemm_bf16_lines256x128_kernel<false, true>>(a, grid, st) : launch_fast<gemm_bf16_lines256x128_kernel<false, false>>(a, grid, st);
             else rc = bf ? launch_fast<gemm_bf16_lines256x128_kernel<true, true>>(a, grid, st) : launch_fast<gemm_bf16_lines256x128_kernel<true, false>>(a, grid, st);
         } else if (tiling == TILE_128x128) {

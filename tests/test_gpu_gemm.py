@@ -402,6 +402,14 @@ def test_gemm_lines_of_rows_anywhere_integer_inputs_are_exact(M, N, more, K, b_i
     assert not np.isfinite(got[list(bad_rows)]).any() and not np.isfinite(got[:, bad_col]).any()
 
 
+@pytest.mark.parametrize("M,N,more", [(1025, 1032, 0), (2100, 2056, 960)])
+@pytest.mark.parametrize("K", [1296, 1312, 1328])          # multiples of 16 and 32: some rows start at a line
+@pytest.mark.parametrize("b_is_nk", [True, False])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_gemm_lines_of_rows_that_start_alike_integer_inputs_are_exact(M, N, more, K, b_is_nk, shift):
+    test_gemm_lines_of_rows_anywhere_integer_inputs_are_exact(M, N, more, K, b_is_nk, shift)
+
+
 @pytest.mark.parametrize("M,N,K,tile", [(300, 192, 200, (16, 32)), (640, 640, 136, (64, 32)), (90, 5400, 128, (32, 64)), (1000, 960, 320, (64, 64)),
                                         (1200, 1280, 72, (128, 128)), (2100, 2112, 128, (256, 128)), (2100, 3712, 128, (256, 256)), (4100, 4224, 320, (256, 256))])
 @pytest.mark.parametrize("out", ["bf16", "f32"])

@@ -76,3 +76,12 @@ def test_the_benchmark_names_the_kernels_that_are_launched(launched):
     for (M, N, K, nk, out), line in zip(asked, lines):
         name = re.search(r"\d(gemm_bf16_\w+?_kernel)[IE]", line)[1]
         assert bench.gemm_kernel_name(lg.lagom_gemm_describe(M, N, K, out), M, N, K, nk, out) == name, (M, N, K, nk, out)
+
+
+@pytest.mark.parametrize("M,N,name,first,alike_nk,alike_kn", [(1200, 1288, "lines128", {True: 640, False: 1280}, 64, 32), (2100, 2056, "lines256x128", {True: 1536, False: 1536}, 32, 16)])
+def test_tiles_in_lines_where_rows_start_differently(launched, M, N, name, first, alike_nk, alike_kn):
+    """Rows of every class of K modulo 64: tiles hold lines where few enough rows start at one, from the size on where that pays."""
+    asked = [(M, N, K, nk) for nk in (True, False) for base in (first[nk] - 64, first[nk], 4096) for K in range(base, base + 64, 8)]
+    lines = launched("gemm", *("%d,%d,%d,%d,%d" % (*a, lg.LAGOM_BF16) for a in asked))
+    for (_, _, K, nk), line in zip(asked, lines):
+        assert ("_%s_kernel" % name in line) == (K >= first[nk] and K % (alike_nk if nk else alike_kn) != 0), (K, nk, line)
