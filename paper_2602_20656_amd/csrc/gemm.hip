@@ -269,16 +269,15 @@ __device__ __forceinline__ void store_ragged(char* out, u32x4 val, int64_t left)
 }
 
 // A store through the L2 to memory: nothing of it is left to be written back when the kernel ends.  (The compiler has no such store of this
-// size; behind one of 16 bytes a vector instruction may write its registers two wait states later, which the compiler does not see to.)  For results of 128 and 256 x 128 tiles whose rows begin and end inside 128-byte
-// lines, of which two wavefronts write parts, and for some products with K split over wavefronts, whose lines four write (split_gemm_body); results of whole lines go past
-// the L2 (us, past -> through: 2048 x 2048 x 256 fp32 7.5 -> 7.9, x 1024 13.0 -> 13.6), and so do those of 256 x 256 tiles (4100 x 4200 x 2056 [K,N] fp32
-// 67.9 -> 73.8; 4096 x 4000 x 2048 fp32, one round, 55.3 -> 55.4).  us, past -> through: 2048 x 2040 x 256 fp32 8.6 -> 7.3, 5742 x 1000 x 128 [K,N] 7.8 -> 7.0,
-// 713 x 5672 x 640 fp32 13.6 -> 12.6, 1100 x 3000 x 512 [K,N] 8.8 -> 8.4, 3000 x 3064 x 512 16.8 -> 15.3, 1841 x 4392 x 376 [K,N] fp32 17.5 -> 16.8; in the L2 -> through:
-// 512 x 1920 x 1024 [K,N] fp32 7.7 -> 7.3, 1024 x 1024 x 1024 7.3 -> 7.1, fp32 7.5 -> 7.1.  Rows off the 16-byte grid (store_ragged) stay in the
-// L2, which puts their pieces together: 933 x 1226 x 1032 fp32 12.7 -> 15.8, 7456 x 542 x 824 17.0 -> 21.4.
-__device__ __forceinline__ bool rows_off_line(const GemmArgs& p, int element) { return (((uintptr_t)p.C | (uintptr_t)(p.N * element)) & 127) != 0; }
+// size; behind one of 16 bytes a vector instruction may write its registers two wait states later, which the compiler does not see to.)  For fp32 results of
+// products with K split over wavefronts whose rows lie on the 64-byte grid, of which a store fills 64 bytes at a time: us, in the L2 -> through, results in the last-level cache
+// | results that are not: 1000 x 960 x 320 5.77 -> 5.32 | 6.61 -> 6.14, 1024 x 1024 x 1024 7.04 -> 6.53 | 8.76 -> 8.24, 512 x 1904 x 1024 [K,N] 7.93 -> 7.46 | 10.1 -> 9.6, 640 x 624 x 136
+// 4.31 -> 4.11 | 4.78 -> 4.60, 90 x 5408 x 128 4.19 -> 4.05 | 4.69 -> 4.52, 512 x 496 x 512 3.95 -> 3.87 | 4.84 -> 4.75.  Parts of 64 bytes gain as much in that cache,
+// but memory takes them badly: 1000 x 952 x 320 5.75 -> 5.37 | 6.59 -> 7.02, 1000 x 956 x 320 5.77 -> 5.59 | 6.58 -> 7.29, bf16 (32 bytes a store) 1000 x 960 x 320 5.56 -> 5.32 | 6.38 -> 6.69,
+// 1000 x 958 x 320 5.58 -> 6.69.  So do rows of 128 and 256 x 128 tiles that end inside lines: past the L2 -> through 2048 x 2040 x 256 fp32 8.21 -> 7.23 | 8.64 ->
+// 11.50, 5742 x 1000 x 128 [K,N] 7.78 -> 6.97 | 8.15 -> 10.70, 713 x 5672 x 640 fp32 13.5 -> 12.1 | 14.5 -> 19.6, on the 64-byte grid 2000 x 2000 x 1024 fp32
+// 11.2 -> 10.9 | 11.5 -> 13.7.
 __device__ __forceinline__ void store_through(char* out, u32x4 val) { asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(out), "v"(val) : "memory"); }
-__device__ __forceinline__ void store_through(char* out, uint2 val) { asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(out), "v"(val) : "memory"); }
 
 // Clears an operand fragment in the lanes that do not keep theirs.
 template <class FRAG>
@@ -931,14 +930,10 @@ __device__ __forceinline__ void small_gemm_body(const GemmArgs& p, int tm, int t
         const int r = rd_row + ROWS_PER_READ * e;
         return *reinterpret_cast<const u32x4*>(st + r * ROW_BYTES + ((rd_cv ^ (r & (GROUPS - 1))) << 4));
     };
-    if (__builtin_expect(N % VEC == 0 && !rows_off_line(p, ESZ), 1)) {
+    if (__builtin_expect(N % VEC == 0, 1)) {
 #pragma unroll
         for (int e = 0; e < WROWS / ROWS_PER_READ; ++e, out += rows_on)
             if (ROWS_PER_READ * e < rows) __builtin_nontemporal_store(read(e), reinterpret_cast<u32x4*>(out));
-    } else if (N % VEC == 0) {
-#pragma unroll
-        for (int e = 0; e < WROWS / ROWS_PER_READ; ++e, out += rows_on)
-            if (ROWS_PER_READ * e < rows) store_through(out, read(e));
     } else {   // rolled: unrolled, the code alone, which a launch has to fetch, costs 2 to 7 % (3001 x 1001 x 512 8.9 us, so 8.25)
 #pragma unroll 1
         for (int e = 0; e < WROWS / ROWS_PER_READ; ++e, out += rows_on)
@@ -1181,11 +1176,7 @@ __device__ __forceinline__ void split_gemm_body(const GemmArgs& p, int tm, int t
 #pragma unroll
         for (int j = 0; j < NJ; ++j) partial[wave * T::ITEMS + (i * NJ + j) * 64 + lane] = acc[i][j];
     __syncthreads();
-    // Through the L2 to memory (store_through) where that pays, else into the L2, which puts the pieces of a line together.  Off the grid of four
-    // elements through the L2 costs 0 - 20 % (1000 x 958 x 320 5.58 -> 6.69); on it, us, in the L2 -> through: 64 rows 1000 x 960 x 320 5.59 -> 5.33, fp32 5.77 -> 5.30, 512 x 1920 x 1024 [K,N]
-    // 7.14 -> 6.88, 640 x 644 x 136 fp32 4.34 -> 4.25 (bf16 4.23 -> 4.23); 32 rows fp32 512 x 512 x 512 3.95 -> 3.88, but 512 x 508 x 512 3.97 -> 4.05, bf16 3.89 ->
-    // 3.89 and 3.92 -> 4.04, 90 x 5404 x 128 4.09 -> 4.17; 16 rows 33 x 1000 x 4096 5.85 -> 5.90.
-    const bool through = T::TM == 64 ? N % 4 == 0 : T::TM == 32 && !out_bf16 && N % 8 == 0;
+    const bool through = T::TM >= 32 && !out_bf16 && (((uintptr_t)p.C | (uintptr_t)(4 * N)) & 63) == 0;
     for (int item = tid; item < T::ITEMS; item += 64 * WAVES) {
         f32x4 x = partial[item];
 #pragma unroll
@@ -1199,8 +1190,7 @@ __device__ __forceinline__ void split_gemm_body(const GemmArgs& p, int tm, int t
             u32x2_aligned2 v;
             v[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[0], x[1]}, bf16x2));
             v[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[2], x[3]}, bf16x2));
-            if (T::TM == 64 && through) store_through(reinterpret_cast<char*>(out), uint2{v[0], v[1]});
-            else if (col + 4 <= N) *reinterpret_cast<u32x2_aligned2*>(out) = v;
+            if (col + 4 <= N) *reinterpret_cast<u32x2_aligned2*>(out) = v;
             else
 #pragma unroll
                 for (int e = 0; e < 3; ++e)
