@@ -1445,7 +1445,11 @@ int choose_mixed(const GemmArgs& g, MixedArgs* out) {
 //   one round   4100 x 4200 x 2056 [K,N] 253 -> 258 | 123 -> 129 | 95 -> 104    4352 x 4096 x 2048 227 -> 232 | 108 -> 115 | 81 -> 88
 //   two, three  4100 x 8200 x 1024 243 -> 240 | 117 -> 113 | 90 -> 86           8200 x 6200 x 2048 296 -> 296 | 193 -> 181 | 171 -> 182
 // (with the pieces behind the first 128 large tiles the same).  Quadrants in front of large tiles gain nothing (4096 x 6144 x 2048 fp32 91.4 -> 93.0).
-constexpr int kLead = kRound / 2;
+// That is with results in the last-level cache.  With others from call to call, all behind -> 128 in front, bf16, fp32: 4100 x 4200 x 2056 [K,N] 77.0 -> 71.8, 82.5 -> 74.3,
+// 4160 x 4224 x 3000 109 -> 100, 112 -> 103, 4096 x 4288 x 1024 38.6 -> 37.5, 42.7 -> 40.7, x 2048 63.3 -> 62.8, 67.2 -> 66.8, 4096 x 4160 x 1024 38.0 -> 37.9, 41.3 -> 42.1, 8200 x 6200 x 2048
+// 174 -> 168, 190 -> 181, but not behind a long K, of which the two halves of the chip then load different parts: 4096 x 4160 x 4096 109 -> 113, 113 -> 119 (in the cache 104 ->
+// 103, 109 -> 106), 4096 x 4224 x 4096 110 -> 112, 114 -> 117; nor where a full round of pieces goes with a single one: 4352 x 4096 x 2048 [K,N] 65.1 -> 65.1, 70.5 -> 71.2.
+constexpr int kLead = kRound / 2, kLeadOfOneRound = kRound * 7 / 8, kLeadMaxK = 3072;
 bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
     const int rest = (int)(tiles % kRound);
@@ -1467,7 +1471,7 @@ bool choose_pieces(const GemmArgs& g, PiecesArgs* out) {
     }
     if (n_inside + n_right + n_low > kRound) return false;
     a.inside = (int32_t)n_inside; a.right = (int32_t)n_right; a.pieces = (int32_t)(n_inside + n_right + n_low);
-    a.lead = (a.pieces < kLead ? a.pieces : kLead) & ~7;
+    if (g.K < kLeadMaxK && (a.nlarge > kRound || a.pieces <= kLeadOfOneRound)) a.lead = (a.pieces < kLead ? a.pieces : kLead) & ~7;
     *out = a;
     return true;
 }
