@@ -609,7 +609,7 @@ extern "C" int lagom_contention_sweep(const lagom_comm_desc* launches, int nlaun
         comp_alone = sum(yi);
         return rc;
     };
-    auto settle = [&]() { return (int)(kSettleUs / (comp_alone + 40.0)); };     // repetitions, each with 40 us of the host's
+    auto settle = [&]() { return (int)(kSettleUs / (comp_alone + 40.0)); };     // repetitions; what lies between products is 16 us for one, 118 for eight
     if (int rc = reference(0)) return rc;
     if (int rc = reference(settle())) return rc;
     for (int p = 0; p < npoints; ++p) {
